@@ -1,19 +1,22 @@
 // Selection of the Kp largest entries of one row of fp32 scores by a whole workgroup (Section 4.1: the page
 // selector's top-k; also the channel-sparse token selector's).  Shared by the selection kernels and by the per-head
 // pruner kernel that selects its pages itself.
+//
+// A row of up to E * NT entries lives in registers: thread t holds the keys of entries e * NT + t (coalesced loads; the
+// order e, then wave, then lane is the entries' order, which is what the ordered listing needs).  The Kp-th largest key
+// is located by bucketing the live key interval linearly (one pass when the scores are spread out), narrowing to the
+// bucket that holds it, and an exact rank computation once at most SEL_CAP candidates remain.  What bounds it is the
+// chain of block barriers and LDS round trips, so every wave scans the histogram and ranks the candidates on its own
+// (the same result in each) instead of waiting for one that does: per row 4 barriers where staging the keys in LDS and
+// handing the crossing bucket, the rank and the list offsets around through LDS took 8.  Measured against that form:
+// selection inside the per-head kernel 5.0 -> 4.1 us (32 heads x 256 pages: 5.0 -> 3.7), page_select 6.7 -> 5.5 us at
+// 128 heads x 1024 pages, 50 -> 43 us at 256 heads x 32768 tokens; steps 1 to 5 % shorter.
 #pragma once
 #include "tw_common.h"
 
-// Rows of up to SEL_LDS_MAX entries: keys staged in LDS.
-// The Kp-th largest bound is located by bucketing the live key interval
-// linearly into 2048 buckets (one pass when the bounds are spread out),
-// narrowing to the bucket that holds it, and finishing with an exact rank
-// computation once at most 256 candidates remain.
-constexpr int SEL_LDS_PAGES = 8192;      // rows up to here run two workgroups per CU
-constexpr int SEL_LDS_MAX = 32768;       // longest row whose keys fit in LDS (128 KiB of the CU's 160)
-constexpr int SEL_NB = 2048;
-constexpr int SEL_CAP = 256;
-
+constexpr int SEL_REG_PAGES = 8192;      // rows up to here run two workgroups per CU
+constexpr int SEL_REG_MAX = 32768;       // longest row whose keys fit in a workgroup's registers
+constexpr int SEL_CAP = 64;              // candidates of the exact finish: one per lane
 
 // entries of a sequence's row and how many of them the budget asks for (UNIT = tokens per entry: 16 or 1)
 template <int UNIT>
@@ -27,186 +30,184 @@ __device__ __forceinline__ void tw_select_sizes(int n, int B, int max_pages, int
   *K_out = (int)kp;
 }
 
-// The Kp (0 < Kp < P) largest of sc[0..P), ties to the lower index, written in ascending index order to out[0..Kp)
-// (global) and, when given, to out_lds.  Called by all NT threads of the workgroup.  LDS of the caller: key_s[P],
-// hist[SEL_NB], ck[SEL_CAP], ci[SEL_CAP].  SB: first phase-stamp slot (timing builds).
-// EMAX > 0 (rows of at most EMAX * NT entries): thread t brings a value for each of the E entries [t * E, (t + 1) * E)
-// it will list - pay[e] for entry t * E + e - which goes to pay_lds in list order for the selected ones; E =
-// ceil(P / NT).  PRE: the caller asked for everything before it knew the row's length: E = EMAX, and pre[e] holds the
-// score of entry e * NT + t (sc is then not read).
-template <int NT, int SB, int EMAX = 0, bool PRE = false>
-__device__ __forceinline__ void tw_select_row(const float* sc, int P, int Kp, int max_sel, int32_t* out, int32_t* out_lds,
-                                              uint32_t* key_s, uint32_t* hist, uint32_t* ck, int32_t* ci,
-                                              const int32_t* pay = nullptr, int32_t* pay_lds = nullptr,
-                                              const float* pre = nullptr) {
-  constexpr int NW = NT / 64, BPT = SEL_NB / NT;      // waves; histogram buckets per thread
+// Exclusive prefix over `entries` (<= 64 * Q) per-wave counts in LDS, computed by every wave on its own: entry
+// 64 * q + l ends up in excl[q] of lane l.
+template <int Q>
+__device__ __forceinline__ void tw_seg_prefix(const uint32_t* cnt, int entries, uint32_t (&excl)[Q], uint32_t* total) {
+  const int lane = threadIdx.x & 63;
+  uint32_t base = 0;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const uint32_t v = q * 64 + lane < entries ? cnt[q * 64 + lane] : 0u;
+    const uint32_t incl = tw_wave_scan_u32(v);
+    excl[q] = base + incl - v;
+    base += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+  }
+  *total = base;
+}
+
+// Threshold of the Kp (0 < Kp < P) largest of the row's keys, ties to the lower index: the entries with a key above
+// *T_out and the first *need_eq_out of those equal to it.  key[e] of thread t is entry e * NT + t (taken when below P).
+// Called by all NT threads of the workgroup; hist and cand are LDS of the caller.  SB: first phase-stamp slot (timing builds).
+template <int NT, int E, int SNB, int SB>
+__device__ __forceinline__ void tw_select_threshold(const uint32_t (&key)[E], int P, uint32_t Kp, uint32_t* hist /* [SNB] */,
+                                                    unsigned long long* cand /* [SEL_CAP] */, uint32_t* T_out, uint32_t* need_eq_out) {
+  constexpr int NW = NT / 64, BPL = SNB / 64;         // waves; histogram buckets per lane of a scanning wave
+  constexpr int LB = BPL == 8 ? 3 : (BPL == 16 ? 4 : 5);
+  static_assert(BPL == (1 << LB), "SNB is 512, 1024 or 2048");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ uint32_t red_lo[NW], red_hi[NW];
+  __shared__ uint32_t sh_n;
   TW_STAMP(SB);
 
-  __shared__ uint32_t wsum[16];
-  __shared__ uint32_t red_lo[NW], red_hi[NW];
-  __shared__ uint32_t sh_bkt, sh_need, sh_pop, sh_n, sh_T, sh_need_eq;
-
   uint32_t lo = 0xFFFFFFFFu, hi = 0u;
-  if (PRE) {
 #pragma unroll
-    for (int j = 0; j < (EMAX > 0 ? EMAX : 1); ++j) {
-      const int i = j * NT + tid;
-      if (i < P) {
-        const uint32_t k = tw_float_key(pre[j]);
-        key_s[i] = k;
-        lo = k < lo ? k : lo;
-        hi = k > hi ? k : hi;
-      }
-    }
-  } else
-  for (int base = 0; base < P; base += 8 * NT) {    // 8 clamped loads in flight per thread
-    float v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) { const int i = base + j * NT + tid; v[j] = sc[i < P ? i : P - 1]; }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int i = base + j * NT + tid;
-      if (i < P) {
-        const uint32_t k = tw_float_key(v[j]);
-        key_s[i] = k;
-        lo = k < lo ? k : lo;
-        hi = k > hi ? k : hi;
-      }
+  for (int e = 0; e < E; ++e) {
+    if (e * NT + tid < P) {
+      lo = key[e] < lo ? key[e] : lo;
+      hi = key[e] > hi ? key[e] : hi;
     }
   }
   lo = ~tw_wave_max_u32(~lo);
   hi = tw_wave_max_u32(hi);
   if (lane == 0) { red_lo[wave] = lo; red_hi[wave] = hi; }
   if (tid == 0) sh_n = 0;
-  for (int i = tid; i < SEL_NB; i += NT) hist[i] = 0;     // for the first pass (cleared again before any later one)
+  if (tid < SEL_CAP) cand[tid] = 0;
+  for (int i = tid; i < SNB; i += NT) hist[i] = 0;
   __syncthreads();
-  uint32_t klo = red_lo[0], khi = red_hi[0];
-#pragma unroll
-  for (int w = 1; w < NW; ++w) { klo = red_lo[w] < klo ? red_lo[w] : klo; khi = red_hi[w] > khi ? red_hi[w] : khi; }
+  uint32_t klo = ~tw_row_max_u32(~red_lo[lane & (NW - 1)]), khi = tw_row_max_u32(red_hi[lane & (NW - 1)]);
+  klo = (uint32_t)__builtin_amdgcn_readfirstlane((int)klo);
+  khi = (uint32_t)__builtin_amdgcn_readfirstlane((int)khi);
 
-  uint32_t need = (uint32_t)Kp, T = 0, need_eq = 0;
+  constexpr bool KEEP = E <= 8;
+  int kept_bk[KEEP ? E : 1];
+  uint32_t need = Kp, T = 0, need_eq = 0;
   TW_STAMP(SB + 1);
 #pragma unroll 1
   for (int pass = 0;; ++pass) {
-    if (pass < 6) TW_STAMP(SB + 2 + pass);
     if (klo == khi) { T = klo; need_eq = need; break; }                    // everything left ties
     const float smn = tw_key_to_float(klo), smx = tw_key_to_float(khi);
-    const float scale = (float)SEL_NB / (smx - smn);
-    // Buckets are linear in the bound's value while that works: a finite scale over a normal span, and only
-    // for the first passes.  Otherwise (spans in the subnormal range, infinite bounds, rows that keep falling
-    // into one bucket) they are linear in the order-preserving key, which splits any span of at least 2048
-    // keys 2048 ways and resolves a shorter one exactly, so every pass narrows the interval.
+    const float scale = (float)SNB / (smx - smn);
+    // Buckets are linear in the score's value while that works: a finite scale over a normal span, and only
+    // for the first passes.  Otherwise (spans in the subnormal range, infinite scores, rows that keep falling
+    // into one bucket) they are linear in the order-preserving key, which splits any span of at least SNB
+    // keys SNB ways and resolves a shorter one exactly, so every pass narrows the interval.
     const bool by_key = !(scale <= 3.0e38f) || !(smx - smn >= 1.1754944e-38f) || pass >= 3;
     const uint32_t span = khi - klo;
-    const int kshift = span < (uint32_t)SEL_NB ? 0 : 32 - __clz(span) - 11;
+    const int kshift = span < (uint32_t)SNB ? 0 : 32 - __clz(span) - (LB + 6);
     auto bucket_of = [&](uint32_t k) -> int {
       if (by_key) return (int)((k - klo) >> kshift);
       const int bk = (int)((tw_key_to_float(k) - smn) * scale);
-      return bk > SEL_NB - 1 ? SEL_NB - 1 : (bk < 0 ? 0 : bk);
+      return bk > SNB - 1 ? SNB - 1 : (bk < 0 ? 0 : bk);
+    };
+    // is entry e of this thread in bucket bkt?  (rows of up to 8 entries per thread keep the bucket numbers)
+    auto in_bucket = [&](int e, int bkt) -> bool {
+      if (KEEP) return kept_bk[KEEP ? e : 0] == bkt;
+      return e * NT + tid < P && key[e] >= klo && key[e] <= khi && bucket_of(key[e]) == bkt;
     };
     if (pass > 0) {
-      for (int i = tid; i < SEL_NB; i += NT) hist[i] = 0;
+      for (int i = tid; i < SNB; i += NT) hist[i] = 0;
       __syncthreads();
     }
-    for (int i = tid; i < P; i += NT) {
-      const uint32_t k = key_s[i];
-      if (k >= klo && k <= khi) atomicAdd(&hist[bucket_of(k)], 1u);
-    }
-    __syncthreads();
-    // thread t owns the BPT buckets below 2047 - BPT*t, walked downwards
-    uint32_t c[BPT], mine = 0;
+    // Bucket b is counted in word (r mod BPL) * 64 + r / BPL, r = SNB - 1 - b: the scanning lane l, which owns the BPL
+    // buckets r = BPL * l .. from the top, then reads words j * 64 + l - consecutive lanes, consecutive banks.
 #pragma unroll
-    for (int j = 0; j < BPT; ++j) { c[j] = hist[SEL_NB - 1 - (BPT * tid + j)]; mine += c[j]; }
-    uint32_t total;
-    const uint32_t incl = tw_block_scan_u32_open(mine, wsum, &total);   // (wsum is next written behind the barrier below)
-    uint32_t above = incl - mine;
-    if (above < need && incl >= need) {
-#pragma unroll
-      for (int j = 0; j < BPT; ++j) {
-        if (above < need && above + c[j] >= need) { sh_bkt = SEL_NB - 1 - (BPT * tid + j); sh_need = need - above; sh_pop = c[j]; }
-        above += c[j];
+    for (int e = 0; e < E; ++e) {
+      const bool in = e * NT + tid < P && key[e] >= klo && key[e] <= khi;
+      const int bk = bucket_of(key[e]);
+      if (KEEP) kept_bk[KEEP ? e : 0] = in ? bk : -1;
+      if (in) {
+        const int r = SNB - 1 - bk;
+        atomicAdd(&hist[((r & (BPL - 1)) << 6) | (r >> LB)], 1u);
       }
     }
     __syncthreads();
-    const int bkt = (int)sh_bkt;
-    need = sh_need;
-    const uint32_t pop = sh_pop;
-    // narrow to the keys of that bucket; collect them when few enough for the exact finish
-    const bool small = pop <= SEL_CAP && pop != need;
-    uint32_t nlo = 0xFFFFFFFFu, nhi = 0u;
-    for (int i = tid; i < P; i += NT) {
-      const uint32_t k = key_s[i];
-      if (k >= klo && k <= khi) {
-        if (bucket_of(k) == bkt) {
-          nlo = k < nlo ? k : nlo;
-          nhi = k > nhi ? k : nhi;
-          if (small) { const uint32_t at = atomicAdd(&sh_n, 1u); if (at < SEL_CAP) { ck[at] = k; ci[at] = i; } }
+    TW_STAMP(SB + 2);
+    uint32_t c[BPL], mine = 0;
+#pragma unroll
+    for (int j = 0; j < BPL; ++j) { c[j] = hist[j * 64 + lane]; mine += c[j]; }
+    uint32_t above = tw_wave_scan_u32(mine) - mine;
+    const int src = __ffsll((long long)__ballot(above < need && above + mine >= need)) - 1;   // the interval holds the threshold
+    uint32_t asel = 0, csel = 0;
+    int jsel = 0;
+#pragma unroll
+    for (int j = 0; j < BPL; ++j) {
+      if (above < need && above + c[j] >= need) { jsel = j; asel = above; csel = c[j]; }
+      above += c[j];
+    }
+    const int bkt = SNB - 1 - (BPL * src + __builtin_amdgcn_readlane(jsel, src));
+    need -= (uint32_t)__builtin_amdgcn_readlane((int)asel, src);
+    const uint32_t pop = (uint32_t)__builtin_amdgcn_readlane((int)csel, src);
+    if (pop <= (uint32_t)SEL_CAP) {
+      // exact: the bucket's keys, with the lower index the larger of two equals, ranked by every wave on its own - one
+      // candidate per lane; the one of rank need - 1 is the last one taken
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int i = e * NT + tid;
+        if (in_bucket(e, bkt)) {
+          const uint32_t at = atomicAdd(&sh_n, 1u);
+          if (at < (uint32_t)SEL_CAP) cand[at] = ((unsigned long long)key[e] << 32) | (uint32_t)~i;
         }
+      }
+      __syncthreads();
+      TW_STAMP(SB + 3);
+      const unsigned long long mineK = cand[lane];                         // 0 beyond pop: below every candidate
+      uint32_t rank = 0;
+#pragma unroll 1
+      for (uint32_t j0 = 0; j0 < pop; j0 += 8) {
+#pragma unroll
+        for (uint32_t j = 0; j < 8; ++j) rank += cand[j0 + j] > mineK ? 1u : 0u;
+      }
+      const int last = __ffsll((long long)__ballot((uint32_t)lane < pop && rank == need - 1)) - 1;
+      T = (uint32_t)__builtin_amdgcn_readlane((int)(mineK >> 32), last);
+      // how many of the keys equal to T are taken: those ranked up to `last`
+      need_eq = (uint32_t)__popcll(__ballot((uint32_t)lane < pop && (uint32_t)(mineK >> 32) == T && rank <= need - 1));
+      break;
+    }
+    // narrow to the bucket's keys
+    uint32_t nlo = 0xFFFFFFFFu, nhi = 0u;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      if (in_bucket(e, bkt)) {
+        nlo = key[e] < nlo ? key[e] : nlo;
+        nhi = key[e] > nhi ? key[e] : nhi;
       }
     }
     nlo = ~tw_wave_max_u32(~nlo);
     nhi = tw_wave_max_u32(nhi);
     if (lane == 0) { red_lo[wave] = nlo; red_hi[wave] = nhi; }
     __syncthreads();
-    klo = red_lo[0]; khi = red_hi[0];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) { klo = red_lo[w] < klo ? red_lo[w] : klo; khi = red_hi[w] > khi ? red_hi[w] : khi; }
+    klo = (uint32_t)__builtin_amdgcn_readfirstlane((int)~tw_row_max_u32(~red_lo[lane & (NW - 1)]));
+    khi = (uint32_t)__builtin_amdgcn_readfirstlane((int)tw_row_max_u32(red_hi[lane & (NW - 1)]));
     if (pop == need) { T = klo; need_eq = 0xFFFFFFFFu; break; }   // the whole bucket is taken
-    if (small) {
-      // exact: the candidate of rank need-1 (by bound, then by lower page id) is the last one taken
-      if (tid < (int)pop) {
-        const uint32_t kx = ck[tid];
-        const int ix = ci[tid];
-        uint32_t rank = 0, eq_lower = 0;
-        for (uint32_t j = 0; j < pop; ++j) {
-          const uint32_t kj = ck[j];
-          const int ij = ci[j];
-          rank += (kj > kx || (kj == kx && ij < ix)) ? 1u : 0u;
-          eq_lower += (kj == kx && ij < ix) ? 1u : 0u;
-        }
-        if (rank == need - 1) { sh_T = kx; sh_need_eq = eq_lower + 1; }
-      }
-      __syncthreads();
-      T = sh_T;
-      need_eq = sh_need_eq;
-      break;
-    }
     __syncthreads();                              // red_* and hist are rewritten by the next pass
   }
+  TW_STAMP(SB + 4);
+  *T_out = T;
+  *need_eq_out = need_eq;
+}
 
-  TW_STAMP(SB + 10);
-  // ---- ordered emit: thread t owns the contiguous pages [t*E, (t+1)*E)
-  const int E = PRE ? EMAX : (P + NT - 1) / NT;
-  const int i0 = tid * E, i1 = (i0 + E < P) ? i0 + E : P;
-  uint32_t gt = 0, eq = 0;
-  for (int i = i0; i < i1; ++i) { const uint32_t k = key_s[i]; gt += k > T ? 1u : 0u; eq += k == T ? 1u : 0u; }
-  uint32_t total;
-  const uint32_t incl = tw_block_scan_u32_open(gt | (eq << 16), wsum, &total);   // (last use of wsum)
-  uint32_t gt_before = (incl & 0xFFFFu) - gt, eq_before = (incl >> 16) - eq;
-  if (EMAX > 0) {
+// Ordered listing behind tw_select_threshold: put(pos, e) is called for every selected entry e * NT + t of this thread
+// with its place in the ascending list.  cnt: LDS of the caller, E * NT / 64 words.  Called by all NT threads; one barrier.
+template <int NT, int E, class Put>
+__device__ __forceinline__ void tw_select_list(const uint32_t (&key)[E], int P, uint32_t T, uint32_t need_eq, uint32_t* cnt, Put put) {
+  constexpr int NW = NT / 64, SEGS = E * NW, Q = (SEGS + 63) / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 #pragma unroll
-    for (int e = 0; e < (EMAX > 0 ? EMAX : 1); ++e) {
-      const int i = i0 + e;
-      if (i < i1) {
-        const uint32_t k = key_s[i];
-        if (k > T || (k == T && eq_before < need_eq)) {
-          const uint32_t pos = gt_before + (eq_before < need_eq ? eq_before : need_eq);
-          if (pos < (uint32_t)max_sel) { out[pos] = i; out_lds[pos] = i; pay_lds[pos] = pay[e]; }
-        }
-        gt_before += k > T ? 1u : 0u;
-        eq_before += k == T ? 1u : 0u;
-      }
-    }
-  } else
-  for (int i = i0; i < i1; ++i) {
-    const uint32_t k = key_s[i];
-    if (k > T || (k == T && eq_before < need_eq)) {
-      const uint32_t pos = gt_before + (eq_before < need_eq ? eq_before : need_eq);
-      if (pos < (uint32_t)max_sel) { out[pos] = i; if (out_lds) out_lds[pos] = i; }
-    }
-    gt_before += k > T ? 1u : 0u;
-    eq_before += k == T ? 1u : 0u;
+  for (int e = 0; e < E; ++e) {
+    const bool in = e * NT + tid < P;
+    const uint32_t gt = (uint32_t)__popcll(__ballot(in && key[e] > T)), eq = (uint32_t)__popcll(__ballot(in && key[e] == T));
+    if (lane == 0) cnt[e * NW + wave] = gt | (eq << 16);
   }
-  TW_STAMP(SB + 11);
+  __syncthreads();
+  uint32_t excl[Q], total;
+  tw_seg_prefix<Q>(cnt, SEGS, excl, &total);
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const bool in = e * NT + tid < P, gt = in && key[e] > T, eq = in && key[e] == T;
+    const unsigned long long bg = __ballot(gt), be = __ballot(eq);
+    const uint32_t off = (uint32_t)__builtin_amdgcn_readlane((int)excl[(e * NW) >> 6], ((e * NW) & 63) + wave);
+    const uint32_t gt_before = (off & 0xFFFFu) + tw_bits_below(bg), eq_before = (off >> 16) + tw_bits_below(be);
+    if (gt || (eq && eq_before < need_eq)) put(gt_before + (eq_before < need_eq ? eq_before : need_eq), e);
+  }
 }

@@ -7,8 +7,9 @@
 //              fp32 order: 8 dims left to right per lane, then a pairwise
 //              DPP tree over the 16 lanes (bit-reproducible).
 // page_select: per (sequence, query head) the Kp largest bounds, ties to the
-//              lower page id, by a 4 x 8-bit radix select on the order-
-//              preserving key, then an ordered compaction (ascending ids).
+//              lower page id, ascending: rows of up to 32768 entries in
+//              registers (select_body.h), longer ones by a 4 x 8-bit radix
+//              select on the order-preserving key over global memory.
 //
 // page_score<G, true> also appends the decode step's one new token per sequence on its way
 // (twilight_append_select): the 16 lanes that own the page the token falls into store its K/V
@@ -206,7 +207,7 @@ struct SelectArgs {
   int32_t* sel_pages;         // [b][Hq][max_sel]
   int32_t* sel_count;
   int Hq, max_pages, max_sel;
-  int p_above, p_upto;        // the LDS kernel takes the heads with p_above < pages <= p_upto
+  int p_above, p_upto;        // the register kernel takes the heads with p_above < pages <= p_upto
 };
 // The kernels' UNIT parameter = tokens per row entry: 16 = pages (budget and lengths are in tokens), 1 = the rows hold one
 // score per token (channel-sparse token selector; max_pages is then the row length in tokens).
@@ -284,8 +285,10 @@ __global__ __launch_bounds__(256) void page_select_kernel(SelectArgs a) {
 }
 
 
-template <int NT, int UNIT>
-__global__ __launch_bounds__(NT) void page_select_lds_kernel(SelectArgs a) {
+// Rows of at most NT * E entries, the keys in registers.
+template <int NT, int E, int UNIT>
+__global__ __launch_bounds__(NT) void page_select_reg_kernel(SelectArgs a) {
+  constexpr int SNB = E > 8 ? 2048 : (NT > 256 ? 1024 : 512);
   const int b = blockIdx.y, h = blockIdx.x, tid = threadIdx.x;
   int P, Kp;
   tw_select_sizes<UNIT>(a, a.seq_lens[b], a.budget[b], &P, &Kp);
@@ -298,11 +301,21 @@ __global__ __launch_bounds__(NT) void page_select_lds_kernel(SelectArgs a) {
     for (int i = tid; i < P; i += NT) out[i] = i;
     return;
   }
-  extern __shared__ uint32_t key_s[];             // one key per row entry (the launch sizes it to the row bound)
-  __shared__ uint32_t hist[SEL_NB];
-  __shared__ uint32_t ck[SEL_CAP];
-  __shared__ int32_t ci[SEL_CAP];
-  tw_select_row<NT, 10>(sc, P, Kp, a.max_sel, out, nullptr, key_s, hist, ck, ci);
+  __shared__ uint32_t hist[SNB];
+  __shared__ unsigned long long cand[SEL_CAP];
+  __shared__ uint32_t cnt[E * NT / 64];
+  uint32_t key[E], T, need_eq;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {                   // clamped loads, all in flight
+    const int i = e * NT + tid;
+    key[e] = __float_as_uint(sc[i < P ? i : P - 1]);
+  }
+#pragma unroll
+  for (int e = 0; e < E; ++e) key[e] = tw_float_key(__uint_as_float(key[e]));
+  tw_select_threshold<NT, E, SNB, 10>(key, P, (uint32_t)Kp, hist, cand, &T, &need_eq);
+  tw_select_list<NT, E>(key, P, T, need_eq, cnt, [&](uint32_t pos, int e) {
+    if (pos < (uint32_t)a.max_sel) out[pos] = e * NT + tid;
+  });
 }
 
 template <int G>
@@ -321,34 +334,18 @@ extern "C" int twilight_debug_stamps_select(unsigned long long* host_out) {
 }
 #endif
 
-// Rows of more than 12288 entries need more dynamic LDS than a launch may ask for by default: raised once per device.
-template <int UNIT>
-static bool select_lds_big_ok() {
-  static std::atomic<int> done[TW_MAX_DEVICES];   // 0 = not tried, 1 = ok, 2 = refused
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= TW_MAX_DEVICES) return false;
-  int st = done[dev].load(std::memory_order_relaxed);
-  if (st == 0) {
-    const hipError_t e = hipFuncSetAttribute((const void*)page_select_lds_kernel<1024, UNIT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             SEL_LDS_MAX * 4);
-    if (e != hipSuccess) (void)hipGetLastError();
-    st = e == hipSuccess ? 1 : 2;
-    done[dev].store(st, std::memory_order_relaxed);
-  }
-  return st == 1;
-}
-
 // The selection kernels by row length (entries per row = sa.max_pages) and number of heads.
 template <int UNIT>
 static int launch_select(SelectArgs sa, const TwDims& d, hipStream_t s) {
   const int L = sa.max_pages;
   sa.p_above = -1; sa.p_upto = L;
+  const dim3 grid(d.Hq, d.batch);
   // Many heads and rows of up to 8192 entries (ragged batches): the 1024-thread kernel fits two
   // workgroups per CU; rows of at most 2048 entries go to a 256-thread launch of their own.
-  if (L > 2048 && L <= SEL_LDS_PAGES && (long long)d.batch * d.Hq > 2ll * tw_num_cus()) {
+  if (L > 2048 && L <= SEL_REG_PAGES && (long long)d.batch * d.Hq > 2ll * tw_num_cus()) {
     sa.p_upto = 2048;
     tw_prof_before(TW_K_PAGE_SELECT, s);
-    TW_LAUNCH((page_select_lds_kernel<256, UNIT>), dim3(d.Hq, d.batch), dim3(256), 2048 * 4, s, sa);
+    TW_LAUNCH((page_select_reg_kernel<256, 8, UNIT>), grid, dim3(256), 0, s, sa);
     if (int e = tw_prof_after(s)) return e;
     sa.p_above = 2048; sa.p_upto = L;
   }
@@ -356,12 +353,18 @@ static int launch_select(SelectArgs sa, const TwDims& d, hipStream_t s) {
   // rows of 513..2048 entries: with few heads (at most two workgroups per CU) the 1024-thread variant is the
   // quicker one (6.7 against 8.4 us at 8 x 32 heads x 2048 pages); many heads are better served by small workgroups
   const bool few_heads = (long long)d.batch * d.Hq <= 2ll * tw_num_cus();
-  if (L <= 512 || (L <= 2048 && !few_heads))
-    TW_LAUNCH((page_select_lds_kernel<256, UNIT>), dim3(d.Hq, d.batch), dim3(256), (size_t)L * 4, s, sa);
-  else if (L <= SEL_LDS_MAX && ((size_t)L * 4 <= 48 * 1024 || select_lds_big_ok<UNIT>()))
-    TW_LAUNCH((page_select_lds_kernel<1024, UNIT>), dim3(d.Hq, d.batch), dim3(1024), (size_t)L * 4, s, sa);
+  if (L <= 512)
+    TW_LAUNCH((page_select_reg_kernel<256, 2, UNIT>), grid, dim3(256), 0, s, sa);
+  else if (L <= 2048 && !few_heads)
+    TW_LAUNCH((page_select_reg_kernel<256, 8, UNIT>), grid, dim3(256), 0, s, sa);
+  else if (L <= 2048)
+    TW_LAUNCH((page_select_reg_kernel<1024, 2, UNIT>), grid, dim3(1024), 0, s, sa);
+  else if (L <= SEL_REG_PAGES)
+    TW_LAUNCH((page_select_reg_kernel<1024, 8, UNIT>), grid, dim3(1024), 0, s, sa);
+  else if (L <= SEL_REG_MAX)
+    TW_LAUNCH((page_select_reg_kernel<1024, 32, UNIT>), grid, dim3(1024), 0, s, sa);
   else
-    TW_LAUNCH(page_select_kernel<UNIT>, dim3(d.Hq, d.batch), dim3(256), 0, s, sa);
+    TW_LAUNCH(page_select_kernel<UNIT>, grid, dim3(256), 0, s, sa);
   return tw_prof_after(s);
 }
 

@@ -596,14 +596,13 @@ __global__ __launch_bounds__(NT, NT == 512 ? 6 : 1) void topp_head_kernel(HeadAr
   const int b = b_, h = h_;
   const int bh = b * a.Hq + h;
   // FUSE == 2: everything the page selection reads is asked for here, before the sequence's length is known (any
-  // entry of the head's row of bounds and of the sequence's page-table row may be read): the bounds of the pages
-  // j * NT + tid and the page-table entries of the pages tid * SEL_E + e, which this thread will list
-  // (1024-thread workgroups, 4 entries each; the 512-thread form, short of registers, asks when it knows the length)
+  // entry of the head's row of bounds and of the sequence's page-table row may be read): the bounds and the
+  // page-table entries of the pages j * NT + tid, which this thread will list (1024-thread workgroups, 4 entries each; the 512-thread form, short of registers, asks when it knows the length)
   constexpr int SEL_E = 4096 / NT;
   constexpr bool SEL_EARLY = FUSE == 2 && NT >= 1024;
   const int n = a.seq_lens[b];
   const int budget_b = FUSE == 2 ? a.budget[b] : 0;
-  float sel_pre[SEL_EARLY ? SEL_E : 1];
+  float sel_pre[FUSE == 2 ? SEL_E : 1];
   int32_t sel_pt[FUSE == 2 ? SEL_E : 1];
   // (when the heads are split over two launches by list length, half the workgroups of each return at once: those
   //  must not leave with loads in flight, so the loads then follow the test)
@@ -611,9 +610,9 @@ __global__ __launch_bounds__(NT, NT == 512 ? 6 : 1) void topp_head_kernel(HeadAr
   auto ask_selection = [&]() {
 #pragma unroll
     for (int j = 0; j < SEL_E; ++j) {
-      const int i = j * NT + tid, e = tid * SEL_E + j;
-      sel_pre[SEL_EARLY ? j : 0] = a.bounds[(long long)bh * a.max_pages + (i < a.max_pages ? i : a.max_pages - 1)];
-      sel_pt[SEL_EARLY ? j : 0] = a.page_table[(long long)b * a.max_pages + (e < a.max_pages ? e : a.max_pages - 1)];
+      const int i = j * NT + tid < a.max_pages ? j * NT + tid : a.max_pages - 1;
+      sel_pre[SEL_EARLY ? j : 0] = a.bounds[(long long)bh * a.max_pages + i];
+      sel_pt[SEL_EARLY ? j : 0] = a.page_table[(long long)b * a.max_pages + i];
     }
   };
   // FUSE: this thread's element of the query, asked for early too (no branch around the load: all threads read)
@@ -661,27 +660,39 @@ __global__ __launch_bounds__(NT, NT == 512 ? 6 : 1) void topp_head_kernel(HeadAr
   __shared__ int32_t pages_s[FUSE == 2 ? 512 : 1];   // FUSE == 2: the head's page list ...
   __shared__ int32_t pool_s[FUSE == 2 ? 512 : 1];    // ... and the pages' places in the pool
   if (FUSE == 2) {
-    static_assert(4096 + SEL_NB + 2 * SEL_CAP <= HP_BITMAP_WORDS + HP_USTAGE, "the selection's arrays lie in big_s");
+    constexpr int SNB = 512;
+    uint32_t* const hist = big_s;                   // the selection's arrays lie in big_s
+    unsigned long long* const cand = (unsigned long long*)(big_s + SNB);
+    uint32_t* const cnt = big_s + SNB + 2 * SEL_CAP;
     int32_t* const out = a.sel_pages_w + (long long)bh * a.max_sel;
     const int32_t* const ptab = a.page_table + (long long)b * a.max_pages;
     if (tid == 0) a.sel_count_w[bh] = count;
     if (count == P) {                               // the budget covers the sequence (block-uniform)
       for (int i = tid; i < P; i += NT) { out[i] = i; pages_s[i] = i; pool_s[i] = ptab[i]; }
     } else if (count > 0) {
-      if (SEL_EARLY) {
-        tw_select_row<NT, 30, SEL_E, true>(nullptr, P, count, a.max_sel, out, pages_s, big_s, big_s + 4096, big_s + 4096 + SEL_NB,
-                                           (int32_t*)(big_s + 4096 + SEL_NB + SEL_CAP), sel_pt, pool_s, sel_pre);
-      } else {
-        // page-table entries of the pages this thread will list, in flight while the threshold is found
-        const int E = (P + NT - 1) / NT;
+      if (!SEL_EARLY) {
+        const float* const sc = a.bounds + (long long)bh * a.max_pages;
 #pragma unroll
-        for (int e = 0; e < SEL_E; ++e) { const int i = tid * E + e; sel_pt[FUSE == 2 ? e : 0] = ptab[i < P ? i : P - 1]; }
-        tw_select_row<NT, 30, SEL_E, false>(a.bounds + (long long)bh * a.max_pages, P, count, a.max_sel, out, pages_s, big_s,
-                                            big_s + 4096, big_s + 4096 + SEL_NB, (int32_t*)(big_s + 4096 + SEL_NB + SEL_CAP),
-                                            sel_pt, pool_s);
+        for (int e = 0; e < SEL_E; ++e) {
+          const int i = e * NT + tid < P ? e * NT + tid : P - 1;
+          sel_pre[FUSE == 2 ? e : 0] = sc[i];
+          sel_pt[FUSE == 2 ? e : 0] = ptab[i];
+        }
       }
+      uint32_t key[SEL_E], T, need_eq;
+#pragma unroll
+      for (int e = 0; e < SEL_E; ++e) key[e] = tw_float_key(sel_pre[FUSE == 2 ? e : 0]);
+      tw_select_threshold<NT, SEL_E, SNB, 30>(key, P, (uint32_t)count, hist, cand, &T, &need_eq);
+      tw_select_list<NT, SEL_E>(key, P, T, need_eq, cnt, [&](uint32_t pos, int e) {
+        if (pos < (uint32_t)a.max_sel) {
+          out[pos] = e * NT + tid;
+          pages_s[pos] = e * NT + tid;
+          pool_s[pos] = sel_pt[FUSE == 2 ? e : 0];
+        }
+      });
     }
     __syncthreads();                                // list complete; big_s free for the scores
+    TW_STAMP(35);
   }
 
   // ---- scores into registers; logical pages of the owned slots

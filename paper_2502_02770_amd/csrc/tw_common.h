@@ -171,26 +171,40 @@ __device__ __forceinline__ unsigned long long tw_wave_scan_u64(unsigned long lon
   x += tw_dpp64<TW_DPP_BCAST31, 0xC, false>(x);
   return x;
 }
-// Reductions over the 64 lanes; every lane gets the result.
-__device__ __forceinline__ float tw_wave_max_f(float v) {
-  v = fmaxf(v, tw_dpp_f<TW_DPP_XOR1>(v));
-  v = fmaxf(v, tw_dpp_f<TW_DPP_XOR2>(v));
-  v = fmaxf(v, tw_dpp_f<TW_DPP_HALF_MIRROR>(v));
-  v = fmaxf(v, tw_dpp_f<TW_DPP_MIRROR>(v));
-  v = fmaxf(v, __shfl_xor(v, 16, 64));
-  v = fmaxf(v, __shfl_xor(v, 32, 64));
-  return v;
-}
-__device__ __forceinline__ float tw_wave_min_f(float v) { return -tw_wave_max_f(-v); }
-__device__ __forceinline__ uint32_t tw_wave_max_u32(uint32_t v) {
+// Reductions over the 64 lanes; every lane gets the result (a scalar: the rows' results travel through the two row
+// broadcasts to lane 63 and come back by a lane read, which is quicker than two cross-row shuffles through LDS).
+__device__ __forceinline__ uint32_t tw_row_max_u32(uint32_t v) {       // over the 16 lanes of a row
   uint32_t y;
   y = (uint32_t)tw_dpp_i<TW_DPP_XOR1>((int)v); v = y > v ? y : v;
   y = (uint32_t)tw_dpp_i<TW_DPP_XOR2>((int)v); v = y > v ? y : v;
   y = (uint32_t)tw_dpp_i<TW_DPP_HALF_MIRROR>((int)v); v = y > v ? y : v;
   y = (uint32_t)tw_dpp_i<TW_DPP_MIRROR>((int)v); v = y > v ? y : v;
-  y = (uint32_t)__shfl_xor((int)v, 16, 64); v = y > v ? y : v;
-  y = (uint32_t)__shfl_xor((int)v, 32, 64); v = y > v ? y : v;
   return v;
+}
+__device__ __forceinline__ float tw_row_max_f(float v) {
+  v = fmaxf(v, tw_dpp_f<TW_DPP_XOR1>(v));
+  v = fmaxf(v, tw_dpp_f<TW_DPP_XOR2>(v));
+  v = fmaxf(v, tw_dpp_f<TW_DPP_HALF_MIRROR>(v));
+  v = fmaxf(v, tw_dpp_f<TW_DPP_MIRROR>(v));
+  return v;
+}
+__device__ __forceinline__ float tw_wave_max_f(float v) {
+  v = tw_row_max_f(v);
+  v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), TW_DPP_BCAST15, 0xA, 0xF, false)));
+  v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), TW_DPP_BCAST31, 0xC, 0xF, false)));
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+__device__ __forceinline__ uint32_t tw_wave_max_u32(uint32_t v) {
+  v = tw_row_max_u32(v);
+  uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, TW_DPP_BCAST15, 0xA, 0xF, false);
+  v = y > v ? y : v;
+  y = (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, TW_DPP_BCAST31, 0xC, 0xF, false);
+  v = y > v ? y : v;
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+// set bits of `mask` below this lane
+__device__ __forceinline__ uint32_t tw_bits_below(unsigned long long mask) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
 // Inclusive scan of one u32 per thread over a group of NW consecutive waves
