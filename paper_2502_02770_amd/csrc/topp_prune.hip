@@ -25,6 +25,7 @@ namespace {
 
 constexpr float kInv127 = 0x1.020408p-7f;    // fp32(1/127)
 constexpr float kRsqrtD = 0x1.6a09e6p-4f;    // fp32(1/sqrt(128))
+constexpr float kLog2e = 0x1.715476p+0f;
 
 // ------------------------------------------------------------------ int4_score
 struct ScoreArgs {
@@ -39,6 +40,8 @@ struct ScoreArgs {
   int32_t* dots;              // [b][Hq][cand_stride][4] or nullptr
   uint32_t* arrive;           // [b][Hkv] arrival counters of the top-p kernel that follows, or nullptr
   uint32_t* headmax;          // [b][Hq][HM_SLOTS] keys whose maximum is the head's largest score (atomicMax), or nullptr
+  unsigned long long* ghist;  // [b][Hq][WH_NB] histograms, added to (HIST kernels) ...
+  const WhGrid* hgrid;        // ... over the grids [b][Hq]
   const uint32_t* chmask;     // [Hkv][4] channels of the query that take part (bit d % 32 of word d / 32), or nullptr = all
   int Hq, Hkv, max_pages, max_sel, cand_stride, pw;   // pw: pages per wave (<= 64)
   int rotate;                 // list mode with a grid a multiple of 8 wide: chunk = (column - group % 8) mod width
@@ -46,37 +49,45 @@ struct ScoreArgs {
 };
 
 // q of NH consecutive heads -> int8 (symmetric per head: sq = max|q| * (1/127), round half even),
-// 4 values per word, and c = sq / sqrt(128) per head.  Called by all threads of the block (>= 128).
+// 4 values per word, and c = sq / sqrt(128) per head.  Called by all threads of the block; wave w takes the heads w,
+// w + waves, ..., two values per lane, with all of its loads out first (one head after the other by the whole block, each
+// with its load and two barriers, kept every workgroup of an 8-head scoring launch about 5 us from its first page).
 // chmask: 4 words of the KV head's channel set, or nullptr - channels outside it get the int8 value 0 (the scale sq
 // is that of the whole query), which restricts the estimate to the set (channel-sparse token selector).
-template <int NH>
-__device__ __forceinline__ void tw_quantize_q(const uint16_t* q, int (*qi_s)[32], float* red, float* c_s,
-                                              const uint32_t* chmask = nullptr) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-#pragma unroll 1
-  for (int h = 0; h < NH; ++h) {
-    float v = 0.f;
-    if (tid < 128) v = __uint_as_float((uint32_t)q[h * 128 + tid] << 16);
-    float av = fabsf(v);
+template <int NH, int NT = 256>
+__device__ __forceinline__ void tw_quantize_q(const uint16_t* q, int (*qi_s)[32], float* c_s, const uint32_t* chmask = nullptr) {
+  constexpr int NW = NT / 64, R = (NH + NW - 1) / NW;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t raw[R];
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) av = fmaxf(av, __shfl_xor(av, o, 64));
-    if (lane == 0 && wave < 2) red[wave] = av;     // the 128 values sit in waves 0 and 1
-    __syncthreads();
-    const float amax = fmaxf(red[0], red[1]);
-    const float sq = __fmul_rn(amax, kInv127);
-    if (tid < 128) {
+  for (int r = 0; r < R; ++r) {
+    const int h = wave + r * NW < NH ? wave + r * NW : NH - 1;
+    raw[r] = ((const uint32_t*)q)[h * 64 + lane];
+  }
+  const uint32_t cm = chmask ? chmask[lane >> 4] >> ((2 * lane) & 31) : 3u;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int h = wave + r * NW;
+    const float v[2] = {tw_bf16_lo(raw[r]), tw_bf16_hi(raw[r])};
+    const float sq = __fmul_rn(tw_wave_max_f(fmaxf(fabsf(v[0]), fabsf(v[1]))), kInv127);
+    uint32_t bytes = 0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
       int qi = 0;
       if (sq > 0.f) {
-        float t = rintf(__fdiv_rn(v, sq));
+        float t = rintf(__fdiv_rn(v[i], sq));
         t = fminf(fmaxf(t, -127.f), 127.f);
         qi = (int)t;
       }
-      if (chmask && !((chmask[tid >> 5] >> (tid & 31)) & 1u)) qi = 0;
-      ((int8_t*)qi_s[h])[tid] = (int8_t)qi;
+      if (!((cm >> i) & 1u)) qi = 0;
+      bytes |= ((uint32_t)qi & 0xFFu) << (8 * i);
     }
-    if (tid == 0) c_s[h] = __fmul_rn(sq, kRsqrtD);
-    __syncthreads();
+    if (h < NH) {                                  // wave-uniform
+      ((uint16_t*)qi_s[h])[lane] = (uint16_t)bytes;
+      if (lane == 0) c_s[h] = __fmul_rn(sq, kRsqrtD);
+    }
   }
+  __syncthreads();
 }
 
 // The same for one head whose 128 values the threads 0..127 already hold (v; others pass 0).
@@ -207,9 +218,8 @@ __global__ __launch_bounds__(256) void int4_score_kernel(ScoreArgs a) {
 
   // ---- quantise q of the NH heads to int8 (symmetric, per head)
   __shared__ int qi_s[NH][32];
-  __shared__ float red[4];
   __shared__ float c_s[NH];
-  tw_quantize_q<NH>(a.q + ((long long)(b * a.Hq + h0)) * 128, qi_s, red, c_s, a.chmask ? a.chmask + g * 4 : nullptr);
+  tw_quantize_q<NH>(a.q + ((long long)(b * a.Hq + h0)) * 128, qi_s, c_s, a.chmask ? a.chmask + g * 4 : nullptr);
   const int j = lane & 3;                       // this lane's group of 32 dims
   int qw[NH][8], qs128[NH];
   float qsf[NH], cc[NH];
@@ -343,9 +353,8 @@ __global__ __launch_bounds__(256) void int4_score_tokens_kernel(ScoreArgs a) {
   translate();
 
   __shared__ int qi_s[1][32];
-  __shared__ float red[4];
   __shared__ float c_s[1];
-  tw_quantize_q<1>(a.q + ((long long)(b * a.Hq + h0)) * 128, qi_s, red, c_s);
+  tw_quantize_q<1>(a.q + ((long long)(b * a.Hq + h0)) * 128, qi_s, c_s);
   int qw[8], qs = 0;
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
@@ -396,7 +405,10 @@ __global__ __launch_bounds__(256) void int4_score_tokens_kernel(ScoreArgs a) {
 // operations as the vector kernel, so the scores are bit-identical.
 typedef int tw_i32x4 __attribute__((ext_vector_type(4)));
 
-template <int NHG, bool DOTS, int UNR>           // NHG groups of 4 heads
+// HIST: the long-row pruner's histogram (topp_common.h) is made here, while the scores are in registers: one integer LDS
+// add per score in a kernel that waits for memory.  At 4 x 64 heads x 262144 tokens it costs 9 us of 185, a pass over
+// the stored scores 55 us.  (Floating-point LDS adds of the scores' weights: 360 us.)
+template <int NHG, bool DOTS, int UNR, bool HIST = false>           // NHG groups of 4 heads
 __global__ __launch_bounds__(256) void int4_score_mfma_kernel(ScoreArgs a) {
   constexpr int NH = 4 * NHG;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -421,9 +433,20 @@ __global__ __launch_bounds__(256) void int4_score_mfma_kernel(ScoreArgs a) {
   if (npages > a.pw) npages = a.pw;
 
   __shared__ int qi_s[NH][32];
-  __shared__ float red[4];
   __shared__ float c_s[NH];
-  tw_quantize_q<NH>(a.q + ((long long)(b * a.Hq + h0)) * 128, qi_s, red, c_s, a.chmask ? a.chmask + g * 4 : nullptr);
+  __shared__ uint32_t hist_s[HIST ? NH * WH_LDS : 1];
+  float hinv[NHG], hoff[NHG], hls[NHG];          // t = s * hinv + hoff
+  if (HIST) {
+    for (int i = tid; i < NH * WH_LDS; i += 256) hist_s[i] = 0;
+#pragma unroll
+    for (int hg = 0; hg < NHG; ++hg) {
+      const WhGrid gr = a.hgrid[b * a.Hq + h0 + hg * 4 + (lane >> 4)];
+      hinv[hg] = 1.0f / gr.scale;
+      hoff[hg] = -gr.ref * hinv[hg];
+      hls[hg] = gr.scale * kLog2e;
+    }
+  }
+  tw_quantize_q<NH>(a.q + ((long long)(b * a.Hq + h0)) * 128, qi_s, c_s, a.chmask ? a.chmask + g * 4 : nullptr);
 
   const int kb = lane >> 4, t = lane & 15;       // B operand / result: k-block (= group of dims) or head, token
   // A operand: row m = lane & 15 = 4 * head + group; this lane's k-block only meets its own group
@@ -502,6 +525,11 @@ __global__ __launch_bounds__(256) void int4_score_mfma_kernel(ScoreArgs a) {
           hm[hg] = fmaxf(hm[hg], s);
           const long long row = ((long long)(b * a.Hq + h0 + hg * 4 + kb)) * a.cand_stride;
           a.scores[row + slot] = s;
+          if (HIST) {
+            uint32_t w;
+            const int bk = wh_bucket(__builtin_fmaf(valid ? s : 0.f, hinv[hg], hoff[hg]), hls[hg], &w);
+            atomicAdd(&hist_s[(hg * 4 + kb) * WH_LDS + bk], valid ? w : 0u);
+          }
           if (DOTS) ((tw_i32x4*)a.dots)[row + slot] = valid ? c : tw_i32x4{0, 0, 0, 0};
         }
       }
@@ -526,7 +554,127 @@ __global__ __launch_bounds__(256) void int4_score_mfma_kernel(ScoreArgs a) {
         atomicMax(a.headmax + ((long long)(b * a.Hq + h0 + tid) * HM_SLOTS + (blockIdx.x & (HM_SLOTS - 1))) * TW_CTR, tw_float_key(mx));
     }
   }
+  if (HIST) {
+    __syncthreads();
+    for (int i = tid; i < NH * WH_NB; i += 256) {
+      const int h = i / WH_NB, k = i % WH_NB;
+      const uint32_t c = hist_s[h * WH_LDS + k];
+      if (c) atomicAdd(a.ghist + (long long)(b * a.Hq + h0 + h) * WH_NB + k, (unsigned long long)c);
+    }
+  }
 }
+
+// ------------------------------------------------------------------ sample of a row, for its histogram's grid
+// Ahead of the full-row scoring of the long-row pruner: one workgroup per query head scores 64 pages spread evenly over
+// the sequence (8 waves x 8 pages), and the top-p threshold of the sampled scores (to 1/256 of their range) and their
+// weighted deviation place the head's histogram.  The workgroups beyond the heads clear the workspace words that the passes behind this one add to.
+// Bound by its chain of dependent loads; one workgroup per KV head, scoring its heads one after the other on
+// batch * Hkv of the 256 CUs, took 18.8 us at 4 x 8 groups of 8 heads, this 10.4.
+struct SampleArgs {
+  ScoreArgs s;
+  WhGrid* hgrid;
+  uint4* zero;
+  long long zero16;
+  int heads;                  // batch * Hq
+  float p;
+};
+constexpr int SMP_NT = 512, SMP_ZERO_WGS = 256;
+
+__global__ __launch_bounds__(SMP_NT) void row_sample_kernel(SampleArgs sa) {
+  constexpr int NW = SMP_NT / 64, K = 64 / NW;
+  const ScoreArgs& a = sa.s;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if ((int)blockIdx.x >= sa.heads) {
+    for (long long i = (long long)(blockIdx.x - sa.heads) * SMP_NT + tid; i < sa.zero16; i += (long long)SMP_ZERO_WGS * SMP_NT)
+      sa.zero[i] = make_uint4(0, 0, 0, 0);
+    return;
+  }
+  const int bh = blockIdx.x, b = bh / a.Hq, h = bh % a.Hq, g = h / (a.Hq / a.Hkv);
+  const int n = a.seq_lens[b];
+  int P = n > 0 ? (n + TW_PAGE - 1) / TW_PAGE : 0;
+  if (P > a.max_pages) P = a.max_pages;
+  uint4 raw[K][1];
+  uint32_t meta[K];
+  int lp[K];
+  bool ok[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    lp[k] = (int)(((long long)(wave * K + k) * P) >> 6);           // below P (0 when there is none)
+    const int pp = a.page_table[(long long)b * a.max_pages + lp[k]];
+    ok[k] = P > 0 && pp >= 0 && pp < a.pool_pages;
+    const long long blk = ((long long)(ok[k] ? pp : 0) * a.Hkv + g) * 64;
+    tw_load_raw<4>(a.kq_pool, blk + lane, raw[k]);
+    meta[k] = a.kq_meta[blk + lane];
+  }
+  __shared__ int qi_s[1][32];
+  __shared__ float c_s[1];
+  __shared__ float mx_s[NW], sum_s[NW][3];
+  tw_quantize_q<1, SMP_NT>(a.q + (long long)bh * 128, qi_s, c_s);
+  const int j = lane & 3;
+  int qw[8], qs = 0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    qw[k] = qi_s[0][8 * j + k];
+    qs = __builtin_amdgcn_sdot4(qw[k], 0x01010101, qs, false);
+  }
+  float sv[K], mx = -__builtin_inff();
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    int u[8];
+    tw_unpack_codes<4>(raw[k], u);
+    const float T = tw_token_sum(meta[k], tw_group_dot(qw, u, 0), (float)qs);
+    sv[k] = ok[k] && lp[k] * TW_PAGE + (lane >> 2) < n ? __fmul_rn(T, c_s[0]) : -__builtin_inff();
+    mx = fmaxf(mx, sv[k]);
+  }
+  mx = tw_wave_max_f(mx);
+  if (lane == 0) mx_s[wave] = mx;
+  __syncthreads();
+  mx = mx_s[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) mx = fmaxf(mx, mx_s[w]);
+  const bool some = mx > -__builtin_inff() && mx < __builtin_inff();
+  float w0 = 0.f, w1 = 0.f, w2 = 0.f;              // (all four lanes of a token's quad: the sums' ratios do not mind)
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    if (some && sv[k] > -__builtin_inff()) {
+      const float t = sv[k] - mx, w = __expf(t);
+      w0 += w; w1 += w * t; w2 += w * t * t;
+    }
+  }
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) { w0 += __shfl_xor(w0, o, 64); w1 += __shfl_xor(w1, o, 64); w2 += __shfl_xor(w2, o, 64); }
+  if (lane == 0) { sum_s[wave][0] = w0; sum_s[wave][1] = w1; sum_s[wave][2] = w2; }
+  __syncthreads();
+  __shared__ uint32_t hist_s[256];
+  if (tid < 256) hist_s[tid] = 0;
+  __syncthreads();
+  w0 = w1 = w2 = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) { w0 += sum_s[w][0]; w1 += sum_s[w][1]; w2 += sum_s[w][2]; }
+  WhGrid gr = wh_grid(w0, w1, w2);                 // ref relative to mx, and below it
+  const float reach = 16.0f * gr.scale - gr.ref;   // from the maximum to four deviations below that first guess
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const float d = mx - sv[k];
+    if (some && j == 0 && d < reach) atomicAdd(&hist_s[(int)(d / reach * 255.0f)], (uint32_t)(__expf(-d) * 1048576.0f));
+  }
+  __syncthreads();
+  if (wave == 0) {
+    uint32_t c[4], mine = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) { mine += hist_s[4 * lane + k]; c[k] = mine; }
+    const uint32_t incl = tw_wave_scan_u32(mine);
+    const float target = sa.p * (float)__shfl(incl, 63, 64);
+    int bin = 4 * lane + 3;
+#pragma unroll
+    for (int k = 2; k >= 0; --k) bin = (float)(incl - mine + c[k]) >= target ? 4 * lane + k : bin;
+    const int at = __ffsll((long long)__ballot((float)incl >= target)) - 1;
+    if (some && at >= 0) gr.ref = -((float)__shfl(bin, at, 64) + 0.5f) * (1.0f / 255.0f) * reach;
+    if (some) gr.ref += mx;
+    if (lane == 0) sa.hgrid[bh] = gr;
+  }
+}
+
 
 // ------------------------------------------------------------------ top-p per head, scores in registers
 // One workgroup (1024 threads, or 512 for the short rows of a split launch) per
@@ -1194,11 +1342,14 @@ void launch_score(const ScoreArgs& a, dim3 grid, bool dots, int bits, hipStream_
   else TW_LAUNCH((int4_score_kernel<NH, FULL, false, 2>), grid, dim3(256), 0, s, a);
 }
 
+bool score_uses_mfma(const TwDims& d, bool full) { return full && d.G >= 4 && d.bits == 4; }
+
 int run_score(const twilight_kv_t* kv, const TwDims& d, const void* q, const int32_t* sel_pages,
               const int32_t* sel_count, int32_t max_sel, float* scores, int32_t* dots, uint32_t* arrive,
-              uint32_t* headmax, hipStream_t s, const uint32_t* chmask = nullptr) {
+              uint32_t* headmax, hipStream_t s, const uint32_t* chmask = nullptr, unsigned long long* ghist = nullptr,
+              const WhGrid* hgrid = nullptr) {
   ScoreArgs a;
-  a.arrive = arrive; a.headmax = headmax; a.chmask = chmask;
+  a.arrive = arrive; a.headmax = headmax; a.chmask = chmask; a.ghist = ghist; a.hgrid = hgrid;
   a.q = (const uint16_t*)q; a.sel_pages = sel_pages; a.sel_count = sel_count;
   a.page_table = kv->page_table; a.seq_lens = kv->seq_lens;
   a.kq_pool = (const uint4*)kv->kq_pool; a.kq_meta = (const uint32_t*)kv->kq_meta;
@@ -1212,7 +1363,7 @@ int run_score(const twilight_kv_t* kv, const TwDims& d, const void* q, const int
 #ifdef TW_TUNING                                 // tuning builds only: the shipped library reads no environment
   static const int pw_env = getenv("TW_INT4_PW") ? atoi(getenv("TW_INT4_PW")) : 0;
   static const int x_env = getenv("TW_INT4_X") ? atoi(getenv("TW_INT4_X")) : 0;
-  static const bool valu_only = getenv("TW_INT4_VALU") != nullptr;   // vector-ALU kernel for every G
+  static const bool valu_only = getenv("TW_INT4_VALU") && !ghist;   // vector-ALU kernel for every G
 #else
   constexpr int pw_env = 0, x_env = 0;
   constexpr bool valu_only = false;
@@ -1237,13 +1388,15 @@ int run_score(const twilight_kv_t* kv, const TwDims& d, const void* q, const int
   }
   tw_prof_before(TW_K_INT4_SCORE, s);
   if (!full) launch_score<1, false>(a, grid, dots != nullptr, d.bits, s);
-  else if (d.G >= 4 && d.bits == 4 && !valu_only) {               // matrix-core kernel: 4 or 8 heads share every page
+  else if (score_uses_mfma(d, full) && !valu_only) {              // matrix-core kernel: 4 or 8 heads share every page
     // 8 pages in flight per wave (the kernel needs few registers, so 4 to 7 waves per SIMD stay resident)
     if (d.G == 4) {
       if (dots) TW_LAUNCH((int4_score_mfma_kernel<1, true, 4>), grid, dim3(256), 0, s, a);
+      else if (ghist) TW_LAUNCH((int4_score_mfma_kernel<1, false, 8, true>), grid, dim3(256), 0, s, a);
       else      TW_LAUNCH((int4_score_mfma_kernel<1, false, 8>), grid, dim3(256), 0, s, a);
     } else {
       if (dots) TW_LAUNCH((int4_score_mfma_kernel<2, true, 4>), grid, dim3(256), 0, s, a);
+      else if (ghist) TW_LAUNCH((int4_score_mfma_kernel<2, false, 8, true>), grid, dim3(256), 0, s, a);
       else      TW_LAUNCH((int4_score_mfma_kernel<2, false, 8>), grid, dim3(256), 0, s, a);
     }
   } else switch (d.G) {
@@ -1255,6 +1408,18 @@ int run_score(const twilight_kv_t* kv, const TwDims& d, const void* q, const int
   return tw_prof_after(s);
 }
 
+
+int run_row_sample(const twilight_kv_t* kv, const TwDims& d, const void* q, float p, WhGrid* hgrid, uint4* zero, long long zero16,
+                   hipStream_t s) {
+  SampleArgs a = {};
+  a.s.q = (const uint16_t*)q; a.s.page_table = kv->page_table; a.s.seq_lens = kv->seq_lens;
+  a.s.kq_pool = (const uint4*)kv->kq_pool; a.s.kq_meta = (const uint32_t*)kv->kq_meta;
+  a.s.Hq = d.Hq; a.s.Hkv = d.Hkv; a.s.max_pages = d.max_pages; a.s.pool_pages = d.pool_pages;
+  a.hgrid = hgrid; a.zero = zero; a.zero16 = zero16; a.heads = d.batch * d.Hq; a.p = p;
+  tw_prof_before(TW_K_TOPP, s);
+  TW_LAUNCH(row_sample_kernel, dim3(a.heads + SMP_ZERO_WGS), dim3(SMP_NT), 0, s, a);
+  return tw_prof_after(s);
+}
 
 template <int NT, int EPT, bool TOK, int FUSE>
 void launch_topp_one(const HeadArgs& f, int G, dim3 grid, hipStream_t s) {
@@ -1303,11 +1468,11 @@ int tw_score_all_tokens_masked(const twilight_kv_t* kv, const TwDims& d, const v
   return run_score(kv, d, q, nullptr, nullptr, 0, scores, nullptr, nullptr, nullptr, s, chmask);
 }
 
-int tw_prune_wide_init(const TwDims& d, const PruneWs& L, void* ws, hipStream_t s);
+int tw_prune_wide_init(const PruneWs& L, void* ws, bool full, hipStream_t s);
 int tw_prune_wide(const TwDims& d, const PruneWs& L, void* ws, const twilight_kv_t* kv, const int32_t* sel_pages,
                   const int32_t* sel_count, int max_sel, int cand_stride, float p, int32_t* kept_count,
                   int32_t* kept_idx, int kept_stride, int32_t* union_count, int32_t* union_idx, int union_stride,
-                  uint32_t* status, hipStream_t s);
+                  uint32_t* status, bool hist_done, hipStream_t s);
 
 // Register-resident per-head kernel: per-head lists of at most 8192 candidates on sequences whose
 // position bitmap fits in LDS; everything else takes the multi-workgroup path.
@@ -1325,18 +1490,20 @@ PruneWs tw_prune_layout(const TwDims& d, int bound_pages, bool full) {
   const bool head = tw_prune_uses_head_kernel(d, full, bound_pages);
   L.headmax = o; o += head ? 256 : al(bh * HM_SLOTS * TW_CTR * 4);   // (the long-row path clears from here ...)
   L.arrive = o;  o += al((size_t)d.batch * d.Hkv * TW_CTR * 4);
-  L.bitmaps = o; o += al(bh * (size_t)L.words_stride * 4);
   if (head) {                                                // the long-row buffers are not needed
-    L.ghistM = L.ghistC = L.ucount = L.kdef = L.state = L.ulist = L.segcnt = o;
+    L.bitmaps = o; o += al(bh * (size_t)L.words_stride * 4);
+    L.ghist = L.grid = L.range = L.sums = L.ucount = L.kdef = L.ulist = L.segcnt = o;
     L.total = o;
     return L;
   }
-  L.ghistM = o;  o += al(bh * 2048 * 8);
-  L.ghistC = o;  o += al(bh * 2048 * 4);
+  L.ghist = o;   o += al(bh * WH_NB * 8);
+  L.sums = o;    o += al(bh * WS_SUMS * 8);
   L.ucount = o;  o += al(bh * TW_CTR * 4);
-  L.kdef = o;    o += al(bh * TW_CTR * 4);
-  L.state = o;   o += al(bh * 48);                       // (... up to here)
-  L.ulist = o;   o += al(bh * 4096 * 8);
+  L.kdef = o;    o += al(bh * TW_CTR * 4);               // (... to here, with page lists to the bitmaps' end)
+  L.bitmaps = o; o += al(bh * (size_t)L.words_stride * 4);
+  L.grid = o;    o += al(bh * sizeof(WhGrid));
+  L.range = o;   o += al(bh * 16);
+  L.ulist = o;   o += al(bh * (size_t)WIDE_LIST_CAP * 8);
   L.segcnt = o;  o += al(bh * (size_t)((L.words_stride + 255) / 256) * 4);   // set bits per 256-word segment of a row's bitmap(s)
   L.total = o;
   return L;
@@ -1380,13 +1547,20 @@ extern "C" int twilight_topp_prune(const twilight_kv_t* kv, const void* q, const
   uint32_t* arrive = (uint32_t*)((char*)ws + L.arrive);
   const bool use_head = tw_prune_uses_head_kernel(d, full, bound);
 
-  if (!use_head)
-    if (int e = tw_prune_wide_init(d, L, ws, s)) return e;     // clears headmax before the scoring kernel folds into it
+  const bool hist = !use_head && p < 1.0f && score_uses_mfma(d, full);
+  if (hist) {                                    // the sample's launch clears what the next ones add to
+    if (int e = run_row_sample(kv, d, q, p, (WhGrid*)((char*)ws + L.grid), (uint4*)headmax, (long long)((L.bitmaps - L.headmax) / 16), s))
+      return e;
+  } else if (!use_head) {
+    if (int e = tw_prune_wide_init(L, ws, full, s)) return e;  // clears headmax before the scoring kernel folds into it
+  }
+  unsigned long long* const ghist = hist ? (unsigned long long*)((char*)ws + L.ghist) : nullptr;
+  WhGrid* const hgrid = hist ? (WhGrid*)((char*)ws + L.grid) : nullptr;
   if (int e = run_score(kv, d, q, sel_pages, sel_count, max_sel, scores, nullptr, use_head ? arrive : nullptr,
-                        use_head ? nullptr : headmax, s)) return e;
+                        use_head ? nullptr : headmax, s, nullptr, ghist, hgrid)) return e;
   if (!use_head)
     return tw_prune_wide(d, L, ws, kv, sel_pages, sel_count, max_sel, cand_stride, p, kept_count, kept_idx, kept_stride,
-                         union_count, union_idx, union_stride, status, s);
+                         union_count, union_idx, union_stride, status, hist, s);
 
   // per-head page lists short enough for registers and sequences that fit the LDS bitmap: one
   // launch does top-p per head and, in the last head of each group to finish, the group's union
@@ -1449,7 +1623,7 @@ PruneWs tw_prune_layout_tokens(const TwDims& d, int max_cand) {
   L.headmax = o;
   L.arrive = o;  o += al((size_t)d.batch * d.Hkv * TW_CTR * 4);
   L.bitmaps = o; o += al(bh * (size_t)L.words_stride * 4);
-  L.ghistM = L.ghistC = L.ucount = L.kdef = L.state = L.ulist = L.segcnt = o;
+  L.ghist = L.grid = L.range = L.sums = L.ucount = L.kdef = L.ulist = L.segcnt = o;
   L.total = o;
   return L;
 }
@@ -1458,7 +1632,7 @@ static int run_score_tokens(const twilight_kv_t* kv, const TwDims& d, const void
                             const int32_t* cand_count, int32_t max_cand, float* scores, int32_t* dots,
                             uint32_t* arrive, hipStream_t s) {
   ScoreArgs a;
-  a.arrive = arrive; a.headmax = nullptr; a.chmask = nullptr;
+  a.arrive = arrive; a.headmax = nullptr; a.chmask = nullptr; a.ghist = nullptr; a.hgrid = nullptr;
   a.q = (const uint16_t*)q; a.sel_pages = cand_tokens; a.sel_count = cand_count;
   a.page_table = kv->page_table; a.seq_lens = kv->seq_lens;
   a.kq_pool = (const uint4*)kv->kq_pool; a.kq_meta = (const uint32_t*)kv->kq_meta;

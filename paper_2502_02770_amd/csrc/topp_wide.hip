@@ -1,38 +1,39 @@
 // Stage 2b/c for long candidate rows (paper: Algorithm 1, Definition 3.3,
-// Appendix B.2): the same threshold search as the register-resident kernel,
-// spread over many workgroups per head.  Used when a head has more than 8192
+// Appendix B.2): the threshold set of the register-resident kernel, spread
+// over many workgroups per head.  Used when a head has more than 8192
 // candidates (every token a candidate - no selector in front - or very large
 // budgets) or the sequence is too long for the in-LDS bitmap.
 //
-//   wide_init     clears histograms / lists / bitmaps, resets per-head state
-//   (int4_score   also folds the row maximum into headmax with atomicMax)
-//   wide_hist     one pass over the scores: LDS histogram of the current rank
-//                 interval per workgroup, flushed to the head's global one
-//   wide_decide   one wave per head scans the 2048 buckets and narrows the
-//                 interval (or finishes when <= 4096 scores are left in it,
-//                 which one pass achieves on rows of a million smooth scores)
-//   wide_emit     second pass: kept for sure -> bitmap, undecided -> a short
-//                 per-head list
-//   wide_resolve  finish on the undecided list inside one workgroup (narrowing
+//   row_sample    (topp_prune.hip) scores a sample of the row, which places the head's histogram grid; clears the
+//                 per-head histogram, counters and sums
+//   (scoring      also folds the row maximum into headmax with atomicMax and the scores into the mass histogram)
+//   wide_init, wide_hist   clearing, and grid and histogram from the stored scores: behind the scoring kernels that do
+//                 not make the histogram themselves
+//   wide_decide   one wave per head: the bucket or two of the histogram that the threshold falls into
+//   wide_emit     one pass over the scores: those above the buckets -> bitmap, those inside -> a short per-head list,
+//                 and the exact fixed-point masses of the row and of the scores above
+//   wide_resolve  finds the exact threshold among the listed scores inside one workgroup (narrowing
 //                 in LDS, then exact on the scores' own bits), sets their bits
 //   bitmap_list   bitmap(s) -> ascending index list (per-head kept list, and
 //                 the union of a KV head's query heads)
-// All sums are 64-bit fixed point and all atomics are integer adds / maxima,
-// so results do not depend on scheduling.
+//
+// What bounds it is the traffic of the score rows: written once by the scoring kernel and read once here.  Masses are
+// relative to the row's largest score, which is known only when all are scored, so a histogram of exact masses would
+// take a pass over the rows of its own; masses relative to a histogram grid are enough to say where the
+// threshold lies, and wide_resolve checks that with the exact sums: a row whose threshold is not among its listed
+// scores - or with more than W_CAP of them - is searched again from its scores by wide_resolve.
+// At 4 x 64 heads x 262144 tokens: 322 -> 289 us for the whole pruner (scoring 177 -> 185, emit 52 as before, and no
+// histogram passes: 55 us and four launches of 4 us that found nothing left to do).
+//
+// The deciding sums are 64-bit fixed point over the same terms in any order, so the sets do not depend on scheduling
+// (nor on where the histogram cut).
 #include <stdlib.h>
 #include "topp_common.h"
 
 namespace {
 
-struct WideState {           // per head
-  uint32_t rlo, shift, pop, flags, pass, mk;    // mk: key of the head's largest score (0 = none), set by the first decide
-  unsigned long long A, target;
-};
-constexpr uint32_t WF_DONE = 1, WF_EMPTY = 4, WF_TIER_ALL = 8;
 constexpr int W_SLOTS = 32;                    // candidate slots per thread
-constexpr int W_CAP = 4096;                    // undecided scores that the resolve kernel takes
-constexpr int W_NB = 2048;                     // buckets per pass: pass 0 covers every rank (32 logits at 1/64)
-constexpr int W_BITS = 11;
+constexpr int W_CAP = WIDE_LIST_CAP;           // undecided scores that the resolve kernel takes
 
 struct WideArgs {
   const float* scores;
@@ -40,9 +41,10 @@ struct WideArgs {
   const int32_t* sel_count;
   const int32_t* seq_lens;
   const uint32_t* headmax;    // [bh][HM_SLOTS] (padded): max = key of the head's largest score, 0 = no valid score
-  WideState* state;
-  unsigned long long* ghistM;
-  uint32_t* ghistC;
+  unsigned long long* ghist;  // [bh][WH_NB]
+  WhGrid* hgrid;              // [bh]
+  float4* range;              // [bh] {largest score, d_hi, d_lo, -}
+  unsigned long long* sums;   // [bh][WS_SUMS]: mass of the row, mass above the undecided range
   uint2* ulist;               // [bh][W_CAP] {key, token}
   uint32_t* ucount;
   uint32_t* kdef;
@@ -54,14 +56,9 @@ struct WideArgs {
   float p;
 };
 
-__global__ __launch_bounds__(256) void wide_init_kernel(uint4* zero_base, size_t n16, WideState* st, int nbh) {
+__global__ __launch_bounds__(256) void wide_init_kernel(uint4* zero_base, size_t n16) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n16) zero_base[i] = make_uint4(0, 0, 0, 0);
-  if (i < (size_t)nbh) {
-    WideState s;
-    s.rlo = 0; s.shift = 16; s.pop = 0; s.flags = 0; s.pass = 0; s.mk = 0; s.A = 0; s.target = 0;
-    st[i] = s;
-  }
 }
 
 // the head's largest score: maximum over the words the scoring workgroups folded into
@@ -97,111 +94,120 @@ __device__ __forceinline__ void wide_load(const float* row, int chunk0, int tid,
   }
 }
 
-template <int NT>
-__global__ __launch_bounds__(NT) void wide_hist_kernel(WideArgs a) {
-  constexpr int W_CHUNK = NT * W_SLOTS;
+// Grid and histogram from the stored scores.  Every workgroup of a head takes the same sample of its row - 1024 scores
+// evenly spread - so all lay the same grid; the first one leaves it for the passes that follow.
+__global__ __launch_bounds__(1024) void wide_hist_kernel(WideArgs a) {
+  constexpr int NT = 1024, W_CHUNK = NT * W_SLOTS;
   const int bh = blockIdx.y, b = bh / a.Hq, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const WideState st = a.state[bh];
-  if (st.flags & WF_DONE) return;
   const int N = wide_count(a, b, bh) * TW_PAGE;
   if ((long long)blockIdx.x * W_CHUNK >= N) return;
-  const uint32_t mk = wide_headmax(a.headmax, bh, lane);
-  if (mk == 0) return;
-  const float m = tw_key_to_float(mk);
   const int chunk0 = blockIdx.x * W_CHUNK;
-
-  __shared__ unsigned long long histM[W_NB];
-  __shared__ uint32_t histC[W_NB];
-  for (int i = tid; i < W_NB; i += NT) { histM[i] = 0; histC[i] = 0; }
+  const float* const row = a.scores + (long long)bh * a.cand_stride;
+  const float sv = row[(int)(((long long)tid * N) >> 10)];
+  const float mx = tw_key_to_float(wide_headmax(a.headmax, bh, lane));
+  __shared__ unsigned long long hist[WH_NB];
+  __shared__ float sum_s[16][3];
+  for (int i = tid; i < WH_NB; i += NT) hist[i] = 0;
   float s[W_SLOTS];
-  wide_load<NT>(a.scores + (long long)bh * a.cand_stride, chunk0, tid, N, a.cand_stride, s);
+  wide_load<NT>(row, chunk0, tid, N, a.cand_stride, s);
+  float w0 = 0.f, w1 = 0.f, w2 = 0.f;
+  if (sv > -__builtin_inff() && mx < __builtin_inff()) {
+    const float t = sv - mx, w = __expf(t);
+    w0 = w; w1 = w * t; w2 = w * t * t;
+  }
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) { w0 += __shfl_xor(w0, o, 64); w1 += __shfl_xor(w1, o, 64); w2 += __shfl_xor(w2, o, 64); }
+  if (lane == 0) { sum_s[wave][0] = w0; sum_s[wave][1] = w1; sum_s[wave][2] = w2; }
   __syncthreads();
+  w0 = w1 = w2 = 0.f;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) { w0 += sum_s[w][0]; w1 += sum_s[w][1]; w2 += sum_s[w][2]; }
+  WhGrid gr = wh_grid(w0, w1, w2);
+  if (w0 > 0.f) gr.ref += mx;
+  if (blockIdx.x == 0 && tid == 0) a.hgrid[bh] = gr;
+  const float inv = 1.0f / gr.scale, off = -gr.ref * inv, lscale = gr.scale * 0x1.715476p+0f;
 #pragma unroll
   for (int e = 0; e < W_SLOTS; ++e) {
-    const uint32_t r = hp_rank_only(m, s[e]);       // the exponential only for scores that take part
-    if (r != HP_NONE && r >= st.rlo) {
-      const uint32_t bk = (r - st.rlo) >> st.shift;
-      if (bk < W_NB) {
-        atomicAdd(&histM[bk], hp_fix(hp_numer(m, s[e])));
-        atomicAdd(&histC[bk], 1u);
-      }
-    }
+    uint32_t w;
+    const bool valid = s[e] > -__builtin_inff();
+    const int bk = wh_bucket(__builtin_fmaf(valid ? s[e] : 0.f, inv, off), lscale, &w);
+    if (valid) atomicAdd(&hist[bk], (unsigned long long)w);
   }
   __syncthreads();
-  for (int i = tid; i < W_NB; i += NT) {
-    const uint32_t c = histC[i];
-    if (c) { atomicAdd(&a.ghistM[(long long)bh * W_NB + i], histM[i]); atomicAdd(&a.ghistC[(long long)bh * W_NB + i], c); }
+  for (int i = tid; i < WH_NB; i += NT) {
+    const unsigned long long c = hist[i];
+    if (c) atomicAdd(&a.ghist[(long long)bh * WH_NB + i], c);
   }
 }
 
-// One wave per head: scan the 2048 buckets (lane l owns 32l .. 32l+31), find the one where the
-// mass reaches the target, narrow the interval to it.
+// The scores among which the head's threshold lies, by its histogram: distances to the maximum d_hi <= d < d_lo.
+__device__ __forceinline__ void wide_range(const unsigned long long* gh, WhGrid gr, float m, float p, int lane, float* d_hi, float* d_lo) {
+  constexpr int BPL = WH_NB / 64;
+  static_assert(WH_NB % 64 == 0, "whole buckets per lane");
+  float mb[BPL], mine = 0.f;
+#pragma unroll
+  for (int k = 0; k < BPL; ++k) {
+    const int bk = BPL * lane + k;
+    const float t = bk < WH_HALF ? wh_edge(WH_HALF - bk) : -wh_edge(bk - WH_HALF);             // upper edge
+    mb[k] = (float)gh[bk] * __expf(fminf(gr.ref + t * gr.scale - m, 80.f));
+    mine += mb[k];
+  }
+  float incl = mine;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const float y = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += y;
+  }
+  const float Z = __shfl(incl, 63, 64);
+  *d_hi = 0.f; *d_lo = HP_REACH;                         // a histogram that says nothing: everything is undecided
+  if (!(Z > 0.f) || !(Z < __builtin_inff()) || __shfl(mb[0], 0, 64) > 0.f) return;     // wave-uniform
+  // margin: roundings of the weights and of these sums, and what lies beyond the last bucket's edge
+  const float eps = 5e-5f * Z + __shfl(mb[BPL - 1], 63, 64);
+  const float t0 = p * Z - eps, t1 = p * Z + eps;
+  int b0 = WH_NB, b1 = WH_NB;
+  float cum = incl - mine;
+#pragma unroll
+  for (int k = 0; k < BPL; ++k) {
+    cum += mb[k];
+    if (b0 == WH_NB && cum >= t0) b0 = BPL * lane + k;
+    if (b1 == WH_NB && cum >= t1) b1 = BPL * lane + k;
+  }
+  const unsigned long long h0 = __ballot(b0 < WH_NB), h1 = __ballot(b1 < WH_NB);
+  b0 = h0 ? __shfl(b0, __ffsll((long long)h0) - 1, 64) : WH_NB - 1;
+  b1 = h1 ? __shfl(b1, __ffsll((long long)h1) - 1, 64) : WH_NB - 1;
+  // In steps of 2^-10 logits: whole ranks (2^-22), so that scores of one rank, which may end as one tier, stay together.
+  if (b0 > 0) {
+    const float t = b0 < WH_HALF ? wh_edge(WH_HALF - b0) : -wh_edge(b0 - WH_HALF);             // upper edge of b0
+    const float d = floorf((m - (gr.ref + t * gr.scale)) * 1024.f) * 0.0009765625f;
+    *d_hi = fminf(fmaxf(d, 0.f), HP_REACH);
+  }
+  if (b1 < WH_NB - 1) {
+    const float t = b1 < WH_HALF ? wh_edge(WH_HALF - 1 - b1) : -wh_edge(b1 + 1 - WH_HALF);     // lower edge of b1
+    const float d = ceilf((m - (gr.ref + t * gr.scale)) * 1024.f) * 0.0009765625f;
+    *d_lo = fminf(fmaxf(d, 0.f), HP_REACH);
+  }
+}
+
+// (A launch of its own: in the prologue of every wide_emit workgroup this made that kernel 81 us instead of 52 + this one's 4.8.)
 __global__ __launch_bounds__(64) void wide_decide_kernel(WideArgs a) {
-  constexpr int BPL = W_NB / 64;
   const int bh = blockIdx.x, lane = threadIdx.x;
-  WideState st = a.state[bh];
-  if (st.flags & WF_DONE) return;
-  st.mk = wide_headmax(a.headmax, bh, lane);
-  if (st.mk == 0) { if (lane == 0) { st.flags = WF_DONE | WF_EMPTY; a.state[bh] = st; } return; }
-  unsigned long long* gm = a.ghistM + (long long)bh * W_NB;
-  uint32_t* gc = a.ghistC + (long long)bh * W_NB;
-  unsigned long long mb[BPL], mine = 0;
-#pragma unroll
-  for (int k = 0; k < BPL; ++k) { mb[k] = gm[BPL * lane + k]; mine += mb[k]; }
-  const unsigned long long incl = tw_wave_scan_u64(mine);
-  const unsigned long long total = __shfl(incl, 63, 64);
-  if (st.pass == 0) {                             // pass 0 sees every score that has mass: total = Z
-    const double t = ceil((double)a.p * (double)total);
-    st.target = t < 1.0 ? 1ull : (unsigned long long)t;
-    if (st.target > total) st.target = total;
-  }
-  const unsigned long long before = st.A + incl - mine;
-  const bool hit = before < st.target && before + mine >= st.target;
-  const unsigned long long bal = __ballot(hit);
-  bool again = false;
-  if (bal == 0) {
-    st.flags |= WF_DONE | WF_TIER_ALL;            // unreachable: the interval holds the crossing by construction
-  } else {
-    const int src = __ffsll((long long)bal) - 1;
-    unsigned long long cum = before, asel = before;
-    int bsel = 0;
-#pragma unroll
-    for (int k = 0; k < BPL; ++k) {
-      if (cum < st.target && cum + mb[k] >= st.target) { bsel = k; asel = cum; }
-      cum += mb[k];
-    }
-    const int bucket = BPL * src + __shfl(bsel, src, 64);
-    st.A = __shfl(asel, src, 64);
-    st.pop = gc[bucket];
-    st.rlo += (uint32_t)bucket << st.shift;
-    if (st.pop <= (uint32_t)W_CAP) st.flags |= WF_DONE;
-    else if (st.shift == 0) st.flags |= WF_DONE | WF_TIER_ALL;   // > W_CAP scores of one rank: keep them all
-    else { st.shift = st.shift >= W_BITS ? st.shift - W_BITS : 0; again = true; }
-  }
-  st.pass += 1;
-  if (again) {
-#pragma unroll
-    for (int k = 0; k < BPL; ++k) { gm[BPL * lane + k] = 0; gc[BPL * lane + k] = 0; }
-  }
-  if (lane == 0) a.state[bh] = st;
+  const float m = tw_key_to_float(wide_headmax(a.headmax, bh, lane));   // (no valid score: a NaN, nothing takes part)
+  float d_hi = 0.f, d_lo = HP_REACH;
+  wide_range(a.ghist + (long long)bh * WH_NB, a.hgrid[bh], m, a.p, lane, &d_hi, &d_lo);
+  if (lane == 0) a.range[bh] = make_float4(m, d_hi, d_lo, 0.f);
 }
 
 template <int NT>
 __global__ __launch_bounds__(NT) void wide_emit_kernel(WideArgs a) {
-  constexpr int W_CHUNK = NT * W_SLOTS;
+  constexpr int W_CHUNK = NT * W_SLOTS, NW = NT / 64;
   const int bh = blockIdx.y, b = bh / a.Hq, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const WideState st = a.state[bh];
-  if (!a.keep_all && st.mk == 0) return;          // no valid score: bitmap stays empty
   const int count = wide_count(a, b, bh);
   const int N = count * TW_PAGE;
   if ((long long)blockIdx.x * W_CHUNK >= N) return;
-  const float m = tw_key_to_float(st.mk);
   const int chunk0 = blockIdx.x * W_CHUNK;
-  // a search that did not finish in the passes given keeps its whole interval
-  const bool tier = (st.flags & WF_TIER_ALL) || !(st.flags & WF_DONE);
-  const uint32_t rhi = st.rlo + (st.shift >= 32 ? 0xFFFFFFFFu : (1u << st.shift)) - 1u;
   float s[W_SLOTS];
   wide_load<NT>(a.scores + (long long)bh * a.cand_stride, chunk0, tid, N, a.cand_stride, s);
+  const float4 rg = a.range[bh];
   int pg[W_SLOTS / 4];                            // logical page of each group of 4 slots (page lists only)
 #pragma unroll
   for (int v = 0; v < W_SLOTS / 4; ++v) {
@@ -212,19 +218,28 @@ __global__ __launch_bounds__(NT) void wide_emit_kernel(WideArgs a) {
     }
   }
   uint32_t mask = 0, umask = 0;                   // bit e: slot e of this thread is kept / undecided
+  unsigned long long Z = 0, A = 0;                // masses of all, of the kept
+  if (a.keep_all) {
 #pragma unroll
-  for (int e = 0; e < W_SLOTS; ++e) {
-    const bool valid = s[e] > -__builtin_inff();
-    bool keep, und = false;
-    if (a.keep_all) keep = valid;
-    else {
-      const uint32_t r = hp_rank_only(m, s[e]);
-      const bool part = valid && r != HP_NONE;
-      keep = part && (r < st.rlo || (tier && r <= rhi));
-      und = part && !tier && r >= st.rlo && r <= rhi;
+    for (int e = 0; e < W_SLOTS; ++e) mask |= (s[e] > -__builtin_inff() ? 1u : 0u) << e;
+  } else {
+    const float m = rg.x, d_hi = rg.y, d_lo = rg.z;
+    uint32_t zh = 0, zl = 0, ah = 0, al = 0;                    // sums of the masses' upper and lower 20 bits
+#pragma unroll
+    for (int e = 0; e < W_SLOTS; ++e) {
+      const float d = __fsub_rn(m, s[e]);
+      uint32_t h, l;
+      hp_fix20(__expf(-(d < HP_REACH ? d : 100.f)), &h, &l);    // beyond the reach: no mass
+      const bool keep = d < d_hi;
+      zh += h; zl += l;
+      ah += keep ? h : 0u; al += keep ? l : 0u;
+      mask |= (keep ? 1u : 0u) << e;
+      umask |= (d < d_lo ? 1u : 0u) << e;
+      if ((e & 3) == 3) __builtin_amdgcn_sched_barrier(0);       // four at a time: all 32 interleaved take twice the registers
     }
-    mask |= (keep ? 1u : 0u) << e;
-    umask |= (und ? 1u : 0u) << e;
+    umask &= ~mask;
+    Z = ((unsigned long long)zh << 20) + zl;
+    A = ((unsigned long long)ah << 20) + al;
   }
   // undecided scores go onto the head's list: one atomic per wave reserves room for all its lanes
   {
@@ -235,15 +250,13 @@ __global__ __launch_bounds__(NT) void wide_emit_kernel(WideArgs a) {
       uint32_t ubase = 0;
       if (lane == 63) ubase = atomicAdd(&a.ucount[(long long)bh * TW_CTR], wtotal);
       uint32_t at = __shfl(ubase, 63, 64) + incl - mine;
-#pragma unroll
-      for (int e = 0; e < W_SLOTS; ++e) {
-        if ((umask >> e) & 1u) {
-          if (at < (uint32_t)W_CAP) {
-            const int slot = wide_slot<NT>(chunk0, e >> 2, tid) + (e & 3);
-            const int tok = a.sel_pages ? pg[e >> 2] * TW_PAGE + (slot & 15) : slot;
-            a.ulist[(long long)bh * W_CAP + at] = make_uint2(tw_float_key(s[e]), (uint32_t)tok);
-          }
-          ++at;
+      // (few scores: their words are read again, so that none of the 32 has to stay in a register for this)
+      for (uint32_t x = umask; x; x &= x - 1, ++at) {
+        const int e = __ffs((int)x) - 1;
+        const int slot = wide_slot<NT>(chunk0, e >> 2, tid) + (e & 3);
+        if (at < (uint32_t)W_CAP) {
+          const int tok = a.sel_pages ? a.sel_pages[(long long)bh * a.max_sel + (slot >> 4)] * TW_PAGE + (slot & 15) : slot;
+          a.ulist[(long long)bh * W_CAP + at] = make_uint2(tw_float_key(a.scores[(long long)bh * a.cand_stride + slot]), (uint32_t)tok);
         }
       }
     }
@@ -266,144 +279,243 @@ __global__ __launch_bounds__(NT) void wide_emit_kernel(WideArgs a) {
       if ((lane & 7) == 0 && c < N && (c >> 5) < a.words_stride) bm[c >> 5] = x;
     }
   }
-  uint32_t cnt = tw_wave_scan_u32(__popc(mask));
-  __shared__ uint32_t wc[16];
-  if (lane == 63) wc[wave] = cnt;
+  const uint32_t cnt = tw_wave_scan_u32(__popc(mask));
+  Z = tw_wave_scan_u64(Z);
+  A = tw_wave_scan_u64(A);
+  __shared__ uint32_t wc[NW];
+  __shared__ unsigned long long wz[NW], wa[NW];
+  if (lane == 63) { wc[wave] = cnt; wz[wave] = Z; wa[wave] = A; }
   __syncthreads();
   if (tid == 0) {
     uint32_t t = 0;
-    for (int w = 0; w < NT / 64; ++w) t += wc[w];
+    unsigned long long tz = 0, ta = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) { t += wc[w]; tz += wz[w]; ta += wa[w]; }
     if (t) atomicAdd(&a.kdef[(long long)bh * TW_CTR], t);
+    if (tz) atomicAdd(&a.sums[(long long)bh * WS_SUMS], tz);
+    if (ta) atomicAdd(&a.sums[(long long)bh * WS_SUMS + 1], ta);
   }
 }
 
-// One workgroup per head.  The undecided scores (rank inside the interval that the passes over
-// the whole row ended with) sit in registers, 4 per thread; the interval is narrowed 9 bits per
-// round with a 512-bucket LDS histogram until at most 64 scores are left, and those are compared
-// exactly on the scores' own bits: T = the largest key whose upper set reaches the target mass.
 constexpr int WR_EPT = W_CAP / 1024;
 constexpr int WR_CAP = 64;
-__global__ __launch_bounds__(1024) void wide_resolve_kernel(WideArgs a) {
-  const int bh = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const WideState st = a.state[bh];
-  __shared__ unsigned long long histM[HP_NB];
-  __shared__ uint32_t histC[HP_NB];
-  __shared__ unsigned long long cand_mass[WR_CAP];
-  __shared__ uint32_t cand_key[WR_CAP];
-  __shared__ uint32_t red[16];
-  __shared__ uint32_t sh_n, sh_T;
-  const bool search = !a.keep_all && st.mk != 0 && (st.flags & WF_DONE) && !(st.flags & WF_TIER_ALL);
-  uint32_t cn = 0;
-  if (search) { cn = a.ucount[(long long)bh * TW_CTR]; if (cn > (uint32_t)W_CAP) cn = W_CAP; }
-  const float m = tw_key_to_float(st.mk);
-  uint32_t key[WR_EPT], tok[WR_EPT], rk[WR_EPT];
-  float ef[WR_EPT];
-#pragma unroll
-  for (int e = 0; e < WR_EPT; ++e) {
-    const uint32_t i = (uint32_t)(e * 1024 + tid);
-    const uint2 x = a.ulist[(long long)bh * W_CAP + (i < cn ? i : 0u)];   // cn = 0: slot 0 is inside the buffer, masked
-    key[e] = x.x; tok[e] = x.y;
-    rk[e] = i < cn ? hp_rank(m, tw_key_to_float(x.x), &ef[e]) : HP_NONE;
-  }
-  if (tid == 0) sh_n = 0;
-  __syncthreads();
-  uint32_t T = 0xFFFFFFFFu;                         // nothing from the list unless a threshold is found
-  if (cn > 0) {                                     // block-uniform
-    uint32_t rlo = st.rlo, pop = cn;
-    int shift = (int)st.shift;
-    unsigned long long A = st.A;
-    const unsigned long long target = st.target;
+struct ResolveLds {
+  unsigned long long histM[HP_NB];
+  uint32_t histC[HP_NB];
+  unsigned long long cand_mass[WR_CAP];
+  uint32_t cand_key[WR_CAP];
+  uint32_t red[16];
+  uint32_t n, T;
+};
+
+// Threshold among scores of ranks [rlo, rlo + 2^shift): the largest key whose upper set, with the mass A above the
+// interval, reaches `target`.  The interval is narrowed 9 bits per round with a 512-bucket LDS histogram until at most
+// 64 scores are left, and those are compared exactly on the scores' own bits; more than 64 scores of one rank are one
+// tier.  each(f) calls f(key, score) for every score of this thread; called by all 1024 threads.  *found: the interval
+// holds the crossing.
+template <class Each>
+__device__ __forceinline__ uint32_t wide_threshold(Each each, float m, uint32_t rlo, int shift, uint32_t pop, unsigned long long A,
+                                                   unsigned long long target, ResolveLds& L, bool* found) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  *found = false;
+  if (tid == 0) L.n = 0;
 #pragma unroll 1
-    while (pop > (uint32_t)WR_CAP && shift > 0) {
-      const int nshift = shift >= 9 ? shift - 9 : 0;
-      const uint32_t nb = 1u << (shift - nshift);   // buckets that cover the interval
-      for (int i = tid; i < HP_NB; i += 1024) { histM[i] = 0; histC[i] = 0; }
-      __syncthreads();
-#pragma unroll
-      for (int e = 0; e < WR_EPT; ++e) {
-        if (rk[e] != HP_NONE && rk[e] >= rlo) {
-          const uint32_t bk = (rk[e] - rlo) >> nshift;
-          if (bk < nb) { atomicAdd(&histM[bk], hp_fix(ef[e])); atomicAdd(&histC[bk], 1u); }
-        }
+  for (bool first = true; pop > (uint32_t)WR_CAP && (shift > 0 || first); first = false) {
+    const int nshift = shift >= 9 ? shift - 9 : 0;
+    const uint32_t nb = 1u << (shift - nshift);   // buckets that cover the interval
+    __syncthreads();
+    for (int i = tid; i < HP_NB; i += 1024) { L.histM[i] = 0; L.histC[i] = 0; }
+    __syncthreads();
+    each([&](uint32_t, float s) {
+      float e;
+      const uint32_t r = hp_rank(m, s, &e);
+      if (r != HP_NONE && r >= rlo) {
+        const uint32_t bk = (r - rlo) >> nshift;
+        if (bk < nb) { atomicAdd(&L.histM[bk], hp_fix(e)); atomicAdd(&L.histC[bk], 1u); }
       }
-      __syncthreads();
-      unsigned long long mb[8], mine = 0;           // every wave scans on its own: lane l owns buckets 8l .. 8l+7
+    });
+    __syncthreads();
+    unsigned long long mb[8], mine = 0;           // every wave scans on its own: lane l owns buckets 8l .. 8l+7
 #pragma unroll
-      for (int k = 0; k < 8; ++k) { mb[k] = histM[8 * lane + k]; mine += mb[k]; }
-      const unsigned long long incl = tw_wave_scan_u64(mine);
-      const unsigned long long before = A + incl - mine;
-      const bool hit = before < target && before + mine >= target;
-      const unsigned long long bal = __ballot(hit);
-      if (bal == 0) { pop = 0xFFFFFFFFu; shift = nshift; break; }   // unreachable: the interval holds the crossing
-      const int src = __ffsll((long long)bal) - 1;
-      unsigned long long cum = before, asel = before;
-      int bsel = 0;
+    for (int k = 0; k < 8; ++k) { mb[k] = L.histM[8 * lane + k]; mine += mb[k]; }
+    const unsigned long long incl = tw_wave_scan_u64(mine);
+    const unsigned long long before = A + incl - mine;
+    const bool hit = before < target && before + mine >= target;
+    const unsigned long long bal = __ballot(hit);
+    if (bal == 0) return 0xFFFFFFFFu;             // (the same in every wave)
+    const int src = __ffsll((long long)bal) - 1;
+    unsigned long long cum = before, asel = before;
+    int bsel = 0;
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        if (cum < target && cum + mb[k] >= target) { bsel = k; asel = cum; }
-        cum += mb[k];
-      }
-      const int bucket = 8 * src + __shfl(bsel, src, 64);
-      A = __shfl(asel, src, 64);
-      pop = histC[bucket];
-      rlo += (uint32_t)bucket << nshift;
-      shift = nshift;
-      __syncthreads();                              // all scans done before the histogram is cleared
+    for (int k = 0; k < 8; ++k) {
+      if (cum < target && cum + mb[k] >= target) { bsel = k; asel = cum; }
+      cum += mb[k];
     }
-    const uint32_t rhi = rlo + (1u << shift) - 1u;
-    const bool small = pop <= (uint32_t)WR_CAP;
-    uint32_t kmin = 0xFFFFFFFFu;
+    const int bucket = 8 * src + __shfl(bsel, src, 64);
+    A = __shfl(asel, src, 64);
+    pop = L.histC[bucket];
+    rlo += (uint32_t)bucket << nshift;
+    shift = nshift;
+  }
+  const uint32_t rhi = rlo + (1u << shift) - 1u;
+  const bool small = pop <= (uint32_t)WR_CAP;
+  uint32_t kmin = 0xFFFFFFFFu;
+  __syncthreads();                                // L.n cleared; scans done
+  each([&](uint32_t k, float s) {
+    float e;
+    const uint32_t r = hp_rank(m, s, &e);
+    if (r != HP_NONE && r >= rlo && r <= rhi) {
+      kmin = k < kmin ? k : kmin;
+      if (small) {
+        const uint32_t at = atomicAdd(&L.n, 1u);
+        if (at < (uint32_t)WR_CAP) { L.cand_key[at] = k; L.cand_mass[at] = hp_fix(e); }
+      }
+    }
+  });
+  if (!small) {                                   // more than WR_CAP scores of one rank: keep them all
+    kmin = ~tw_wave_max_u32(~kmin);
+    if (lane == 0) L.red[wave] = kmin;
+  }
+  __syncthreads();
+  if (wave == 0) {
+    uint32_t T;
+    if (small) {
+      const uint32_t n = L.n < (uint32_t)WR_CAP ? L.n : (uint32_t)WR_CAP;
+      const uint32_t kx = lane < (int)n ? L.cand_key[lane] : 0u;
+      unsigned long long S = 0;
+#pragma unroll 4
+      for (uint32_t j = 0; j < n; ++j) S += L.cand_key[j] >= kx ? L.cand_mass[j] : 0ull;
+      const uint32_t best = (lane < (int)n && A + S >= target) ? kx : 0u;
+      T = tw_wave_max_u32(best);
+    } else {
+      T = L.red[0];
+#pragma unroll
+      for (int w = 1; w < 16; ++w) T = L.red[w] < T ? L.red[w] : T;
+    }
+    if (lane == 0) L.T = T;
+  }
+  __syncthreads();
+  const uint32_t T = L.T;
+  *found = T != 0u && A < target;
+  return *found ? T : 0xFFFFFFFFu;
+}
+
+// One workgroup per head.  The undecided scores sit in registers, 8 per thread.  A head whose list overflowed or does
+// not hold the threshold (the exact sums decide) is searched from its whole row instead, and its bitmap written anew.
+__global__ __launch_bounds__(1024) void wide_resolve_kernel(WideArgs a) {
+  const int bh = blockIdx.x, b = bh / a.Hq, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ ResolveLds L;
+  __shared__ uint32_t red_hi[16];
+  __shared__ unsigned long long zred[16];
+  const uint32_t mk = wide_headmax(a.headmax, bh, lane);
+  const bool search = !a.keep_all && mk != 0;
+  const float m = tw_key_to_float(mk);
+  uint32_t* const bm = a.bitmaps + (long long)bh * a.words_stride;
+  uint32_t add = 0;
+  bool whole_row = false;
+  if (search) {                                   // block-uniform
+    const uint32_t listed = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.ucount[(long long)bh * TW_CTR]);
+    const unsigned long long Z = a.sums[(long long)bh * WS_SUMS], A = a.sums[(long long)bh * WS_SUMS + 1];
+    const uint32_t cn = listed < (uint32_t)W_CAP ? listed : (uint32_t)W_CAP;
+    uint32_t key[WR_EPT], tok[WR_EPT];
+    uint32_t rmin = 0xFFFFFFFFu, rmax = 0u;
 #pragma unroll
     for (int e = 0; e < WR_EPT; ++e) {
-      if (rk[e] != HP_NONE && rk[e] >= rlo && rk[e] <= rhi) {
-        kmin = key[e] < kmin ? key[e] : kmin;
-        if (small) {
-          const uint32_t at = atomicAdd(&sh_n, 1u);
-          if (at < (uint32_t)WR_CAP) { cand_key[at] = key[e]; cand_mass[at] = hp_fix(ef[e]); }
+      const uint32_t i = (uint32_t)(e * 1024 + tid);
+      key[e] = 0; tok[e] = 0;
+      if (e * 1024u >= cn) continue;              // (block-uniform)
+      const uint2 x = a.ulist[(long long)bh * W_CAP + (i < cn ? i : 0u)];
+      key[e] = x.x; tok[e] = x.y;
+      if (i < cn) {
+        const uint32_t r = hp_rank_only(m, tw_key_to_float(x.x));
+        rmin = r < rmin ? r : rmin;
+        rmax = r > rmax ? r : rmax;
+      }
+    }
+    rmin = ~tw_wave_max_u32(~rmin);
+    rmax = tw_wave_max_u32(rmax);
+    if (lane == 0) { L.red[wave] = rmin; red_hi[wave] = rmax; }
+    __syncthreads();
+    rmin = ~tw_row_max_u32(~L.red[lane & 15]);
+    rmax = tw_row_max_u32(red_hi[lane & 15]);
+    rmin = (uint32_t)__builtin_amdgcn_readfirstlane((int)rmin);
+    rmax = (uint32_t)__builtin_amdgcn_readfirstlane((int)rmax);
+    uint32_t T = 0xFFFFFFFFu;
+    bool found = false;
+    const unsigned long long target = hp_target(a.p, Z);
+    if (listed > 0 && listed <= (uint32_t)W_CAP && A < target) {            // block-uniform
+      const uint32_t span = rmax - rmin;
+      auto each = [&](auto f) {
+#pragma unroll
+        for (int e = 0; e < WR_EPT; ++e)
+          if (e * 1024u < cn && (uint32_t)(e * 1024 + tid) < cn) f(key[e], tw_key_to_float(key[e]));
+      };
+      T = wide_threshold(each, m, rmin, span ? 32 - __clz(span) : 0, cn, A, target, L, &found);
+    }
+    if (found) {
+#pragma unroll
+      for (int e = 0; e < WR_EPT; ++e) {
+        if ((uint32_t)(e * 1024 + tid) < cn && key[e] >= T && (tok[e] >> 5) < (uint32_t)a.words_stride) {
+          atomicOr(&bm[tok[e] >> 5], 1u << (tok[e] & 31));
+          add += 1;
         }
       }
     }
-    if (!small) {                                   // more than WR_CAP scores of one rank: keep them all
-      kmin = ~tw_wave_max_u32(~kmin);
-      if (lane == 0) red[wave] = kmin;
-    }
-    __syncthreads();
-    if (wave == 0) {
-      if (small) {
-        const uint32_t n = sh_n < (uint32_t)WR_CAP ? sh_n : (uint32_t)WR_CAP;
-        const uint32_t kx = lane < (int)n ? cand_key[lane] : 0u;
-        unsigned long long S = 0;
-#pragma unroll 4
-        for (uint32_t j = 0; j < n; ++j) S += cand_key[j] >= kx ? cand_mass[j] : 0ull;
-        const uint32_t best = (lane < (int)n && A + S >= target) ? kx : 0u;
-        T = tw_wave_max_u32(best);
-      } else {
-        uint32_t r = red[0];
-#pragma unroll
-        for (int w = 1; w < 16; ++w) r = red[w] < r ? red[w] : r;
-        T = r;
-      }
-      if (lane == 0) sh_T = T;
-    }
-    __syncthreads();
-    T = sh_T;
-    if (T == 0) T = 0xFFFFFFFFu;                    // unreachable (the interval holds the crossing): keep none of the list
-    __syncthreads();                                // red is reused below
+    whole_row = !found;
   }
-  uint32_t add = 0;
+  if (whole_row) {                                // block-uniform
+    const int count = wide_count(a, b, bh);
+    const int N = count * TW_PAGE;
+    const float* row = a.scores + (long long)bh * a.cand_stride;
+    auto each = [&](auto f) {
+#pragma unroll 1
+      for (int c0 = tid * 4; c0 < N; c0 += 4 * 4096) {                        // four loads in flight per thread
+        float4 x[4];
 #pragma unroll
-  for (int e = 0; e < WR_EPT; ++e) {
-    if (rk[e] != HP_NONE && key[e] >= T && (tok[e] >> 5) < (uint32_t)a.words_stride) {
-      atomicOr(&a.bitmaps[(long long)bh * a.words_stride + (tok[e] >> 5)], 1u << (tok[e] & 31));
-      add += 1;
+        for (int v = 0; v < 4; ++v) x[v] = *(const float4*)(row + (c0 + v * 4096 < N ? c0 + v * 4096 : N - 4));
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          if (c0 + v * 4096 < N) {
+            const float y[4] = {x[v].x, x[v].y, x[v].z, x[v].w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) f(tw_float_key(y[k]), y[k]);
+          }
+        }
+      }
+    };
+    unsigned long long Z = 0;
+    each([&](uint32_t, float s) { if (hp_rank_only(m, s) != HP_NONE) Z += hp_fix(hp_numer(m, s)); });
+    Z = tw_wave_scan_u64(Z);
+    if (lane == 63) zred[wave] = Z;
+    __syncthreads();
+    Z = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) Z += zred[w];
+    bool found;
+    const uint32_t T = wide_threshold(each, m, 0u, 27, 0xFFFFFFFFu, 0ull, hp_target(a.p, Z), L, &found);
+    // 16 slots = one page = one half word of the bitmap per thread
+    for (int i = tid; i < count; i += 1024) {
+      uint32_t bits = 0;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float4 x = *(const float4*)(row + i * 16 + 4 * v);
+        const float y[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          bits |= (hp_rank_only(m, y[k]) != HP_NONE && tw_float_key(y[k]) >= T ? 1u : 0u) << (4 * v + k);
+      }
+      const int pgi = a.sel_pages ? a.sel_pages[(long long)bh * a.max_sel + i] : i;
+      if (pgi >= 0 && (pgi >> 1) < a.words_stride) ((unsigned short*)bm)[pgi] = (unsigned short)bits;
+      add += __popc(bits);
     }
   }
   add = tw_wave_scan_u32(add);
-  if (lane == 63) red[wave] = add;
+  __syncthreads();                                // red is reused
+  if (lane == 63) L.red[wave] = add;
   __syncthreads();
   if (tid == 0) {
-    uint32_t t = a.kdef[(long long)bh * TW_CTR];
-    for (int w = 0; w < 16; ++w) t += red[w];
+    uint32_t t = whole_row ? 0u : a.kdef[(long long)bh * TW_CTR];
+    for (int w = 0; w < 16; ++w) t += L.red[w];
     a.kept_count[bh] = (int32_t)t;
   }
 }
@@ -426,13 +538,21 @@ struct ListArgs {
 // (long rows), or counted in place (rows of a few segments); it then stages its own positions
 // in LDS and copies them out coalesced.  The workgroup of the last segment also writes the count.
 constexpr int BL_SEG = 256;
+__device__ __forceinline__ int list_words(const ListArgs& a, int row) {
+  const int n = a.seq_lens[row / a.rows_per_seq];
+  int P = n > 0 ? (n + TW_PAGE - 1) / TW_PAGE : 0;
+  if (P > a.max_pages) P = a.max_pages;
+  const int ntok = P * TW_PAGE < n ? P * TW_PAGE : n;
+  return (ntok + 31) >> 5;
+}
 template <int NB>
 __global__ __launch_bounds__(256) void bitmap_count_kernel(ListArgs a) {
   const int row = blockIdx.y, seg = blockIdx.x, tid = threadIdx.x;
+  const int nwords = list_words(a, row);            // (words beyond the sequence's end were never written)
   const uint32_t* bm = a.bitmaps + (long long)row * a.maps_per_row * a.words_stride;
   const int wi = seg * BL_SEG + tid;
   uint32_t w = 0;
-  if (wi < a.words_stride) {
+  if (wi < nwords) {
 #pragma unroll
     for (int hh = 0; hh < NB; ++hh) w |= bm[(long long)hh * a.words_stride + wi];
   }
@@ -444,12 +564,8 @@ __global__ __launch_bounds__(256) void bitmap_count_kernel(ListArgs a) {
 
 template <int NB>
 __global__ __launch_bounds__(256) void bitmap_list_kernel(ListArgs a) {
-  const int row = blockIdx.y, seg = blockIdx.x, b = row / a.rows_per_seq, tid = threadIdx.x;
-  const int n = a.seq_lens[b];
-  int P = n > 0 ? (n + TW_PAGE - 1) / TW_PAGE : 0;
-  if (P > a.max_pages) P = a.max_pages;
-  const int ntok = P * TW_PAGE < n ? P * TW_PAGE : n;
-  const int nwords = (ntok + 31) >> 5;
+  const int row = blockIdx.y, seg = blockIdx.x, tid = threadIdx.x;
+  const int nwords = list_words(a, row);
   const int nseg = (nwords + BL_SEG - 1) / BL_SEG;
   if (seg >= nseg && !(seg == 0 && nseg == 0)) return;
   __shared__ uint32_t ws32[16];
@@ -518,64 +634,48 @@ int launch_list(ListArgs a, int rows, uint32_t* segcnt, hipStream_t s) {
 
 }  // namespace
 
-// Everything after the scores have been written (and headmax filled by the scoring kernel).
-// tw_prune_wide_init must have been enqueued BEFORE the scoring kernel.
-int tw_prune_wide_init(const TwDims& d, const PruneWs& L, void* ws, hipStream_t s) {
-  const size_t n16 = (L.state - L.headmax) / 16;
-  const int nbh = d.batch * d.Hq;
-  const size_t n = n16 > (size_t)nbh ? n16 : (size_t)nbh;
+// Everything after the scores have been written (headmax filled by the scoring kernel; hist_done: the mass histogram
+// too).  tw_prune_wide_init must have been enqueued BEFORE the scoring kernel.
+int tw_prune_wide_init(const PruneWs& L, void* ws, bool full, hipStream_t s) {
+  // every token a candidate: every bitmap word inside a sequence is written, the bitmaps need no clearing
+  const size_t n16 = ((full ? L.bitmaps : L.grid) - L.headmax) / 16;
   tw_prof_before(TW_K_TOPP, s);
-  TW_LAUNCH(wide_init_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                     (uint4*)((char*)ws + L.headmax), n16, (WideState*)((char*)ws + L.state), nbh);
+  TW_LAUNCH(wide_init_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, s, (uint4*)((char*)ws + L.headmax), n16);
   return tw_prof_after(s);
 }
 
 int tw_prune_wide(const TwDims& d, const PruneWs& L, void* ws, const twilight_kv_t* kv, const int32_t* sel_pages,
                   const int32_t* sel_count, int max_sel, int cand_stride, float p, int32_t* kept_count,
                   int32_t* kept_idx, int kept_stride, int32_t* union_count, int32_t* union_idx, int union_stride,
-                  uint32_t* status, hipStream_t s) {
+                  uint32_t* status, bool hist_done, hipStream_t s) {
   char* base = (char*)ws;
   WideArgs a;
   a.scores = (const float*)(base + L.scores); a.sel_pages = sel_pages; a.sel_count = sel_count; a.seq_lens = kv->seq_lens;
-  a.headmax = (const uint32_t*)(base + L.headmax); a.state = (WideState*)(base + L.state);
-  a.ghistM = (unsigned long long*)(base + L.ghistM); a.ghistC = (uint32_t*)(base + L.ghistC);
+  a.headmax = (const uint32_t*)(base + L.headmax); a.ghist = (unsigned long long*)(base + L.ghist); a.hgrid = (WhGrid*)(base + L.grid);
+  a.range = (float4*)(base + L.range);
+  a.sums = (unsigned long long*)(base + L.sums);
   a.ulist = (uint2*)(base + L.ulist);
   a.ucount = (uint32_t*)(base + L.ucount); a.kdef = (uint32_t*)(base + L.kdef);
   a.bitmaps = (uint32_t*)(base + L.bitmaps); a.kept_count = kept_count; a.status = status;
   a.Hq = d.Hq; a.max_pages = d.max_pages; a.max_sel = max_sel; a.cand_stride = cand_stride;
   a.words_stride = L.words_stride; a.keep_all = p >= 1.0f ? 1 : 0; a.p = p;
   const int nbh = d.batch * d.Hq;
-  // measured at 4 x 262144 tokens x 64 heads: histogram pass 72 / 77 / 83 us with 1024 / 512 / 256 threads (fewer
-  // flushes of the LDS histogram per score), emit pass 86 / 69 / 58 us (small workgroups overlap their load and
-  // compute phases; at 88 registers only one 1024-thread workgroup fits a CU)
+  // histogram pass: large workgroups (fewer flushes of the LDS histogram per score); emit pass: small ones (they
+  // overlap their load and compute phases)
   constexpr int HIST_NT = 1024, EMIT_NT = 256;
-#ifdef TW_TUNING                                 // tuning builds only: the shipped library reads no environment
-  static const int emit_nt = getenv("TW_WIDE_EMIT_NT") ? atoi(getenv("TW_WIDE_EMIT_NT")) : EMIT_NT;
-  static const int hist_nt = getenv("TW_WIDE_HIST_NT") ? atoi(getenv("TW_WIDE_HIST_NT")) : HIST_NT;
-#else
-  constexpr int emit_nt = EMIT_NT, hist_nt = HIST_NT;
-#endif
   auto grid_for = [&](int nt) { return dim3((cand_stride + nt * W_SLOTS - 1) / (nt * W_SLOTS), nbh); };
+  if (!a.keep_all && !hist_done) {
+    tw_prof_before(TW_K_TOPP, s);
+    TW_LAUNCH(wide_hist_kernel, grid_for(HIST_NT), dim3(HIST_NT), 0, s, a);
+    if (int e = tw_prof_after(s)) return e;
+  }
   if (!a.keep_all) {
-    // pass 0 locates the 1/64-logit bucket of the threshold; two 11-bit refinements at most follow
-    // (a head stops as soon as <= 4096 scores are left, normally after pass 0; its later passes
-    //  return at once)
-    for (int pass = 0; pass < 3; ++pass) {
-      tw_prof_before(TW_K_TOPP, s);
-      if (hist_nt == 256)      TW_LAUNCH(wide_hist_kernel<256>, grid_for(256), dim3(256), 0, s, a);
-      else if (hist_nt == 512) TW_LAUNCH(wide_hist_kernel<512>, grid_for(512), dim3(512), 0, s, a);
-      else                     TW_LAUNCH(wide_hist_kernel<1024>, grid_for(1024), dim3(1024), 0, s, a);
-      if (int e = tw_prof_after(s)) return e;
-      tw_prof_before(TW_K_TOPP, s);
-      TW_LAUNCH(wide_decide_kernel, dim3(nbh), dim3(64), 0, s, a);
-      if (int e = tw_prof_after(s)) return e;
-    }
+    tw_prof_before(TW_K_TOPP, s);
+    TW_LAUNCH(wide_decide_kernel, dim3(nbh), dim3(64), 0, s, a);
+    if (int e = tw_prof_after(s)) return e;
   }
   tw_prof_before(TW_K_TOPP, s);
-  if (emit_nt == 128)       TW_LAUNCH(wide_emit_kernel<128>, grid_for(128), dim3(128), 0, s, a);
-  else if (emit_nt == 512)  TW_LAUNCH(wide_emit_kernel<512>, grid_for(512), dim3(512), 0, s, a);
-  else if (emit_nt == 1024) TW_LAUNCH(wide_emit_kernel<1024>, grid_for(1024), dim3(1024), 0, s, a);
-  else                      TW_LAUNCH(wide_emit_kernel<256>, grid_for(256), dim3(256), 0, s, a);
+  TW_LAUNCH(wide_emit_kernel<EMIT_NT>, grid_for(EMIT_NT), dim3(EMIT_NT), 0, s, a);
   if (int e = tw_prof_after(s)) return e;
   tw_prof_before(TW_K_TOPP, s);
   TW_LAUNCH(wide_resolve_kernel, dim3(nbh), dim3(1024), 0, s, a);

@@ -1951,3 +1951,37 @@ def test_selector_and_pruner_at_the_head_count_limit():
     assert T.twilight_workspace_bytes(T.TW_WS_SELECT, kv, 3) == 0          # 65536 heads: over the limit
     with pytest.raises(T.TwilightError):
         T.twilight_select_pages(kv, q, w.budget.to(dev), st.sel_pages, st.sel_count, 3, st.ws_select)
+
+
+@pytest.mark.parametrize("keys", ["plain", "shifted", "one_bucket", "one_spike", "scaled"])
+@pytest.mark.parametrize("heads,bits,p", [((8, 1), 4, 0.95), ((8, 2), 4, 0.9999), ((8, 2), 4, 1e-4), ((4, 4), 4, 0.9), ((8, 2), 8, 0.95)],
+                         ids=["g8", "g4_high_p", "g4_low_p", "mha", "codes8"])
+def test_long_rows_where_the_histogram_can_miss(keys, heads, bits, p):
+    """Rows of the multi-workgroup top-p whose scores sit far from zero, all in one histogram bucket (the listed
+    scores overflow and the row is searched again), under one spike that no sample sees, or spread over hundreds of
+    logits; lengths at and beside the workgroups' and the list's limits.  The sets are the oracle's."""
+    lens = [8193, 16384, 20001, 150] if bits == 4 else [9000, 40]
+    w = synth.make_workload("hist", lens, num_q_heads=heads[0], num_kv_heads=heads[1], p=p, heavy_frac=0.005,
+                            alpha_range=(0.0, 4.0), full_selector=True, need_v=False, shuffle_pool=True, seed=91)
+    k = w.k.float()
+    if keys == "shifted":
+        k -= 4.0 * torch.sign(w.q[0, 0].float())
+    elif keys == "one_bucket":
+        k *= 1e-3
+    elif keys == "one_spike":
+        k[7777] = 3.0 * w.q[0, :heads[1]].float()
+    elif keys == "scaled":
+        k *= 40.0
+    w.k[:] = k.to(torch.bfloat16)
+    cache = build_cache(w, bits=bits)
+    st, q = run_pipeline(w, cache)
+    assert int(st.status.item()) == 0
+    G = heads[0] // heads[1]
+    for b in range(len(lens)):
+        r = oracle_seq(w, b, bits=bits)
+        for h in range(heads[0]):
+            check_topp(st.kept_idx[b, h, :int(st.kept_count[b, h])].cpu().numpy(), r["s_hat"][h], r["cand"][h], p)
+        for g in range(heads[1]):
+            gi = b * heads[1] + g
+            mine = np.unique(np.concatenate([st.kept_idx[b, h, :int(st.kept_count[b, h])].cpu().numpy() for h in range(g * G, g * G + G)]))
+            assert st.union_idx[gi, :int(st.union_count[gi])].cpu().numpy().tolist() == mine.tolist()
