@@ -4,7 +4,8 @@
 //
 // A row of up to E * NT entries lives in registers: thread t holds the keys of entries e * NT + t (coalesced loads; the
 // order e, then wave, then lane is the entries' order, which is what the ordered listing needs).  The Kp-th largest key
-// is located by bucketing the live key interval linearly (one pass when the scores are spread out), narrowing to the
+// (slots beyond the row's length are skipped by the whole workgroup, up to 8 slots per thread: a row far below the bound
+// costs what its own length does; 32 such branches cost a full row of 32768 entries 6 of 47 us) is located by bucketing the live key interval linearly (one pass when the scores are spread out), narrowing to the
 // bucket that holds it, and an exact rank computation once at most SEL_CAP candidates remain.  What bounds it is the
 // chain of block barriers and LDS round trips, so every wave scans the histogram and ranks the candidates on its own
 // (the same result in each) instead of waiting for one that does: per row 4 barriers where staging the keys in LDS and
@@ -56,6 +57,7 @@ __device__ __forceinline__ void tw_select_threshold(const uint32_t (&key)[E], in
   constexpr int LB = BPL == 8 ? 3 : (BPL == 16 ? 4 : 5);
   static_assert(BPL == (1 << LB), "SNB is 512, 1024 or 2048");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const auto in_row = [&](int e) { return E > 8 || e * NT < P; };
   __shared__ uint32_t red_lo[NW], red_hi[NW];
   __shared__ uint32_t sh_n;
   TW_STAMP(SB);
@@ -63,7 +65,7 @@ __device__ __forceinline__ void tw_select_threshold(const uint32_t (&key)[E], in
   uint32_t lo = 0xFFFFFFFFu, hi = 0u;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    if (e * NT + tid < P) {
+    if (in_row(e) && e * NT + tid < P) {
       lo = key[e] < lo ? key[e] : lo;
       hi = key[e] > hi ? key[e] : hi;
     }
@@ -113,6 +115,8 @@ __device__ __forceinline__ void tw_select_threshold(const uint32_t (&key)[E], in
     // buckets r = BPL * l .. from the top, then reads words j * 64 + l - consecutive lanes, consecutive banks.
 #pragma unroll
     for (int e = 0; e < E; ++e) {
+      if (KEEP) kept_bk[KEEP ? e : 0] = -1;
+      if (!in_row(e)) continue;
       const bool in = e * NT + tid < P && key[e] >= klo && key[e] <= khi;
       const int bk = bucket_of(key[e]);
       if (KEEP) kept_bk[KEEP ? e : 0] = in ? bk : -1;
@@ -144,7 +148,7 @@ __device__ __forceinline__ void tw_select_threshold(const uint32_t (&key)[E], in
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const int i = e * NT + tid;
-        if (in_bucket(e, bkt)) {
+        if (in_row(e) && in_bucket(e, bkt)) {
           const uint32_t at = atomicAdd(&sh_n, 1u);
           if (at < (uint32_t)SEL_CAP) cand[at] = ((unsigned long long)key[e] << 32) | (uint32_t)~i;
         }
@@ -168,7 +172,7 @@ __device__ __forceinline__ void tw_select_threshold(const uint32_t (&key)[E], in
     uint32_t nlo = 0xFFFFFFFFu, nhi = 0u;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      if (in_bucket(e, bkt)) {
+      if (in_row(e) && in_bucket(e, bkt)) {
         nlo = key[e] < nlo ? key[e] : nlo;
         nhi = key[e] > nhi ? key[e] : nhi;
       }
@@ -192,18 +196,21 @@ __device__ __forceinline__ void tw_select_threshold(const uint32_t (&key)[E], in
 template <int NT, int E, class Put>
 __device__ __forceinline__ void tw_select_list(const uint32_t (&key)[E], int P, uint32_t T, uint32_t need_eq, uint32_t* cnt, Put put) {
   constexpr int NW = NT / 64, SEGS = E * NW, Q = (SEGS + 63) / 64;
+  const auto in_row = [&](int e) { return E > 8 || e * NT < P; };
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
+    if (!in_row(e)) continue;
     const bool in = e * NT + tid < P;
     const uint32_t gt = (uint32_t)__popcll(__ballot(in && key[e] > T)), eq = (uint32_t)__popcll(__ballot(in && key[e] == T));
     if (lane == 0) cnt[e * NW + wave] = gt | (eq << 16);
   }
   __syncthreads();
   uint32_t excl[Q], total;
-  tw_seg_prefix<Q>(cnt, SEGS, excl, &total);
+  tw_seg_prefix<Q>(cnt, ((P + NT - 1) / NT) * NW, excl, &total);
 #pragma unroll
   for (int e = 0; e < E; ++e) {
+    if (!in_row(e)) continue;
     const bool in = e * NT + tid < P, gt = in && key[e] > T, eq = in && key[e] == T;
     const unsigned long long bg = __ballot(gt), be = __ballot(eq);
     const uint32_t off = (uint32_t)__builtin_amdgcn_readlane((int)excl[(e * NW) >> 6], ((e * NW) & 63) + wave);

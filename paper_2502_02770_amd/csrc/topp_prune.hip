@@ -728,8 +728,9 @@ constexpr int HP_USTAGE = 4096;               // union lists up to this length l
 // scoring launch wrote: the workgroup's waves share the list (one page of 64 (token, group) lanes per wave and step,
 // the arithmetic of int4_score_kernel), the scores cross to their owner threads through LDS.
 // FUSE == 2: the page list too is made here, from the bounds of all pages (the selection of page_select_lds_kernel).
-template <int NT, int EPT, int G, bool TOK = false, int FUSE = 0>
-__global__ __launch_bounds__(NT, NT == 512 ? 6 : 1) void topp_head_kernel(HeadArgs a) {
+// BITS: width of the quantised copy's codes (FUSE == 2; else 4).
+template <int NT, int EPT, int G, bool TOK = false, int FUSE = 0, int BITS = 4>
+__global__ __launch_bounds__(NT, NT <= 512 ? 6 : 1) void topp_head_kernel(HeadArgs a) {
   constexpr int NW = NT / 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int b_ = blockIdx.y, h_ = blockIdx.x;
@@ -746,7 +747,10 @@ __global__ __launch_bounds__(NT, NT == 512 ? 6 : 1) void topp_head_kernel(HeadAr
   // FUSE == 2: everything the page selection reads is asked for here, before the sequence's length is known (any
   // entry of the head's row of bounds and of the sequence's page-table row may be read): the bounds and the
   // page-table entries of the pages j * NT + tid, which this thread will list (1024-thread workgroups, 4 entries each; the 512-thread form, short of registers, asks when it knows the length)
-  constexpr int SEL_E = 4096 / NT;
+  // FUSE == 2 with few candidates: the row of pages is bounded too (the launch's rule), and LDS is sized for that
+  constexpr bool SMALL = FUSE == 2 && NT <= 512 && EPT == 4;
+  constexpr int SEL_E = SMALL ? 4 : 4096 / NT;
+  constexpr int BWORDS = SMALL ? SEL_E * NT * TW_PAGE / 32 : HP_BITMAP_WORDS, USTAGE = SMALL ? 4 * NT : HP_USTAGE;
   constexpr bool SEL_EARLY = FUSE == 2 && NT >= 1024;
   const int n = a.seq_lens[b];
   const int budget_b = FUSE == 2 ? a.budget[b] : 0;
@@ -797,16 +801,16 @@ __global__ __launch_bounds__(NT, NT == 512 ? 6 : 1) void topp_head_kernel(HeadAr
   __shared__ uint32_t histC[HP_NB];
   __shared__ unsigned long long cand_mass[HP_CAP];
   __shared__ uint32_t cand_key[HP_CAP];
-  __shared__ uint32_t big_s[HP_BITMAP_WORDS + HP_USTAGE];   // position bitmap, then the union list on its way out
+  __shared__ uint32_t big_s[BWORDS + USTAGE];               // position bitmap, then the union list on its way out
   uint32_t* const bitmap = big_s;                            // (FUSE: first the scores on their way to their owners)
-  int32_t* const ustage = (int32_t*)(big_s + HP_BITMAP_WORDS);
+  int32_t* const ustage = (int32_t*)(big_s + BWORDS);
   __shared__ unsigned long long tail_s[NW];
   __shared__ uint32_t ws32[16];
   __shared__ float redf[NW];
   __shared__ uint32_t sh_n, sh_kept, sh_T, sh_last;
 
-  __shared__ int32_t pages_s[FUSE == 2 ? 512 : 1];   // FUSE == 2: the head's page list ...
-  __shared__ int32_t pool_s[FUSE == 2 ? 512 : 1];    // ... and the pages' places in the pool
+  __shared__ int32_t pages_s[FUSE == 2 ? NT * EPT / TW_PAGE : 1];   // FUSE == 2: the head's page list ...
+  __shared__ int32_t pool_s[FUSE == 2 ? NT * EPT / TW_PAGE : 1];    // ... and the pages' places in the pool
   if (FUSE == 2) {
     constexpr int SNB = 512;
     uint32_t* const hist = big_s;                   // the selection's arrays lie in big_s
@@ -822,6 +826,7 @@ __global__ __launch_bounds__(NT, NT == 512 ? 6 : 1) void topp_head_kernel(HeadAr
         const float* const sc = a.bounds + (long long)bh * a.max_pages;
 #pragma unroll
         for (int e = 0; e < SEL_E; ++e) {
+          if (e * NT >= P) continue;                 // (block-uniform)
           const int i = e * NT + tid < P ? e * NT + tid : P - 1;
           sel_pre[FUSE == 2 ? e : 0] = sc[i];
           sel_pt[FUSE == 2 ? e : 0] = ptab[i];
@@ -850,13 +855,13 @@ __global__ __launch_bounds__(NT, NT == 512 ? 6 : 1) void topp_head_kernel(HeadAr
   float s[EPT];
   int pg[NPG];
   if (FUSE) {
-    static_assert(NT * EPT <= (HP_BITMAP_WORDS + HP_USTAGE), "scores of a row must fit the staging array");
+    static_assert(NT * EPT <= BWORDS + USTAGE, "scores of a row must fit the staging array");
     float* const sc_s = (float*)big_s;
     __shared__ int qi_s[1][32];
     __shared__ float qred[4];
     __shared__ float qc_s[1];
     // this wave's share of the list: lane k holds its k-th page (at most EPT * 4 <= 32 of them)
-    constexpr int UF = NT >= 1024 ? 8 : 4;            // pages in flight per wave (register budget)
+    constexpr int UF = (NT >= 1024 || EPT == 4 ? 8 : 4) / (BITS == 8 ? 2 : 1);   // pages in flight per wave (register budget)
     const int ppw = ((count + NW - 1) / NW + UF - 1) & ~(UF - 1);
     const int first = __builtin_amdgcn_readfirstlane(wave) * ppw;   // (scalar: the loop below is wave-uniform)
     int my_lp = -1, my_pool = -1;
@@ -878,13 +883,14 @@ __global__ __launch_bounds__(NT, NT == 512 ? 6 : 1) void topp_head_kernel(HeadAr
       qs = __builtin_amdgcn_sdot4(qw[k], 0x01010101, qs, false);
     }
     const float qsf = (float)qs, cc = qc_s[0];
+    const int qs128 = BITS == 8 ? 128 * qs : 0;       // 8-bit codes enter the signed dot4 as code - 128
 #pragma unroll 1
     for (int k0 = 0; k0 < npages; k0 += UF) {
       // UF pages per round: all their loads first (unconditional: lanes past the wave's last page hold pool -1 and
       // read pool page 0), then the arithmetic; every lane of a quad stores the token's score (same word), so the
       // round has no branches and the loads stay together.  Slots past the list's end get -inf (inside the array:
       // NW * ppw <= NT * EPT / 16 pages).
-      uint4 nib[UF];
+      uint4 nib[UF][BITS == 8 ? 2 : 1];
       uint32_t meta[UF];
       int lpk[UF], plk[UF];
 #pragma unroll
@@ -892,18 +898,15 @@ __global__ __launch_bounds__(NT, NT == 512 ? 6 : 1) void topp_head_kernel(HeadAr
         lpk[kk] = __builtin_amdgcn_readlane(my_lp, (k0 + kk) & 63);
         plk[kk] = __builtin_amdgcn_readlane(my_pool, (k0 + kk) & 63);
         const long long blk = ((long long)(plk[kk] >= 0 ? plk[kk] : 0) * a.Hkv + g) * 64;
-        nib[kk] = a.kq_pool[blk + lane];
+        tw_load_raw<BITS>(a.kq_pool, blk + lane, nib[kk]);
         meta[kk] = a.kq_meta[blk + lane];
       }
 #pragma unroll
       for (int kk = 0; kk < UF; ++kk) {
         int u[8];
-        u[0] = nib[kk].x & 0x0F0F0F0F; u[1] = (nib[kk].x >> 4) & 0x0F0F0F0F;
-        u[2] = nib[kk].y & 0x0F0F0F0F; u[3] = (nib[kk].y >> 4) & 0x0F0F0F0F;
-        u[4] = nib[kk].z & 0x0F0F0F0F; u[5] = (nib[kk].z >> 4) & 0x0F0F0F0F;
-        u[6] = nib[kk].w & 0x0F0F0F0F; u[7] = (nib[kk].w >> 4) & 0x0F0F0F0F;
+        tw_unpack_codes<BITS>(nib[kk], u);
         const bool valid = plk[kk] >= 0 && lpk[kk] * TW_PAGE + (lane >> 2) < n;
-        const float T = tw_token_sum(meta[kk], tw_group_dot(qw, u, 0), qsf);
+        const float T = tw_token_sum(meta[kk], tw_group_dot(qw, u, qs128), qsf);
         sc_s[(first + k0 + kk) * TW_PAGE + (lane >> 2)] = valid ? __fmul_rn(T, cc) : -__builtin_inff();
       }
     }
@@ -962,7 +965,7 @@ __global__ __launch_bounds__(NT, NT == 512 ? 6 : 1) void topp_head_kernel(HeadAr
     // rank and numerator of every score: computed once and kept, or (512-thread workgroups, which are there
     // to fit more of them on a CU) recomputed from the score where needed - a few instructions that save
     // 2 * EPT registers
-    constexpr bool RECOMP = NT <= 512;
+    constexpr bool RECOMP = NT <= 512 && EPT > 4;
     uint32_t rk[RECOMP ? 1 : EPT];
     float ef[RECOMP ? 1 : EPT];
     if (!RECOMP) {
@@ -1114,7 +1117,7 @@ __global__ __launch_bounds__(NT, NT == 512 ? 6 : 1) void topp_head_kernel(HeadAr
     for (int e = 0; e < EPT; ++e) {
       if ((keep >> e) & 1u) {                       // kept => valid score => a token inside the sequence
         const int tok = pg[e % NPG];
-        if (tok < HP_BITMAP_WORDS * 32) atomicOr(&bitmap[tok >> 5], 1u << (tok & 31));
+        if (tok < BWORDS * 32) atomicOr(&bitmap[tok >> 5], 1u << (tok & 31));
         if (out) { if (pos < (uint32_t)a.kept_stride) out[pos] = tok; ++pos; }
       }
     }
@@ -1125,7 +1128,7 @@ __global__ __launch_bounds__(NT, NT == 512 ? 6 : 1) void topp_head_kernel(HeadAr
     const uint32_t mask = (keep >> (16 * v)) & ((1u << PB) - 1u);
     if (mask) {
       const int tok0 = pg[v] * TW_PAGE + (EPT < 16 ? (c0 & 15) : 0);
-      if (tok0 + 15 < HP_BITMAP_WORDS * 32) atomicOr(&bitmap[tok0 >> 5], mask << (tok0 & 31));
+      if (tok0 + 15 < BWORDS * 32) atomicOr(&bitmap[tok0 >> 5], mask << (tok0 & 31));
       if (a.kept_idx) {
         int32_t* out = a.kept_idx + (long long)bh * a.kept_stride;
 #pragma unroll
@@ -1232,7 +1235,7 @@ __global__ __launch_bounds__(NT, NT == 512 ? 6 : 1) void topp_head_kernel(HeadAr
     for (int w = 0; w < NW; ++w) { const uint32_t t = ws32[w]; run += w < wave ? t : 0u; utotal += t; }
     TW_STAMP_IF(gi == 0, 16);
     // positions staged in LDS and copied out coalesced when they fit (the usual case; block-uniform), else stored directly
-    const bool staged = utotal <= (uint32_t)HP_USTAGE;
+    const bool staged = utotal <= (uint32_t)USTAGE;
     auto put = [&](uint32_t pos, int tok) {
       if (staged) ustage[pos] = tok;
       else if (pos < (uint32_t)a.union_stride) uout[pos] = tok;
@@ -1283,7 +1286,7 @@ __global__ __launch_bounds__(NT, NT == 512 ? 6 : 1) void topp_head_kernel(HeadAr
     const uint32_t uincl = tw_block_scan_u32(ucnt, ws32, &utotal);
     TW_STAMP_IF(gi == 0, 16);
     uint32_t upos = uincl - ucnt;
-    if (utotal <= (uint32_t)HP_USTAGE) {               // block-uniform; the usual case
+    if (utotal <= (uint32_t)USTAGE) {               // block-uniform; the usual case
       // positions staged in LDS, then copied out coalesced: a dense word costs its thread 32 scattered
       // stores otherwise, one store instruction of the whole wave each (1.5 us of the kernel's tail)
       for (int i = w0; i < w1; ++i) {
@@ -1421,13 +1424,13 @@ int run_row_sample(const twilight_kv_t* kv, const TwDims& d, const void* q, floa
   return tw_prof_after(s);
 }
 
-template <int NT, int EPT, bool TOK, int FUSE>
+template <int NT, int EPT, bool TOK, int FUSE, int BITS>
 void launch_topp_one(const HeadArgs& f, int G, dim3 grid, hipStream_t s) {
   switch (G) {
-    case 1: TW_LAUNCH((topp_head_kernel<NT, EPT, 1, TOK, FUSE>), grid, dim3(NT), 0, s, f); break;
-    case 2: TW_LAUNCH((topp_head_kernel<NT, EPT, 2, TOK, FUSE>), grid, dim3(NT), 0, s, f); break;
-    case 4: TW_LAUNCH((topp_head_kernel<NT, EPT, 4, TOK, FUSE>), grid, dim3(NT), 0, s, f); break;
-    default: TW_LAUNCH((topp_head_kernel<NT, EPT, 8, TOK, FUSE>), grid, dim3(NT), 0, s, f); break;
+    case 1: TW_LAUNCH((topp_head_kernel<NT, EPT, 1, TOK, FUSE, BITS>), grid, dim3(NT), 0, s, f); break;
+    case 2: TW_LAUNCH((topp_head_kernel<NT, EPT, 2, TOK, FUSE, BITS>), grid, dim3(NT), 0, s, f); break;
+    case 4: TW_LAUNCH((topp_head_kernel<NT, EPT, 4, TOK, FUSE, BITS>), grid, dim3(NT), 0, s, f); break;
+    default: TW_LAUNCH((topp_head_kernel<NT, EPT, 8, TOK, FUSE, BITS>), grid, dim3(NT), 0, s, f); break;
   }
 }
 
@@ -1435,10 +1438,16 @@ void launch_topp_one(const HeadArgs& f, int G, dim3 grid, hipStream_t s) {
 //  - few heads: one 1024-thread workgroup per head (4 or 8 candidates per thread);
 //  - more heads than CUs and rows of at most 4096 candidates: 512-thread workgroups, two to a CU (a 1024-thread
 //    workgroup has a CU to itself at this register count: 8 x 32 x 4 = 1024 heads took 35.8 us that way, 22.9 us so);
+//  - rows of at most 2048 candidates (and, with the selection inside, at most 2048 pages): 512-thread workgroups with 4
+//    candidates per thread, whatever the number of heads.  The kernel is a chain of block barriers; half the waves make
+//    each shorter (32 heads x 1024 candidates 13.4 -> 10.8 us, 320 x 1136 15.6 -> 12.0), and with the LDS arrays sized
+//    for the short rows four workgroups share a CU (2048 heads x 1024 candidates of 512 pages 48.1 -> 30.6);
+//  - rows of at most 1024 candidates and 1024 pages with more heads than CUs: 256-thread workgroups (2048 heads x 256
+//    candidates 39.8 -> 23.9 us; 32 heads x 1024 candidates 10.8 -> 11.1, so few heads keep the 512 threads);
 //  - many heads with a bound above 4096 candidates (ragged batches): heads of at most 4096 candidates go to a
 //    512-thread launch of their own, the longer ones to the 1024-thread launch.
-// FUSE: the kernels score the candidates themselves (page lists, 4-bit codes).
-template <bool TOK, int FUSE = 0>
+// FUSE: the kernels score the candidates themselves (page lists).
+template <bool TOK, int FUSE = 0, int BITS = 4>
 int launch_topp(HeadArgs f, const TwDims& d, int cand_stride, hipStream_t s) {
   const dim3 grid(d.Hq, d.batch);
   const long long heads = (long long)d.batch * d.Hq;
@@ -1447,14 +1456,16 @@ int launch_topp(HeadArgs f, const TwDims& d, int cand_stride, hipStream_t s) {
   if (cand_stride > 4096 && heads > 2ll * tw_num_cus()) {
     f.n_upto = 4096;
     tw_prof_before(FUSE == 2 ? TW_K_SELECT_SCORE_TOPP : (FUSE == 1 ? TW_K_SCORE_TOPP : TW_K_TOPP), s);
-    launch_topp_one<512, 8, TOK, FUSE>(f, d.G, grid, s);
+    launch_topp_one<512, 8, TOK, FUSE, BITS>(f, d.G, grid, s);
     if (int e = tw_prof_after(s)) return e;
     f.n_above = 4096; f.n_upto = cand_stride;
   }
   tw_prof_before(FUSE == 2 ? TW_K_SELECT_SCORE_TOPP : (FUSE == 1 ? TW_K_SCORE_TOPP : TW_K_TOPP), s);
-  if (cand_stride <= 4096 && heads > tw_num_cus()) launch_topp_one<512, 8, TOK, FUSE>(f, d.G, grid, s);
-  else if (cand_stride <= 4096) launch_topp_one<1024, 4, TOK, FUSE>(f, d.G, grid, s);
-  else launch_topp_one<1024, 8, TOK, FUSE>(f, d.G, grid, s);
+  if (FUSE == 2 && heads > tw_num_cus() && cand_stride <= 1024 && d.max_pages <= 1024) launch_topp_one<FUSE == 2 ? 256 : 512, 4, TOK, FUSE, BITS>(f, d.G, grid, s);
+  else if (cand_stride <= 2048 && (FUSE != 2 || d.max_pages <= 2048)) launch_topp_one<512, 4, TOK, FUSE, BITS>(f, d.G, grid, s);
+  else if (cand_stride <= 4096 && heads > tw_num_cus()) launch_topp_one<512, 8, TOK, FUSE, BITS>(f, d.G, grid, s);
+  else if (cand_stride <= 4096) launch_topp_one<1024, 4, TOK, FUSE, BITS>(f, d.G, grid, s);
+  else launch_topp_one<1024, 8, TOK, FUSE, BITS>(f, d.G, grid, s);
   return tw_prof_after(s);
 }
 
@@ -1584,7 +1595,7 @@ extern "C" int twilight_topp_prune(const twilight_kv_t* kv, const void* q, const
 // bounds != nullptr: the kernel also selects the head's pages from the bounds of all pages ([b][Hq][max_pages],
 // with the budgets) and writes the lists to sel_pages / sel_count; else it reads the lists from there.
 bool tw_prune_fused_ok(const TwDims& d, int max_sel, bool with_select) {
-  if (d.bits != 4 || max_sel <= 0 || !tw_prune_uses_head_kernel(d, false, max_sel)) return false;
+  if (max_sel <= 0 || !tw_prune_uses_head_kernel(d, false, max_sel) || (d.bits != 4 && !with_select)) return false;
   return !with_select || d.max_pages <= 4096;      // the selection's keys share the kernel's LDS staging array
 }
 int tw_prune_fused(const twilight_kv_t* kv, const TwDims& d, const void* q, const float* bounds, const int32_t* budget,
@@ -1602,6 +1613,8 @@ int tw_prune_fused(const twilight_kv_t* kv, const TwDims& d, const void* q, cons
   f.q = (const uint16_t*)q; f.page_table = kv->page_table; f.kq_pool = (const uint4*)kv->kq_pool;
   f.kq_meta = (const uint32_t*)kv->kq_meta; f.pool_pages = d.pool_pages;
   f.bounds = bounds; f.budget = budget; f.sel_pages_w = sel_pages; f.sel_count_w = sel_count;
+  if (bounds && d.bits == 8) return launch_topp<false, 2, 8>(f, d, max_sel * TW_PAGE, s);
+  if (bounds && d.bits == 2) return launch_topp<false, 2, 2>(f, d, max_sel * TW_PAGE, s);
   if (bounds) return launch_topp<false, 2>(f, d, max_sel * TW_PAGE, s);
   return launch_topp<false, 1>(f, d, max_sel * TW_PAGE, s);
 }

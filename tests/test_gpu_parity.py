@@ -523,8 +523,7 @@ def _lists_equal(a, b, what):
 @pytest.mark.parametrize("bits", [4, 2, 8])
 def test_select_prune_equals_the_separate_calls_with_append(bits):
     """twilight_select_prune with the step's new token: the cache, the page lists, the kept sets and the unions are
-    those of twilight_append_select followed by twilight_topp_prune, bit for bit (4-bit codes: the one-launch
-    selector + pruner; 2 and 8 bits: the call falls back to the separate launches)."""
+    those of twilight_append_select followed by twilight_topp_prune, bit for bit, for every width of the codes."""
     T = _T()
     lens = [1009, 48, 33, 2049, 513, 700]
     w = synth.make_workload("selprune", lens, budget=[max(16, n // 4) for n in lens], p=0.9, heavy_frac=0.02,
@@ -1985,3 +1984,24 @@ def test_long_rows_where_the_histogram_can_miss(keys, heads, bits, p):
             gi = b * heads[1] + g
             mine = np.unique(np.concatenate([st.kept_idx[b, h, :int(st.kept_count[b, h])].cpu().numpy() for h in range(g * G, g * G + G)]))
             assert st.union_idx[gi, :int(st.union_count[gi])].cpu().numpy().tolist() == mine.tolist()
+
+
+@pytest.mark.parametrize("bits", [2, 4, 8])
+@pytest.mark.parametrize("max_sel,n,seqs", [(127, 32768, 2), (128, 32753, 2), (128, 32769, 2), (129, 9000, 2), (256, 40001, 2),
+                                            (512, 20000, 2), (1, 17, 2), (64, 16384, 36), (64, 16385, 36), (65, 16000, 36), (3, 50, 36)])
+def test_one_launch_select_prune_at_the_limits_of_its_workgroup_sizes(bits, max_sel, n, seqs):
+    """64 / 65 pages listed with more heads than CUs (1024 candidates, 1024 / 1025 pages), 128 / 129 pages listed (2048 candidates), 2048 / 2049 pages in the row and 256 pages (4096 candidates) are where
+    the one-launch selector + pruner changes its workgroup; every code width against the separate calls."""
+    T = _T()
+    w = synth.make_workload("limits", [n] + [1 + n // (2 + i) for i in range(1, seqs)], num_q_heads=8, num_kv_heads=2,
+                            budget=[max_sel * 16] + [max_sel * 5 + i for i in range(1, seqs)],
+                            p=0.9, heavy_frac=0.01, alpha_range=(0.0, 3.0), shuffle_pool=True, need_v=False, seed=92)
+    cache = build_cache(w, bits=bits)
+    q, budget = w.q.to(cache.device), w.budget.to(cache.device)
+    sa = T.DecodeStep(cache, max_sel=max_sel, with_kept_idx=True)
+    sb = T.DecodeStep(cache, max_sel=max_sel, with_kept_idx=True)
+    sa.select(q, budget)
+    sa.prune(q, w.p)
+    sb.select_prune(None, None, None, q, budget, w.p)
+    torch.cuda.synchronize()
+    _lists_equal(sa, sb, "select_prune")
