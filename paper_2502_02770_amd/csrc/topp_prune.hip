@@ -1371,6 +1371,10 @@ int run_score(const twilight_kv_t* kv, const TwDims& d, const void* q, const int
   constexpr int pw_env = 0, x_env = 0;
   constexpr bool valu_only = false;
 #endif
+  // With the histogram every workgroup ends by adding its non-empty buckets to the heads' words, on which the row's other
+  // workgroups queue: at most 96 to a row (1 x 32 heads x 100034 tokens: 391 to a row 54 us, 98 26, 49 23; 1 x 64 heads x
+  // 26293: 103 to a row 30 us, 51 18; fewer than that leaves the chip idle: 2 x 32 x 85246 with 83 to a row 31 us, 42 37).
+  if (ghist) while (a.pw < 64 && bound > 96 * 4 * a.pw) a.pw *= 2;
   if (pw_env >= 4 && pw_env <= 64) a.pw = pw_env;
   dim3 grid((bound + 4 * a.pw - 1) / (4 * a.pw), d.batch * (full ? d.Hkv : d.Hq));
   a.rotate = 0;

@@ -96,24 +96,30 @@ __device__ __forceinline__ void wide_load(const float* row, int chunk0, int tid,
 
 // Grid and histogram from the stored scores.  Every workgroup of a head takes the same sample of its row - 1024 scores
 // evenly spread - so all lay the same grid; the first one leaves it for the passes that follow.
-__global__ __launch_bounds__(1024) void wide_hist_kernel(WideArgs a) {
-  constexpr int NT = 1024, W_CHUNK = NT * W_SLOTS;
+template <int NT>
+__global__ __launch_bounds__(NT) void wide_hist_kernel(WideArgs a) {
+  constexpr int W_CHUNK = NT * W_SLOTS, NW = NT / 64, K = 1024 / NT;
   const int bh = blockIdx.y, b = bh / a.Hq, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int N = wide_count(a, b, bh) * TW_PAGE;
   if ((long long)blockIdx.x * W_CHUNK >= N) return;
   const int chunk0 = blockIdx.x * W_CHUNK;
   const float* const row = a.scores + (long long)bh * a.cand_stride;
-  const float sv = row[(int)(((long long)tid * N) >> 10)];
+  float sv[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) sv[k] = row[(int)(((long long)(k * NT + tid) * N) >> 10)];
   const float mx = tw_key_to_float(wide_headmax(a.headmax, bh, lane));
   __shared__ unsigned long long hist[WH_NB];
-  __shared__ float sum_s[16][3];
+  __shared__ float sum_s[NW][3];
   for (int i = tid; i < WH_NB; i += NT) hist[i] = 0;
   float s[W_SLOTS];
   wide_load<NT>(row, chunk0, tid, N, a.cand_stride, s);
   float w0 = 0.f, w1 = 0.f, w2 = 0.f;
-  if (sv > -__builtin_inff() && mx < __builtin_inff()) {
-    const float t = sv - mx, w = __expf(t);
-    w0 = w; w1 = w * t; w2 = w * t * t;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    if (sv[k] > -__builtin_inff() && mx < __builtin_inff()) {
+      const float t = sv[k] - mx, w = __expf(t);
+      w0 += w; w1 += w * t; w2 += w * t * t;
+    }
   }
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) { w0 += __shfl_xor(w0, o, 64); w1 += __shfl_xor(w1, o, 64); w2 += __shfl_xor(w2, o, 64); }
@@ -121,7 +127,7 @@ __global__ __launch_bounds__(1024) void wide_hist_kernel(WideArgs a) {
   __syncthreads();
   w0 = w1 = w2 = 0.f;
 #pragma unroll
-  for (int w = 0; w < 16; ++w) { w0 += sum_s[w][0]; w1 += sum_s[w][1]; w2 += sum_s[w][2]; }
+  for (int w = 0; w < NW; ++w) { w0 += sum_s[w][0]; w1 += sum_s[w][1]; w2 += sum_s[w][2]; }
   WhGrid gr = wh_grid(w0, w1, w2);
   if (w0 > 0.f) gr.ref += mx;
   if (blockIdx.x == 0 && tid == 0) a.hgrid[bh] = gr;
@@ -297,7 +303,6 @@ __global__ __launch_bounds__(NT) void wide_emit_kernel(WideArgs a) {
   }
 }
 
-constexpr int WR_EPT = W_CAP / 1024;
 constexpr int WR_CAP = 64;
 struct ResolveLds {
   unsigned long long histM[HP_NB];
@@ -311,9 +316,9 @@ struct ResolveLds {
 // Threshold among scores of ranks [rlo, rlo + 2^shift): the largest key whose upper set, with the mass A above the
 // interval, reaches `target`.  The interval is narrowed 9 bits per round with a 512-bucket LDS histogram until at most
 // 64 scores are left, and those are compared exactly on the scores' own bits; more than 64 scores of one rank are one
-// tier.  each(f) calls f(key, score) for every score of this thread; called by all 1024 threads.  *found: the interval
+// tier.  each(f) calls f(key, score) for every score of this thread; called by all NT threads.  *found: the interval
 // holds the crossing.
-template <class Each>
+template <int NT, class Each>
 __device__ __forceinline__ uint32_t wide_threshold(Each each, float m, uint32_t rlo, int shift, uint32_t pop, unsigned long long A,
                                                    unsigned long long target, ResolveLds& L, bool* found) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -324,7 +329,7 @@ __device__ __forceinline__ uint32_t wide_threshold(Each each, float m, uint32_t 
     const int nshift = shift >= 9 ? shift - 9 : 0;
     const uint32_t nb = 1u << (shift - nshift);   // buckets that cover the interval
     __syncthreads();
-    for (int i = tid; i < HP_NB; i += 1024) { L.histM[i] = 0; L.histC[i] = 0; }
+    for (int i = tid; i < HP_NB; i += NT) { L.histM[i] = 0; L.histC[i] = 0; }
     __syncthreads();
     each([&](uint32_t, float s) {
       float e;
@@ -390,7 +395,7 @@ __device__ __forceinline__ uint32_t wide_threshold(Each each, float m, uint32_t 
     } else {
       T = L.red[0];
 #pragma unroll
-      for (int w = 1; w < 16; ++w) T = L.red[w] < T ? L.red[w] : T;
+      for (int w = 1; w < NT / 64; ++w) T = L.red[w] < T ? L.red[w] : T;
     }
     if (lane == 0) L.T = T;
   }
@@ -400,13 +405,20 @@ __device__ __forceinline__ uint32_t wide_threshold(Each each, float m, uint32_t 
   return *found ? T : 0xFFFFFFFFu;
 }
 
-// One workgroup per head.  The undecided scores sit in registers, 8 per thread.  A head whose list overflowed or does
-// not hold the threshold (the exact sums decide) is searched from its whole row instead, and its bitmap written anew.
-__global__ __launch_bounds__(1024) void wide_resolve_kernel(WideArgs a) {
+// One workgroup per head walks the head's list (a few dozen scores as a rule, some thousand in a near-uniform row).  A
+// head whose list overflowed or does not hold the threshold (the exact sums decide) is searched from its whole row
+// instead, and its bitmap written anew.
+template <int NT>
+__global__ __launch_bounds__(NT) void wide_resolve_kernel(WideArgs a) {
+  constexpr int NW = NT / 64;
   const int bh = blockIdx.x, b = bh / a.Hq, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   __shared__ ResolveLds L;
-  __shared__ uint32_t red_hi[16];
-  __shared__ unsigned long long zred[16];
+  __shared__ uint32_t red_hi[NW];
+  __shared__ unsigned long long zred[NW];
+  const uint2* const list = a.ulist + (long long)bh * W_CAP;
+  const uint2 first = list[tid];                  // (inside the buffer whatever the list's length; all loads of the prologue together)
+  const uint32_t listed = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.ucount[(long long)bh * TW_CTR]);
+  const unsigned long long Z0 = a.sums[(long long)bh * WS_SUMS], A0 = a.sums[(long long)bh * WS_SUMS + 1];
   const uint32_t mk = wide_headmax(a.headmax, bh, lane);
   const bool search = !a.keep_all && mk != 0;
   const float m = tw_key_to_float(mk);
@@ -414,52 +426,45 @@ __global__ __launch_bounds__(1024) void wide_resolve_kernel(WideArgs a) {
   uint32_t add = 0;
   bool whole_row = false;
   if (search) {                                   // block-uniform
-    const uint32_t listed = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.ucount[(long long)bh * TW_CTR]);
-    const unsigned long long Z = a.sums[(long long)bh * WS_SUMS], A = a.sums[(long long)bh * WS_SUMS + 1];
     const uint32_t cn = listed < (uint32_t)W_CAP ? listed : (uint32_t)W_CAP;
-    uint32_t key[WR_EPT], tok[WR_EPT];
-    uint32_t rmin = 0xFFFFFFFFu, rmax = 0u;
-#pragma unroll
-    for (int e = 0; e < WR_EPT; ++e) {
-      const uint32_t i = (uint32_t)(e * 1024 + tid);
-      key[e] = 0; tok[e] = 0;
-      if (e * 1024u >= cn) continue;              // (block-uniform)
-      const uint2 x = a.ulist[(long long)bh * W_CAP + (i < cn ? i : 0u)];
-      key[e] = x.x; tok[e] = x.y;
-      if (i < cn) {
-        const uint32_t r = hp_rank_only(m, tw_key_to_float(x.x));
-        rmin = r < rmin ? r : rmin;
-        rmax = r > rmax ? r : rmax;
-      }
-    }
-    rmin = ~tw_wave_max_u32(~rmin);
-    rmax = tw_wave_max_u32(rmax);
-    if (lane == 0) { L.red[wave] = rmin; red_hi[wave] = rmax; }
-    __syncthreads();
-    rmin = ~tw_row_max_u32(~L.red[lane & 15]);
-    rmax = tw_row_max_u32(red_hi[lane & 15]);
-    rmin = (uint32_t)__builtin_amdgcn_readfirstlane((int)rmin);
-    rmax = (uint32_t)__builtin_amdgcn_readfirstlane((int)rmax);
+    auto walk = [&](auto f) {                     // f(key, token); the first NT entries sit in registers
+      if ((uint32_t)tid < cn) f(first.x, first.y);
+#pragma unroll 4
+      for (uint32_t i = (uint32_t)(NT + tid); i < cn; i += NT) { const uint2 x = list[i]; f(x.x, x.y); }
+    };
     uint32_t T = 0xFFFFFFFFu;
     bool found = false;
-    const unsigned long long target = hp_target(a.p, Z);
-    if (listed > 0 && listed <= (uint32_t)W_CAP && A < target) {            // block-uniform
-      const uint32_t span = rmax - rmin;
-      auto each = [&](auto f) {
-#pragma unroll
-        for (int e = 0; e < WR_EPT; ++e)
-          if (e * 1024u < cn && (uint32_t)(e * 1024 + tid) < cn) f(key[e], tw_key_to_float(key[e]));
-      };
-      T = wide_threshold(each, m, rmin, span ? 32 - __clz(span) : 0, cn, A, target, L, &found);
+    const unsigned long long target = hp_target(a.p, Z0);
+    if (listed > 0 && listed <= (uint32_t)W_CAP && A0 < target) {           // block-uniform
+      uint32_t rlo = 0;
+      int shift = 0;
+      if (cn > (uint32_t)WR_CAP) {                // ranks the list spans (a short one is resolved as it is: 27 bits hold every rank)
+        uint32_t rmin = 0xFFFFFFFFu, rmax = 0u;
+        walk([&](uint32_t k, uint32_t) {
+          const uint32_t r = hp_rank_only(m, tw_key_to_float(k));
+          rmin = r < rmin ? r : rmin;
+          rmax = r > rmax ? r : rmax;
+        });
+        rmin = ~tw_wave_max_u32(~rmin);
+        rmax = tw_wave_max_u32(rmax);
+        if (lane == 0) { L.red[wave] = rmin; red_hi[wave] = rmax; }
+        __syncthreads();
+        rlo = (uint32_t)__builtin_amdgcn_readfirstlane((int)~tw_row_max_u32(~L.red[lane & (NW - 1)]));
+        const uint32_t span = (uint32_t)__builtin_amdgcn_readfirstlane((int)tw_row_max_u32(red_hi[lane & (NW - 1)])) - rlo;
+        shift = span ? 32 - __clz(span) : 0;
+      } else {
+        shift = 27;
+      }
+      auto each = [&](auto f) { walk([&](uint32_t k, uint32_t) { f(k, tw_key_to_float(k)); }); };
+      T = wide_threshold<NT>(each, m, rlo, shift, cn, A0, target, L, &found);
     }
     if (found) {
-#pragma unroll
-      for (int e = 0; e < WR_EPT; ++e) {
-        if ((uint32_t)(e * 1024 + tid) < cn && key[e] >= T && (tok[e] >> 5) < (uint32_t)a.words_stride) {
-          atomicOr(&bm[tok[e] >> 5], 1u << (tok[e] & 31));
+      walk([&](uint32_t k, uint32_t t) {
+        if (k >= T && (t >> 5) < (uint32_t)a.words_stride) {
+          atomicOr(&bm[t >> 5], 1u << (t & 31));
           add += 1;
         }
-      }
+      });
     }
     whole_row = !found;
   }
@@ -469,13 +474,13 @@ __global__ __launch_bounds__(1024) void wide_resolve_kernel(WideArgs a) {
     const float* row = a.scores + (long long)bh * a.cand_stride;
     auto each = [&](auto f) {
 #pragma unroll 1
-      for (int c0 = tid * 4; c0 < N; c0 += 4 * 4096) {                        // four loads in flight per thread
+      for (int c0 = tid * 4; c0 < N; c0 += 16 * NT) {                        // four loads in flight per thread
         float4 x[4];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) x[v] = *(const float4*)(row + (c0 + v * 4096 < N ? c0 + v * 4096 : N - 4));
+        for (int v = 0; v < 4; ++v) x[v] = *(const float4*)(row + (c0 + v * 4 * NT < N ? c0 + v * 4 * NT : N - 4));
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          if (c0 + v * 4096 < N) {
+          if (c0 + v * 4 * NT < N) {
             const float y[4] = {x[v].x, x[v].y, x[v].z, x[v].w};
 #pragma unroll
             for (int k = 0; k < 4; ++k) f(tw_float_key(y[k]), y[k]);
@@ -490,11 +495,11 @@ __global__ __launch_bounds__(1024) void wide_resolve_kernel(WideArgs a) {
     __syncthreads();
     Z = 0;
 #pragma unroll
-    for (int w = 0; w < 16; ++w) Z += zred[w];
+    for (int w = 0; w < NW; ++w) Z += zred[w];
     bool found;
-    const uint32_t T = wide_threshold(each, m, 0u, 27, 0xFFFFFFFFu, 0ull, hp_target(a.p, Z), L, &found);
+    const uint32_t T = wide_threshold<NT>(each, m, 0u, 27, 0xFFFFFFFFu, 0ull, hp_target(a.p, Z), L, &found);
     // 16 slots = one page = one half word of the bitmap per thread
-    for (int i = tid; i < count; i += 1024) {
+    for (int i = tid; i < count; i += NT) {
       uint32_t bits = 0;
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
@@ -515,7 +520,7 @@ __global__ __launch_bounds__(1024) void wide_resolve_kernel(WideArgs a) {
   __syncthreads();
   if (tid == 0) {
     uint32_t t = whole_row ? 0u : a.kdef[(long long)bh * TW_CTR];
-    for (int w = 0; w < 16; ++w) t += L.red[w];
+    for (int w = 0; w < NW; ++w) t += L.red[w];
     a.kept_count[bh] = (int32_t)t;
   }
 }
@@ -660,13 +665,14 @@ int tw_prune_wide(const TwDims& d, const PruneWs& L, void* ws, const twilight_kv
   a.Hq = d.Hq; a.max_pages = d.max_pages; a.max_sel = max_sel; a.cand_stride = cand_stride;
   a.words_stride = L.words_stride; a.keep_all = p >= 1.0f ? 1 : 0; a.p = p;
   const int nbh = d.batch * d.Hq;
-  // histogram pass: large workgroups (fewer flushes of the LDS histogram per score); emit pass: small ones (they
+  // histogram pass: large workgroups (fewer flushes of the LDS histogram per score) unless a row fits a small one; emit pass: small ones (they
   // overlap their load and compute phases)
   constexpr int HIST_NT = 1024, EMIT_NT = 256;
   auto grid_for = [&](int nt) { return dim3((cand_stride + nt * W_SLOTS - 1) / (nt * W_SLOTS), nbh); };
   if (!a.keep_all && !hist_done) {
     tw_prof_before(TW_K_TOPP, s);
-    TW_LAUNCH(wide_hist_kernel, grid_for(HIST_NT), dim3(HIST_NT), 0, s, a);
+    if (cand_stride <= 256 * W_SLOTS) TW_LAUNCH(wide_hist_kernel<256>, grid_for(256), dim3(256), 0, s, a);
+    else TW_LAUNCH(wide_hist_kernel<HIST_NT>, grid_for(HIST_NT), dim3(HIST_NT), 0, s, a);
     if (int e = tw_prof_after(s)) return e;
   }
   if (!a.keep_all) {
@@ -678,7 +684,9 @@ int tw_prune_wide(const TwDims& d, const PruneWs& L, void* ws, const twilight_kv
   TW_LAUNCH(wide_emit_kernel<EMIT_NT>, grid_for(EMIT_NT), dim3(EMIT_NT), 0, s, a);
   if (int e = tw_prof_after(s)) return e;
   tw_prof_before(TW_K_TOPP, s);
-  TW_LAUNCH(wide_resolve_kernel, dim3(nbh), dim3(1024), 0, s, a);
+  // one 1024-thread workgroup fits a CU; more heads than CUs share them better in small ones
+  if (nbh > tw_num_cus()) TW_LAUNCH(wide_resolve_kernel<256>, dim3(nbh), dim3(256), 0, s, a);
+  else TW_LAUNCH(wide_resolve_kernel<1024>, dim3(nbh), dim3(1024), 0, s, a);
   if (int e = tw_prof_after(s)) return e;
 
   uint32_t* segcnt = (uint32_t*)(base + L.segcnt);
