@@ -730,7 +730,7 @@ constexpr int HP_USTAGE = 4096;               // union lists up to this length l
 // FUSE == 2: the page list too is made here, from the bounds of all pages (the selection of page_select_lds_kernel).
 // BITS: width of the quantised copy's codes (FUSE == 2; else 4).
 template <int NT, int EPT, int G, bool TOK = false, int FUSE = 0, int BITS = 4>
-__global__ __launch_bounds__(NT, NT <= 512 ? 6 : 1) void topp_head_kernel(HeadArgs a) {
+__global__ __launch_bounds__(NT, NT <= 512 ? (EPT > 8 ? 4 : 6) : 1) void topp_head_kernel(HeadArgs a) {
   constexpr int NW = NT / 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int b_ = blockIdx.y, h_ = blockIdx.x;
@@ -756,9 +756,6 @@ __global__ __launch_bounds__(NT, NT <= 512 ? 6 : 1) void topp_head_kernel(HeadAr
   const int budget_b = FUSE == 2 ? a.budget[b] : 0;
   float sel_pre[FUSE == 2 ? SEL_E : 1];
   int32_t sel_pt[FUSE == 2 ? SEL_E : 1];
-  // (when the heads are split over two launches by list length, half the workgroups of each return at once: those
-  //  must not leave with loads in flight, so the loads then follow the test)
-  const bool all_heads = a.n_above < 0 && a.n_upto >= a.cand_stride;
   auto ask_selection = [&]() {
 #pragma unroll
     for (int j = 0; j < SEL_E; ++j) {
@@ -769,7 +766,7 @@ __global__ __launch_bounds__(NT, NT <= 512 ? 6 : 1) void topp_head_kernel(HeadAr
   };
   // FUSE: this thread's element of the query, asked for early too (no branch around the load: all threads read)
   uint32_t q_raw = 0u;
-  if (FUSE && all_heads) {
+  if (FUSE) {
     if (SEL_EARLY) ask_selection();
     q_raw = (uint32_t)a.q[(long long)bh * 128 + (tid & 127)];
     __builtin_amdgcn_sched_barrier(0);               // these loads are issued before anything below waits for the lengths
@@ -789,10 +786,6 @@ __global__ __launch_bounds__(NT, NT <= 512 ? 6 : 1) void topp_head_kernel(HeadAr
   }
   const int N = TOK ? count : count * TW_PAGE;
   if (N <= a.n_above || N > a.n_upto) return;     // another launch's head (block-uniform)
-  if (FUSE && !all_heads) {
-    if (SEL_EARLY) ask_selection();
-    q_raw = (uint32_t)a.q[(long long)bh * 128 + (tid & 127)];
-  }
   const float* row = a.scores + (long long)bh * a.cand_stride;
   const int c0 = tid * EPT;
   TW_STAMP(0);
@@ -1448,8 +1441,13 @@ void launch_topp_one(const HeadArgs& f, int G, dim3 grid, hipStream_t s) {
 //    for the short rows four workgroups share a CU (2048 heads x 1024 candidates of 512 pages 48.1 -> 30.6);
 //  - rows of at most 1024 candidates and 1024 pages with more heads than CUs: 256-thread workgroups (2048 heads x 256
 //    candidates 39.8 -> 23.9 us; 32 heads x 1024 candidates 10.8 -> 11.1, so few heads keep the 512 threads);
-//  - many heads with a bound above 4096 candidates (ragged batches): heads of at most 4096 candidates go to a
-//    512-thread launch of their own, the longer ones to the 1024-thread launch.
+//  - many heads with a bound above 4096 candidates, scoring inside: 512-thread workgroups with 16 candidates per thread,
+//    two to a CU, for all heads - one's scoring streams while the other is in its barriers (64 ragged sequences x 32
+//    heads: 131.8 us as a 512-thread launch for the lists up to 4096 and a 1024-thread one, a workgroup per CU, for the
+//    longer ones -> 117.9; 32 x 32 heads x 8192 candidates 138.5 -> 111.7.  Dispatching the longest sequences first: no
+//    gain.);
+//  - the same on stored scores (FUSE == 0): heads of at most 4096 candidates in a 512-thread launch of their own, the
+//    longer ones in the 1024-thread launch.
 // FUSE: the kernels score the candidates themselves (page lists).
 template <bool TOK, int FUSE = 0, int BITS = 4>
 int launch_topp(HeadArgs f, const TwDims& d, int cand_stride, hipStream_t s) {
@@ -1457,9 +1455,9 @@ int launch_topp(HeadArgs f, const TwDims& d, int cand_stride, hipStream_t s) {
   const long long heads = (long long)d.batch * d.Hq;
   f.remap = (FUSE != 0 && ((long long)d.batch * d.Hkv) % 8 == 0) ? 1 : 0;
   f.n_above = -1; f.n_upto = cand_stride;
-  if (cand_stride > 4096 && heads > 2ll * tw_num_cus()) {
+  if (FUSE == 0 && cand_stride > 4096 && heads > 2ll * tw_num_cus()) {
     f.n_upto = 4096;
-    tw_prof_before(FUSE == 2 ? TW_K_SELECT_SCORE_TOPP : (FUSE == 1 ? TW_K_SCORE_TOPP : TW_K_TOPP), s);
+    tw_prof_before(TW_K_TOPP, s);
     launch_topp_one<512, 8, TOK, FUSE, BITS>(f, d.G, grid, s);
     if (int e = tw_prof_after(s)) return e;
     f.n_above = 4096; f.n_upto = cand_stride;
@@ -1469,6 +1467,7 @@ int launch_topp(HeadArgs f, const TwDims& d, int cand_stride, hipStream_t s) {
   else if (cand_stride <= 2048 && (FUSE != 2 || d.max_pages <= 2048)) launch_topp_one<512, 4, TOK, FUSE, BITS>(f, d.G, grid, s);
   else if (cand_stride <= 4096 && heads > tw_num_cus()) launch_topp_one<512, 8, TOK, FUSE, BITS>(f, d.G, grid, s);
   else if (cand_stride <= 4096) launch_topp_one<1024, 4, TOK, FUSE, BITS>(f, d.G, grid, s);
+  else if (FUSE != 0 && heads > 2ll * tw_num_cus()) launch_topp_one<512, FUSE != 0 ? 16 : 8, TOK, FUSE, BITS>(f, d.G, grid, s);
   else launch_topp_one<1024, 8, TOK, FUSE, BITS>(f, d.G, grid, s);
   return tw_prof_after(s);
 }
