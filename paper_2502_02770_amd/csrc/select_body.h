@@ -31,6 +31,24 @@ __device__ __forceinline__ void tw_select_sizes(int n, int B, int max_pages, int
   *K_out = (int)kp;
 }
 
+// Key of a long row's entry (more than 8 per thread): order-preserving, at least 1 for an entry of the row, 0 beyond its end.
+// (Comparisons with the row's length at every use kept 32 lane masks alive and spilled the 32-entry form's registers.)
+__device__ __forceinline__ uint32_t tw_select_key(float v, bool in) {
+  const uint32_t k = tw_float_key(v);
+  return in ? (k > 1u ? k : 1u) : 0u;
+}
+
+// Long rows' keys leave no registers for anything else per entry: what one phase derived from them (buckets, comparisons)
+// is derived again by the next instead of being kept - which the compiler does, into scratch memory, if it sees the same
+// keys in both.
+template <int E>
+__device__ __forceinline__ void tw_forget(uint32_t (&key)[E]) {
+  if (E > 8) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) asm volatile("" : "+v"(key[e]));
+  }
+}
+
 // Exclusive prefix over `entries` (<= 64 * Q) per-wave counts in LDS, computed by every wave on its own: entry
 // 64 * q + l ends up in excl[q] of lane l.
 template <int Q>
@@ -48,16 +66,18 @@ __device__ __forceinline__ void tw_seg_prefix(const uint32_t* cnt, int entries, 
 }
 
 // Threshold of the Kp (0 < Kp < P) largest of the row's keys, ties to the lower index: the entries with a key above
-// *T_out and the first *need_eq_out of those equal to it.  key[e] of thread t is entry e * NT + t (taken when below P).
+// *T_out and the first *need_eq_out of those equal to it.  key[e] of thread t is entry e * NT + t (tw_select_key when E > 8, else the
+// float's key, of any value beyond the row's end).
 // Called by all NT threads of the workgroup; hist and cand are LDS of the caller.  SB: first phase-stamp slot (timing builds).
 template <int NT, int E, int SNB, int SB>
-__device__ __forceinline__ void tw_select_threshold(const uint32_t (&key)[E], int P, uint32_t Kp, uint32_t* hist /* [SNB] */,
+__device__ __forceinline__ void tw_select_threshold(uint32_t (&key)[E], int P, uint32_t Kp, uint32_t* hist /* [SNB] */,
                                                     unsigned long long* cand /* [SEL_CAP] */, uint32_t* T_out, uint32_t* need_eq_out) {
   constexpr int NW = NT / 64, BPL = SNB / 64;         // waves; histogram buckets per lane of a scanning wave
   constexpr int LB = BPL == 8 ? 3 : (BPL == 16 ? 4 : 5);
   static_assert(BPL == (1 << LB), "SNB is 512, 1024 or 2048");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const auto in_row = [&](int e) { return E > 8 || e * NT < P; };
+  const auto live = [&](int e) { return E > 8 || e * NT + tid < P; };   // (more than 8: the key says so)
   __shared__ uint32_t red_lo[NW], red_hi[NW];
   __shared__ uint32_t sh_n;
   TW_STAMP(SB);
@@ -65,12 +85,12 @@ __device__ __forceinline__ void tw_select_threshold(const uint32_t (&key)[E], in
   uint32_t lo = 0xFFFFFFFFu, hi = 0u;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    if (in_row(e) && e * NT + tid < P) {
-      lo = key[e] < lo ? key[e] : lo;
-      hi = key[e] > hi ? key[e] : hi;
-    }
+    if (!in_row(e) || !live(e)) continue;
+    const uint32_t k = E > 8 ? key[e] - 1u : key[e];   // (0 wraps round and does not count)
+    lo = k < lo ? k : lo;
+    hi = key[e] > hi ? key[e] : hi;
   }
-  lo = ~tw_wave_max_u32(~lo);
+  lo = ~tw_wave_max_u32(~lo) + (E > 8 ? 1u : 0u);
   hi = tw_wave_max_u32(hi);
   if (lane == 0) { red_lo[wave] = lo; red_hi[wave] = hi; }
   if (tid == 0) sh_n = 0;
@@ -84,6 +104,7 @@ __device__ __forceinline__ void tw_select_threshold(const uint32_t (&key)[E], in
   constexpr bool KEEP = E <= 8;
   int kept_bk[KEEP ? E : 1];
   uint32_t need = Kp, T = 0, need_eq = 0;
+  tw_forget<E>(key);
   TW_STAMP(SB + 1);
 #pragma unroll 1
   for (int pass = 0;; ++pass) {
@@ -105,43 +126,48 @@ __device__ __forceinline__ void tw_select_threshold(const uint32_t (&key)[E], in
     // is entry e of this thread in bucket bkt?  (rows of up to 8 entries per thread keep the bucket numbers)
     auto in_bucket = [&](int e, int bkt) -> bool {
       if (KEEP) return kept_bk[KEEP ? e : 0] == bkt;
-      return e * NT + tid < P && key[e] >= klo && key[e] <= khi && bucket_of(key[e]) == bkt;
+      return live(e) && key[e] - klo <= span && bucket_of(key[e]) == bkt;
     };
     if (pass > 0) {
       for (int i = tid; i < SNB; i += NT) hist[i] = 0;
       __syncthreads();
     }
-    // Bucket b is counted in word (r mod BPL) * 64 + r / BPL, r = SNB - 1 - b: the scanning lane l, which owns the BPL
-    // buckets r = BPL * l .. from the top, then reads words j * 64 + l - consecutive lanes, consecutive banks.
+    // Bucket b, r = SNB - 1 - b = BPL * l + j, is counted in word j * 64 + l: the scanning lane l, which owns the BPL
+    // buckets r = BPL * l .. from the top, reads one word per j with consecutive lanes on consecutive banks.  Long rows
+    // rotate the words of a j by j, so that their many adds, which crowd into neighbouring buckets, spread over the banks
+    // too (with the registers of tw_select_key and tw_forget 256 rows x 32768 entries 41 -> 31 us; short rows lose 1 us).
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       if (KEEP) kept_bk[KEEP ? e : 0] = -1;
       if (!in_row(e)) continue;
-      const bool in = e * NT + tid < P && key[e] >= klo && key[e] <= khi;
+      const bool in = live(e) && key[e] - klo <= span;
       const int bk = bucket_of(key[e]);
       if (KEEP) kept_bk[KEEP ? e : 0] = in ? bk : -1;
       if (in) {
         const int r = SNB - 1 - bk;
-        atomicAdd(&hist[((r & (BPL - 1)) << 6) | (r >> LB)], 1u);
+        atomicAdd(&hist[((r & (BPL - 1)) << 6) | (((r >> LB) + (E > 8 ? r & (BPL - 1) : 0)) & 63)], 1u);
       }
     }
     __syncthreads();
     TW_STAMP(SB + 2);
     uint32_t c[BPL], mine = 0;
 #pragma unroll
-    for (int j = 0; j < BPL; ++j) { c[j] = hist[j * 64 + lane]; mine += c[j]; }
+    for (int j = 0; j < BPL; ++j) { c[j] = hist[j * 64 + ((lane + (E > 8 ? j : 0)) & 63)]; mine += c[j]; }
     uint32_t above = tw_wave_scan_u32(mine) - mine;
     const int src = __ffsll((long long)__ballot(above < need && above + mine >= need)) - 1;   // the interval holds the threshold
     uint32_t asel = 0, csel = 0;
+    if (E > 8) asm volatile("" ::: "memory");
     int jsel = 0;
 #pragma unroll
     for (int j = 0; j < BPL; ++j) {
-      if (above < need && above + c[j] >= need) { jsel = j; asel = above; csel = c[j]; }
-      above += c[j];
+      const uint32_t cj = E > 8 ? hist[j * 64 + ((lane + j) & 63)] : c[j];   // (read again rather than kept)
+      if (above < need && above + cj >= need) { jsel = j; asel = above; csel = cj; }
+      above += cj;
     }
     const int bkt = SNB - 1 - (BPL * src + __builtin_amdgcn_readlane(jsel, src));
     need -= (uint32_t)__builtin_amdgcn_readlane((int)asel, src);
     const uint32_t pop = (uint32_t)__builtin_amdgcn_readlane((int)csel, src);
+    tw_forget<E>(key);
     if (pop <= (uint32_t)SEL_CAP) {
       // exact: the bucket's keys, with the lower index the larger of two equals, ranked by every wave on its own - one
       // candidate per lane; the one of rank need - 1 is the last one taken
@@ -186,6 +212,7 @@ __device__ __forceinline__ void tw_select_threshold(const uint32_t (&key)[E], in
     if (pop == need) { T = klo; need_eq = 0xFFFFFFFFu; break; }   // the whole bucket is taken
     __syncthreads();                              // red_* and hist are rewritten by the next pass
   }
+  tw_forget<E>(key);
   TW_STAMP(SB + 4);
   *T_out = T;
   *need_eq_out = need_eq;
@@ -194,24 +221,25 @@ __device__ __forceinline__ void tw_select_threshold(const uint32_t (&key)[E], in
 // Ordered listing behind tw_select_threshold: put(pos, e) is called for every selected entry e * NT + t of this thread
 // with its place in the ascending list.  cnt: LDS of the caller, E * NT / 64 words.  Called by all NT threads; one barrier.
 template <int NT, int E, class Put>
-__device__ __forceinline__ void tw_select_list(const uint32_t (&key)[E], int P, uint32_t T, uint32_t need_eq, uint32_t* cnt, Put put) {
+__device__ __forceinline__ void tw_select_list(uint32_t (&key)[E], int P, uint32_t T, uint32_t need_eq, uint32_t* cnt, Put put) {
   constexpr int NW = NT / 64, SEGS = E * NW, Q = (SEGS + 63) / 64;
-  const auto in_row = [&](int e) { return E > 8 || e * NT < P; };
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const auto in_row = [&](int e) { return E > 8 || e * NT < P; };
+  const auto live = [&](int e) { return E > 8 || e * NT + tid < P; };
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     if (!in_row(e)) continue;
-    const bool in = e * NT + tid < P;
-    const uint32_t gt = (uint32_t)__popcll(__ballot(in && key[e] > T)), eq = (uint32_t)__popcll(__ballot(in && key[e] == T));
+    const uint32_t gt = (uint32_t)__popcll(__ballot(live(e) && key[e] > T)), eq = (uint32_t)__popcll(__ballot(live(e) && key[e] == T));
     if (lane == 0) cnt[e * NW + wave] = gt | (eq << 16);
   }
   __syncthreads();
+  tw_forget<E>(key);
   uint32_t excl[Q], total;
   tw_seg_prefix<Q>(cnt, ((P + NT - 1) / NT) * NW, excl, &total);
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     if (!in_row(e)) continue;
-    const bool in = e * NT + tid < P, gt = in && key[e] > T, eq = in && key[e] == T;
+    const bool gt = live(e) && key[e] > T, eq = live(e) && key[e] == T;
     const unsigned long long bg = __ballot(gt), be = __ballot(eq);
     const uint32_t off = (uint32_t)__builtin_amdgcn_readlane((int)excl[(e * NW) >> 6], ((e * NW) & 63) + wave);
     const uint32_t gt_before = (off & 0xFFFFu) + tw_bits_below(bg), eq_before = (off >> 16) + tw_bits_below(be);

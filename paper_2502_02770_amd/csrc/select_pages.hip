@@ -311,7 +311,8 @@ __global__ __launch_bounds__(NT) void page_select_reg_kernel(SelectArgs a) {
     key[e] = __float_as_uint(sc[i < P ? i : P - 1]);
   }
 #pragma unroll
-  for (int e = 0; e < E; ++e) key[e] = tw_float_key(__uint_as_float(key[e]));
+  for (int e = 0; e < E; ++e)
+    key[e] = E > 8 ? tw_select_key(__uint_as_float(key[e]), e * NT + tid < P) : tw_float_key(__uint_as_float(key[e]));
   tw_select_threshold<NT, E, SNB, 10>(key, P, (uint32_t)Kp, hist, cand, &T, &need_eq);
   tw_select_list<NT, E>(key, P, T, need_eq, cnt, [&](uint32_t pos, int e) {
     if (pos < (uint32_t)a.max_sel) out[pos] = e * NT + tid;
