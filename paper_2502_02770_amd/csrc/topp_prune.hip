@@ -794,7 +794,10 @@ __global__ __launch_bounds__(NT, NT <= 512 ? (EPT > 8 ? 4 : 6) : 1) void topp_he
   __shared__ uint32_t histC[HP_NB];
   __shared__ unsigned long long cand_mass[HP_CAP];
   __shared__ uint32_t cand_key[HP_CAP];
-  __shared__ uint32_t big_s[BWORDS + USTAGE];               // position bitmap, then the union list on its way out
+  // position bitmap, then the union list on its way out; before that the selection's 64-bit candidates and the staged
+  // scores, read 16 bytes at a time
+  __shared__ __align__(16) uint32_t big_s[BWORDS + USTAGE];
+  static_assert(__alignof__(big_s) >= 16, "read as float4 and as 64-bit words");
   uint32_t* const bitmap = big_s;                            // (FUSE: first the scores on their way to their owners)
   int32_t* const ustage = (int32_t*)(big_s + BWORDS);
   __shared__ unsigned long long tail_s[NW];
@@ -806,6 +809,7 @@ __global__ __launch_bounds__(NT, NT <= 512 ? (EPT > 8 ? 4 : 6) : 1) void topp_he
   __shared__ int32_t pool_s[FUSE == 2 ? NT * EPT / TW_PAGE : 1];    // ... and the pages' places in the pool
   if (FUSE == 2) {
     constexpr int SNB = 512;
+    static_assert(SNB % 2 == 0, "the candidates behind the histogram are 64-bit words");
     uint32_t* const hist = big_s;                   // the selection's arrays lie in big_s
     unsigned long long* const cand = (unsigned long long*)(big_s + SNB);
     uint32_t* const cnt = big_s + SNB + 2 * SEL_CAP;
