@@ -86,18 +86,20 @@ __device__ __forceinline__ void tw_select_threshold(uint32_t (&key)[E], int P, u
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     if (!in_row(e) || !live(e)) continue;
-    const uint32_t k = E > 8 ? key[e] - 1u : key[e];   // (0 wraps round and does not count)
+    // (more than 8: the minimum is over key - 1 until all waves' are in - the 0 beyond the row's end wraps round and does
+    //  not count, and neither does a wave that holds nothing else)
+    const uint32_t k = E > 8 ? key[e] - 1u : key[e];
     lo = k < lo ? k : lo;
     hi = key[e] > hi ? key[e] : hi;
   }
-  lo = ~tw_wave_max_u32(~lo) + (E > 8 ? 1u : 0u);
+  lo = ~tw_wave_max_u32(~lo);
   hi = tw_wave_max_u32(hi);
   if (lane == 0) { red_lo[wave] = lo; red_hi[wave] = hi; }
   if (tid == 0) sh_n = 0;
   if (tid < SEL_CAP) cand[tid] = 0;
   for (int i = tid; i < SNB; i += NT) hist[i] = 0;
   __syncthreads();
-  uint32_t klo = ~tw_row_max_u32(~red_lo[lane & (NW - 1)]), khi = tw_row_max_u32(red_hi[lane & (NW - 1)]);
+  uint32_t klo = ~tw_row_max_u32(~red_lo[lane & (NW - 1)]) + (E > 8 ? 1u : 0u), khi = tw_row_max_u32(red_hi[lane & (NW - 1)]);
   klo = (uint32_t)__builtin_amdgcn_readfirstlane((int)klo);
   khi = (uint32_t)__builtin_amdgcn_readfirstlane((int)khi);
 

@@ -36,3 +36,61 @@ def test_page_lists_at_the_row_lengths_of_the_selection_kernels(P):
             U = O.page_upper_bounds(synth.bits(q[0, h]), u16(mm[:, 0, 0]), u16(mm[:, 0, 1]))
             want = O.select_pages(U, budget, n)
             assert st.sel_pages[0, h, :int(st.sel_count[0, h])].cpu().numpy().tolist() == want.tolist(), (budget, h)
+
+
+def _random_bounds(T, lens, max_pages, heads=(32, 8), pool=64, seed=0):
+    """Cache whose pages carry random key bounds (pool pages shared by the sequences) and a query."""
+    g = torch.Generator().manual_seed(seed)
+    table = (torch.arange(len(lens) * max_pages, dtype=torch.int32) % pool).view(len(lens), max_pages)
+    cache = T.PagedKV(heads[0], heads[1], table, torch.tensor(lens), pool, need_v=False)
+    mm = torch.randn(pool, heads[1], 2, 128, generator=g).sort(dim=2).values.to(torch.bfloat16)
+    cache.page_minmax.copy_(mm)
+    return cache, torch.randn(len(lens), heads[0], 128, generator=g).to(torch.bfloat16).cuda()
+
+
+def _selection_us(T, pages, max_pages, batch):
+    """Median time of the selection kernels (without the bounds) for `batch` x 32 rows of `pages` entries."""
+    B = T.binding
+    cache, q = _random_bounds(T, [16 * pages] * batch, max_pages)
+    st = T.DecodeStep(cache, max_sel=max(1, pages // 8))
+    budget = torch.full((batch,), 2 * pages, dtype=torch.int32, device="cuda")
+    for _ in range(3):
+        st.select(q, budget)
+    torch.cuda.synchronize()
+    B.twilight_prof_enable(1)
+    for _ in range(15):
+        st.select(q, budget)
+    torch.cuda.synchronize()
+    rec = B.twilight_prof_collect()
+    B.twilight_prof_enable(0)
+    runs = np.array([ms for _, ms in rec]).reshape(15, -1) * 1e3
+    return float(np.median(runs[:, 1:].sum(axis=1)))
+
+
+def test_short_rows_under_a_long_bound_cost_no_more_than_full_ones():
+    """512 rows of 500 entries under a bound of 9000 (most waves of the selection hold no entry at all): the slots
+    beyond the row's end must not be bucketed."""
+    T = _T()
+    short, full = _selection_us(T, 500, 9000, 16), _selection_us(T, 9000, 9000, 16)
+    assert short < full, (short, full)
+
+
+@pytest.mark.parametrize("max_pages", [2500, 9000, 17000])
+def test_page_lists_of_short_rows_under_a_long_bound(max_pages):
+    """Rows far shorter than the bound that chooses the selection kernel, down to one with a wave's worth of entries:
+    page lists bit for bit."""
+    T = _T()
+    pages = [max_pages, 1100, 700, 65, 17, 2]
+    cache, q = _random_bounds(T, [16 * P for P in pages], max_pages, heads=(2, 1), pool=4096, seed=max_pages)
+    for cut in (2, 7):
+        budget = [16 * max(1, P // cut) for P in pages]
+        st = T.DecodeStep(cache, max_sel=max_pages // cut)
+        st.select(q, torch.tensor(budget, dtype=torch.int32, device="cuda"))
+        torch.cuda.synchronize()
+        mm = cache.page_minmax.cpu()
+        for b, P in enumerate(pages):
+            rows = mm[cache.page_table[b, :P].cpu().long(), 0]
+            for h in range(2):
+                U = O.page_upper_bounds(synth.bits(q[b, h].cpu()), u16(rows[:, 0]), u16(rows[:, 1]))
+                want = O.select_pages(U, budget[b], 16 * P)
+                assert st.sel_pages[b, h, :int(st.sel_count[b, h])].cpu().numpy().tolist() == want.tolist(), (b, h, cut)
