@@ -286,9 +286,13 @@ __global__ __launch_bounds__(256) void page_select_kernel(SelectArgs a) {
 
 
 // Rows of at most NT * E entries, the keys in registers.
+// Rows of 2049 to 8192 entries: what bounds many of them is how many workgroups wait at their barriers side by side, so
+// the form is held to 64 registers (two workgroups of 16 waves per CU), with 512 buckets, 8 per scanning lane, instead of
+// 1024: 1024 rows x 2500 entries 27.9 us at 72 registers, one workgroup per CU -> 21.3, x 8192 entries 37.9 -> 31.5; a
+// row per CU is unchanged (256 x 8192 8.9).  With 1024 buckets in 64 registers (the histogram read twice) 22.5 and 32.6.
 template <int NT, int E, int UNIT>
-__global__ __launch_bounds__(NT) void page_select_reg_kernel(SelectArgs a) {
-  constexpr int SNB = E > 8 ? 2048 : (NT > 256 ? 1024 : 512);
+__global__ __launch_bounds__(NT, NT == 1024 && E == 8 ? 8 : 1) void page_select_reg_kernel(SelectArgs a) {
+  constexpr int SNB = E > 8 ? 2048 : (NT == 1024 && E == 2 ? 1024 : 512);
   const int b = blockIdx.y, h = blockIdx.x, tid = threadIdx.x;
   int P, Kp;
   tw_select_sizes<UNIT>(a, a.seq_lens[b], a.budget[b], &P, &Kp);

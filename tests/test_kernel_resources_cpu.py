@@ -1,0 +1,69 @@
+"""Registers and scratch of the built kernels, read from the code objects inside libtwilight.so: where a dispatch rule
+counts on several workgroups per compute unit, the kernel has to fit them (512 vector registers per lane of a SIMD,
+allocated in eights; 4 SIMDs; a 1024-thread workgroup is 4 waves on each)."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+msgpack = pytest.importorskip("msgpack")
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    """{demangled name: metadata} of every kernel in the library."""
+    import paper_2502_02770_amd as T
+    if not os.path.exists(T.binding.LIB_PATH):
+        from paper_2502_02770_amd.build import build
+        build(verbose=False)
+    blob = open(T.binding.LIB_PATH, "rb").read()
+    found, magic = {}, b"__CLANG_OFFLOAD_BUNDLE__"
+    at = blob.find(magic)
+    while at >= 0:
+        n, = struct.unpack_from("<Q", blob, at + len(magic))
+        pos = at + len(magic) + 8
+        for _ in range(n):
+            off, size, idlen = struct.unpack_from("<QQQ", blob, pos)
+            name = blob[pos + 24:pos + 24 + idlen]
+            pos += 24 + idlen
+            if b"gfx950" in name:
+                for k in _metadata(blob[at + off:at + off + size]):
+                    found[k[".name"]] = k
+        at = blob.find(magic, at + 1)
+    names = list(found)
+    plain = subprocess.run(["c++filt"], input="\n".join(names), capture_output=True, text=True, check=True).stdout.splitlines()
+    return {re.sub(r"^void |\(anonymous namespace\)::|\(.*$", "", p.replace("(anonymous namespace)::", "")): found[n] for n, p in zip(names, plain)}
+
+
+def _metadata(elf):
+    """amdhsa.kernels of a code object: the AMDGPU note (type 32) of its note sections."""
+    shoff, = struct.unpack_from("<Q", elf, 40)
+    shentsize, shnum = struct.unpack_from("<HH", elf, 58)
+    for i in range(shnum):
+        _, kind, _, _, off, size = struct.unpack_from("<IIQQQQ", elf, shoff + i * shentsize)
+        if kind != 7:
+            continue
+        end = off + size
+        while off < end:
+            namesz, descsz, ntype = struct.unpack_from("<III", elf, off)
+            desc = off + 12 + (namesz + 3 & ~3)
+            if ntype == 32:
+                return msgpack.unpackb(elf[desc:desc + descsz], strict_map_key=False)["amdhsa.kernels"]
+            off = desc + (descsz + 3 & ~3)
+    return []
+
+
+def _fits(k, workgroups):
+    """Do `workgroups` workgroups of the kernel's size share a compute unit by its vector registers?"""
+    regs = (k[".vgpr_count"] + 7) // 8 * 8
+    waves = k[".max_flat_workgroup_size"] // 64
+    return (waves * workgroups + 3) // 4 * regs <= 512
+
+
+@pytest.mark.parametrize("unit", [16, 1])
+def test_selection_of_up_to_8192_entries_runs_two_workgroups_per_cu(kernels, unit):
+    k = kernels["page_select_reg_kernel<1024, 8, %d>" % unit]
+    assert _fits(k, 2), k[".vgpr_count"]
+    assert k[".vgpr_spill_count"] == 0
