@@ -4,20 +4,27 @@
 //
 // A row of up to E * NT entries lives in registers: thread t holds the keys of entries e * NT + t (coalesced loads; the
 // order e, then wave, then lane is the entries' order, which is what the ordered listing needs).  The Kp-th largest key
-// (slots beyond the row's length are skipped by the whole workgroup, up to 8 slots per thread: a row far below the bound
-// costs what its own length does; 32 such branches cost a full row of 32768 entries 6 of 47 us) is located by bucketing the live key interval linearly (one pass when the scores are spread out), narrowing to the
-// bucket that holds it, and an exact rank computation once at most SEL_CAP candidates remain.  What bounds it is the
-// chain of block barriers and LDS round trips, so every wave scans the histogram and ranks the candidates on its own
-// (the same result in each) instead of waiting for one that does: per row 4 barriers where staging the keys in LDS and
-// handing the crossing bucket, the rank and the list offsets around through LDS took 8.  Measured against that form:
-// selection inside the per-head kernel 5.0 -> 4.1 us (32 heads x 256 pages: 5.0 -> 3.7), page_select 6.7 -> 5.5 us at
-// 128 heads x 1024 pages, 50 -> 43 us at 256 heads x 32768 tokens; steps 1 to 5 % shorter.
+// is located by bucketing the live key interval linearly (one pass when the scores are spread out), narrowing to the
+// bucket that holds it, and an exact rank computation once at most SEL_CAP candidates remain.
+//
+// What bounds it is the chain of block barriers and LDS round trips, so every wave scans the histogram and ranks the
+// candidates on its own (the same result in each) instead of waiting for one that does: 4 barriers per row, where keys
+// staged in LDS, with the crossing bucket, the rank and the list offsets handed around through LDS, took 8.  Against that
+// form: selection inside the per-head kernel 5.0 -> 4.1 us (32 heads x 256 pages 5.0 -> 3.7), page_select 6.7 -> 5.5 us
+// at 128 heads x 1024 pages, 10.8 -> 9.0 at 256 x 8192, 47 -> 26 at 256 x 32768 entries.
+//
+// Slots beyond the row's length are skipped by the whole workgroup, so that a row costs what its own length does: one by
+// one up to 8 slots per thread, in groups of 4 beyond.  (512 rows x 9000 entries with 16 slots 15.5 us in groups of 4,
+// 17.3 in groups of 8, 15.7 in groups of 2; 256 full rows of 32768 in groups of 4 25.9, 24.9 without any skipping, and
+// 22.7 -> 20.9 at 24000 entries.)
 #pragma once
 #include "tw_common.h"
 
-constexpr int SEL_REG_PAGES = 8192;      // rows up to here run two workgroups per CU
+constexpr int SEL_REG_PAGES = 8192;      // rows up to here may be split over two launches by length
+constexpr int SEL_REG_TWO = 16384;       // rows up to here run two 1024-thread workgroups per CU (16 keys a thread in 64 registers)
 constexpr int SEL_REG_MAX = 32768;       // longest row whose keys fit in a workgroup's registers
 constexpr int SEL_CAP = 64;              // candidates of the exact finish: one per lane
+constexpr int SEL_GROUP = 4;             // slots skipped together where a thread has more than 8
 
 // entries of a sequence's row and how many of them the budget asks for (UNIT = tokens per entry: 16 or 1)
 template <int UNIT>
@@ -49,6 +56,26 @@ __device__ __forceinline__ void tw_forget(uint32_t (&key)[E]) {
   }
 }
 
+// f(e) for this thread's slots e * NT + t that the row reaches, by a block-uniform test per slot, or per group of
+// SEL_GROUP slots where a thread has more than 8.
+// skipped(e) for the others.
+template <int NT, int E, class F, class S>
+__device__ __forceinline__ void tw_each_slot(int P, F f, S skipped) {
+  constexpr int GRP = E > 8 ? SEL_GROUP : 1;
+#pragma unroll
+  for (int g = 0; g < E; g += GRP) {
+    if (g * NT < P) {
+#pragma unroll
+      for (int e = g; e < g + GRP; ++e) f(e);
+    } else {
+#pragma unroll
+      for (int e = g; e < g + GRP; ++e) skipped(e);
+    }
+  }
+}
+template <int NT, int E, class F>
+__device__ __forceinline__ void tw_each_slot(int P, F f) { tw_each_slot<NT, E>(P, f, [](int) {}); }
+
 // Exclusive prefix over `entries` (<= 64 * Q) per-wave counts in LDS, computed by every wave on its own: entry
 // 64 * q + l ends up in excl[q] of lane l.
 template <int Q>
@@ -75,23 +102,21 @@ __device__ __forceinline__ void tw_select_threshold(uint32_t (&key)[E], int P, u
   constexpr int NW = NT / 64, BPL = SNB / 64;         // waves; histogram buckets per lane of a scanning wave
   constexpr int LB = BPL == 8 ? 3 : (BPL == 16 ? 4 : 5);
   static_assert(BPL == (1 << LB), "SNB is 512, 1024 or 2048");
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const auto in_row = [&](int e) { return E > 8 || e * NT < P; };
+  const int tid = threadIdx.x, lane = tid & 63, wave = E > 8 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
   const auto live = [&](int e) { return E > 8 || e * NT + tid < P; };   // (more than 8: the key says so)
   __shared__ uint32_t red_lo[NW], red_hi[NW];
   __shared__ uint32_t sh_n;
   TW_STAMP(SB);
 
   uint32_t lo = 0xFFFFFFFFu, hi = 0u;
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    if (!in_row(e) || !live(e)) continue;
+  tw_each_slot<NT, E>(E > 8 ? P : E * NT, [&](int e) {     // (up to 8: the test per lane says it all)
+    if (!live(e)) return;
     // (more than 8: the minimum is over key - 1 until all waves' are in - the 0 beyond the row's end wraps round and does
     //  not count, and neither does a wave that holds nothing else)
     const uint32_t k = E > 8 ? key[e] - 1u : key[e];
     lo = k < lo ? k : lo;
     hi = key[e] > hi ? key[e] : hi;
-  }
+  });
   lo = ~tw_wave_max_u32(~lo);
   hi = tw_wave_max_u32(hi);
   if (lane == 0) { red_lo[wave] = lo; red_hi[wave] = hi; }
@@ -103,7 +128,7 @@ __device__ __forceinline__ void tw_select_threshold(uint32_t (&key)[E], int P, u
   klo = (uint32_t)__builtin_amdgcn_readfirstlane((int)klo);
   khi = (uint32_t)__builtin_amdgcn_readfirstlane((int)khi);
 
-  constexpr bool KEEP = E <= 8;
+  constexpr bool KEEP = E <= 8, REREAD = BPL > 16;
   int kept_bk[KEEP ? E : 1];
   uint32_t need = Kp, T = 0, need_eq = 0;
   tw_forget<E>(key);
@@ -135,34 +160,32 @@ __device__ __forceinline__ void tw_select_threshold(uint32_t (&key)[E], int P, u
       __syncthreads();
     }
     // Bucket b, r = SNB - 1 - b = BPL * l + j, is counted in word j * 64 + l: the scanning lane l, which owns the BPL
-    // buckets r = BPL * l .. from the top, reads one word per j with consecutive lanes on consecutive banks.  Long rows
-    // rotate the words of a j by j, so that their many adds, which crowd into neighbouring buckets, spread over the banks
-    // too (with the registers of tw_select_key and tw_forget 256 rows x 32768 entries 41 -> 31 us; short rows lose 1 us).
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      if (KEEP) kept_bk[KEEP ? e : 0] = -1;
-      if (!in_row(e)) continue;
+    // buckets r = BPL * l .. from the top, reads one word per j with consecutive lanes on consecutive banks.  The longest
+    // rows rotate the words of a j by j, so that their many adds, which crowd into neighbouring buckets, spread over the
+    // banks too (with the registers of tw_select_key and tw_forget 256 rows x 32768 entries 41 -> 31 us; with 16 slots or
+    // fewer it costs more than it gives: 512 rows x 9000 entries 17.3 -> 18.5).
+    tw_each_slot<NT, E>(P, [&](int e) {
       const bool in = live(e) && key[e] - klo <= span;
       const int bk = bucket_of(key[e]);
       if (KEEP) kept_bk[KEEP ? e : 0] = in ? bk : -1;
       if (in) {
         const int r = SNB - 1 - bk;
-        atomicAdd(&hist[((r & (BPL - 1)) << 6) | (((r >> LB) + (E > 8 ? r & (BPL - 1) : 0)) & 63)], 1u);
+        atomicAdd(&hist[((r & (BPL - 1)) << 6) | (((r >> LB) + (E > 16 ? r & (BPL - 1) : 0)) & 63)], 1u);
       }
-    }
+    }, [&](int e) { if (KEEP) kept_bk[KEEP ? e : 0] = -1; });
     __syncthreads();
     TW_STAMP(SB + 2);
     uint32_t c[BPL], mine = 0;
 #pragma unroll
-    for (int j = 0; j < BPL; ++j) { c[j] = hist[j * 64 + ((lane + (E > 8 ? j : 0)) & 63)]; mine += c[j]; }
+    for (int j = 0; j < BPL; ++j) { c[j] = hist[j * 64 + ((lane + (E > 16 ? j : 0)) & 63)]; mine += c[j]; }
     uint32_t above = tw_wave_scan_u32(mine) - mine;
     const int src = __ffsll((long long)__ballot(above < need && above + mine >= need)) - 1;   // the interval holds the threshold
     uint32_t asel = 0, csel = 0;
-    if (E > 8) asm volatile("" ::: "memory");
+    if (REREAD) asm volatile("" ::: "memory");
     int jsel = 0;
 #pragma unroll
     for (int j = 0; j < BPL; ++j) {
-      const uint32_t cj = E > 8 ? hist[j * 64 + ((lane + j) & 63)] : c[j];   // (read again rather than kept)
+      const uint32_t cj = REREAD ? hist[j * 64 + ((lane + j) & 63)] : c[j];   // (read again rather than kept)
       if (above < need && above + cj >= need) { jsel = j; asel = above; csel = cj; }
       above += cj;
     }
@@ -173,14 +196,13 @@ __device__ __forceinline__ void tw_select_threshold(uint32_t (&key)[E], int P, u
     if (pop <= (uint32_t)SEL_CAP) {
       // exact: the bucket's keys, with the lower index the larger of two equals, ranked by every wave on its own - one
       // candidate per lane; the one of rank need - 1 is the last one taken
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
+      tw_each_slot<NT, E>(KEEP ? E * NT : P, [&](int e) {
         const int i = e * NT + tid;
-        if (in_row(e) && in_bucket(e, bkt)) {
+        if (in_bucket(e, bkt)) {
           const uint32_t at = atomicAdd(&sh_n, 1u);
           if (at < (uint32_t)SEL_CAP) cand[at] = ((unsigned long long)key[e] << 32) | (uint32_t)~i;
         }
-      }
+      });
       __syncthreads();
       TW_STAMP(SB + 3);
       const unsigned long long mineK = cand[lane];                         // 0 beyond pop: below every candidate
@@ -198,13 +220,12 @@ __device__ __forceinline__ void tw_select_threshold(uint32_t (&key)[E], int P, u
     }
     // narrow to the bucket's keys
     uint32_t nlo = 0xFFFFFFFFu, nhi = 0u;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      if (in_row(e) && in_bucket(e, bkt)) {
+    tw_each_slot<NT, E>(KEEP ? E * NT : P, [&](int e) {
+      if (in_bucket(e, bkt)) {
         nlo = key[e] < nlo ? key[e] : nlo;
         nhi = key[e] > nhi ? key[e] : nhi;
       }
-    }
+    });
     nlo = ~tw_wave_max_u32(~nlo);
     nhi = tw_wave_max_u32(nhi);
     if (lane == 0) { red_lo[wave] = nlo; red_hi[wave] = nhi; }
@@ -225,26 +246,21 @@ __device__ __forceinline__ void tw_select_threshold(uint32_t (&key)[E], int P, u
 template <int NT, int E, class Put>
 __device__ __forceinline__ void tw_select_list(uint32_t (&key)[E], int P, uint32_t T, uint32_t need_eq, uint32_t* cnt, Put put) {
   constexpr int NW = NT / 64, SEGS = E * NW, Q = (SEGS + 63) / 64;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const auto in_row = [&](int e) { return E > 8 || e * NT < P; };
+  const int tid = threadIdx.x, lane = tid & 63, wave = E > 8 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
   const auto live = [&](int e) { return E > 8 || e * NT + tid < P; };
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    if (!in_row(e)) continue;
+  tw_each_slot<NT, E>(P, [&](int e) {
     const uint32_t gt = (uint32_t)__popcll(__ballot(live(e) && key[e] > T)), eq = (uint32_t)__popcll(__ballot(live(e) && key[e] == T));
     if (lane == 0) cnt[e * NW + wave] = gt | (eq << 16);
-  }
+  });
   __syncthreads();
   tw_forget<E>(key);
   uint32_t excl[Q], total;
   tw_seg_prefix<Q>(cnt, ((P + NT - 1) / NT) * NW, excl, &total);
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    if (!in_row(e)) continue;
+  tw_each_slot<NT, E>(P, [&](int e) {
     const bool gt = live(e) && key[e] > T, eq = live(e) && key[e] == T;
     const unsigned long long bg = __ballot(gt), be = __ballot(eq);
     const uint32_t off = (uint32_t)__builtin_amdgcn_readlane((int)excl[(e * NW) >> 6], ((e * NW) & 63) + wave);
     const uint32_t gt_before = (off & 0xFFFFu) + tw_bits_below(bg), eq_before = (off >> 16) + tw_bits_below(be);
     if (gt || (eq && eq_before < need_eq)) put(gt_before + (eq_before < need_eq ? eq_before : need_eq), e);
-  }
+  });
 }

@@ -285,29 +285,11 @@ __global__ __launch_bounds__(256) void page_select_kernel(SelectArgs a) {
 }
 
 
-// Rows of at most NT * E entries, the keys in registers.
-// Rows of 2049 to 8192 entries: what bounds many of them is how many workgroups wait at their barriers side by side, so
-// the form is held to 64 registers (two workgroups of 16 waves per CU), with 512 buckets, 8 per scanning lane, instead of
-// 1024: 1024 rows x 2500 entries 27.9 us at 72 registers, one workgroup per CU -> 21.3, x 8192 entries 37.9 -> 31.5; a
-// row per CU is unchanged (256 x 8192 8.9).  With 1024 buckets in 64 registers (the histogram read twice) 22.5 and 32.6.
-template <int NT, int E, int UNIT>
-__global__ __launch_bounds__(NT, NT == 1024 && E == 8 ? 8 : 1) void page_select_reg_kernel(SelectArgs a) {
-  constexpr int SNB = E > 8 ? 2048 : (NT == 1024 && E == 2 ? 1024 : 512);
-  const int b = blockIdx.y, h = blockIdx.x, tid = threadIdx.x;
-  int P, Kp;
-  tw_select_sizes<UNIT>(a, a.seq_lens[b], a.budget[b], &P, &Kp);
-  if (P <= a.p_above || P > a.p_upto) return;     // another launch's head (block-uniform)
-  const float* sc = a.scores + ((long long)(b * a.Hq + h)) * a.max_pages;
-  int32_t* out = a.sel_pages + ((long long)(b * a.Hq + h)) * a.max_sel;
-  if (tid == 0) a.sel_count[b * a.Hq + h] = Kp;
-  if (Kp == 0) return;
-  if (Kp == P) {
-    for (int i = tid; i < P; i += NT) out[i] = i;
-    return;
-  }
-  __shared__ uint32_t hist[SNB];
-  __shared__ unsigned long long cand[SEL_CAP];
-  __shared__ uint32_t cnt[E * NT / 64];
+// The body of page_select_reg_kernel for a row of at most NT * E entries of which 0 < Kp < P are taken.
+template <int NT, int E, int SNB>
+__device__ __forceinline__ void select_row(const float* sc, int P, int Kp, int max_sel, int32_t* out, uint32_t* hist,
+                                           unsigned long long* cand, uint32_t* cnt) {
+  const int tid = threadIdx.x;
   uint32_t key[E], T, need_eq;
 #pragma unroll
   for (int e = 0; e < E; ++e) {                   // clamped loads, all in flight
@@ -319,8 +301,38 @@ __global__ __launch_bounds__(NT, NT == 1024 && E == 8 ? 8 : 1) void page_select_
     key[e] = E > 8 ? tw_select_key(__uint_as_float(key[e]), e * NT + tid < P) : tw_float_key(__uint_as_float(key[e]));
   tw_select_threshold<NT, E, SNB, 10>(key, P, (uint32_t)Kp, hist, cand, &T, &need_eq);
   tw_select_list<NT, E>(key, P, T, need_eq, cnt, [&](uint32_t pos, int e) {
-    if (pos < (uint32_t)a.max_sel) out[pos] = e * NT + tid;
+    if (pos < (uint32_t)max_sel) out[pos] = e * NT + tid;
   });
+}
+
+// Rows of at most NT * E entries, the keys in registers.
+// 8 and 16 slots per thread (rows of 2049 to 16384 entries): what bounds many rows is how many workgroups wait at their
+// barriers side by side, so these forms are held to 64 registers - two workgroups of 16 waves per CU - with 512 buckets, 8
+// per scanning lane.  1024 rows x 2500 entries 27.9 us with 72 registers and 1024 buckets, one workgroup per CU -> 21.3,
+// x 8192 37.9 -> 29.5 (256 x 8192, a row per CU: 8.9 as before); 1024 rows x 16384 in the 32-slot form 78 -> 42.
+// Above 8 slots a row of up to a quarter of the form's length takes a body of its own, with fewer slots and without the
+// longest rows' sentinel keys: 64 ragged sequences x 32 heads of up to 32768 tokens 105 -> 78 us, up to 9000 37.9 -> 31.5.
+template <int NT, int E, int UNIT>
+__global__ __launch_bounds__(NT, E == 8 || E == 16 ? 8 : 1) void page_select_reg_kernel(SelectArgs a) {
+  constexpr int SNB = E > 16 ? 2048 : (NT == 1024 && E == 2 ? 1024 : 512);
+  const int b = blockIdx.y, h = blockIdx.x, tid = threadIdx.x;
+  int P, Kp;
+  tw_select_sizes<UNIT>(a, a.seq_lens[b], a.budget[b], &P, &Kp);
+  if (P <= a.p_above || P > a.p_upto) return;     // another launch's head (block-uniform)
+  int32_t* out = a.sel_pages + ((long long)(b * a.Hq + h)) * a.max_sel;
+  const float* sc = a.scores + ((long long)(b * a.Hq + h)) * a.max_pages;
+  if (tid == 0) a.sel_count[b * a.Hq + h] = Kp;
+  if (Kp == 0) return;
+  if (Kp == P) {
+    for (int i = tid; i < P; i += NT) out[i] = i;
+    return;
+  }
+  __shared__ uint32_t hist[SNB];
+  __shared__ unsigned long long cand[SEL_CAP];
+  __shared__ uint32_t cnt[E * NT / 64];
+  constexpr int SHORT = E > 16 ? 8 : 4;
+  if (E > 8 && P <= SHORT * NT) select_row<NT, SHORT, 512>(sc, P, Kp, a.max_sel, out, hist, cand, cnt);   // (block-uniform)
+  else select_row<NT, E, SNB>(sc, P, Kp, a.max_sel, out, hist, cand, cnt);
 }
 
 template <int G>
@@ -345,8 +357,8 @@ static int launch_select(SelectArgs sa, const TwDims& d, hipStream_t s) {
   const int L = sa.max_pages;
   sa.p_above = -1; sa.p_upto = L;
   const dim3 grid(d.Hq, d.batch);
-  // Many heads and rows of up to 8192 entries (ragged batches): the 1024-thread kernel fits two
-  // workgroups per CU; rows of at most 2048 entries go to a 256-thread launch of their own.
+  // Many heads and rows of up to 8192 entries (ragged batches): rows of at most 2048 entries go to a 256-thread launch
+  // of their own, eight of which share a CU (two of the 1024-thread kernel).
   if (L > 2048 && L <= SEL_REG_PAGES && (long long)d.batch * d.Hq > 2ll * tw_num_cus()) {
     sa.p_upto = 2048;
     tw_prof_before(TW_K_PAGE_SELECT, s);
@@ -366,6 +378,8 @@ static int launch_select(SelectArgs sa, const TwDims& d, hipStream_t s) {
     TW_LAUNCH((page_select_reg_kernel<1024, 2, UNIT>), grid, dim3(1024), 0, s, sa);
   else if (L <= SEL_REG_PAGES)
     TW_LAUNCH((page_select_reg_kernel<1024, 8, UNIT>), grid, dim3(1024), 0, s, sa);
+  else if (L <= SEL_REG_TWO)
+    TW_LAUNCH((page_select_reg_kernel<1024, 16, UNIT>), grid, dim3(1024), 0, s, sa);
   else if (L <= SEL_REG_MAX)
     TW_LAUNCH((page_select_reg_kernel<1024, 32, UNIT>), grid, dim3(1024), 0, s, sa);
   else

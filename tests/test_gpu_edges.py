@@ -75,12 +75,19 @@ def test_short_rows_under_a_long_bound_cost_no_more_than_full_ones():
     assert short < full, (short, full)
 
 
-@pytest.mark.parametrize("max_pages", [2500, 9000, 17000])
-def test_page_lists_of_short_rows_under_a_long_bound(max_pages):
-    """Rows far shorter than the bound that chooses the selection kernel, down to one with a wave's worth of entries:
-    page lists bit for bit."""
+def test_selection_time_follows_the_length_of_the_row():
+    """512 rows of a quarter of the bound's length: the selection handles their entries, not the bound's."""
     T = _T()
-    pages = [max_pages, 1100, 700, 65, 17, 2]
+    short, full = _selection_us(T, 8000, 32768, 16), _selection_us(T, 32768, 32768, 16)
+    assert short < 0.55 * full, (short, full)
+
+
+@pytest.mark.parametrize("max_pages", [2500, 9000, 16384, 16385, 32768])
+def test_page_lists_of_short_rows_under_a_long_bound(max_pages):
+    """Rows shorter than the bound that chooses the selection kernel, at the lengths where its body or the groups of slots
+    that it skips change, down to one with a wave's worth of entries: page lists bit for bit."""
+    T = _T()
+    pages = [max_pages, 1100, 700, 65, 17, 2] + [P + i for P in (4096, 8192, 12288, 28672) for i in (0, 1) if P + i < max_pages]
     cache, q = _random_bounds(T, [16 * P for P in pages], max_pages, heads=(2, 1), pool=4096, seed=max_pages)
     for cut in (2, 7):
         budget = [16 * max(1, P // cut) for P in pages]

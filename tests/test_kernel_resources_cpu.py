@@ -63,7 +63,12 @@ def _fits(k, workgroups):
 
 
 @pytest.mark.parametrize("unit", [16, 1])
-def test_selection_of_up_to_8192_entries_runs_two_workgroups_per_cu(kernels, unit):
-    k = kernels["page_select_reg_kernel<1024, 8, %d>" % unit]
+@pytest.mark.parametrize("slots", [8, 16])
+def test_selection_of_up_to_16384_entries_runs_two_workgroups_per_cu(kernels, slots, unit):
+    k = kernels["page_select_reg_kernel<1024, %d, %d>" % (slots, unit)]
     assert _fits(k, 2), k[".vgpr_count"]
-    assert k[".vgpr_spill_count"] == 0
+
+
+def test_the_selection_kernels_spill_no_vector_registers(kernels):
+    spilled = {n: k[".vgpr_spill_count"] for n, k in kernels.items() if n.startswith("page_select")}
+    assert len(spilled) == 14 and not any(spilled.values()), spilled
