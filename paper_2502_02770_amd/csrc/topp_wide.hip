@@ -309,14 +309,20 @@ struct ResolveLds {
   uint32_t histC[HP_NB];
   unsigned long long cand_mass[WR_CAP];
   uint32_t cand_key[WR_CAP];
-  uint32_t red[16];
+  uint32_t red[16], red2[16];
   uint32_t n, T;
 };
+// Block-wide minimum of lo and maximum of hi over waves whose results are in red / red2 (every lane gets them).
+template <int NW>
+__device__ __forceinline__ void wide_min_max(const ResolveLds& L, int lane, uint32_t* lo, uint32_t* hi) {
+  *lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)~tw_row_max_u32(~L.red[lane & (NW - 1)]));
+  *hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)tw_row_max_u32(L.red2[lane & (NW - 1)]));
+}
 
 // Threshold among scores of ranks [rlo, rlo + 2^shift): the largest key whose upper set, with the mass A above the
 // interval, reaches `target`.  The interval is narrowed 9 bits per round with a 512-bucket LDS histogram until at most
 // 64 scores are left, and those are compared exactly on the scores' own bits; more than 64 scores of one rank are one
-// tier.  each(f) calls f(key, score) for every score of this thread; called by all NT threads.  *found: the interval
+// tier, and an interval that holds one score value only, however often, needs no narrowing.  each(f) calls f(key, score) for every score of this thread; called by all NT threads.  *found: the interval
 // holds the crossing.
 template <int NT, class Each>
 __device__ __forceinline__ uint32_t wide_threshold(Each each, float m, uint32_t rlo, int shift, uint32_t pop, unsigned long long A,
@@ -331,15 +337,30 @@ __device__ __forceinline__ uint32_t wide_threshold(Each each, float m, uint32_t 
     __syncthreads();
     for (int i = tid; i < HP_NB; i += NT) { L.histM[i] = 0; L.histC[i] = 0; }
     __syncthreads();
-    each([&](uint32_t, float s) {
-      float e;
-      const uint32_t r = hp_rank(m, s, &e);
-      if (r != HP_NONE && r >= rlo) {
-        const uint32_t bk = (r - rlo) >> nshift;
-        if (bk < nb) { atomicAdd(&L.histM[bk], hp_fix(e)); atomicAdd(&L.histC[bk], 1u); }
+    // A thread's consecutive scores of one bucket are added up before they go to LDS (rows of equal keys put all their
+    // scores into one bucket: 131072 of them 135 us a pass when each was added by itself).
+    uint32_t cb = 0, cc = 0, klo = 0xFFFFFFFFu, khi = 0u;
+    unsigned long long cm = 0;
+    auto flush = [&]() {
+      if (cc) { atomicAdd(&L.histM[cb], cm); atomicAdd(&L.histC[cb], cc); }
+    };
+    each([&](uint32_t k, float s) {
+      const uint32_t r = hp_rank_only(m, s);
+      const uint32_t bk = (r - rlo) >> nshift;
+      if (r != HP_NONE && r >= rlo && bk < nb) {
+        klo = k < klo ? k : klo;
+        khi = k > khi ? k : khi;
+        if (bk != cb) { flush(); cb = bk; cm = 0; cc = 0; }
+        cm += hp_fix(hp_numer(m, s));
+        cc += 1;
       }
     });
+    flush();
+    klo = ~tw_wave_max_u32(~klo);
+    khi = tw_wave_max_u32(khi);
+    if (lane == 0) { L.red[wave] = klo; L.red2[wave] = khi; }
     __syncthreads();
+    wide_min_max<NT / 64>(L, lane, &klo, &khi);
     unsigned long long mb[8], mine = 0;           // every wave scans on its own: lane l owns buckets 8l .. 8l+7
 #pragma unroll
     for (int k = 0; k < 8; ++k) { mb[k] = L.histM[8 * lane + k]; mine += mb[k]; }
@@ -348,6 +369,7 @@ __device__ __forceinline__ uint32_t wide_threshold(Each each, float m, uint32_t 
     const bool hit = before < target && before + mine >= target;
     const unsigned long long bal = __ballot(hit);
     if (bal == 0) return 0xFFFFFFFFu;             // (the same in every wave)
+    if (klo == khi) { *found = true; return klo; }
     const int src = __ffsll((long long)bal) - 1;
     unsigned long long cum = before, asel = before;
     int bsel = 0;
@@ -367,13 +389,12 @@ __device__ __forceinline__ uint32_t wide_threshold(Each each, float m, uint32_t 
   uint32_t kmin = 0xFFFFFFFFu;
   __syncthreads();                                // L.n cleared; scans done
   each([&](uint32_t k, float s) {
-    float e;
-    const uint32_t r = hp_rank(m, s, &e);
+    const uint32_t r = hp_rank_only(m, s);
     if (r != HP_NONE && r >= rlo && r <= rhi) {
       kmin = k < kmin ? k : kmin;
       if (small) {
         const uint32_t at = atomicAdd(&L.n, 1u);
-        if (at < (uint32_t)WR_CAP) { L.cand_key[at] = k; L.cand_mass[at] = hp_fix(e); }
+        if (at < (uint32_t)WR_CAP) { L.cand_key[at] = k; L.cand_mass[at] = hp_fix(hp_numer(m, s)); }
       }
     }
   });
@@ -407,14 +428,15 @@ __device__ __forceinline__ uint32_t wide_threshold(Each each, float m, uint32_t 
 
 // One workgroup per head walks the head's list (a few dozen scores as a rule, some thousand in a near-uniform row).  A
 // head whose list overflowed or does not hold the threshold (the exact sums decide) is searched from its whole row
-// instead, and its bitmap written anew.
+// instead, and its bitmap written anew: one to three narrowing passes over the row (one where the undecided scores are
+// all equal), the exact one and the bitmap's, bound by one workgroup's loads in flight.  Whole top-p of such rows:
+// 256 heads x 262144 equal keys 198 us (ordinary keys 85), logits within 0.01 of each other 187, keys drawn from four
+// rows 264; 32 heads x 131072 75 / 31 (the list holds them) / 68 (ordinary keys 26).
 template <int NT>
 __global__ __launch_bounds__(NT) void wide_resolve_kernel(WideArgs a) {
   constexpr int NW = NT / 64;
   const int bh = blockIdx.x, b = bh / a.Hq, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   __shared__ ResolveLds L;
-  __shared__ uint32_t red_hi[NW];
-  __shared__ unsigned long long zred[NW];
   const uint2* const list = a.ulist + (long long)bh * W_CAP;
   const uint2 first = list[tid];                  // (inside the buffer whatever the list's length; all loads of the prologue together)
   const uint32_t listed = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.ucount[(long long)bh * TW_CTR]);
@@ -447,10 +469,10 @@ __global__ __launch_bounds__(NT) void wide_resolve_kernel(WideArgs a) {
         });
         rmin = ~tw_wave_max_u32(~rmin);
         rmax = tw_wave_max_u32(rmax);
-        if (lane == 0) { L.red[wave] = rmin; red_hi[wave] = rmax; }
+        if (lane == 0) { L.red[wave] = rmin; L.red2[wave] = rmax; }
         __syncthreads();
-        rlo = (uint32_t)__builtin_amdgcn_readfirstlane((int)~tw_row_max_u32(~L.red[lane & (NW - 1)]));
-        const uint32_t span = (uint32_t)__builtin_amdgcn_readfirstlane((int)tw_row_max_u32(red_hi[lane & (NW - 1)])) - rlo;
+        wide_min_max<NW>(L, lane, &rlo, &rmax);
+        const uint32_t span = rmax - rlo;
         shift = span ? 32 - __clz(span) : 0;
       } else {
         shift = 27;
@@ -488,16 +510,17 @@ __global__ __launch_bounds__(NT) void wide_resolve_kernel(WideArgs a) {
         }
       }
     };
-    unsigned long long Z = 0;
-    each([&](uint32_t, float s) { if (hp_rank_only(m, s) != HP_NONE) Z += hp_fix(hp_numer(m, s)); });
-    Z = tw_wave_scan_u64(Z);
-    if (lane == 63) zred[wave] = Z;
-    __syncthreads();
-    Z = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) Z += zred[w];
-    bool found;
-    const uint32_t T = wide_threshold<NT>(each, m, 0u, 27, 0xFFFFFFFFu, 0ull, hp_target(a.p, Z), L, &found);
+    // first among the ranks that the histogram left undecided (an overflowed list), then - the sums say that the
+    // threshold is not there - among all
+    const unsigned long long target = hp_target(a.p, Z0);
+    uint32_t T = 0xFFFFFFFFu;
+    bool found = false;
+    if (A0 < target) {                              // block-uniform
+      const float4 rg = a.range[bh];
+      const uint32_t rlo = (uint32_t)(rg.y * 4194304.f), span = (uint32_t)(rg.z * 4194304.f) - rlo;   // (rg.y < rg.z <= 27.5)
+      T = wide_threshold<NT>(each, m, rlo, span > 1u ? 32 - __clz(span - 1u) : 0, 0xFFFFFFFFu, A0, target, L, &found);
+    }
+    if (!found) T = wide_threshold<NT>(each, m, 0u, 27, 0xFFFFFFFFu, 0ull, target, L, &found);
     // 16 slots = one page = one half word of the bitmap per thread
     for (int i = tid; i < count; i += NT) {
       uint32_t bits = 0;

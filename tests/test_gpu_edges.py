@@ -101,3 +101,37 @@ def test_page_lists_of_short_rows_under_a_long_bound(max_pages):
                 U = O.page_upper_bounds(synth.bits(q[b, h].cpu()), u16(rows[:, 0]), u16(rows[:, 1]))
                 want = O.select_pages(U, budget[b], 16 * P)
                 assert st.sel_pages[b, h, :int(st.sel_count[b, h])].cpu().numpy().tolist() == want.tolist(), (b, h, cut)
+
+
+def _prune_us(T, keys, batch, n, heads, p=0.95):
+    """Median time of the pruner's kernels with every token a candidate; keys(gen) -> [batch * n, kv_heads, 128]."""
+    B = T.binding
+    g = torch.Generator(device="cuda").manual_seed(7)
+    pages = (n + 15) // 16
+    cache = T.PagedKV(heads[0], heads[1], torch.arange(batch * pages, dtype=torch.int32).view(batch, pages),
+                      torch.tensor([n] * batch), batch * pages, need_v=False)
+    cache.fill(keys(g).to(torch.bfloat16), None, [i * n for i in range(batch + 1)])
+    q = torch.randn(batch, heads[0], 128, device="cuda", generator=g).to(torch.bfloat16)
+    st = T.DecodeStep(cache)
+    for _ in range(3):
+        st.prune(q, p)
+    torch.cuda.synchronize()
+    B.twilight_prof_enable(1)
+    for _ in range(9):
+        st.prune(q, p)
+    torch.cuda.synchronize()
+    rec = B.twilight_prof_collect()
+    B.twilight_prof_enable(0)
+    return float(np.median(np.array([ms for _, ms in rec]).reshape(9, -1).sum(axis=1)) * 1e3)
+
+
+def test_long_rows_of_equal_keys_are_searched_quickly():
+    """Rows whose listed scores overflow (all keys equal, or drawn from four) are searched again from the scores by one
+    workgroup per row: that must not take several times what the rest of the pruner takes.  (Every score of such a row
+    falls into one bucket, so one LDS add per score makes it a serial chain.)"""
+    T = _T()
+    n, Hkv = 65536, 2
+    plain = _prune_us(T, lambda g: torch.randn(n, Hkv, 128, device="cuda", generator=g), 1, n, (8, Hkv))
+    equal = _prune_us(T, lambda g: torch.randn(1, Hkv, 128, device="cuda", generator=g).expand(n, Hkv, 128), 1, n, (8, Hkv))
+    few = _prune_us(T, lambda g: torch.randn(4, Hkv, 128, device="cuda", generator=g)[torch.randint(0, 4, (n,), device="cuda", generator=g)], 1, n, (8, Hkv))
+    assert equal < 3 * plain and few < 3 * plain, (plain, equal, few)
