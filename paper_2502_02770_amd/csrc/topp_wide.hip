@@ -167,16 +167,41 @@ __device__ __forceinline__ void wide_range(const unsigned long long* gh, WhGrid 
   const float Z = __shfl(incl, 63, 64);
   *d_hi = 0.f; *d_lo = HP_REACH;                         // a histogram that says nothing: everything is undecided
   if (!(Z > 0.f) || !(Z < __builtin_inff()) || __shfl(mb[0], 0, 64) > 0.f) return;     // wave-uniform
-  // margin: roundings of the weights and of these sums, and what lies beyond the last bucket's edge
-  const float eps = 5e-5f * Z + __shfl(mb[BPL - 1], 63, 64);
-  const float t0 = p * Z - eps, t1 = p * Z + eps;
+  // The buckets in which the kept mass may reach p of the whole, summed from the top down below p = 1/2 and from the bottom
+  // up above: there the mass left out has to fall to 1 - p of the whole, and the sums' roundings are relative to it.
+  // Margin: roundings of the weights (2^-19 of a bucket's edge) and of these sums, with much to spare, and what lies beyond
+  // the last bucket's edge.  (5e-5 of the whole mass whatever p is is more than p = 0.99999 leaves out: every score below
+  // the threshold was then undecided, and peaked rows, whose tail is most of their scores, overflowed their lists: logits
+  // of deviation 4, 32 heads x 131072 at p = 0.99999 107 -> 30 us of top-p, 256 x 262144 at p = 0.9999 285 -> 90.  At
+  // p = 0.99999 there, 316 -> 221: the row's sample is too small to place the grid, and some of the lists still overflow.)
+  const float left = 1.f - p;
+  const float eps = fminf(5e-5f, 1e-3f * left) * Z + __shfl(mb[BPL - 1], 63, 64);
   int b0 = WH_NB, b1 = WH_NB;
-  float cum = incl - mine;
+  if (p < 0.5f) {
+    const float t0 = p * Z - eps, t1 = p * Z + eps;
+    float cum = incl - mine;
 #pragma unroll
-  for (int k = 0; k < BPL; ++k) {
-    cum += mb[k];
-    if (b0 == WH_NB && cum >= t0) b0 = BPL * lane + k;
-    if (b1 == WH_NB && cum >= t1) b1 = BPL * lane + k;
+    for (int k = 0; k < BPL; ++k) {
+      cum += mb[k];
+      if (b0 == WH_NB && cum >= t0) b0 = BPL * lane + k;
+      if (b1 == WH_NB && cum >= t1) b1 = BPL * lane + k;
+    }
+  } else {
+    float below = mine;                                  // mass of this lane's buckets and of those below them
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const float y = __shfl_down(below, o, 64);
+      if (lane + o < 64) below += y;
+    }
+    below = __shfl_down(below, 1, 64);
+    if (lane == 63) below = 0.f;
+    const float t0 = left * Z + eps, t1 = left * Z - eps;
+#pragma unroll
+    for (int k = BPL - 1; k >= 0; --k) {
+      if (below <= t0) b0 = BPL * lane + k;
+      if (below <= t1) b1 = BPL * lane + k;
+      below += mb[k];
+    }
   }
   const unsigned long long h0 = __ballot(b0 < WH_NB), h1 = __ballot(b1 < WH_NB);
   b0 = h0 ? __shfl(b0, __ffsll((long long)h0) - 1, 64) : WH_NB - 1;

@@ -135,3 +135,14 @@ def test_long_rows_of_equal_keys_are_searched_quickly():
     equal = _prune_us(T, lambda g: torch.randn(1, Hkv, 128, device="cuda", generator=g).expand(n, Hkv, 128), 1, n, (8, Hkv))
     few = _prune_us(T, lambda g: torch.randn(4, Hkv, 128, device="cuda", generator=g)[torch.randint(0, 4, (n,), device="cuda", generator=g)], 1, n, (8, Hkv))
     assert equal < 3 * plain and few < 3 * plain, (plain, equal, few)
+
+
+def test_long_peaked_rows_with_p_near_one_list_few_scores():
+    """Logits of deviation 4, p = 0.99999: what is left out is a hundred-thousandth of the mass but most of the scores.
+    The scores that the histogram leaves undecided must still fit the list (a row searched again takes several times the
+    whole of top-p otherwise)."""
+    T = _T()
+    n, Hkv = 65536, 2
+    keys = lambda g: 4 * torch.randn(n, Hkv, 128, device="cuda", generator=g)
+    plain, near = _prune_us(T, keys, 1, n, (8, Hkv), 0.95), _prune_us(T, keys, 1, n, (8, Hkv), 0.99999)
+    assert near < 1.4 * plain, (plain, near)
