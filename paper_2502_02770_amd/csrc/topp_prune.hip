@@ -62,7 +62,7 @@ __device__ __forceinline__ void tw_quantize_q(const uint16_t* q, int (*qi_s)[32]
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int h = wave + r * NW < NH ? wave + r * NW : NH - 1;
-    raw[r] = ((const uint32_t*)q)[h * 64 + lane];
+    __builtin_memcpy(&raw[r], q + (h * 64 + lane) * 2, 4);     // (bf16 rows may begin at any element: no more than 2-byte alignment)
   }
   const uint32_t cm = chmask ? chmask[lane >> 4] >> ((2 * lane) & 31) : 3u;
 #pragma unroll

@@ -5,7 +5,7 @@ import torch
 
 from oracle import twilight_oracle as O
 from workloads import synth
-from tests.gpu_util import u16
+from tests.gpu_util import build_cache, u16
 
 pytestmark = pytest.mark.gpu
 
@@ -146,3 +146,25 @@ def test_long_peaked_rows_with_p_near_one_list_few_scores():
     keys = lambda g: 4 * torch.randn(n, Hkv, 128, device="cuda", generator=g)
     plain, near = _prune_us(T, keys, 1, n, (8, Hkv), 0.95), _prune_us(T, keys, 1, n, (8, Hkv), 0.99999)
     assert near < 1.4 * plain, (plain, near)
+
+
+def test_query_rows_at_an_odd_element():
+    """The scoring and pruning entry points take a query that begins at any bf16 element."""
+    T = _T()
+    w = synth.make_workload("oddq", [700, 9000], num_q_heads=8, num_kv_heads=2, budget=512, p=0.9, heavy_frac=0.01,
+                            alpha_range=(0.0, 3.0), need_v=False, seed=93)
+    cache = build_cache(w)
+    q = w.q.cuda()
+    odd = torch.zeros(q.numel() + 1, dtype=torch.bfloat16, device="cuda")[1:].view(q.shape)
+    odd.copy_(q)
+    assert odd.data_ptr() % 4 == 2
+    full, listed = T.DecodeStep(cache), T.DecodeStep(cache, max_sel=32)
+    listed.select(q, w.budget.cuda())
+    for st in (full, listed):
+        got = []
+        for x in (q, odd):
+            st.union_idx.fill_(-1)
+            st.prune(x, w.p)
+            torch.cuda.synchronize()
+            got.append([t.clone() for t in (st.kept_count, st.union_count, st.union_idx)])
+        assert all(torch.equal(a, b) for a, b in zip(*got))
