@@ -556,23 +556,25 @@ def test_select_prune_equals_the_separate_calls_with_append(bits):
     pipeline_against_oracle(w, bits, b_)
 
 
-@pytest.mark.parametrize("shape", ["few_heads", "heads_over_cus", "split_launch", "over_4096_pages", "few_heads_long_lists",
-                                   "mha", "gqa8", "empty_and_full"])
+@pytest.mark.parametrize("shape", ["few_heads", "heads_over_cus", "split_launch", "over_512_pages_listed", "over_4096_pages",
+                                   "few_heads_long_lists", "mha", "gqa8", "empty_and_full"])
 def test_select_prune_equals_the_separate_calls(shape):
-    """Every launch shape of twilight_select_prune against twilight_select_pages + twilight_topp_prune: one
-    1024-thread workgroup per head; 512-thread workgroups when there are more heads than CUs; the two launches of a
-    ragged batch with lists above 4096 candidates; sequences of more than 4096 pages (page lists made by the
-    selection kernel, scoring inside the top-p kernel); a single long sequence (all launches separate); one and
-    eight query heads per KV head; an empty sequence, a zero budget and budgets that cover whole sequences."""
+    """Every route of twilight_select_prune against twilight_select_pages + twilight_topp_prune: few heads; more heads
+    than CUs; a ragged batch of more than two heads per CU with lists above 4096 candidates (one launch with 16
+    candidates per thread against the separate calls' two launches by list length); lists above 8192 candidates (the
+    long-row kernels on both sides); sequences of more than 4096 pages (page lists made by the selection kernel, scoring
+    inside the top-p kernel); a single long sequence (all launches separate); one and eight query heads per KV head; an
+    empty sequence, a zero budget and budgets that cover whole sequences."""
     T = _T()
     kw = dict(p=0.9, heavy_frac=0.01, alpha_range=(0.0, 3.0), shuffle_pool=True)
     if shape == "few_heads":
         w = synth.make_workload(shape, [5000, 1234, 16], num_q_heads=8, num_kv_heads=2, budget=[1024, 400, 16], seed=51, **kw)
     elif shape == "heads_over_cus":
         w = synth.make_workload(shape, [900 + 211 * i for i in range(10)], budget=512, seed=52, **kw)
-    elif shape == "split_launch":
+    elif shape in ("split_launch", "over_512_pages_listed"):
         lens = [40_000, 70_000] + [600 + 150 * i for i in range(16)]
-        w = synth.make_workload(shape, lens, budget=[n // 8 for n in lens], seed=53, **kw)
+        most = 8192 if shape == "split_launch" else 10 ** 6
+        w = synth.make_workload(shape, lens, budget=[min(n // 8, most) for n in lens], seed=53, **kw)
     elif shape == "over_4096_pages":
         w = synth.make_workload(shape, [70_000, 3000], num_q_heads=8, num_kv_heads=2, budget=2048, seed=54, **kw)
     elif shape == "few_heads_long_lists":
@@ -911,8 +913,9 @@ def test_full_size_pruner_stress_sampled():
 
 
 def test_full_size_ragged_batch_sampled():
-    """Benchmark config C5 at full size (64 ragged sequences in one shuffled pool, budget n/8): the split
-    top-p launch and the balanced decode work list at the size bench.py --config 4 times."""
+    """Benchmark config C5 at full size (64 ragged sequences in one shuffled pool, budget n/8): the one-launch
+    selector + pruner with 16 candidates per thread and the balanced decode work list at the size bench.py --config 4
+    times."""
     w = synth.config(4)
     cache = build_cache(w)
     st, q = run_pipeline(w, cache, with_kept=True)
@@ -965,17 +968,30 @@ def test_scaled_benchmark_configs(idx, scale, batch):
     check_sets_and_output(w, cache, st)
 
 
-def test_many_heads_mixed_row_lengths_split_launch():
-    """More than two heads per CU and a candidate bound above 4096: top-p runs as two launches, heads of
-    at most 4096 candidates in 512-thread workgroups, longer ones in 1024-thread workgroups."""
+@pytest.mark.parametrize("most", [8192, 10 ** 6], ids=["split_launch", "long_rows"])
+def test_many_heads_mixed_row_lengths_split_launch(most):
+    """More than two heads per CU and a candidate bound above 4096.  Up to 8192 candidates: the top-p of stored scores runs
+    as two launches, heads of at most 4096 candidates in 512-thread workgroups, longer ones in 1024-thread workgroups.
+    Beyond: the long-row kernels on page lists."""
+    T = _T()
     lens = [40_000, 70_000] + [600 + 150 * i for i in range(16)]            # 18 sequences x 32 heads = 576 heads
-    w = synth.make_workload("mixed", lens, budget=[n // 8 for n in lens], p=0.95, heavy_frac=0.01,
+    w = synth.make_workload("mixed", lens, budget=[min(n // 8, most) for n in lens], p=0.95, heavy_frac=0.01,
                             alpha_range=(0.0, 3.0), shuffle_pool=True, seed=31)
     cache = build_cache(w)
     st, q = run_pipeline(w, cache)
     assert int(st.status.item()) == 0
     assert st.max_sel * 16 > 4096 and w.batch * w.num_q_heads > 512
     check_sets_and_output(w, cache, st)
+    # the separate calls: the launches that the docstring names, the same sets
+    s2 = T.DecodeStep(cache, max_sel=st.max_sel, with_kept_idx=True)
+    s2.select(q, w.budget.to(cache.device))
+    T.twilight_prof_enable(1)
+    s2.prune(q, w.p)
+    torch.cuda.synchronize()
+    names = [name for name, _ in T.twilight_prof_collect()]
+    T.twilight_prof_enable(0)
+    assert names == (["int4_score", "topp", "topp"] if most == 8192 else ["topp", "int4_score"] + ["topp"] * 4 + ["union"] * (len(names) - 6)), names
+    _lists_equal(st, s2, "separate calls")
 
 
 def test_long_sequence_fallback_paths():
@@ -1303,8 +1319,8 @@ def test_token_lists_keep_all_at_p1_and_report_overflow():
 
 
 def test_more_heads_than_cus_short_rows():
-    """More (sequence, query head) rows than CUs with rows of at most 4096 candidates: top-p runs in
-    512-thread workgroups, two to a CU."""
+    """More (sequence, query head) rows than CUs with short candidate lists: top-p runs in 256-thread workgroups, several
+    to a CU."""
     lens = [900 + 211 * i for i in range(10)]                              # 10 sequences x 32 heads = 320 rows
     w = synth.make_workload("manyshort", lens, budget=512, p=0.9, heavy_frac=0.01, alpha_range=(0.0, 3.0),
                             shuffle_pool=True, seed=33)
@@ -1988,10 +2004,12 @@ def test_long_rows_where_the_histogram_can_miss(keys, heads, bits, p):
 
 @pytest.mark.parametrize("bits", [2, 4, 8])
 @pytest.mark.parametrize("max_sel,n,seqs", [(127, 32768, 2), (128, 32753, 2), (128, 32769, 2), (129, 9000, 2), (256, 40001, 2),
-                                            (512, 20000, 2), (1, 17, 2), (64, 16384, 36), (64, 16385, 36), (65, 16000, 36), (3, 50, 36)])
+                                            (1, 17, 2), (64, 16384, 36), (64, 16385, 36), (65, 16000, 36), (3, 50, 36)])
 def test_one_launch_select_prune_at_the_limits_of_its_workgroup_sizes(bits, max_sel, n, seqs):
-    """64 / 65 pages listed with more heads than CUs (1024 candidates, 1024 / 1025 pages), 128 / 129 pages listed (2048 candidates), 2048 / 2049 pages in the row and 256 pages (4096 candidates) are where
-    the one-launch selector + pruner changes its workgroup; every code width against the separate calls."""
+    """64 / 65 pages listed with more heads than CUs (1024 candidates, 1024 / 1025 pages), 128 / 129 pages listed (2048
+    candidates), 2048 / 2049 pages in the row and 256 pages (4096 candidates) are where the one-launch selector + pruner
+    changes its workgroup; every code width against the separate calls.  (Lists above 4096 candidates take the one launch
+    only with at least as many heads as CUs: the next test.)"""
     T = _T()
     w = synth.make_workload("limits", [n] + [1 + n // (2 + i) for i in range(1, seqs)], num_q_heads=8, num_kv_heads=2,
                             budget=[max_sel * 16] + [max_sel * 5 + i for i in range(1, seqs)],
@@ -2005,3 +2023,39 @@ def test_one_launch_select_prune_at_the_limits_of_its_workgroup_sizes(bits, max_
     sb.select_prune(None, None, None, q, budget, w.p)
     torch.cuda.synchronize()
     _lists_equal(sa, sb, "select_prune")
+
+
+@pytest.mark.parametrize("bits,heads,seqs,max_sel",
+                         [(bits, (8, 2), seqs, m) for bits in (2, 4, 8) for seqs, m in ((36, 129), (36, 256), (36, 257), (36, 512), (65, 257), (65, 512))] +
+                         [(4, (16, 2), 33, 512), (4, (8, 4), 65, 511), (4, (8, 8), 65, 300)])
+def test_one_launch_select_prune_of_many_heads_with_long_lists(bits, heads, seqs, max_sel):
+    """More heads than CUs (36 x 8) with lists of 2049 to 4096 candidates (512 threads x 8) and beyond (1024 x 8), and more
+    than two heads per CU with lists beyond 4096 candidates (512 x 16, all 64 lanes of a wave's page list at 512 pages):
+    every code width against the separate calls, and the longest sequence against the oracle."""
+    T = _T()
+    n = 32 * max_sel + 3
+    assert n <= 4096 * 16 and seqs * heads[0] > 256
+    w = synth.make_workload("manylong", [n] + [1 + n // (2 + i) for i in range(1, seqs)], num_q_heads=heads[0], num_kv_heads=heads[1],
+                            budget=[max_sel * 16] + [max_sel * 5 + i for i in range(1, seqs)], p=0.9, heavy_frac=0.01,
+                            alpha_range=(0.0, 3.0), shuffle_pool=True, need_v=False, seed=94)
+    cache = build_cache(w, bits=bits)
+    q, budget = w.q.to(cache.device), w.budget.to(cache.device)
+    sa = T.DecodeStep(cache, max_sel=max_sel, with_kept_idx=True)
+    sb = T.DecodeStep(cache, max_sel=max_sel, with_kept_idx=True)
+    sa.select(q, budget)
+    sa.prune(q, w.p)
+    T.twilight_prof_enable(1)
+    sb.select_prune(None, None, None, q, budget, w.p)
+    torch.cuda.synchronize()
+    names = [name for name, _ in T.twilight_prof_collect()]
+    T.twilight_prof_enable(0)
+    assert names == ["page_score", "select_score_topp"]
+    _lists_equal(sa, sb, "select_prune")
+    r = oracle_seq(w, 0, bits=bits)
+    G = heads[0] // heads[1]
+    for h in range(heads[0]):
+        assert sb.sel_pages[0, h, :int(sb.sel_count[0, h])].cpu().numpy().tolist() == r["pages"][h].tolist()
+        check_topp(sb.kept_idx[0, h, :int(sb.kept_count[0, h])].cpu().numpy(), r["s_hat"][h], r["cand"][h], w.p)
+    for g in range(heads[1]):
+        mine = np.unique(np.concatenate([sb.kept_idx[0, h, :int(sb.kept_count[0, h])].cpu().numpy() for h in range(g * G, g * G + G)]))
+        assert sb.union_idx[g, :int(sb.union_count[g])].cpu().numpy().tolist() == mine.tolist()
