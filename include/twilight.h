@@ -202,13 +202,13 @@ int twilight_append_select(const twilight_kv_t* kv, const void* k_new, const voi
  * v_new, new_pos all NULL) followed by twilight_topp_prune over the selected
  * pages computes - the same cache update, page lists, kept sets and unions,
  * bit for bit.  Where a head's list is short enough for one workgroup
- * (quant_bits = 4, max_sel <= 512 pages, sequences of at most 196608 tokens,
- * and not just a few heads with more than 4096 candidates each) the call is
- * two launches instead of four: the bounds of all pages, then one workgroup
- * per query head that picks the head's pages (sequences of at most 4096 pages;
- * longer ones keep the selection launch), scores their tokens from the
- * quantised K copy, runs top-p and, as the last head of its group, lists the
- * union.  Otherwise it runs the launches of the separate calls.  The
+ * (max_sel <= 512 pages, sequences of at most 4096 pages, and not just a few
+ * heads with more than 4096 candidates each) the call is two launches instead
+ * of four: the bounds of all pages, then one workgroup per query head that
+ * picks the head's pages, scores their tokens from the quantised K copy, runs
+ * top-p and, as the last head of its group, lists the union.  Sequences of up
+ * to 196608 tokens keep the selection launch in between (quant_bits = 4).
+ * Otherwise it runs the launches of the separate calls.  The
  * workspace needs no initialising.
  *   sel_pages, sel_count   out, as twilight_select_pages
  *   kept_count ... status  out, as twilight_topp_prune

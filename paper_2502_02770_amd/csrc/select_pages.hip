@@ -502,7 +502,7 @@ extern "C" int twilight_append_select(const twilight_kv_t* kv, const void* k_new
 
 // Selector and pruner in one call (Section 4.1's pipeline up to the pruned index sets): page bounds (with the step's
 // new token appended on the way when k_new is given), then - where the lists are short enough for one workgroup per
-// head - a single launch that picks each head's pages, scores their tokens from the 4-bit copy of K, runs top-p and
+// head - a single launch that picks each head's pages, scores their tokens from the quantised copy of K, runs top-p and
 // builds the group's union; otherwise the launches of twilight_select_pages and twilight_topp_prune.
 extern "C" int twilight_select_prune(const twilight_kv_t* kv, const void* k_new, const void* v_new, const int32_t* new_pos,
                                      const void* q, const int32_t* budget_tokens, float p,

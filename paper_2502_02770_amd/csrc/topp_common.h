@@ -95,9 +95,9 @@ __device__ __forceinline__ int wh_bucket(float t, float lscale, uint32_t* q) {
 }
 // |t| at which bucket u (from 0) of either half begins
 __device__ __forceinline__ float wh_edge(int u) { return __uint_as_float(0x3F000000u + ((uint32_t)u << 17)) - 0.5f; }
-// The scale is a quarter of the deviation, but at least 1/8 logit: the grid then reaches 64 logits to either side.
 // The grid for a row's top-p threshold, from sums over a sample of its scores, weighted by w = exp(s - max of the
 // sample): the scores that carry the mass have mean sws / sw, and p = 0.8 .. 0.99 of it ends one or two deviations below.
+// The scale is a quarter of the deviation, but at least 1/8 logit: the grid then reaches 64 logits to either side.
 __device__ __forceinline__ WhGrid wh_grid(float sw, float sws, float swss) {
   WhGrid g;
   g.ref = 0.f; g.scale = 1.f;

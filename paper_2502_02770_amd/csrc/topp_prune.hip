@@ -675,12 +675,12 @@ __global__ __launch_bounds__(SMP_NT) void row_sample_kernel(SampleArgs sa) {
   }
 }
 
-
 // ------------------------------------------------------------------ top-p per head, scores in registers
-// One workgroup (1024 threads, or 512 for the short rows of a split launch) per
+// One workgroup of 256 to 1024 threads (the rules at launch_topp) per
 // (sequence, query head); thread t owns the contiguous candidate slots
 // [t*EPT, (t+1)*EPT).  Rank (fixed-point distance to the max logit) and softmax
-// numerator of every score are computed once and stay in registers.  Pass 0
+// numerator of every score are computed once and stay in registers, or are
+// recomputed where those are short.  Pass 0
 // buckets the ranks within 8 logits of the max at 1/64 logit and only sums up
 // everything further down (no atomics); the crossing bucket is narrowed 9 bits
 // per pass until at most HP_CAP scores remain, which are resolved exactly on the
@@ -727,7 +727,7 @@ constexpr int HP_USTAGE = 4096;               // union lists up to this length l
 // FUSE >= 1: the estimated scores are computed here, from the head's page list, instead of being read from the row a
 // scoring launch wrote: the workgroup's waves share the list (one page of 64 (token, group) lanes per wave and step,
 // the arithmetic of int4_score_kernel), the scores cross to their owner threads through LDS.
-// FUSE == 2: the page list too is made here, from the bounds of all pages (the selection of page_select_lds_kernel).
+// FUSE == 2: the page list too is made here, from the bounds of all pages (the selection of page_select_reg_kernel).
 // BITS: width of the quantised copy's codes (FUSE == 2; else 4).
 template <int NT, int EPT, int G, bool TOK = false, int FUSE = 0, int BITS = 4>
 __global__ __launch_bounds__(NT, NT <= 512 ? (EPT > 8 ? 4 : 6) : 1) void topp_head_kernel(HeadArgs a) {
@@ -746,7 +746,8 @@ __global__ __launch_bounds__(NT, NT <= 512 ? (EPT > 8 ? 4 : 6) : 1) void topp_he
   const int bh = b * a.Hq + h;
   // FUSE == 2: everything the page selection reads is asked for here, before the sequence's length is known (any
   // entry of the head's row of bounds and of the sequence's page-table row may be read): the bounds and the
-  // page-table entries of the pages j * NT + tid, which this thread will list (1024-thread workgroups, 4 entries each; the 512-thread form, short of registers, asks when it knows the length)
+  // page-table entries of the pages j * NT + tid, which this thread will list (1024-thread workgroups, 4 entries each;
+  // the smaller ones, short of registers, ask when they know the length)
   // FUSE == 2 with few candidates: the row of pages is bounded too (the launch's rule), and LDS is sized for that
   constexpr bool SMALL = FUSE == 2 && NT <= 512 && EPT == 4;
   constexpr int SEL_E = SMALL ? 4 : 4096 / NT;
@@ -857,7 +858,8 @@ __global__ __launch_bounds__(NT, NT <= 512 ? (EPT > 8 ? 4 : 6) : 1) void topp_he
     __shared__ int qi_s[1][32];
     __shared__ float qred[4];
     __shared__ float qc_s[1];
-    // this wave's share of the list: lane k holds its k-th page (at most EPT * 4 <= 32 of them)
+    // this wave's share of the list: lane k holds its k-th page
+    static_assert(EPT * 64 / TW_PAGE <= 64, "a wave's share of the longest list has a lane for every page");
     constexpr int UF = (NT >= 1024 || EPT == 4 ? 8 : 4) / (BITS == 8 ? 2 : 1);   // pages in flight per wave (register budget)
     const int ppw = ((count + NW - 1) / NW + UF - 1) & ~(UF - 1);
     const int first = __builtin_amdgcn_readfirstlane(wave) * ppw;   // (scalar: the loop below is wave-uniform)
@@ -1442,7 +1444,8 @@ void launch_topp_one(const HeadArgs& f, int G, dim3 grid, hipStream_t s) {
 //  - rows of at most 2048 candidates (and, with the selection inside, at most 2048 pages): 512-thread workgroups with 4
 //    candidates per thread, whatever the number of heads.  The kernel is a chain of block barriers; half the waves make
 //    each shorter (32 heads x 1024 candidates 13.4 -> 10.8 us, 320 x 1136 15.6 -> 12.0), and with the LDS arrays sized
-//    for the short rows four workgroups share a CU (2048 heads x 1024 candidates of 512 pages 48.1 -> 30.6);
+//    for the short rows three workgroups share a CU, by their registers (four with 2- and 8-bit codes; 2048 heads x 1024
+//    candidates of 512 pages 48.1 -> 30.6);
 //  - rows of at most 1024 candidates and 1024 pages with more heads than CUs: 256-thread workgroups (2048 heads x 256
 //    candidates 39.8 -> 23.9 us; 32 heads x 1024 candidates 10.8 -> 11.1, so few heads keep the 512 threads);
 //  - many heads with a bound above 4096 candidates, scoring inside: 512-thread workgroups with 16 candidates per thread,

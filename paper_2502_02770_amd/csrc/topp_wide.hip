@@ -22,7 +22,7 @@
 // take a pass over the rows of its own; masses relative to a histogram grid are enough to say where the
 // threshold lies, and wide_resolve checks that with the exact sums: a row whose threshold is not among its listed
 // scores - or with more than W_CAP of them - is searched again from its scores by wide_resolve.
-// At 4 x 64 heads x 262144 tokens: 322 -> 289 us for the whole pruner (scoring 177 -> 185, emit 52 as before, and no
+// At 4 x 64 heads x 262144 tokens: 322 -> 281 us for the whole pruner (scoring 177 -> 185, emit 52 as before, and no
 // histogram passes: 55 us and four launches of 4 us that found nothing left to do).
 //
 // The deciding sums are 64-bit fixed point over the same terms in any order, so the sets do not depend on scheduling

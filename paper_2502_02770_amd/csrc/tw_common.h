@@ -207,36 +207,6 @@ __device__ __forceinline__ uint32_t tw_bits_below(unsigned long long mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// Inclusive scan of one u32 per thread over a group of NW consecutive waves
-// (a whole block, or a team inside it).  `wsum` points at the group's NW
-// words of LDS scratch; w = wave index inside the group.  EVERY thread of
-// the block must call it (two block barriers inside).
-template <int NW>
-__device__ __forceinline__ uint32_t tw_group_scan_u32(uint32_t v, uint32_t* wsum, int w, uint32_t* total) {
-  const uint32_t x = tw_wave_scan_u32(v);
-  if ((threadIdx.x & 63) == 63) wsum[w] = x;
-  __syncthreads();
-  uint32_t off = 0, tot = 0;
-#pragma unroll
-  for (int i = 0; i < NW; ++i) { const uint32_t t = wsum[i]; off += i < w ? t : 0u; tot += t; }
-  __syncthreads();
-  *total = tot;
-  return x + off;
-}
-template <int NW>
-__device__ __forceinline__ unsigned long long tw_group_scan_u64(unsigned long long v, unsigned long long* wsum, int w,
-                                                                unsigned long long* total) {
-  const unsigned long long x = tw_wave_scan_u64(v);
-  if ((threadIdx.x & 63) == 63) wsum[w] = x;
-  __syncthreads();
-  unsigned long long off = 0, tot = 0;
-#pragma unroll
-  for (int i = 0; i < NW; ++i) { const unsigned long long t = wsum[i]; off += i < w ? t : 0ull; tot += t; }
-  __syncthreads();
-  *total = tot;
-  return x + off;
-}
-
 // Block-wide inclusive scan of one u32 per thread, blockDim.x a multiple of 64
 // and at most 1024.  `wsum` is LDS scratch of 16 words.  Returns the inclusive
 // prefix; *total gets the block sum.  Ends with a barrier, so it can be called
@@ -249,18 +219,6 @@ __device__ __forceinline__ uint32_t tw_block_scan_u32(uint32_t v, uint32_t* wsum
   uint32_t off = 0, tot = 0;
   for (int i = 0; i < nw; ++i) { const uint32_t t = wsum[i]; off += i < wave ? t : 0u; tot += t; }
   __syncthreads();
-  *total = tot;
-  return x + off;
-}
-
-// The same without the closing barrier: the caller passes a block barrier of its own before `wsum` is written again.
-__device__ __forceinline__ uint32_t tw_block_scan_u32_open(uint32_t v, uint32_t* wsum, uint32_t* total) {
-  const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  const uint32_t x = tw_wave_scan_u32(v);
-  if ((threadIdx.x & 63) == 63) wsum[wave] = x;
-  __syncthreads();
-  uint32_t off = 0, tot = 0;
-  for (int i = 0; i < nw; ++i) { const uint32_t t = wsum[i]; off += i < wave ? t : 0u; tot += t; }
   *total = tot;
   return x + off;
 }
