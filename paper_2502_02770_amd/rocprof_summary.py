@@ -56,7 +56,7 @@ def trace_rows(d):
 
 
 def write_trace(d, title, command, out=sys.stdout):
-    out.write("# %s\n\nCommand (from /tmp on the MI355X box, TMPDIR=/tmp):\n\n    %s\n\n" % (title, command))
+    out.write("# %s\n\nCommand (from /tmp, TMPDIR=/tmp):\n\n    %s\n\n" % (title, command))
     out.write("Durations in ns, from the kernel trace's start and end timestamps.\n\n")
     out.write("| Kernel | Grid (threads) | Calls | Median | Average | Min | Max |\n|---|---|---|---|---|---|---|\n")
     for r in trace_rows(d):
@@ -78,7 +78,7 @@ def write_traffic(dfetch, dwrite, title, command, out=sys.stdout):
         raise SystemExit("no calibration copy (run bench.py with --calib-copy)")
     ffac = CALIB_BYTES / 1024.0 / fe[cal[0]]
     wfac = CALIB_BYTES / 1024.0 / wr[cal[0]]
-    out.write("# %s\n\nCommands (two separate runs, from /tmp on the MI355X box, TMPDIR=/tmp):\n\n" % title)
+    out.write("# %s\n\nCommands (two separate runs, from /tmp, TMPDIR=/tmp):\n\n" % title)
     for c in ("FETCH_SIZE", "WRITE_SIZE"):
         out.write("    " + command.replace("COUNTER", c) + "\n")
     out.write("\nCounter values are KiB per dispatch (median over the dispatches of the kernel at that grid size).\n"
