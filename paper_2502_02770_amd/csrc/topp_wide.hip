@@ -146,8 +146,8 @@ __global__ __launch_bounds__(NT) void wide_hist_kernel(WideArgs a) {
   }
 }
 
-// The scores among which the head's threshold lies, by its histogram: distances to the maximum d_hi <= d < d_lo.
-__device__ __forceinline__ void wide_range(const unsigned long long* gh, WhGrid gr, float m, float p, int lane, float* d_hi, float* d_lo) {
+// The scores among which the head's threshold lies, by its histogram of N scores: distances to the maximum d_hi <= d < d_lo.
+__device__ __forceinline__ void wide_range(const unsigned long long* gh, WhGrid gr, float m, float p, int N, int lane, float* d_hi, float* d_lo) {
   constexpr int BPL = WH_NB / 64;
   static_assert(WH_NB % 64 == 0, "whole buckets per lane");
   float mb[BPL], mine = 0.f;
@@ -169,13 +169,15 @@ __device__ __forceinline__ void wide_range(const unsigned long long* gh, WhGrid 
   if (!(Z > 0.f) || !(Z < __builtin_inff()) || __shfl(mb[0], 0, 64) > 0.f) return;     // wave-uniform
   // The buckets in which the kept mass may reach p of the whole, summed from the top down below p = 1/2 and from the bottom
   // up above: there the mass left out has to fall to 1 - p of the whole, and the sums' roundings are relative to it.
-  // Margin: roundings of the weights (2^-19 of a bucket's edge) and of these sums, with much to spare, and what lies beyond
-  // the last bucket's edge.  (5e-5 of the whole mass whatever p is is more than p = 0.99999 leaves out: every score below
-  // the threshold was then undecided, and peaked rows, whose tail is most of their scores, overflowed their lists: logits
-  // of deviation 4, 32 heads x 131072 at p = 0.99999 107 -> 30 us of top-p, 256 x 262144 at p = 0.9999 285 -> 90.  At
-  // p = 0.99999 there, 316 -> 221: the row's sample is too small to place the grid, and some of the lists still overflow.)
+  // Margin: roundings of the weights (2^-19 of a bucket's edge) and of these sums, with much to spare; what the exact
+  // masses, whole multiples of 2^-40, drop of each score, or of one beyond their reach (here in units of 2^-19); what lies
+  // beyond the last bucket's edge.  (5e-5 of the whole mass whatever p is is more than p = 0.99999 leaves out: every score
+  // below the threshold was then undecided, and peaked rows, whose tail is most of their scores, overflowed their lists;
+  // without the second term some lists miss the threshold.  Logits of deviation 4, 32 heads x 131072 at p = 0.99999 and
+  // 0.999999: 107 -> 30 and 32 us of top-p, 256 x 262144 at p = 0.9999 and 0.99999: 285 -> 86 and 316 -> 90, 219 without
+  // the second term.)
   const float left = 1.f - p;
-  const float eps = fminf(5e-5f, 1e-3f * left) * Z + __shfl(mb[BPL - 1], 63, 64);
+  const float eps = fminf(5e-5f, 1e-3f * left) * Z + (float)N * 0x1p-20f + __shfl(mb[BPL - 1], 63, 64);
   int b0 = WH_NB, b1 = WH_NB;
   if (p < 0.5f) {
     const float t0 = p * Z - eps, t1 = p * Z + eps;
@@ -222,9 +224,10 @@ __device__ __forceinline__ void wide_range(const unsigned long long* gh, WhGrid 
 // (A launch of its own: in the prologue of every wide_emit workgroup this made that kernel 81 us instead of 52 + this one's 4.8.)
 __global__ __launch_bounds__(64) void wide_decide_kernel(WideArgs a) {
   const int bh = blockIdx.x, lane = threadIdx.x;
+  const int N = wide_count(a, bh / a.Hq, bh) * TW_PAGE;
   const float m = tw_key_to_float(wide_headmax(a.headmax, bh, lane));   // (no valid score: a NaN, nothing takes part)
   float d_hi = 0.f, d_lo = HP_REACH;
-  wide_range(a.ghist + (long long)bh * WH_NB, a.hgrid[bh], m, a.p, lane, &d_hi, &d_lo);
+  wide_range(a.ghist + (long long)bh * WH_NB, a.hgrid[bh], m, a.p, N, lane, &d_hi, &d_lo);
   if (lane == 0) a.range[bh] = make_float4(m, d_hi, d_lo, 0.f);
 }
 

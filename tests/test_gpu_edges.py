@@ -137,14 +137,15 @@ def test_long_rows_of_equal_keys_are_searched_quickly():
     assert equal < 3 * plain and few < 3 * plain, (plain, equal, few)
 
 
-def test_long_peaked_rows_with_p_near_one_list_few_scores():
-    """Logits of deviation 4, p = 0.99999: what is left out is a hundred-thousandth of the mass but most of the scores.
-    The scores that the histogram leaves undecided must still fit the list (a row searched again takes several times the
-    whole of top-p otherwise)."""
+@pytest.mark.parametrize("p", [0.99999, 0.999999])
+def test_long_peaked_rows_with_p_near_one_list_few_scores(p):
+    """Logits of deviation 4 and p near 1: what is left out is next to none of the mass - of the size of what the exact masses
+    (multiples of 2^-40) drop of every score - but most of the scores.  The scores that the histogram leaves undecided
+    must still fit the list and hold the threshold (a row searched again takes several times the whole of top-p)."""
     T = _T()
-    n, Hkv = 65536, 2
+    n, Hkv = 65536, 8
     keys = lambda g: 4 * torch.randn(n, Hkv, 128, device="cuda", generator=g)
-    plain, near = _prune_us(T, keys, 1, n, (8, Hkv), 0.95), _prune_us(T, keys, 1, n, (8, Hkv), 0.99999)
+    plain, near = _prune_us(T, keys, 1, n, (64, Hkv), 0.95), _prune_us(T, keys, 1, n, (64, Hkv), p)
     assert near < 1.4 * plain, (plain, near)
 
 
