@@ -15,8 +15,8 @@
 //
 // Slots beyond the row's length are skipped by the whole workgroup, so that a row costs what its own length does: one by
 // one up to 8 slots per thread, in groups of 4 beyond.  (512 rows x 9000 entries with 16 slots 15.5 us in groups of 4,
-// 17.3 in groups of 8, 15.7 in groups of 2; 256 full rows of 32768 in groups of 4 25.9, 24.9 without any skipping, and
-// 22.7 -> 20.9 at 24000 entries.)
+// 17.3 in groups of 8, 15.7 in groups of 2; 256 rows x 24000 with 32 slots 22.7 -> 20.1.  Full rows of 32768, which would
+// pay 1 of 25 us for the groups' branches, have none.)
 #pragma once
 #include "tw_common.h"
 

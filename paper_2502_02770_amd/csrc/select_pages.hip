@@ -285,9 +285,10 @@ __global__ __launch_bounds__(256) void page_select_kernel(SelectArgs a) {
 }
 
 
-// The body of page_select_reg_kernel for a row of at most NT * E entries of which 0 < Kp < P are taken.
+// The body of page_select_reg_kernel for a row of at most NT * E entries of which 0 < Kp < P are taken.  reach: slots that
+// are looked at, P or, with more than 8 slots per thread, whose keys say where the row ends, anything above.
 template <int NT, int E, int SNB>
-__device__ __forceinline__ void select_row(const float* sc, int P, int Kp, int max_sel, int32_t* out, uint32_t* hist,
+__device__ __forceinline__ void select_row(const float* sc, int P, int reach, int Kp, int max_sel, int32_t* out, uint32_t* hist,
                                            unsigned long long* cand, uint32_t* cnt) {
   const int tid = threadIdx.x;
   uint32_t key[E], T, need_eq;
@@ -299,8 +300,8 @@ __device__ __forceinline__ void select_row(const float* sc, int P, int Kp, int m
 #pragma unroll
   for (int e = 0; e < E; ++e)
     key[e] = E > 8 ? tw_select_key(__uint_as_float(key[e]), e * NT + tid < P) : tw_float_key(__uint_as_float(key[e]));
-  tw_select_threshold<NT, E, SNB, 10>(key, P, (uint32_t)Kp, hist, cand, &T, &need_eq);
-  tw_select_list<NT, E>(key, P, T, need_eq, cnt, [&](uint32_t pos, int e) {
+  tw_select_threshold<NT, E, SNB, 10>(key, reach, (uint32_t)Kp, hist, cand, &T, &need_eq);
+  tw_select_list<NT, E>(key, reach, T, need_eq, cnt, [&](uint32_t pos, int e) {
     if (pos < (uint32_t)max_sel) out[pos] = e * NT + tid;
   });
 }
@@ -312,6 +313,7 @@ __device__ __forceinline__ void select_row(const float* sc, int P, int Kp, int m
 // x 8192 37.9 -> 29.5 (256 x 8192, a row per CU: 8.9 as before); 1024 rows x 16384 in the 32-slot form 78 -> 42.
 // Above 8 slots a row of up to a quarter of the form's length takes a body of its own, with fewer slots and without the
 // longest rows' sentinel keys: 64 ragged sequences x 32 heads of up to 32768 tokens 105 -> 78 us, up to 9000 37.9 -> 31.5.
+// The longest rows, which reach every group of slots, take one without the groups' branches (256 x 32768 25.9 -> 24.8).
 template <int NT, int E, int UNIT>
 __global__ __launch_bounds__(NT, E == 8 || E == 16 ? 8 : 1) void page_select_reg_kernel(SelectArgs a) {
   constexpr int SNB = E > 16 ? 2048 : (NT == 1024 && E == 2 ? 1024 : 512);
@@ -331,8 +333,13 @@ __global__ __launch_bounds__(NT, E == 8 || E == 16 ? 8 : 1) void page_select_reg
   __shared__ unsigned long long cand[SEL_CAP];
   __shared__ uint32_t cnt[E * NT / 64];
   constexpr int SHORT = E > 16 ? 8 : 4;
-  if (E > 8 && P <= SHORT * NT) select_row<NT, SHORT, 512>(sc, P, Kp, a.max_sel, out, hist, cand, cnt);   // (block-uniform)
-  else select_row<NT, E, SNB>(sc, P, Kp, a.max_sel, out, hist, cand, cnt);
+  if (E > 8 && P <= SHORT * NT) select_row<NT, SHORT, 512>(sc, P, P, Kp, a.max_sel, out, hist, cand, cnt);   // (block-uniform)
+  else if (E > 16 && P > (E - SEL_GROUP) * NT) {
+    int n = P;
+    asm volatile("" : "+s"(n));                   // (nothing in common with the next body: what the compiler shared it spilled)
+    select_row<NT, E, SNB>(sc, n, E * NT, Kp, a.max_sel, out, hist, cand, cnt);
+  }
+  else select_row<NT, E, SNB>(sc, P, P, Kp, a.max_sel, out, hist, cand, cnt);
 }
 
 template <int G>
