@@ -185,16 +185,21 @@ def percentiles(t):
 
 def decode_balance(T, cache, union_count, union_stride):
     """How evenly the flattened attention work list spreads over the persistent grid: the kernel's own rule
-    (shortest chunk of {c0, 2 c0, 4 c0} that leaves a workgroup at most `ipw` items; workgroup w takes items
-    w, w + grid, ...) applied to the list lengths read back from the device."""
+    (chunk length of twilight_prof.h; workgroup w takes items w, w + grid, ...) applied to the list lengths read back from the device."""
     grid, c0, ipw = T.twilight_decode_plan(cache.kv, T.TW_WS_DECODE, False)
     cnt = [min(int(c), union_stride) for c in union_count.cpu().tolist()]
-    chunk = c0
-    for c in (c0, 2 * c0):
-        if sum(-(-n // c) for n in cnt) > ipw * grid and 2 * c <= 512:
-            chunk = 2 * c
-        else:
+    total, lists = sum(cnt), len(cnt)
+    wgs = min(grid, lists * -(-union_stride // c0))
+    best = None
+    for r in range(1 + lists // wgs, 1 + lists // wgs + ipw):
+        c = max(c0, (total // (wgs * r - lists // 2) + 64) // 64 * 64)
+        if best is None or r * (c + 64) < best[0]:
+            best = (r * (c + 64), c, r)
+    _, chunk, rounds = best
+    for _ in range(3):
+        if sum(-(-n // chunk) for n in cnt) <= rounds * wgs:
             break
+        chunk += (chunk // 32 + 64) // 64 * 64
     items = []
     for n in cnt:
         items += [min(chunk, n - t0) for t0 in range(0, n, chunk)]

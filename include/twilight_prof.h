@@ -56,8 +56,13 @@ const char* twilight_kernel_name(int kernel_id);
  * Launch shape of the attention kernel for a cache shape (host only; only
  * kv's shape fields are read): the persistent grid before it is cut to the
  * number of work items, the shortest chunk of list entries per work item
- * (dense != 0: the all-tokens sweep), and the number of items per workgroup
- * beyond which the kernel doubles the chunk (up to 4 x chunk0, at most 512).
+ * (dense != 0: the all-tokens sweep), and how many numbers of items per
+ * workgroup the kernel weighs against each other.  With W workgroups, T list
+ * entries in N lists and r0 = 1 + N / W, for r = r0 .. r0 + items_per_wg - 1:
+ * c = T / (W * r - N / 2) rounded up to a multiple of 64 (more than T / ...,
+ * at least chunk0); the r with the least r * (c + 64) gives the chunk, made
+ * longer by steps of 1/32 (at least 64) up to three times while the lists
+ * still have more than r * W chunks.
  * which = TW_WS_DECODE or TW_WS_DECODE_PER_HEAD.  For reports on how evenly
  * ragged lists spread over the workgroups (Section 4.2, load balancing).
  */

@@ -4,15 +4,12 @@
 // group's union, the group-wise variable-length form; Section 4.2 load balancing: the
 // (sequence, KV head) lists are flattened into equal-sized work items).
 //
-// Work item = (group, chunk of `chunk` consecutive list entries).  A
-// persistent grid walks the items with a fixed stride; the item -> (group,
-// chunk) map is a prefix sum over the groups' chunk counts that every
-// workgroup rebuilds in LDS from the device-side list lengths, so no host
-// round trip and no extra launch is needed.  Inside an item 16 lanes own one
-// token row (a 16-byte load of K and of V each, 8 dims), the G query heads
-// of the group share every loaded row, and each 16-lane row keeps its own
-// online-softmax state; states are merged by log-sum-exp, first inside the
-// workgroup, then across items by the combine kernel.
+// Work item = (list, chunk of `chunk` consecutive list entries).  Every wave reads the lists' lengths, derives the
+// chunk length that gives each workgroup of the grid the same number of rows (decode_chunk) and finds its
+// workgroup's item by a prefix sum over its lanes, so no host round trip and no extra launch is needed.  Inside an
+// item the four waves walk their rows without meeting: 16 lanes own one token row (a 16-byte load of K and of V each,
+// 8 dims), the G query heads of the group share every loaded row, and each wave keeps its own online-softmax state;
+// the states are merged by log-sum-exp, first the workgroup's, then those of a list's items by the combine kernel.
 //
 // The same kernel serves the per-head variant (the head-wise form of Appendix
 // B.2): one list per query head, G = 1, list l reads KV head l / group size.
@@ -25,8 +22,9 @@ namespace {
 constexpr float kLog2eRsqrtD = 0x1.0527dcp-3f;   // fp32(log2(e) / sqrt(128))
 constexpr float kLn2 = 0x1.62e43p-1f;
 constexpr float kNegBig = -1.0e30f;              // finite stand-in for -inf in running maxima
-constexpr int DEC_MAX_CHUNK = 512;
-constexpr unsigned DEC_ITEMS_PER_WG = 3;         // measured: 64-entry items at 1.2 per workgroup, 128 at 2.5, 256 at 2 were the best choices
+constexpr unsigned DEC_MAX_ROUNDS = 3;           // items per workgroup that decode_chunk weighs against each other
+constexpr unsigned DEC_UNIT = 64;                // entries of a step of the four waves
+constexpr unsigned DEC_ITEM_ROWS = 64;           // rows that an item's set-up and merge are worth
 
 struct DecodeArgs {
   const uint4* q;             // bf16 [b][Hq][16 x uint4]
@@ -40,15 +38,17 @@ struct DecodeArgs {
   float* lse;                 // or nullptr
   int32_t* ws_prefix;         // [NG + 1]
   float2* ws_ml;              // [items][G]
-  float4* ws_acc;             // [items][G][32 x float4]
-  int Hq, Hkv, max_pages, union_stride, NG, chunk;
-  int fix_chunk;              // tuning: use `chunk` as given
+  float2* ws_acc;             // [items][G][64 x float2]
+  int Hq, Hkv, max_pages, union_stride, NG;
+  int chunk0;                 // shortest chunk
   int LH, kv_div;             // lists per sequence (Hkv, or Hq with one list per query head); list l reads KV head l / kv_div
   long long pool_pages;
 };
 
 __device__ __forceinline__ float tw_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+template <int K>
+__device__ __forceinline__ int tw_row_bcast_i(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x150 + K, 0xF, 0xF, false); }
 // row_newbcast:k - lane k of each row of 16 to all lanes of the row
 template <int K>
 __device__ __forceinline__ float tw_row_bcast(float v) {
@@ -56,6 +56,7 @@ __device__ __forceinline__ float tw_row_bcast(float v) {
 }
 #define TW_DPP_ROR4 0x124
 #define TW_DPP_ROR8 0x128
+#define TW_DPP_ROR12 0x12C
 
 typedef __bf16 tw_bf16x2 __attribute__((ext_vector_type(2)));
 // a.lo * b.lo + a.hi * b.hi + c on bf16 pairs (v_dot2c_f32_bf16)
@@ -63,295 +64,372 @@ __device__ __forceinline__ float tw_dot2_bf16(uint32_t a, uint32_t b, float c) {
   return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(tw_bf16x2, a), __builtin_bit_cast(tw_bf16x2, b), c, false);
 }
 
+// v_permlane16_swap / v_permlane32_swap: x and y exchange odd with even rows of 16 lanes, or upper with lower halves
+__device__ __forceinline__ void tw_swap16(float& x, float& y) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  x = __uint_as_float(r[0]); y = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void tw_swap32(float& x, float& y) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  x = __uint_as_float(r[0]); y = __uint_as_float(r[1]);
+}
+// over the wave's four rows of 16 lanes, every lane gets the result
+__device__ __forceinline__ float tw_rows_max(float x) {
+  float y = x;
+  tw_swap16(x, y); x = fmaxf(x, y); y = x;
+  tw_swap32(x, y);
+  return fmaxf(x, y);
+}
+__device__ __forceinline__ float tw_rows_sum(float x) {
+  float y = x;
+  tw_swap16(x, y); x += y; y = x;
+  tw_swap32(x, y);
+  return x + y;
+}
+
+// Chunk length for T list entries in NG lists on W workgroups: r items per workgroup, with the r whose rows and items'
+// fixed cost are least; a list's last chunk is taken to be half full.  The workgroups then end together.  (Chunks of 64,
+// 128 or 256 entries, whichever left at most three items to a workgroup, had 1230 items on 1024 workgroups at 8 x 32768
+// tokens: 12.6 us against 11.8.  Chunks of any multiple of 16 entries leave a wave's last step partly empty: 1.7 us more
+// with one query head per KV head, whose rows need the fewest instructions.)
+__device__ __forceinline__ uint32_t decode_chunk(uint32_t T, uint32_t NG, uint32_t W, uint32_t chunk0, uint32_t* rounds) {
+  uint32_t best = 0xFFFFFFFFu, chunk = chunk0;
+  const uint32_t r0 = 1u + NG / W;                 // (every list is an item)
+  *rounds = r0;
+#pragma unroll
+  for (uint32_t k = 0; k < DEC_MAX_ROUNDS; ++k) {
+    uint32_t c = (T / (W * (r0 + k) - NG / 2u) + DEC_UNIT) & ~(DEC_UNIT - 1u);
+    c = c < chunk0 ? chunk0 : c;
+    const uint32_t cost = (r0 + k) * (c + DEC_ITEM_ROWS);
+    if (cost < best) { best = cost; chunk = c; *rounds = r0 + k; }
+  }
+  return chunk;
+}
+// more than that many items after all (lists whose last chunks are emptier)
+__device__ __forceinline__ uint32_t decode_longer(uint32_t chunk) { return chunk + (((chunk >> 5) + DEC_UNIT) & ~(DEC_UNIT - 1u)); }
+
+// What bounds it: few and short lists the chain length -> list entry -> page table -> K/V row -> merge, so every wave
+// makes the item map and looks its rows up by itself and the only barrier of an item is the merge's (1 x 4096 tokens 5.9 ->
+// 4.7 us, 4 x 16384 8.6 -> 7.3; with the map, the rows and the running maxima passed around the workgroup through LDS
+// it took four and one more per 64 rows).  Long ones HBM, as long as loads keep going out: with a step's rows waited for,
+// used and only then followed by the next step's, dense attention over 8 x 32768 tokens read 5.6 TB/s, now 6.2 (192 -> 173
+// us), and 32 x 32768 gathered rows take 30.5 instead of 31.8.  Three workgroups per CU with four query heads per KV head:
+// the registers of four (128) do not hold the addresses of the rows asked for ahead.
 template <int G>
-__global__ __launch_bounds__(256, G == 4 ? 4 : 1) void sparse_decode_kernel(DecodeArgs a) {
-  constexpr int R = (G + 3) / 4;                 // score values a lane ends up owning per sub-block
-  constexpr int HB = G < 4 ? G : 4;              // heads merged through LDS at a time
+__global__ __launch_bounds__(256, G == 8 ? 2 : (G == 4 ? 3 : 4)) void sparse_decode_kernel(DecodeArgs a) {
+  constexpr int R = (G + 3) / 4;                 // score values a lane ends up owning per step
   extern __shared__ int32_t prefix[];            // [NG + 1]
   __shared__ uint32_t wsum[16];
-  __shared__ uint32_t red3[3][4];
-  __shared__ int32_t rows[DEC_MAX_CHUNK];
-  __shared__ float smax[2][4][8];                // [buffer][wave][head]
-  __shared__ float4 macc[16][HB][32];            // per 16-lane row: accumulators of HB heads
-  __shared__ float ml_s[16][8];                  // per row: softmax denominators
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, seg = tid & 15, rg = tid >> 4;
+  __shared__ float2 macc[4][G][64];              // the waves' accumulators ...
+  __shared__ float2 ml_s[4][G];                  // ... and their (maximum, denominator)
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), seg = tid & 15, row = lane >> 4;
   const bool dense = a.union_idx == nullptr;
   const bool b3 = seg & 8, b2 = seg & 4, b1 = seg & 2, b0 = seg & 1;
-  const int my_t = seg >> 2, my_hc = seg & 3;
+  const int my_t = seg >> 2;
   TW_STAMP(0);
+  const int most = dense ? a.max_pages * TW_PAGE : a.union_stride;      // longest list
+  auto length = [&](int gi) -> uint32_t {
+    const int v = (dense ? a.seq_lens : a.union_count)[dense ? gi / a.LH : gi];
+    return (uint32_t)(v < 0 ? 0 : (v > most ? most : v));
+  };
 
-  // ---- chunk length: the shortest of {c0, 2c0, 4c0} (<= 512) that leaves a workgroup at most
-  //      DEC_ITEMS_PER_WG items, so that short lists are spread over all workgroups (whose phases then
-  //      interleave) and long ones amortise the per-item set-up and merge
-  uint32_t n0 = 0, n1 = 0, n2 = 0;
-  const int c0 = a.chunk;
-  for (int gi = tid; gi < a.NG; gi += 256) {
-    int cnt;
-    if (dense) { cnt = a.seq_lens[gi / a.LH]; if (cnt > a.max_pages * TW_PAGE) cnt = a.max_pages * TW_PAGE; }
-    else { cnt = a.union_count[gi]; if (cnt > a.union_stride) cnt = a.union_stride; }
-    if (cnt < 0) cnt = 0;
-    n0 += (cnt + c0 - 1) / c0; n1 += (cnt + 2 * c0 - 1) / (2 * c0); n2 += (cnt + 4 * c0 - 1) / (4 * c0);
-  }
-  n0 = tw_wave_scan_u32(n0); n1 = tw_wave_scan_u32(n1); n2 = tw_wave_scan_u32(n2);
-  if (lane == 63) { red3[0][wave] = n0; red3[1][wave] = n1; red3[2][wave] = n2; }
-  __syncthreads();
-  n0 = red3[0][0] + red3[0][1] + red3[0][2] + red3[0][3];
-  n1 = red3[1][0] + red3[1][1] + red3[1][2] + red3[1][3];
-  int chunk = c0;
-  if (!a.fix_chunk && n0 > DEC_ITEMS_PER_WG * gridDim.x && 2 * c0 <= DEC_MAX_CHUNK) {
-    chunk = 2 * c0;
-    if (n1 > DEC_ITEMS_PER_WG * gridDim.x && 4 * c0 <= DEC_MAX_CHUNK) chunk = 4 * c0;
-  }
-
-  // ---- item map: exclusive prefix of per-group chunk counts
-  uint32_t run = 0;
-  for (int base = 0; base < a.NG; base += 256) {
-    const int gi = base + tid;
-    uint32_t c = 0;
-    if (gi < a.NG) {
-      int cnt;
-      if (dense) { cnt = a.seq_lens[gi / a.LH]; if (cnt > a.max_pages * TW_PAGE) cnt = a.max_pages * TW_PAGE; }
-      else { cnt = a.union_count[gi]; if (cnt > a.union_stride) cnt = a.union_stride; }
-      if (cnt < 0) cnt = 0;
-      c = (uint32_t)((cnt + chunk - 1) / chunk);
-    }
-    uint32_t total;
-    const uint32_t incl = tw_block_scan_u32(c, wsum, &total);
-    if (gi < a.NG) prefix[gi] = (int32_t)(run + incl - c);
-    run += total;
-  }
-  if (tid == 0) prefix[a.NG] = (int32_t)run;
-  __syncthreads();
-  const int total_items = (int)run;
-  TW_STAMP(1);
-  if (blockIdx.x == 0)
-    for (int i = tid; i <= a.NG; i += 256) a.ws_prefix[i] = prefix[i];
-
+  // ---- chunk length, item map (exclusive prefix of the lists' chunk counts) and this workgroup's first item
+  const uint32_t W = gridDim.x;
+  uint32_t chunk, rounds;
+  int total_items, item = blockIdx.x, gi = 0, ck = 0, nchunks = 0;
+  if (a.NG <= 64) {                               // block-uniform: lane l of every wave holds list l, no barrier
+    const uint32_t c = lane < a.NG ? length(lane) : 0u;
+    chunk = decode_chunk((uint32_t)__builtin_amdgcn_readlane((int)tw_wave_scan_u32(c), 63), (uint32_t)a.NG, W, (uint32_t)a.chunk0, &rounds);
+    uint32_t n = 0, incl = 0;
 #pragma unroll 1
-  for (int item = blockIdx.x; item < total_items; item += gridDim.x) {
-    // group of this item: last gi with prefix[gi] <= item
+    for (int trial = 0; trial < 4; ++trial) {
+      if (trial) chunk = decode_longer(chunk);
+      n = (c + chunk - 1u) / chunk;
+      incl = tw_wave_scan_u32(n);
+      total_items = __builtin_amdgcn_readlane((int)incl, 63);
+      if ((uint32_t)total_items <= rounds * W) break;
+    }
+    // the last lane that begins at or before the item (lanes of empty lists begin where the next one does)
+    gi = __popcll(__ballot(incl - n <= (uint32_t)item)) - 1;
+    ck = item - __builtin_amdgcn_readlane((int)(incl - n), gi);
+    nchunks = __builtin_amdgcn_readlane((int)n, gi);
+    if (wave == 0 && lane < a.NG) prefix[lane] = (int32_t)(incl - n);
+    if (tid == 0) prefix[a.NG] = total_items;
+  } else {                                        // thread t: the lists t * K ..
+    const int K = (a.NG + 255) >> 8, i0 = tid * K;
+    const uint32_t c0 = i0 < a.NG ? length(i0) : 0u, c1 = K > 1 && i0 + 1 < a.NG ? length(i0 + 1) : 0u;   // (the others are read again)
+    auto len_of = [&](int k) -> uint32_t { return k == 0 ? c0 : (k == 1 ? c1 : (i0 + k < a.NG ? length(i0 + k) : 0u)); };
+    uint32_t T = 0, total;
+    for (int k = 0; k < K; ++k) T += len_of(k);
+    (void)tw_block_scan_u32(T, wsum, &total);
+    chunk = decode_chunk(total, (uint32_t)a.NG, W, (uint32_t)a.chunk0, &rounds);
+    uint32_t n = 0, incl = 0;
+#pragma unroll 1
+    for (int trial = 0; trial < 4; ++trial) {
+      if (trial) chunk = decode_longer(chunk);
+      n = 0;
+      for (int k = 0; k < K; ++k) n += (len_of(k) + chunk - 1u) / chunk;
+      incl = tw_block_scan_u32(n, wsum, &total);
+      if (total <= rounds * W) break;             // (block-uniform)
+    }
+    n = incl - n;
+    for (int k = 0; k < K; ++k) {
+      if (i0 + k < a.NG) prefix[i0 + k] = (int32_t)n;
+      n += (len_of(k) + chunk - 1u) / chunk;
+    }
+    total_items = (int)total;
+    if (tid == 0) prefix[a.NG] = total_items;
+    __syncthreads();
+  }
+  if (blockIdx.x == 0) {                          // for the combine kernel
+    __syncthreads();
+    for (int i = tid; i <= a.NG; i += 256) a.ws_prefix[i] = prefix[i];
+  }
+  TW_STAMP(1);
+  // list of an item: the last one with prefix <= item (empty lists begin where the next one does)
+  auto find = [&]() {
     int lo = 0, hi = a.NG;
     while (hi - lo > 1) { const int mid = (lo + hi) >> 1; if (prefix[mid] <= item) lo = mid; else hi = mid; }
-    const int gi = lo, b = gi / a.LH, l = gi % a.LH, g = l / a.kv_div;   // list l of sequence b, KV head g
-    const int ck = item - prefix[gi];
-    const int nchunks = prefix[gi + 1] - prefix[gi];
-    // Everything the row staging reads that does not depend on another load goes out together: the sequence's
-    // length, the list's length, this thread's (at most two) list entries - any entry of the list's row may be read,
-    // those at or beyond the count are ignored below - and q.  The page-table entries then depend on the list
-    // entries, the K/V rows on those: three round trips to memory per item instead of five.
-    const int t0 = ck * chunk;
-    // (dense: the same loads from an address that is always valid, their values unused - no branch between the loads)
+    gi = lo; ck = item - prefix[lo]; nchunks = prefix[lo + 1] - prefix[lo];
+  };
+  if (item >= total_items) return;
+  if (a.NG > 64) find();
+
+#pragma unroll 1
+  for (;;) {
+    const int b = gi / a.LH, l = gi % a.LH, g = l / a.kv_div;   // list l of sequence b, KV head g
+    // Everything the row lookup reads that does not depend on another load goes out together: the sequence's length,
+    // the list's length, this lane's list entry - any entry of the list's row may be read, those at or beyond the
+    // count are ignored below - and q.  The page-table entries then depend on the list entries, the K/V rows on those:
+    // three round trips to memory per item.
+    // In a row of 16 lanes, lane seg looks up entry (seg % 4) * 16 + wave * 4 + row of a step's 64.
+    const int t0 = ck * (int)chunk;
+    const int e0 = (seg & 3) * 16 + wave * 4 + row;
     int nseq = a.seq_lens[b];                    // list entries at or beyond the sequence's end are ignored
     const int32_t* const cnt_p = dense ? a.seq_lens + b : a.union_count + gi;
     int cnt = *cnt_p;
-    int tokv[DEC_MAX_CHUNK / 256];
-#pragma unroll
-    for (int j = 0; j < DEC_MAX_CHUNK / 256; ++j) {
-      const int e = t0 + j * 256 + tid;
-      const int32_t* const tp = dense ? a.seq_lens + b
-                                      : a.union_idx + (long long)gi * a.union_stride + (e < a.union_stride ? e : a.union_stride - 1);
-      const int tv = *tp;
-      tokv[j] = dense ? e : tv;
-    }
+    // (dense: the same loads from an address that is always valid, their values unused)
+    const int32_t* const list = dense ? a.seq_lens + b : a.union_idx + (long long)gi * a.union_stride;
+    const int list_end = dense ? 0 : a.union_stride - 1;
+    auto entry = [&](int e) -> int { return list[t0 + e < list_end ? t0 + e : list_end]; };
+    int raw0 = entry(e0), raw1 = entry(e0 + 64), raw2 = entry(e0 + 128);
     // q of the G heads, this lane's 8 dims, as loaded (bf16 pairs)
     uint4 q[G];
 #pragma unroll
     for (int h = 0; h < G; ++h) q[h] = a.q[((long long)(b * a.Hq + l * G + h)) * 16 + seg];
-    // (keeps the list-entry loads up here: the compiler would otherwise move them down to their first use, behind
-    //  the wait for the two lengths)
-#pragma unroll
-    for (int j = 0; j < DEC_MAX_CHUNK / 256; ++j) asm volatile("" : "+v"(tokv[j]));
+    // (keeps the list-entry loads up here: the compiler would otherwise move them down to their first use, behind the
+    //  wait for the two lengths)
+    asm volatile("" : "+v"(raw0), "+v"(raw1), "+v"(raw2));
     if (nseq > a.max_pages * TW_PAGE) nseq = a.max_pages * TW_PAGE;
     if (dense) cnt = nseq;
     else if (cnt > a.union_stride) cnt = a.union_stride;
-    const int len = cnt - t0 < chunk ? cnt - t0 : chunk;
-
-    // ---- stage the chunk's token rows (pool row ids) in LDS
-#pragma unroll
-    for (int j = 0; j < DEC_MAX_CHUNK / 256; ++j) {
-      const int i = j * 256 + tid;
-      if (i < chunk) {                            // block-uniform per j
-        int r = -1;
-        const int tok = tokv[j];
-        if (i < len && tok >= 0 && tok < nseq) {
-          const long long pp = a.page_table[(long long)b * a.max_pages + (tok >> 4)];
-          if (pp >= 0 && pp < a.pool_pages) r = (int)((pp * a.Hkv + g) * TW_PAGE + (tok & 15));
-        }
-        rows[i] = r;
-      }
-    }
+    nseq = __builtin_amdgcn_readfirstlane(nseq);
+    const int len = __builtin_amdgcn_readfirstlane(cnt - t0 < (int)chunk ? cnt - t0 : (int)chunk);   // (scalar: what depends on it branches without lane masks)
+    // entry e, read as r -> token (-1: does not count) -> the place of its page -> pool row.  (In three steps, so that
+    // a load is not waited for before its value is needed.)
+    auto token = [&](int r, int e) -> int {
+      const int tk = dense ? t0 + e : r;
+      return e < len && tk >= 0 && tk < nseq ? tk : -1;
+    };
+    auto page = [&](int tk) -> int { return a.page_table[(long long)b * a.max_pages + (tk < 0 ? 0 : tk >> 4)]; };
+    auto pool_row = [&](int tk, int pp) -> int {
+      return tk >= 0 && pp >= 0 && pp < a.pool_pages ? (pp * a.Hkv + g) * TW_PAGE + (tk & 15) : -1;
+    };
+    int tok = token(raw0, e0), pp = page(tok);
+    const int tok1 = token(raw1, e0 + 64), pp1 = page(tok1);
+    int ids = pool_row(tok, pp);
+    tok = tok1; pp = pp1;
     if (item == 0) TW_STAMP(2);
-    float acc[G][8], M[G], Mmine[R], lacc[R];
+    float acc[G][8], M[R], lacc[R];
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-      M[h] = kNegBig;
+    for (int h = 0; h < G; ++h)
 #pragma unroll
       for (int i = 0; i < 8; ++i) acc[h][i] = 0.f;
-    }
 #pragma unroll
-    for (int r = 0; r < R; ++r) { Mmine[r] = kNegBig; lacc[r] = 0.f; }
-    __syncthreads();
+    for (int r = 0; r < R; ++r) { M[r] = kNegBig; lacc[r] = 0.f; }
 
-    const int nsub = (len + 63) >> 6;
-#pragma unroll 1
-    for (int sb = 0; sb < nsub; ++sb) {
+    // this wave's steps: those with at least one entry.  The next step's K rows are asked for as soon as this step's dot
+    // products are done, its V rows behind this step's sums, so that a wave's loads keep going out while it computes -
+    // in the registers of the rows just used.  (Unconditional loads, or a wait for one step's rows would take in the
+    // next one's: entries that do not count all read the same 16 bytes and are masked.)
+    const int steps = (len - wave * 4 + 63) >> 6;
+    if (steps > 0) {                              // (wave-uniform)
+      const int own = __builtin_amdgcn_readfirstlane(ids), spare = own < 0 ? 0 : own;
       uint4 kr[4], vr[4];
-      int rr[4];
+      int rr[4];                                 // pool rows of the step whose K rows were asked for last, -1: none
+      auto spread = [&]() {
+        rr[0] = tw_row_bcast_i<0>(ids); rr[1] = tw_row_bcast_i<1>(ids); rr[2] = tw_row_bcast_i<2>(ids); rr[3] = tw_row_bcast_i<3>(ids);
+      };
+      auto ask = [&](uint4 (&x)[4], const uint4* pool) {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        rr[t] = rows[sb * 64 + t * 16 + rg];
-        if (rr[t] >= 0) {
-          kr[t] = tw_ld_stream(a.k_pool + (long long)rr[t] * 16 + seg);
-          vr[t] = tw_ld_stream(a.v_pool + (long long)rr[t] * 16 + seg);
-        } else {
-          kr[t] = make_uint4(0, 0, 0, 0);
-          vr[t] = make_uint4(0, 0, 0, 0);
-        }
-      }
+        for (int t = 0; t < 4; ++t) x[t] = tw_ld_stream(pool + (rr[t] < 0 ? (long long)spare * 16 : (long long)rr[t] * 16 + seg));
+      };
+      spread();
+      ask(kr, a.k_pool);
+      ask(vr, a.v_pool);
 #ifdef TW_PHASE_TIMING
-      if (item == 0 && sb == 0) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); TW_STAMP(3); }
+      if (item == 0) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); TW_STAMP(3); }
 #endif
-      // ---- partial dot products of this lane's 8 dims: val[t*4 + h%4][h/4]
-      float val[16][R];
+#pragma unroll 1
+      for (int st = 0; st < steps; ++st) {
+        const bool valid = (my_t == 0 ? rr[0] : (my_t == 1 ? rr[1] : (my_t == 2 ? rr[2] : rr[3]))) >= 0;
+        const bool void0 = rr[0] < 0, void1 = rr[1] < 0, void2 = rr[2] < 0, void3 = rr[3] < 0;
+        // the pool rows of step st + 1, whose page-table entries were asked for a step ago; those of step st + 2 and the
+        // list entries of step st + 3 are asked for
+        ids = pool_row(tok, pp);
+        tok = token(raw2, (st + 2) * 64 + e0);
+        pp = page(tok);
+        raw2 = entry((st + 3) * 64 + e0);
+        // ---- partial dot products of this lane's 8 dims: val[t*4 + h%4][h/4]
+        float val[16][R];
 #pragma unroll
-      for (int c = 0; c < 16; ++c)
+        for (int c = 0; c < 16; ++c)
 #pragma unroll
-        for (int r = 0; r < R; ++r) val[c][r] = 0.f;
+          for (int r = 0; r < R; ++r) val[c][r] = 0.f;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
+        for (int t = 0; t < 4; ++t) {
 #pragma unroll
-        for (int h = 0; h < G; ++h)              // bf16 pair dot products, fp32 accumulation
-          val[t * 4 + (h & 3)][h >> 2] =
-              tw_dot2_bf16(q[h].w, kr[t].w, tw_dot2_bf16(q[h].z, kr[t].z, tw_dot2_bf16(q[h].y, kr[t].y, tw_dot2_bf16(q[h].x, kr[t].x, 0.f))));
-      }
-      // ---- transposing reduction over the 16 lanes of the row: each step a lane keeps the half
-      //      of the values selected by one bit of its lane id and adds the partner's copy of it;
-      //      lane c ends with the full sum of value c
-      float s_mine[R];
+          for (int h = 0; h < G; ++h)              // bf16 pair dot products, fp32 accumulation
+            val[t * 4 + (h & 3)][h >> 2] =
+                tw_dot2_bf16(q[h].w, kr[t].w, tw_dot2_bf16(q[h].z, kr[t].z, tw_dot2_bf16(q[h].y, kr[t].y, tw_dot2_bf16(q[h].x, kr[t].x, 0.f))));
+        }
+        spread();
+        __builtin_amdgcn_sched_barrier(0);
+        ask(kr, a.k_pool);
+        __builtin_amdgcn_sched_barrier(0);
+        // ---- transposing reduction over the 16 lanes of the row: each step a lane keeps the half
+        //      of the values selected by one bit of its lane id and adds the partner's copy of it;
+        //      lane c ends with the full sum of value c
+        float s_mine[R];
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        float a8[8], a4[4], a2[2];
+        for (int r = 0; r < R; ++r) {
+          float a8[8], a4[4], a2[2];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const float keep = b3 ? val[j + 8][r] : val[j][r], send = b3 ? val[j][r] : val[j + 8][r];
-          a8[j] = keep + tw_dpp_f<TW_DPP_MIRROR>(send);
+          for (int j = 0; j < 8; ++j) {
+            const float keep = b3 ? val[j + 8][r] : val[j][r], send = b3 ? val[j][r] : val[j + 8][r];
+            a8[j] = keep + tw_dpp_f<TW_DPP_MIRROR>(send);
+          }
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float keep = b2 ? a8[j + 4] : a8[j], send = b2 ? a8[j] : a8[j + 4];
+            a4[j] = keep + tw_dpp_f<TW_DPP_HALF_MIRROR>(send);
+          }
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const float keep = b1 ? a4[j + 2] : a4[j], send = b1 ? a4[j] : a4[j + 2];
+            a2[j] = keep + tw_dpp_f<TW_DPP_XOR2>(send);
+          }
+          const float keep = b0 ? a2[1] : a2[0], send = b0 ? a2[0] : a2[1];
+          s_mine[r] = (keep + tw_dpp_f<TW_DPP_XOR1>(send)) * kLog2eRsqrtD;   // base-2 logit
+        }
+        // ---- running maximum per head of this lane, over the wave's 16 entries
+        float sc[R], p_mine[R];
+        bool moved = false;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          float mx = valid ? s_mine[r] : -__builtin_inff();
+          mx = fmaxf(mx, tw_dpp_f<TW_DPP_ROR4>(mx));
+          mx = fmaxf(mx, tw_dpp_f<TW_DPP_ROR8>(mx));
+          const float mn = fmaxf(M[r], tw_rows_max(mx));
+          sc[r] = tw_exp2(M[r] - mn);
+          moved |= M[r] != mn;
+          M[r] = mn;
+          p_mine[r] = valid ? tw_exp2(s_mine[r] - mn) : 0.f;
+          lacc[r] = __builtin_fmaf(lacc[r], sc[r], p_mine[r]);
+        }
+        if (st > 0 && __any(moved)) {              // (wave-uniform)
+#pragma unroll
+          for (int h = 0; h < G; ++h) {
+            const float f = (h & 3) == 0 ? tw_row_bcast<0>(sc[h >> 2]) : (h & 3) == 1 ? tw_row_bcast<1>(sc[h >> 2])
+                          : (h & 3) == 2 ? tw_row_bcast<2>(sc[h >> 2]) : tw_row_bcast<3>(sc[h >> 2]);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[h][i] *= f;
+          }
+        }
+        // ---- every lane needs the 4 x G weights of its row: broadcast them lane by lane
+        float pb[16][R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          pb[0][r] = tw_row_bcast<0>(p_mine[r]);   pb[1][r] = tw_row_bcast<1>(p_mine[r]);
+          pb[2][r] = tw_row_bcast<2>(p_mine[r]);   pb[3][r] = tw_row_bcast<3>(p_mine[r]);
+          pb[4][r] = tw_row_bcast<4>(p_mine[r]);   pb[5][r] = tw_row_bcast<5>(p_mine[r]);
+          pb[6][r] = tw_row_bcast<6>(p_mine[r]);   pb[7][r] = tw_row_bcast<7>(p_mine[r]);
+          pb[8][r] = tw_row_bcast<8>(p_mine[r]);   pb[9][r] = tw_row_bcast<9>(p_mine[r]);
+          pb[10][r] = tw_row_bcast<10>(p_mine[r]); pb[11][r] = tw_row_bcast<11>(p_mine[r]);
+          pb[12][r] = tw_row_bcast<12>(p_mine[r]); pb[13][r] = tw_row_bcast<13>(p_mine[r]);
+          pb[14][r] = tw_row_bcast<14>(p_mine[r]); pb[15][r] = tw_row_bcast<15>(p_mine[r]);
+        }
+        if (__any(void0 | void1 | void2 | void3)) {              // (wave-uniform; the weights are 0, the row need not be finite)
+          if (void0) vr[0] = make_uint4(0, 0, 0, 0);
+          if (void1) vr[1] = make_uint4(0, 0, 0, 0);
+          if (void2) vr[2] = make_uint4(0, 0, 0, 0);
+          if (void3) vr[3] = make_uint4(0, 0, 0, 0);
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float keep = b2 ? a8[j + 4] : a8[j], send = b2 ? a8[j] : a8[j + 4];
-          a4[j] = keep + tw_dpp_f<TW_DPP_HALF_MIRROR>(send);
+        for (int t = 0; t < 4; ++t) {
+          float vf[8];
+          tw_unpack8(vr[t], vf);
+#pragma unroll
+          for (int h = 0; h < G; ++h)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[h][i] = __builtin_fmaf(pb[t * 4 + (h & 3)][h >> 2], vf[i], acc[h][i]);
         }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const float keep = b1 ? a4[j + 2] : a4[j], send = b1 ? a4[j] : a4[j + 2];
-          a2[j] = keep + tw_dpp_f<TW_DPP_XOR2>(send);
-        }
-        const float keep = b0 ? a2[1] : a2[0], send = b0 ? a2[0] : a2[1];
-        s_mine[r] = (keep + tw_dpp_f<TW_DPP_XOR1>(send)) * kLog2eRsqrtD;   // base-2 logit
-      }
-      const bool valid = rows[sb * 64 + my_t * 16 + rg] >= 0;
-      // ---- maximum per head over the sub-block: over t inside the row, the 4 rows of the wave, the 4 waves
-      const int buf = sb & 1;
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        float mx = valid ? s_mine[r] : -__builtin_inff();
-        mx = fmaxf(mx, tw_dpp_f<TW_DPP_ROR4>(mx));
-        mx = fmaxf(mx, tw_dpp_f<TW_DPP_ROR8>(mx));
-        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        if (lane < 4 && r * 4 + lane < G) smax[buf][wave][r * 4 + lane] = mx;
-      }
-      __syncthreads();
-      float sc[G];
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        const float ms = fmaxf(fmaxf(smax[buf][0][h], smax[buf][1][h]), fmaxf(smax[buf][2][h], smax[buf][3][h]));
-        const float mn = fmaxf(M[h], ms);
-        sc[h] = tw_exp2(M[h] - mn);
-        M[h] = mn;
-      }
-      float p_mine[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int hh = (r * 4 + my_hc) < G ? (r * 4 + my_hc) : 0;
-        const float ms = fmaxf(fmaxf(smax[buf][0][hh], smax[buf][1][hh]), fmaxf(smax[buf][2][hh], smax[buf][3][hh]));
-        const float mn = fmaxf(Mmine[r], ms);
-        lacc[r] *= tw_exp2(Mmine[r] - mn);
-        Mmine[r] = mn;
-        p_mine[r] = valid ? tw_exp2(s_mine[r] - mn) : 0.f;
-        lacc[r] += p_mine[r];
-      }
-      if (sb > 0) {
-#pragma unroll
-        for (int h = 0; h < G; ++h)
-#pragma unroll
-          for (int i = 0; i < 8; ++i) acc[h][i] *= sc[h];
-      }
-      // ---- every lane needs the 4 x G weights of its row: broadcast them lane by lane
-      float pb[16][R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        pb[0][r] = tw_row_bcast<0>(p_mine[r]);   pb[1][r] = tw_row_bcast<1>(p_mine[r]);
-        pb[2][r] = tw_row_bcast<2>(p_mine[r]);   pb[3][r] = tw_row_bcast<3>(p_mine[r]);
-        pb[4][r] = tw_row_bcast<4>(p_mine[r]);   pb[5][r] = tw_row_bcast<5>(p_mine[r]);
-        pb[6][r] = tw_row_bcast<6>(p_mine[r]);   pb[7][r] = tw_row_bcast<7>(p_mine[r]);
-        pb[8][r] = tw_row_bcast<8>(p_mine[r]);   pb[9][r] = tw_row_bcast<9>(p_mine[r]);
-        pb[10][r] = tw_row_bcast<10>(p_mine[r]); pb[11][r] = tw_row_bcast<11>(p_mine[r]);
-        pb[12][r] = tw_row_bcast<12>(p_mine[r]); pb[13][r] = tw_row_bcast<13>(p_mine[r]);
-        pb[14][r] = tw_row_bcast<14>(p_mine[r]); pb[15][r] = tw_row_bcast<15>(p_mine[r]);
-      }
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        float vf[8];
-        tw_unpack8(vr[t], vf);
-#pragma unroll
-        for (int h = 0; h < G; ++h)
-#pragma unroll
-          for (int i = 0; i < 8; ++i) acc[h][i] = __builtin_fmaf(pb[t * 4 + (h & 3)][h >> 2], vf[i], acc[h][i]);
+        __builtin_amdgcn_sched_barrier(0);
+        ask(vr, a.v_pool);
       }
     }
 
     if (item == 0) TW_STAMP(4);
-    // ---- merge the 16 rows of the workgroup: all share the running maxima, so plain sums
+    // ---- sum over the wave's four rows, transposing: a lane ends with the two dims d = 2 * (seg * 4 + row), d + 1
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { tw_swap32(acc[h][i], acc[h][i + 4]); acc[h][i] += acc[h][i + 4]; }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) { tw_swap16(acc[h][i], acc[h][i + 2]); acc[h][i] += acc[h][i + 2]; }
+      macc[wave][h][seg * 4 + row] = make_float2(acc[h][0], acc[h][1]);
+    }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       float lr = lacc[r];
       lr += tw_dpp_f<TW_DPP_ROR4>(lr);
       lr += tw_dpp_f<TW_DPP_ROR8>(lr);
-      if (seg < 4 && r * 4 + seg < G) ml_s[rg][r * 4 + seg] = lr;
+      lr = tw_rows_sum(lr);
+      if (lane < 4 && r * 4 + lane < G) ml_s[wave][r * 4 + lane] = make_float2(M[r], lr);
     }
+    __syncthreads();
+    // ---- the four waves: thread -> 2 adjacent output dims of one head
 #pragma unroll
-    for (int hb = 0; hb < G; hb += HB) {
+    for (int c2 = tid; c2 < G * 64; c2 += 256) {
+      const int h = c2 >> 6, d2 = c2 & 63;
+      float2 ml[4];
 #pragma unroll
-      for (int h = 0; h < HB; ++h) {
-        macc[rg][h][seg * 2] = make_float4(acc[hb + h][0], acc[hb + h][1], acc[hb + h][2], acc[hb + h][3]);
-        macc[rg][h][seg * 2 + 1] = make_float4(acc[hb + h][4], acc[hb + h][5], acc[hb + h][6], acc[hb + h][7]);
+      for (int w = 0; w < 4; ++w) ml[w] = ml_s[w][h];
+      const float mx = fmaxf(fmaxf(ml[0].x, ml[1].x), fmaxf(ml[2].x, ml[3].x));
+      float ox = 0.f, oy = 0.f, L = 0.f;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const float f = tw_exp2(ml[w].x - mx);
+        const float2 v = macc[w][h][d2];
+        ox = __builtin_fmaf(v.x, f, ox); oy = __builtin_fmaf(v.y, f, oy);
+        L = __builtin_fmaf(ml[w].y, f, L);
       }
-      __syncthreads();
-      // thread -> 2 adjacent output dims of one head
-      const float2* m2 = (const float2*)&macc[0][0][0];
-      for (int c2 = tid; c2 < HB * 64; c2 += 256) {
-        const int h = hb + c2 / 64, d2 = c2 % 64;
-        float ox = 0.f, oy = 0.f, L = 0.f;
-#pragma unroll
-        for (int w = 0; w < 16; ++w) {
-          const float2 v = m2[w * (HB * 64) + c2];
-          ox += v.x; oy += v.y;
-          L += ml_s[w][h];
-        }
+      if (nchunks == 1) {                       // the item is the whole list: final result
         const int qh = b * a.Hq + l * G + h;
-        if (nchunks == 1) {                     // the item is the whole list: final result
-          const float inv = L > 0.f ? 1.0f / L : 0.f;
-          ((uint32_t*)a.out)[(long long)qh * 64 + d2] = tw_f32_to_bf16(ox * inv) | (tw_f32_to_bf16(oy * inv) << 16);
-          if (a.lse && d2 == 0) a.lse[qh] = L > 0.f ? (M[h >= G ? 0 : h] + __log2f(L)) * kLn2 : -__builtin_inff();
-        } else {
-          ((float2*)a.ws_acc)[((long long)item * G + h) * 64 + d2] = make_float2(ox, oy);
-          if (d2 == 0) a.ws_ml[(long long)item * G + h] = make_float2(M[h >= G ? 0 : h], L);
-        }
+        const float inv = L > 0.f ? 1.0f / L : 0.f;
+        ((uint32_t*)a.out)[(long long)qh * 64 + d2] = tw_f32_to_bf16(ox * inv) | (tw_f32_to_bf16(oy * inv) << 16);
+        if (a.lse && d2 == 0) a.lse[qh] = L > 0.f ? (mx + __log2f(L)) * kLn2 : -__builtin_inff();
+      } else {
+        const long long at = (long long)item * G + h;
+        a.ws_acc[at * 64 + d2] = make_float2(ox, oy);
+        if (d2 == 0) a.ws_ml[at] = make_float2(mx, L);
       }
-      __syncthreads();                          // macc / rows / ml_s are reused
     }
     if (item == 0) TW_STAMP(5);
+    item += (int)gridDim.x;
+    if (item >= total_items) break;
+    __syncthreads();                            // macc / ml_s are reused
+    find();
   }
   if (blockIdx.x == 0) TW_STAMP(6);
 }
@@ -484,7 +562,7 @@ static int decode_impl(const twilight_kv_t* kv, const void* q, const int32_t* co
   hipStream_t s = (hipStream_t)stream;
 
   const long long max_items = tw_decode_max_items(d, dense, stride) / d.Hkv * LH;
-  const size_t prefix_bytes = (((size_t)(NG + 1) * 4) + 255) & ~(size_t)255;
+  const size_t head_bytes = (((size_t)(NG + 1) * 4) + 255) & ~(size_t)255;
   const size_t ml_bytes = (((size_t)max_items * Gk * 8) + 255) & ~(size_t)255;
   DecodeArgs a;
   a.q = (const uint4*)q; a.k_pool = (const uint4*)kv->k_pool; a.v_pool = (const uint4*)kv->v_pool;
@@ -492,16 +570,11 @@ static int decode_impl(const twilight_kv_t* kv, const void* q, const int32_t* co
   a.union_count = dense ? nullptr : count; a.union_idx = idx;
   a.out = (uint4*)out; a.lse = lse;
   a.ws_prefix = (int32_t*)ws;
-  a.ws_ml = (float2*)((char*)ws + prefix_bytes);
-  a.ws_acc = (float4*)((char*)ws + prefix_bytes + ml_bytes);
+  a.ws_ml = (float2*)((char*)ws + head_bytes);
+  a.ws_acc = (float2*)((char*)ws + head_bytes + ml_bytes);
   a.Hq = d.Hq; a.Hkv = d.Hkv; a.max_pages = d.max_pages; a.union_stride = stride;
   a.LH = LH; a.kv_div = per_head ? d.G : 1;
-  a.NG = NG; a.chunk = tw_decode_chunk(dense); a.pool_pages = d.pool_pages;
-  a.fix_chunk = 0;
-#ifdef TW_TUNING
-  static const bool fixed_c0 = getenv("TW_DECODE_C0") != nullptr;   // chunk length as given
-  a.fix_chunk = (!dense && fixed_c0) ? 1 : 0;
-#endif
+  a.NG = NG; a.chunk0 = tw_decode_chunk(dense); a.pool_pages = d.pool_pages;
   const size_t lds = (size_t)(NG + 1) * 4;
   tw_prof_before(TW_K_DECODE, s);
   switch (Gk) {
@@ -544,7 +617,7 @@ extern "C" int twilight_decode_plan(const twilight_kv_t* kv, int which, int32_t 
   }
   *grid = tw_num_cus() * occ;
   *chunk0 = tw_decode_chunk(dense != 0);
-  *items_per_wg = (int32_t)DEC_ITEMS_PER_WG;
+  *items_per_wg = (int32_t)DEC_MAX_ROUNDS;
   return TW_OK;
 }
 

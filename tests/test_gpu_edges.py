@@ -5,7 +5,7 @@ import torch
 
 from oracle import twilight_oracle as O
 from workloads import synth
-from tests.gpu_util import build_cache, u16
+from tests.gpu_util import assert_attention, build_cache, u16
 
 pytestmark = pytest.mark.gpu
 
@@ -169,3 +169,48 @@ def test_query_rows_at_an_odd_element():
             torch.cuda.synchronize()
             got.append([t.clone() for t in (st.kept_count, st.union_count, st.union_idx)])
         assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
+@pytest.mark.parametrize("batch", [3, 20], ids=["few_lists", "many_lists"])
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_attention_over_lists_at_the_edges_of_a_step(G, batch):
+    """Lists of every remainder of a wave's 16 and a workgroup's 64 rows, empty ones, one that is cut into many chunks,
+    entries that do not count in between; the pool's first page holds NaN and belongs to no sequence.  Few lists: the
+    item map in registers, many: through LDS.  Definition 3.1 in float64, the bars of the other attention tests."""
+    T = _T()
+    H, n = 4, 5000
+    rng = np.random.default_rng(100 * G + batch)
+    P = (n + 15) // 16
+    table = 1 + torch.arange(batch * P, dtype=torch.int32).view(batch, P)
+    cache = T.PagedKV(G * H, H, table, torch.full((batch,), n), 1 + batch * P)
+    k = torch.from_numpy(rng.standard_normal((batch * n, H, 128)).astype(np.float32)).to(torch.bfloat16)
+    v = torch.from_numpy(rng.standard_normal((batch * n, H, 128)).astype(np.float32)).to(torch.bfloat16)
+    cache.fill(k.cuda(), v.cuda(), [b * n for b in range(batch + 1)])
+    cache.k_pool[0] = float("nan")
+    cache.v_pool[0] = float("nan")
+    q = torch.from_numpy(rng.standard_normal((batch, G * H, 128)).astype(np.float32)).to(torch.bfloat16)
+    lens = ([0, 1, 2, 3, 4, 5, 15, 16, 17, 31, 48, 63, 64, 65, 66, 68, 80, 127, 128, 129, 191, 192, 193, 255, 257, 600] * 4)[:batch * H]
+    lens[1], lens[3] = 4900, 1300
+    stride = 4928
+    idx = np.zeros((batch * H, stride), np.int32)
+    for l, c in enumerate(lens):
+        idx[l, :c] = np.sort(rng.permutation(n)[:c])
+        if c > 4:                                         # entries that do not count: in front, at the end, anywhere
+            idx[l, [0, c - 1, int(rng.integers(1, c - 1))]] = [-1, n, 1 << 30]
+    st = T.DecodeStep(cache, max_sel=1, union_stride=stride)
+    st.union_count.copy_(torch.tensor(lens, dtype=torch.int32))
+    st.union_idx.copy_(torch.from_numpy(idx))
+    st.attend(q.cuda())
+    torch.cuda.synchronize()
+    out, lse = st.out.cpu().float().numpy(), st.lse.cpu().numpy()
+    for l, c in enumerate(lens):
+        b, g = divmod(l, H)
+        ids = idx[l, :c][(idx[l, :c] >= 0) & (idx[l, :c] < n)]
+        kb, vb = synth.bits(k.view(batch, n, H, 128)[b, :, g]), synth.bits(v.view(batch, n, H, 128)[b, :, g])
+        for h in range(g * G, g * G + G):
+            if not len(ids):
+                assert not out[b, h].any() and np.isneginf(lse[b, h])
+                continue
+            ref, rl = O.attention(synth.bits(q[b, h]), kb, vb, ids)
+            assert_attention(out[b, h].astype(np.float64), ref)
+            assert abs(lse[b, h] - rl) <= 1e-3 * max(1.0, abs(rl))
