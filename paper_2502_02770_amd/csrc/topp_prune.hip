@@ -730,8 +730,13 @@ constexpr int HP_USTAGE = 4096;               // union lists up to this length l
 // FUSE == 2: the page list too is made here, from the bounds of all pages (the selection of page_select_reg_kernel).
 // BITS: width of the quantised copy's codes (FUSE == 2; else 4).
 template <int NT, int EPT, int G, bool TOK = false, int FUSE = 0, int BITS = 4>
-__global__ __launch_bounds__(NT, NT <= 512 ? (EPT > 8 ? 4 : 6) : 1) void topp_head_kernel(HeadArgs a) {
+__global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FUSE != 2 && EPT > 8 ? 4 : 6))) void topp_head_kernel(HeadArgs a) {
   constexpr int NW = NT / 64;
+  // The workgroups that are there to share a CU (many heads, 8 or 16 candidates per thread, scored here) leave the scores
+  // in LDS, where every phase reads them again, instead of holding them in registers: three of 16 candidates per thread
+  // fit a CU instead of two, four of 8 instead of three, and one's scoring streams while the others wait at barriers
+  // (64 ragged sequences x 32 heads 116.6 -> 104.0 us, 32 x 32 heads x 4096 candidates 56.2 -> 53.7).
+  constexpr bool INLDS = FUSE == 2 && NT <= 512 && EPT > 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int b_ = blockIdx.y, h_ = blockIdx.x;
   if (FUSE && a.remap) {
@@ -751,7 +756,9 @@ __global__ __launch_bounds__(NT, NT <= 512 ? (EPT > 8 ? 4 : 6) : 1) void topp_he
   // FUSE == 2 with few candidates: the row of pages is bounded too (the launch's rule), and LDS is sized for that
   constexpr bool SMALL = FUSE == 2 && NT <= 512 && EPT == 4;
   constexpr int SEL_E = SMALL ? 4 : 4096 / NT;
-  constexpr int BWORDS = SMALL ? SEL_E * NT * TW_PAGE / 32 : HP_BITMAP_WORDS, USTAGE = SMALL ? 4 * NT : HP_USTAGE;
+  constexpr int BWORDS = SMALL ? SEL_E * NT * TW_PAGE / 32 : (FUSE == 2 ? 4096 * TW_PAGE / 32 : HP_BITMAP_WORDS);
+  constexpr int USTAGE = SMALL ? 4 * NT : HP_USTAGE;
+  constexpr int AREA = FUSE == 2 ? (NT * EPT > USTAGE ? NT * EPT : USTAGE) : USTAGE;
   constexpr bool SEL_EARLY = FUSE == 2 && NT >= 1024;
   const int n = a.seq_lens[b];
   const int budget_b = FUSE == 2 ? a.budget[b] : 0;
@@ -795,11 +802,12 @@ __global__ __launch_bounds__(NT, NT <= 512 ? (EPT > 8 ? 4 : 6) : 1) void topp_he
   __shared__ uint32_t histC[HP_NB];
   __shared__ unsigned long long cand_mass[HP_CAP];
   __shared__ uint32_t cand_key[HP_CAP];
-  // position bitmap, then the union list on its way out; before that the selection's 64-bit candidates and the staged
-  // scores, read 16 bytes at a time
-  __shared__ __align__(16) uint32_t big_s[BWORDS + USTAGE];
-  static_assert(__alignof__(big_s) >= 16, "read as float4 and as 64-bit words");
-  uint32_t* const bitmap = big_s;                            // (FUSE: first the scores on their way to their owners)
+  // position bitmap, then the union list on its way out; before that the selection's arrays and the scores, read 16
+  // bytes at a time: behind the bitmap (FUSE == 2, whose bitmap covers 4096 pages) or from its first word
+  __shared__ __align__(16) uint32_t big_s[BWORDS + AREA];
+  static_assert(__alignof__(big_s) >= 16 && BWORDS % 4 == 0, "read as float4 and as 64-bit words");
+  uint32_t* const bitmap = big_s;
+  uint32_t* const area = FUSE == 2 ? big_s + BWORDS : big_s;
   int32_t* const ustage = (int32_t*)(big_s + BWORDS);
   __shared__ unsigned long long tail_s[NW];
   __shared__ uint32_t ws32[16];
@@ -811,9 +819,9 @@ __global__ __launch_bounds__(NT, NT <= 512 ? (EPT > 8 ? 4 : 6) : 1) void topp_he
   if (FUSE == 2) {
     constexpr int SNB = 512;
     static_assert(SNB % 2 == 0, "the candidates behind the histogram are 64-bit words");
-    uint32_t* const hist = big_s;                   // the selection's arrays lie in big_s
-    unsigned long long* const cand = (unsigned long long*)(big_s + SNB);
-    uint32_t* const cnt = big_s + SNB + 2 * SEL_CAP;
+    uint32_t* const hist = area;                    // the selection's arrays lie there
+    unsigned long long* const cand = (unsigned long long*)(area + SNB);
+    uint32_t* const cnt = area + SNB + 2 * SEL_CAP;
     int32_t* const out = a.sel_pages_w + (long long)bh * a.max_sel;
     const int32_t* const ptab = a.page_table + (long long)b * a.max_pages;
     if (tid == 0) a.sel_count_w[bh] = count;
@@ -842,26 +850,27 @@ __global__ __launch_bounds__(NT, NT <= 512 ? (EPT > 8 ? 4 : 6) : 1) void topp_he
         }
       });
     }
-    __syncthreads();                                // list complete; big_s free for the scores
+    __syncthreads();                                // list complete; the area free for the scores
     TW_STAMP(35);
   }
 
   // ---- scores into registers; logical pages of the owned slots
   // (loads do not wait for the list length: anything inside the row is readable, slots at or
   //  beyond N are masked afterwards)
-  constexpr int NPG = TOK ? EPT : (EPT + 15) / 16; // pages a thread's slots fall into (a part of one if EPT < 16); TOK: one token per slot
-  float s[EPT];
+  constexpr int NPG = TOK ? EPT : INLDS ? EPT / 4 : (EPT + 15) / 16; // pages a thread's slots fall into (a part of one if EPT < 16); TOK: one token per slot
+  constexpr int SN = INLDS ? 1 : EPT;
+  float s[SN];
   int pg[NPG];
+  float* const sc_s = (float*)area;
   if (FUSE) {
-    static_assert(NT * EPT <= BWORDS + USTAGE, "scores of a row must fit the staging array");
-    float* const sc_s = (float*)big_s;
+    static_assert(NT * EPT <= (FUSE == 2 ? AREA : BWORDS + USTAGE), "scores of a row must fit the staging array");
     __shared__ int qi_s[1][32];
     __shared__ float qred[4];
     __shared__ float qc_s[1];
     // this wave's share of the list: lane k holds its k-th page
     static_assert(EPT * 64 / TW_PAGE <= 64, "a wave's share of the longest list has a lane for every page");
-    constexpr int UF = (NT >= 1024 || EPT == 4 ? 8 : 4) / (BITS == 8 ? 2 : 1);   // pages in flight per wave (register budget)
-    const int ppw = ((count + NW - 1) / NW + UF - 1) & ~(UF - 1);
+    constexpr int UF = (NT >= 1024 || EPT == 4 || (INLDS && EPT == 16) ? 8 : 4) / (BITS == 8 ? 2 : 1);   // pages in flight per wave (register budget)
+    const int ppw = INLDS ? (count + NW - 1) / NW : ((count + NW - 1) / NW + UF - 1) / UF * UF;
     const int first = __builtin_amdgcn_readfirstlane(wave) * ppw;   // (scalar: the loop below is wave-uniform)
     int my_lp = -1, my_pool = -1;
     if (lane < ppw && first + lane < count) {
@@ -883,45 +892,72 @@ __global__ __launch_bounds__(NT, NT <= 512 ? (EPT > 8 ? 4 : 6) : 1) void topp_he
     }
     const float qsf = (float)qs, cc = qc_s[0];
     const int qs128 = BITS == 8 ? 128 * qs : 0;       // 8-bit codes enter the signed dot4 as code - 128
-#pragma unroll 1
-    for (int k0 = 0; k0 < npages; k0 += UF) {
-      // UF pages per round: all their loads first (unconditional: lanes past the wave's last page hold pool -1 and
-      // read pool page 0), then the arithmetic; every lane of a quad stores the token's score (same word), so the
-      // round has no branches and the loads stay together.  Slots past the list's end get -inf (inside the array:
-      // NW * ppw <= NT * EPT / 16 pages).
-      uint4 nib[UF][BITS == 8 ? 2 : 1];
-      uint32_t meta[UF];
-      int lpk[UF], plk[UF];
+    // UF pages in flight per wave.  Several workgroups to a CU: as a ring - a page's codes and (scale, zero) words are asked
+    // for in the registers of the page used last, so that loads keep going out while the wave computes (unconditional, or
+    // the wait for one page would take in the pages behind it: a page past the wave's last reads 16 bytes of the wave's
+    // first); 2 us of the two times above.  One workgroup to a CU, whose waves have a round or two each: in rounds, all of
+    // a round's loads first (8 x 32 heads x 256 pages 22.0 us, as a ring 23.9).  Lanes past the wave's last page hold pool
+    // -1, read pool page 0 in the rounds, and their scores are -inf (inside the array: NW * ppw <= NT * EPT / 16 pages).
+    uint4 nib[UF][BITS == 8 ? 2 : 1];
+    uint32_t meta[UF];
+    const int own = __builtin_amdgcn_readfirstlane(my_pool), spare = own >= 0 ? own : 0;
+    auto ask = [&](int kk, int k) {
+      const int pl = INLDS && k >= npages ? -1 : __builtin_amdgcn_readlane(my_pool, k & 63);   // (lanes past the last page hold -1)
+      const long long blk = ((long long)(pl >= 0 ? pl : (INLDS ? spare : 0)) * a.Hkv + g) * 64;
+      const int at = INLDS && pl < 0 ? 0 : lane;
+      tw_load_raw<BITS>(a.kq_pool, blk + at, nib[kk]);
+      meta[kk] = a.kq_meta[blk + at];
+    };
+    // every lane of a quad stores the token's score (same word)
+    auto use = [&](int kk, int k) {
+      const int lp = __builtin_amdgcn_readlane(my_lp, k & 63), pl = __builtin_amdgcn_readlane(my_pool, k & 63);
+      int u[8];
+      tw_unpack_codes<BITS>(nib[kk], u);
+      const bool valid = pl >= 0 && lp * TW_PAGE + (lane >> 2) < n;
+      const float T = tw_token_sum(meta[kk], tw_group_dot(qw, u, qs128), qsf);
+      sc_s[(first + k) * TW_PAGE + (lane >> 2)] = valid ? __fmul_rn(T, cc) : -__builtin_inff();
+    };
+    int k0 = 0;
+    if (INLDS) {
 #pragma unroll
-      for (int kk = 0; kk < UF; ++kk) {
-        lpk[kk] = __builtin_amdgcn_readlane(my_lp, (k0 + kk) & 63);
-        plk[kk] = __builtin_amdgcn_readlane(my_pool, (k0 + kk) & 63);
-        const long long blk = ((long long)(plk[kk] >= 0 ? plk[kk] : 0) * a.Hkv + g) * 64;
-        tw_load_raw<BITS>(a.kq_pool, blk + lane, nib[kk]);
-        meta[kk] = a.kq_meta[blk + lane];
+      for (int kk = 0; kk < UF; ++kk) ask(kk, kk);
+#pragma unroll 1
+      for (; k0 + UF < npages; k0 += UF) {
+#pragma unroll
+        for (int kk = 0; kk < UF; ++kk) {
+          use(kk, k0 + kk);
+          __builtin_amdgcn_sched_barrier(0);
+          ask(kk, k0 + UF + kk);
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
 #pragma unroll
-      for (int kk = 0; kk < UF; ++kk) {
-        int u[8];
-        tw_unpack_codes<BITS>(nib[kk], u);
-        const bool valid = plk[kk] >= 0 && lpk[kk] * TW_PAGE + (lane >> 2) < n;
-        const float T = tw_token_sum(meta[kk], tw_group_dot(qw, u, qs128), qsf);
-        sc_s[(first + k0 + kk) * TW_PAGE + (lane >> 2)] = valid ? __fmul_rn(T, cc) : -__builtin_inff();
+      for (int kk = 0; kk < UF; ++kk)
+        if (k0 + kk < npages) use(kk, k0 + kk);
+    } else {
+#pragma unroll 1
+      for (; k0 < npages; k0 += UF) {
+#pragma unroll
+        for (int kk = 0; kk < UF; ++kk) ask(kk, k0 + kk);
+#pragma unroll
+        for (int kk = 0; kk < UF; ++kk) use(kk, k0 + kk);
       }
     }
     __syncthreads();
+    if (!INLDS) {
 #pragma unroll
-    for (int v = 0; v < EPT / 4; ++v) {
-      const float4 x = *(const float4*)(sc_s + c0 + 4 * v);
-      s[4 * v] = x.x; s[4 * v + 1] = x.y; s[4 * v + 2] = x.z; s[4 * v + 3] = x.w;
+      for (int v = 0; v < EPT / 4; ++v) {
+        const float4 x = *(const float4*)(sc_s + c0 + 4 * v);
+        s[(4 * v) % SN] = x.x; s[(4 * v + 1) % SN] = x.y; s[(4 * v + 2) % SN] = x.z; s[(4 * v + 3) % SN] = x.w;
+      }
+      if (FUSE == 1) __syncthreads();              // the bitmap, cleared below, lies in the same words
     }
-    __syncthreads();                               // the bitmap, cleared below, lies in the same words
   } else
 #pragma unroll
   for (int v = 0; v < EPT / 4; ++v) {              // clamped, unconditional: all loads go out together
     const int cc = c0 + 4 * v < a.cand_stride ? c0 + 4 * v : a.cand_stride - 4;
     const float4 x = *(const float4*)(row + cc);
-    s[4 * v] = x.x; s[4 * v + 1] = x.y; s[4 * v + 2] = x.z; s[4 * v + 3] = x.w;
+    s[(4 * v) % SN] = x.x; s[(4 * v + 1) % SN] = x.y; s[(4 * v + 2) % SN] = x.z; s[(4 * v + 3) % SN] = x.w;
   }
   if (TOK) {
 #pragma unroll
@@ -933,19 +969,37 @@ __global__ __launch_bounds__(NT, NT <= 512 ? (EPT > 8 ? 4 : 6) : 1) void topp_he
   } else {
 #pragma unroll
     for (int v = 0; v < NPG; ++v) {
-      const int pi = (c0 >> 4) + v < a.max_sel ? (c0 >> 4) + v : a.max_sel - 1;
+      const int p0 = INLDS ? (v * 4 * NT + tid * 4) >> 4 : (c0 >> 4) + v, pi = p0 < a.max_sel ? p0 : a.max_sel - 1;
       pg[v] = FUSE == 2 ? pages_s[pi] : a.sel_pages[(long long)bh * a.max_sel + pi];
     }
   }
+  if (!INLDS) {
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) s[e] = (c0 + e < N) ? s[e] : -__builtin_inff();
+    for (int e = 0; e < EPT; ++e) s[e % SN] = (c0 + e < N) ? s[e % SN] : -__builtin_inff();
+  }
+  // f(e, score) for this thread's slots
+  auto each = [&](auto f) {
+    if constexpr (INLDS) {
+#pragma unroll
+      for (int v = 0; v < EPT / 4; ++v) {
+        const int at = v * 4 * NT + tid * 4;
+        const float4 x = *(const float4*)(sc_s + at);
+        f(4 * v, at < N ? x.x : -__builtin_inff());
+        f(4 * v + 1, at + 1 < N ? x.y : -__builtin_inff());
+        f(4 * v + 2, at + 2 < N ? x.z : -__builtin_inff());
+        f(4 * v + 3, at + 3 < N ? x.w : -__builtin_inff());
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) f(e, s[e % SN]);
+    }
+  };
   for (int i = tid; i < HP_NB; i += NT) { histM[i] = 0; histC[i] = 0; }
   for (int i = tid; i < nwords; i += NT) bitmap[i] = 0;
   if (tid == 0) { sh_n = 0; sh_kept = 0; }
 
-  float m = s[0];
-#pragma unroll
-  for (int e = 1; e < EPT; ++e) m = fmaxf(m, s[e]);
+  float m = -__builtin_inff();
+  each([&](int, float x) { m = fmaxf(m, x); });
   m = tw_wave_max_f(m);
   if (lane == 0) redf[wave] = m;
   __syncthreads();
@@ -967,12 +1021,9 @@ __global__ __launch_bounds__(NT, NT <= 512 ? (EPT > 8 ? 4 : 6) : 1) void topp_he
     constexpr bool RECOMP = NT <= 512 && EPT > 4;
     uint32_t rk[RECOMP ? 1 : EPT];
     float ef[RECOMP ? 1 : EPT];
-    if (!RECOMP) {
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) rk[RECOMP ? 0 : e] = hp_rank(m, s[e], &ef[RECOMP ? 0 : e]);
-    }
-    auto rank_of = [&](int e) -> uint32_t { return RECOMP ? hp_rank_only(m, s[e]) : rk[RECOMP ? 0 : e]; };
-    auto numer_of = [&](int e) -> float { return RECOMP ? hp_numer(m, s[e]) : ef[RECOMP ? 0 : e]; };
+    if (!RECOMP) each([&](int e, float x) { rk[RECOMP ? 0 : e] = hp_rank(m, x, &ef[RECOMP ? 0 : e]); });
+    auto rank_of = [&](int e, float x) -> uint32_t { return RECOMP ? hp_rank_only(m, x) : rk[RECOMP ? 0 : e]; };
+    auto numer_of = [&](int e, float x) -> float { return RECOMP ? hp_numer(m, x) : ef[RECOMP ? 0 : e]; };
     uint32_t rlo = 0, pop = 0;
     int shift = 16, pass = 0;
     unsigned long long A = 0, target = 0;
@@ -983,16 +1034,15 @@ __global__ __launch_bounds__(NT, NT <= 512 ? (EPT > 8 ? 4 : 6) : 1) void topp_he
         __syncthreads();
       }
       unsigned long long below = 0;                // mass past the end of the interval (pass 0 only)
-#pragma unroll
-      for (int e = 0; e < EPT; ++e) {
-        const uint32_t r = rank_of(e);
+      each([&](int e, float x) {
+        const uint32_t r = rank_of(e, x);
         if (r != HP_NONE && r >= rlo) {
           const uint32_t bk = (r - rlo) >> shift;
-          const unsigned long long w = hp_fix(numer_of(e));
+          const unsigned long long w = hp_fix(numer_of(e, x));
           if (bk < HP_NB) { atomicAdd(&histM[bk], w); atomicAdd(&histC[bk], 1u); }
           else below += w;
         }
-      }
+      });
       if (pass == 0) {
         below = tw_wave_scan_u64(below);
         if (lane == 63) tail_s[wave] = below;
@@ -1047,18 +1097,17 @@ __global__ __launch_bounds__(NT, NT <= 512 ? (EPT > 8 ? 4 : 6) : 1) void topp_he
     const uint32_t rhi = rlo + (1u << shift) - 1u;
     const bool small = pop <= HP_CAP;
     uint32_t kmin = 0xFFFFFFFFu;
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      const uint32_t r = rank_of(e);
+    each([&](int e, float x) {
+      const uint32_t r = rank_of(e, x);
       if (r != HP_NONE && r >= rlo && r <= rhi) {
-        const uint32_t k = tw_float_key(s[e]);
+        const uint32_t k = tw_float_key(x);
         kmin = k < kmin ? k : kmin;
         if (small) {
           const uint32_t at = atomicAdd(&sh_n, 1u);
-          if (at < HP_CAP) { cand_key[at] = k; cand_mass[at] = hp_fix(numer_of(e)); }
+          if (at < HP_CAP) { cand_key[at] = k; cand_mass[at] = hp_fix(numer_of(e, x)); }
         }
       }
-    }
+    });
     if (!small) {                                   // > HP_CAP scores within one rank: keep them all
       kmin = ~tw_wave_max_u32(~kmin);
       if (lane == 0) redf[wave] = __uint_as_float(kmin);
@@ -1094,21 +1143,20 @@ __global__ __launch_bounds__(NT, NT <= 512 ? (EPT > 8 ? 4 : 6) : 1) void topp_he
 
   // ---- kept flags, count, optional ascending list; bitmap over token positions
   uint32_t cnt = 0, keep = 0;
-#pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    const bool k = (c0 + e < N) && tw_float_key(s[e]) >= T;
+  each([&](int e, float x) {
+    const bool k = (INLDS ? (e >> 2) * 4 * NT + tid * 4 + (e & 3) : c0 + e) < N && tw_float_key(x) >= T;
     keep |= (k ? 1u : 0u) << e;
     cnt += k ? 1u : 0u;
-  }
+  });
   uint32_t pos = 0;
-  if (a.kept_idx) {                                // ordered positions need a scan over the block
+  if (INLDS || !a.kept_idx) {
+    const uint32_t wsumc = tw_wave_scan_u32(cnt);
+    if (lane == 63 && wsumc) atomicAdd(&sh_kept, wsumc);
+  } else {                                         // ordered positions need a scan over the block
     uint32_t total;
     const uint32_t incl = tw_block_scan_u32(cnt, ws32, &total);
     pos = incl - cnt;
     if (tid == 0) sh_kept = total;
-  } else {
-    const uint32_t wsumc = tw_wave_scan_u32(cnt);
-    if (lane == 63 && wsumc) atomicAdd(&sh_kept, wsumc);
   }
   if (TOK) {
     int32_t* out = a.kept_idx ? a.kept_idx + (long long)bh * a.kept_stride : nullptr;
@@ -1118,6 +1166,24 @@ __global__ __launch_bounds__(NT, NT <= 512 ? (EPT > 8 ? 4 : 6) : 1) void topp_he
         const int tok = pg[e % NPG];
         if (tok < BWORDS * 32) atomicOr(&bitmap[tok >> 5], 1u << (tok & 31));
         if (out) { if (pos < (uint32_t)a.kept_stride) out[pos] = tok; ++pos; }
+      }
+    }
+  } else if (INLDS) {
+    uint32_t run = 0;
+#pragma unroll
+    for (int v = 0; v < NPG; ++v) {
+      const uint32_t mask = (keep >> (4 * v)) & 15u;
+      const int tok0 = pg[v] * TW_PAGE + (tid * 4 & 15);
+      if (mask && tok0 + 3 < BWORDS * 32) atomicOr(&bitmap[tok0 >> 5], mask << (tok0 & 31));
+      if (a.kept_idx) {                             // ordered positions: the slots of v, of all threads, behind those of v - 1
+        uint32_t total;
+        const uint32_t c = __popc(mask), incl = tw_block_scan_u32(c, ws32, &total);
+        pos = run + incl - c;
+        int32_t* out = a.kept_idx + (long long)bh * a.kept_stride;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if ((mask >> e) & 1u) { if (pos < (uint32_t)a.kept_stride) out[pos] = tok0 + e; ++pos; }
+        run += total;
       }
     }
   } else
@@ -1439,8 +1505,9 @@ void launch_topp_one(const HeadArgs& f, int G, dim3 grid, hipStream_t s) {
 
 // Register-resident top-p over rows of at most 8192 candidates (cand_stride = row bound).
 //  - few heads: one 1024-thread workgroup per head (4 or 8 candidates per thread);
-//  - more heads than CUs and rows of at most 4096 candidates: 512-thread workgroups, two to a CU (a 1024-thread
-//    workgroup has a CU to itself at this register count: 8 x 32 x 4 = 1024 heads took 35.8 us that way, 22.9 us so);
+//  - more heads than CUs and rows of at most 4096 candidates: 512-thread workgroups, three or (selection and scores inside)
+//    four to a CU (a 1024-thread workgroup has a CU to itself at this register count: 8 x 32 x 4 = 1024 heads took 35.8 us
+//    that way, 22.9 us two to a CU);
 //  - rows of at most 2048 candidates (and, with the selection inside, at most 2048 pages): 512-thread workgroups with 4
 //    candidates per thread, whatever the number of heads.  The kernel is a chain of block barriers; half the waves make
 //    each shorter (32 heads x 1024 candidates 13.4 -> 10.8 us, 320 x 1136 15.6 -> 12.0), and with the LDS arrays sized
@@ -1448,11 +1515,11 @@ void launch_topp_one(const HeadArgs& f, int G, dim3 grid, hipStream_t s) {
 //    candidates of 512 pages 48.1 -> 30.6);
 //  - rows of at most 1024 candidates and 1024 pages with more heads than CUs: 256-thread workgroups (2048 heads x 256
 //    candidates 39.8 -> 23.9 us; 32 heads x 1024 candidates 10.8 -> 11.1, so few heads keep the 512 threads);
-//  - many heads with a bound above 4096 candidates, scoring inside: 512-thread workgroups with 16 candidates per thread,
-//    two to a CU, for all heads - one's scoring streams while the other is in its barriers (64 ragged sequences x 32
+//  - more heads than CUs (behind a selection launch: than twice the CUs) with a bound above 4096 candidates, scoring inside:
+//    512-thread workgroups with 16 candidates per thread, three (two) to a CU, for all heads - one's scoring streams while the others are in their barriers (64 ragged sequences x 32
 //    heads: 131.8 us as a 512-thread launch for the lists up to 4096 and a 1024-thread one, a workgroup per CU, for the
-//    longer ones -> 117.9; 32 x 32 heads x 8192 candidates 138.5 -> 111.7.  Dispatching the longest sequences first: no
-//    gain.);
+//    longer ones -> 117.9, three to a CU 104.0.  Dispatching the longest sequences first: no gain.  10 x 32 heads x 8192
+//    candidates 56 us with 1024 threads x 8, 53.7 so, 16 x 32 66 and 59.6; 8 x 32 34 and 40);
 //  - the same on stored scores (FUSE == 0): heads of at most 4096 candidates in a 512-thread launch of their own, the
 //    longer ones in the 1024-thread launch.
 // FUSE: the kernels score the candidates themselves (page lists).
@@ -1474,7 +1541,7 @@ int launch_topp(HeadArgs f, const TwDims& d, int cand_stride, hipStream_t s) {
   else if (cand_stride <= 2048 && (FUSE != 2 || d.max_pages <= 2048)) launch_topp_one<512, 4, TOK, FUSE, BITS>(f, d.G, grid, s);
   else if (cand_stride <= 4096 && heads > tw_num_cus()) launch_topp_one<512, 8, TOK, FUSE, BITS>(f, d.G, grid, s);
   else if (cand_stride <= 4096) launch_topp_one<1024, 4, TOK, FUSE, BITS>(f, d.G, grid, s);
-  else if (FUSE != 0 && heads > 2ll * tw_num_cus()) launch_topp_one<512, FUSE != 0 ? 16 : 8, TOK, FUSE, BITS>(f, d.G, grid, s);
+  else if (FUSE == 2 ? heads > tw_num_cus() : FUSE != 0 && heads > 2ll * tw_num_cus()) launch_topp_one<512, FUSE != 0 ? 16 : 8, TOK, FUSE, BITS>(f, d.G, grid, s);
   else launch_topp_one<1024, 8, TOK, FUSE, BITS>(f, d.G, grid, s);
   return tw_prof_after(s);
 }

@@ -69,6 +69,15 @@ def test_selection_of_up_to_16384_entries_runs_two_workgroups_per_cu(kernels, sl
     assert _fits(k, 2), k[".vgpr_count"]
 
 
+@pytest.mark.parametrize("bits", [2, 4, 8])
+@pytest.mark.parametrize("candidates,workgroups", [(8, 4), (16, 3)])
+def test_one_launch_pruner_of_many_heads_shares_the_cu(kernels, candidates, workgroups, bits):
+    for G in (1, 2, 4, 8):
+        k = kernels["topp_head_kernel<512, %d, %d, false, 2, %d>" % (candidates, G, bits)]
+        assert _fits(k, workgroups), k[".vgpr_count"]
+        assert k[".group_segment_fixed_size"] * workgroups <= 160 * 1024
+
+
 def test_the_selection_kernels_spill_no_vector_registers(kernels):
     spilled = {n: k[".vgpr_spill_count"] for n, k in kernels.items() if n.startswith("page_select")}
     assert len(spilled) == 14 and not any(spilled.values()), spilled
