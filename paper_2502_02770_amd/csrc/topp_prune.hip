@@ -1193,7 +1193,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
     const uint32_t mask = (keep >> (16 * v)) & ((1u << PB) - 1u);
     if (mask) {
       const int tok0 = pg[v] * TW_PAGE + (EPT < 16 ? (c0 & 15) : 0);
-      if (tok0 + 15 < BWORDS * 32) atomicOr(&bitmap[tok0 >> 5], mask << (tok0 & 31));
+      if (tok0 + PB - 1 < BWORDS * 32) atomicOr(&bitmap[tok0 >> 5], mask << (tok0 & 31));
       if (a.kept_idx) {
         int32_t* out = a.kept_idx + (long long)bh * a.kept_stride;
 #pragma unroll

@@ -214,3 +214,29 @@ def test_attention_over_lists_at_the_edges_of_a_step(G, batch):
             ref, rl = O.attention(synth.bits(q[b, h]), kb, vb, ids)
             assert_attention(out[b, h].astype(np.float64), ref)
             assert abs(lse[b, h] - rl) <= 1e-3 * max(1.0, abs(rl))
+
+
+@pytest.mark.parametrize("n,max_sel,seqs,separate", [(16384, 64, 36, False), (32768, 128, 2, False), (65536, 256, 2, False), (65536, 256, 32, False),
+                                                     (65536, 512, 32, False), (65536, 512, 36, False), (196608, 512, 1, True)])
+def test_kept_tokens_of_the_last_page_reach_the_union(n, max_sel, seqs, separate):
+    """Rows of pages that fill the kernel's position bitmap exactly: heavy tokens in all of the last page, which end up
+    kept, for every workgroup size; the union is that of the kept lists, the last token included."""
+    T = _T()
+    w = synth.make_workload("last", [n] + [600] * (seqs - 1), num_q_heads=8, num_kv_heads=2, budget=max_sel * 16, p=0.9999,
+                            heavy_frac=0.0, alpha_range=(0.0, 0.0), shuffle_pool=True, need_v=False, seed=96)
+    qh = w.q[0].float().view(2, 4, 128)
+    push = (qh / qh.norm(dim=-1, keepdim=True)).sum(dim=1) * 11.3
+    w.k[n - 16:n] = (w.k[n - 16:n].float() + push).to(torch.bfloat16)
+    cache = build_cache(w)
+    q, budget = w.q.to(cache.device), w.budget.to(cache.device)
+    st = T.DecodeStep(cache, max_sel=max_sel, with_kept_idx=True)
+    if separate:
+        st.select(q, budget)
+        st.prune(q, w.p)
+    else:
+        st.select_prune(None, None, None, q, budget, w.p)
+    torch.cuda.synchronize()
+    for g in range(2):
+        kept = np.unique(np.concatenate([st.kept_idx[0, h, :int(st.kept_count[0, h])].cpu().numpy() for h in range(4 * g, 4 * g + 4)]))
+        assert set(range(n - 16, n)) <= set(kept.tolist())
+        assert st.union_idx[g, :int(st.union_count[g])].cpu().numpy().tolist() == kept.tolist()
