@@ -69,9 +69,9 @@ __global__ __launch_bounds__(256) void page_score_kernel(ScoreArgs a) {
   if (P > a.max_pages) P = a.max_pages;
   // (the counters of a top-p launch that follows are cleared on the way out, after every load of the kernel: a store
   //  ahead of them would turn the scalar loads of the prologue into vector loads that wait for one another)
-  const bool clears = a.arrive && blockIdx.y == 0 && tid == 0;
+  const bool clears = a.arrive && blockIdx.y == 0 && tid <= G;      // the group's counter and one per head
   if (base >= P) {
-    if (clears) a.arrive[(b * a.Hkv + g) * TW_CTR] = 0;
+    if (clears) a.arrive[(b * a.Hkv + g) * TW_CTR + tid] = 0;
     return;
   }
 
@@ -197,7 +197,7 @@ __global__ __launch_bounds__(256) void page_score_kernel(ScoreArgs a) {
       }
     }
   }
-  if (clears) a.arrive[(b * a.Hkv + g) * TW_CTR] = 0;
+  if (clears) a.arrive[(b * a.Hkv + g) * TW_CTR + tid] = 0;
 }
 
 struct SelectArgs {
@@ -508,8 +508,8 @@ extern "C" int twilight_append_select(const twilight_kv_t* kv, const void* k_new
 }
 
 // Selector and pruner in one call (Section 4.1's pipeline up to the pruned index sets): page bounds (with the step's
-// new token appended on the way when k_new is given), then - where the lists are short enough for one workgroup per
-// head - a single launch that picks each head's pages, scores their tokens from the quantised copy of K, runs top-p and
+// new token appended on the way when k_new is given), then - where the lists are short enough for a workgroup's
+// registers - a single launch that picks each head's pages, scores their tokens from the quantised copy of K, runs top-p and
 // builds the group's union; otherwise the launches of twilight_select_pages and twilight_topp_prune.
 extern "C" int twilight_select_prune(const twilight_kv_t* kv, const void* k_new, const void* v_new, const int32_t* new_pos,
                                      const void* q, const int32_t* budget_tokens, float p,
@@ -531,11 +531,13 @@ extern "C" int twilight_select_prune(const twilight_kv_t* kv, const void* k_new,
   // 2: selection and scoring inside the top-p kernel, 1: scoring only, 0: the separate launches
   const int can = tw_prune_fused_ok(d, max_sel, true) ? 2 : (tw_prune_fused_ok(d, max_sel, false) ? 1 : 0);
   int mode = can;
-  // few heads with long lists (a single long sequence): one workgroup per head cannot pull its list fast enough, the
-  // scoring launch's many workgroups can (32 heads x 8192 candidates: 51.8 us per step separately, 56.0 us fused)
+  // fewer heads than CUs with long lists: one workgroup per head cannot pull its list fast enough (32 heads x 8192
+  // candidates: 51.8 us per step separately, 56.0 us fused); several per head can, the scoring launch's many too
   if (max_sel * TW_PAGE > 4096 && (long long)d.batch * d.Hq < tw_num_cus()) mode = 0;
+  const int parts = tw_prune_parts(d, max_sel);
+  if (parts > 1) mode = 2;
 #ifdef TW_TUNING
-  if (const char* e = getenv("TW_FUSE")) { const int m = atoi(e); mode = m < can ? m : can; }
+  if (const char* e = getenv("TW_FUSE")) { const int m = atoi(e); mode = parts > 1 ? mode : (m < can ? m : can); }
 #endif
   if (mode == 0) {
     if (int e = select_impl(kv, q, budget_tokens, sel_pages, sel_count, max_sel, ws, sel_bytes, stream, append, k_new, v_new,
@@ -548,5 +550,5 @@ extern "C" int twilight_select_prune(const twilight_kv_t* kv, const void* k_new,
                           new_pos, arrive, mode == 2)) return e;
   return tw_prune_fused(kv, d, q, mode == 2 ? (const float*)ws : nullptr, budget_tokens, sel_pages, sel_count, max_sel, p,
                         kept_count, kept_idx, kept_stride, union_count, union_idx, union_stride, status, ws_prune,
-                        (hipStream_t)stream);
+                        parts, (hipStream_t)stream);
 }

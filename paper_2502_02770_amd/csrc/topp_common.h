@@ -41,7 +41,8 @@ bool tw_prune_fused_ok(const TwDims& d, int max_sel, bool with_select);
 int tw_prune_fused(const twilight_kv_t* kv, const TwDims& d, const void* q, const float* bounds, const int32_t* budget,
                    int32_t* sel_pages, int32_t* sel_count, int32_t max_sel, float p, int32_t* kept_count, int32_t* kept_idx,
                    int32_t kept_stride, int32_t* union_count, int32_t* union_idx, int32_t union_stride,
-                   uint32_t* status, void* ws, hipStream_t s);
+                   uint32_t* status, void* ws, int parts, hipStream_t s);
+int tw_prune_parts(const TwDims& d, int max_sel);   // workgroups per head of the split form, which selects its pages itself; 1: not split
 
 #ifdef __HIPCC__
 // softmax numerator e in [0, 1] -> floor(e * 2^40), exactly: the top 8 bits and the remaining 32

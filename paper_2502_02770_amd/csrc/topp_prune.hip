@@ -690,6 +690,7 @@ __global__ __launch_bounds__(SMP_NT) void row_sample_kernel(SampleArgs sa) {
 // sorted union.
 struct HeadArgs {
   const float* scores;
+  float* scores_w;            // FUSE == 3: the same rows, written here
   const int32_t* sel_pages;
   const int32_t* sel_count;
   const int32_t* seq_lens;
@@ -716,6 +717,7 @@ struct HeadArgs {
   const int32_t* budget;      // [b] tokens
   int32_t* sel_pages_w;
   int32_t* sel_count_w;
+  int parts;                  // FUSE == 3: workgroups per head
 };
 
 constexpr int HP_CAP = 64;                    // exact resolve handles up to this many scores
@@ -728,42 +730,49 @@ constexpr int HP_USTAGE = 4096;               // union lists up to this length l
 // scoring launch wrote: the workgroup's waves share the list (one page of 64 (token, group) lanes per wave and step,
 // the arithmetic of int4_score_kernel), the scores cross to their owner threads through LDS.
 // FUSE == 2: the page list too is made here, from the bounds of all pages (the selection of page_select_reg_kernel).
-// BITS: width of the quantised copy's codes (FUSE == 2; else 4).
+// FUSE == 3: the same with a.parts workgroups per head, for few heads with long lists, whose lists one workgroup per head
+// pulls too slowly.  Each selects the head's pages (the same list in each), scores its share of them into the head's row,
+// and the last one to get there goes on with top-p alone (1 x 32 heads x 8192 pages, 8192 candidates: page_select 11.4 +
+// int4_score 6.3 + topp 12.8 us -> 27.9; 4 x 32 heads x 4096 pages 32.9 -> 30.5).
+// BITS: width of the quantised copy's codes (FUSE >= 2; else 4).
 template <int NT, int EPT, int G, bool TOK = false, int FUSE = 0, int BITS = 4>
 __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FUSE != 2 && EPT > 8 ? 4 : 6))) void topp_head_kernel(HeadArgs a) {
   constexpr int NW = NT / 64;
+  constexpr bool SELECT = FUSE >= 2, SPLIT = FUSE == 3;
   // The workgroups that are there to share a CU (many heads, 8 or 16 candidates per thread, scored here) leave the scores
   // in LDS, where every phase reads them again, instead of holding them in registers: three of 16 candidates per thread
   // fit a CU instead of two, four of 8 instead of three, and one's scoring streams while the others wait at barriers
   // (64 ragged sequences x 32 heads 116.6 -> 104.0 us, 32 x 32 heads x 4096 candidates 56.2 -> 53.7).
   constexpr bool INLDS = FUSE == 2 && NT <= 512 && EPT > 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int b_ = blockIdx.y, h_ = blockIdx.x;
+  const unsigned parts = SPLIT ? (unsigned)a.parts : 1u;
+  int b_ = blockIdx.y, h_ = blockIdx.x / parts, part = blockIdx.x % parts;
   if (FUSE && a.remap) {
     // Workgroups go to the 8 XCDs round robin in dispatch order.  The G heads of a KV head select largely the
     // same pages: they take G consecutive workgroups of one XCD, so that each finds the others' pages in its L2.
     const unsigned L = blockIdx.y * gridDim.x + blockIdx.x, xcd = L & 7u, r = L >> 3;
-    const unsigned grp = (r / G) * 8u + xcd;             // (sequence, KV head), batch * Hkv a multiple of 8
+    const unsigned grp = (r / (G * parts)) * 8u + xcd;   // (sequence, KV head), batch * Hkv a multiple of 8
     b_ = (int)(grp / (unsigned)a.Hkv);
-    h_ = (int)(grp % (unsigned)a.Hkv) * G + (int)(r % G);
+    h_ = (int)(grp % (unsigned)a.Hkv) * G + (int)(r / parts % G);
+    part = (int)(r % parts);
   }
   const int b = b_, h = h_;
   const int bh = b * a.Hq + h;
-  // FUSE == 2: everything the page selection reads is asked for here, before the sequence's length is known (any
+  // SELECT: everything the page selection reads is asked for here, before the sequence's length is known (any
   // entry of the head's row of bounds and of the sequence's page-table row may be read): the bounds and the
   // page-table entries of the pages j * NT + tid, which this thread will list (1024-thread workgroups, 4 entries each;
   // the smaller ones, short of registers, ask when they know the length)
-  // FUSE == 2 with few candidates: the row of pages is bounded too (the launch's rule), and LDS is sized for that
+  // SELECT with few candidates: the row of pages is bounded too (the launch's rule), and LDS is sized for that
   constexpr bool SMALL = FUSE == 2 && NT <= 512 && EPT == 4;
-  constexpr int SEL_E = SMALL ? 4 : 4096 / NT;
-  constexpr int BWORDS = SMALL ? SEL_E * NT * TW_PAGE / 32 : (FUSE == 2 ? 4096 * TW_PAGE / 32 : HP_BITMAP_WORDS);
+  constexpr int SEL_E = SMALL ? 4 : (SPLIT ? 8192 : 4096) / NT;
+  constexpr int BWORDS = SMALL ? SEL_E * NT * TW_PAGE / 32 : (SELECT ? SEL_E * NT * TW_PAGE / 32 : HP_BITMAP_WORDS);
   constexpr int USTAGE = SMALL ? 4 * NT : HP_USTAGE;
-  constexpr int AREA = FUSE == 2 ? (NT * EPT > USTAGE ? NT * EPT : USTAGE) : USTAGE;
-  constexpr bool SEL_EARLY = FUSE == 2 && NT >= 1024;
+  constexpr int AREA = SELECT ? (NT * EPT > USTAGE ? NT * EPT : USTAGE) : USTAGE;
+  constexpr bool SEL_EARLY = SELECT && NT >= 1024;
   const int n = a.seq_lens[b];
-  const int budget_b = FUSE == 2 ? a.budget[b] : 0;
-  float sel_pre[FUSE == 2 ? SEL_E : 1];
-  int32_t sel_pt[FUSE == 2 ? SEL_E : 1];
+  const int budget_b = SELECT ? a.budget[b] : 0;
+  float sel_pre[SELECT ? SEL_E : 1];
+  int32_t sel_pt[SELECT ? SEL_E : 1];
   auto ask_selection = [&]() {
 #pragma unroll
     for (int j = 0; j < SEL_E; ++j) {
@@ -784,7 +793,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
   const int ntok = P * TW_PAGE < n ? P * TW_PAGE : n;
   const int nwords = (ntok + 31) >> 5;
   int count;
-  if (FUSE == 2) {
+  if (SELECT) {
     int P2;
     tw_select_sizes<TW_PAGE>(n, budget_b, a.max_pages, a.max_sel, &P2, &count);
   } else {
@@ -803,30 +812,32 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
   __shared__ unsigned long long cand_mass[HP_CAP];
   __shared__ uint32_t cand_key[HP_CAP];
   // position bitmap, then the union list on its way out; before that the selection's arrays and the scores, read 16
-  // bytes at a time: behind the bitmap (FUSE == 2, whose bitmap covers 4096 pages) or from its first word
+  // bytes at a time: behind the bitmap (SELECT, whose bitmap covers 4096 pages) or from its first word
   __shared__ __align__(16) uint32_t big_s[BWORDS + AREA];
   static_assert(__alignof__(big_s) >= 16 && BWORDS % 4 == 0, "read as float4 and as 64-bit words");
   uint32_t* const bitmap = big_s;
-  uint32_t* const area = FUSE == 2 ? big_s + BWORDS : big_s;
+  uint32_t* const area = SELECT ? big_s + BWORDS : big_s;
   int32_t* const ustage = (int32_t*)(big_s + BWORDS);
   __shared__ unsigned long long tail_s[NW];
   __shared__ uint32_t ws32[16];
   __shared__ float redf[NW];
   __shared__ uint32_t sh_n, sh_kept, sh_T, sh_last;
 
-  __shared__ int32_t pages_s[FUSE == 2 ? NT * EPT / TW_PAGE : 1];   // FUSE == 2: the head's page list ...
-  __shared__ int32_t pool_s[FUSE == 2 ? NT * EPT / TW_PAGE : 1];    // ... and the pages' places in the pool
-  if (FUSE == 2) {
-    constexpr int SNB = 512;
+  __shared__ int32_t pages_s[SELECT ? NT * EPT / TW_PAGE : 1];   // SELECT: the head's page list ...
+  __shared__ int32_t pool_s[SELECT ? NT * EPT / TW_PAGE : 1];    // ... and the pages' places in the pool
+  if (SELECT) {
+    // (SPLIT: up to 8192 bounds, most of them close together below a few large ones; with 512 buckets their adds queue on
+    //  few words - 4.7 us of histogram, with 1024 2.1, with 2048 the scan takes what the adds save)
+    constexpr int SNB = SPLIT ? 1024 : 512;
     static_assert(SNB % 2 == 0, "the candidates behind the histogram are 64-bit words");
     uint32_t* const hist = area;                    // the selection's arrays lie there
     unsigned long long* const cand = (unsigned long long*)(area + SNB);
     uint32_t* const cnt = area + SNB + 2 * SEL_CAP;
     int32_t* const out = a.sel_pages_w + (long long)bh * a.max_sel;
     const int32_t* const ptab = a.page_table + (long long)b * a.max_pages;
-    if (tid == 0) a.sel_count_w[bh] = count;
+    if (tid == 0 && part == 0) a.sel_count_w[bh] = count;
     if (count == P) {                               // the budget covers the sequence (block-uniform)
-      for (int i = tid; i < P; i += NT) { out[i] = i; pages_s[i] = i; pool_s[i] = ptab[i]; }
+      for (int i = tid; i < P; i += NT) { if (part == 0) out[i] = i; pages_s[i] = i; pool_s[i] = ptab[i]; }
     } else if (count > 0) {
       if (!SEL_EARLY) {
         const float* const sc = a.bounds + (long long)bh * a.max_pages;
@@ -834,19 +845,19 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
         for (int e = 0; e < SEL_E; ++e) {
           if (e * NT >= P) continue;                 // (block-uniform)
           const int i = e * NT + tid < P ? e * NT + tid : P - 1;
-          sel_pre[FUSE == 2 ? e : 0] = sc[i];
-          sel_pt[FUSE == 2 ? e : 0] = ptab[i];
+          sel_pre[SELECT ? e : 0] = sc[i];
+          sel_pt[SELECT ? e : 0] = ptab[i];
         }
       }
       uint32_t key[SEL_E], T, need_eq;
 #pragma unroll
-      for (int e = 0; e < SEL_E; ++e) key[e] = tw_float_key(sel_pre[FUSE == 2 ? e : 0]);
+      for (int e = 0; e < SEL_E; ++e) key[e] = tw_float_key(sel_pre[SELECT ? e : 0]);
       tw_select_threshold<NT, SEL_E, SNB, 30>(key, P, (uint32_t)count, hist, cand, &T, &need_eq);
       tw_select_list<NT, SEL_E>(key, P, T, need_eq, cnt, [&](uint32_t pos, int e) {
         if (pos < (uint32_t)a.max_sel) {
-          out[pos] = e * NT + tid;
+          if (part == 0) out[pos] = e * NT + tid;
           pages_s[pos] = e * NT + tid;
-          pool_s[pos] = sel_pt[FUSE == 2 ? e : 0];
+          pool_s[pos] = sel_pt[SELECT ? e : 0];
         }
       });
     }
@@ -863,24 +874,27 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
   int pg[NPG];
   float* const sc_s = (float*)area;
   if (FUSE) {
-    static_assert(NT * EPT <= (FUSE == 2 ? AREA : BWORDS + USTAGE), "scores of a row must fit the staging array");
+    static_assert(NT * EPT <= (SELECT ? AREA : BWORDS + USTAGE), "scores of a row must fit the staging array");
     __shared__ int qi_s[1][32];
     __shared__ float qred[4];
     __shared__ float qc_s[1];
     // this wave's share of the list: lane k holds its k-th page
     static_assert(EPT * 64 / TW_PAGE <= 64, "a wave's share of the longest list has a lane for every page");
-    constexpr int UF = (NT >= 1024 || EPT == 4 || (INLDS && EPT == 16) ? 8 : 4) / (BITS == 8 ? 2 : 1);   // pages in flight per wave (register budget)
-    const int ppw = INLDS ? (count + NW - 1) / NW : ((count + NW - 1) / NW + UF - 1) / UF * UF;
-    const int first = __builtin_amdgcn_readfirstlane(wave) * ppw;   // (scalar: the loop below is wave-uniform)
+    constexpr int UF = (!SPLIT && NT >= 1024 || EPT == 4 || (INLDS && EPT == 16) ? 8 : 4) / (BITS == 8 ? 2 : 1);   // pages in flight per wave (register budget)
+    // SPLIT: this workgroup's share of the list
+    const int share = SPLIT ? (count + (int)parts - 1) / (int)parts : count, share0 = SPLIT ? part * share : 0;
+    const int share1 = share0 + share < count ? share0 + share : count;
+    const int ppw = INLDS || SPLIT ? (share + NW - 1) / NW : ((share + NW - 1) / NW + UF - 1) / UF * UF;
+    const int first = share0 + __builtin_amdgcn_readfirstlane(wave) * ppw;   // (scalar: the loop below is wave-uniform)
     int my_lp = -1, my_pool = -1;
-    if (lane < ppw && first + lane < count) {
-      my_lp = FUSE == 2 ? pages_s[first + lane] : a.sel_pages[(long long)bh * a.max_sel + first + lane];
+    if (lane < ppw && first + lane < share1) {
+      my_lp = SELECT ? pages_s[first + lane] : a.sel_pages[(long long)bh * a.max_sel + first + lane];
       if (my_lp >= 0 && my_lp < P) {
-        const int pp = FUSE == 2 ? pool_s[first + lane] : a.page_table[(long long)b * a.max_pages + my_lp];
+        const int pp = SELECT ? pool_s[first + lane] : a.page_table[(long long)b * a.max_pages + my_lp];
         if (pp >= 0 && pp < a.pool_pages) my_pool = pp;
       }
     }
-    int npages = count - first;
+    int npages = share1 - first;
     npages = npages < 0 ? 0 : (npages > ppw ? ppw : npages);
     tw_quantize_q1(tid < 128 ? __uint_as_float(q_raw << 16) : 0.f, qi_s, qred, qc_s);
     const int j = lane & 3, g = h / G;
@@ -915,7 +929,10 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
       tw_unpack_codes<BITS>(nib[kk], u);
       const bool valid = pl >= 0 && lp * TW_PAGE + (lane >> 2) < n;
       const float T = tw_token_sum(meta[kk], tw_group_dot(qw, u, qs128), qsf);
-      sc_s[(first + k) * TW_PAGE + (lane >> 2)] = valid ? __fmul_rn(T, cc) : -__builtin_inff();
+      const float sc = valid ? __fmul_rn(T, cc) : -__builtin_inff();
+      const int slot = (first + k) * TW_PAGE + (lane >> 2);
+      if (!SPLIT) sc_s[slot] = sc;
+      else if (k < npages) __hip_atomic_store(a.scores_w + (long long)bh * a.cand_stride + slot, sc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     int k0 = 0;
     if (INLDS) {
@@ -942,6 +959,24 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
 #pragma unroll
         for (int kk = 0; kk < UF; ++kk) use(kk, k0 + kk);
       }
+    }
+    if (SPLIT) {
+      // the hand-off of the bitmaps below: write-through stores, acknowledged, then one count per workgroup; the last one
+      // reads the others' scores past the caches that are not shared by all compute units
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      if (tid == 0)
+        sh_last = __hip_atomic_fetch_add(a.arrive + (b * a.Hkv + h / G) * TW_CTR + 1 + h % G, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1u ? 1u : 0u;
+      __syncthreads();
+      if (!sh_last) return;
+      float x[EPT];
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) {
+        const int i = e * NT + tid < a.cand_stride ? e * NT + tid : a.cand_stride - 1;
+        x[e] = __hip_atomic_load(row + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) sc_s[e * NT + tid] = x[e];
     }
     __syncthreads();
     if (!INLDS) {
@@ -970,7 +1005,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
 #pragma unroll
     for (int v = 0; v < NPG; ++v) {
       const int p0 = INLDS ? (v * 4 * NT + tid * 4) >> 4 : (c0 >> 4) + v, pi = p0 < a.max_sel ? p0 : a.max_sel - 1;
-      pg[v] = FUSE == 2 ? pages_s[pi] : a.sel_pages[(long long)bh * a.max_sel + pi];
+      pg[v] = SELECT ? pages_s[pi] : a.sel_pages[(long long)bh * a.max_sel + pi];
     }
   }
   if (!INLDS) {
@@ -1504,7 +1539,7 @@ void launch_topp_one(const HeadArgs& f, int G, dim3 grid, hipStream_t s) {
 }
 
 // Register-resident top-p over rows of at most 8192 candidates (cand_stride = row bound).
-//  - few heads: one 1024-thread workgroup per head (4 or 8 candidates per thread);
+//  - few heads: one 1024-thread workgroup per head (4 or 8 candidates per thread), or several (tw_prune_parts);
 //  - more heads than CUs and rows of at most 4096 candidates: 512-thread workgroups, three or (selection and scores inside)
 //    four to a CU (a 1024-thread workgroup has a CU to itself at this register count: 8 x 32 x 4 = 1024 heads took 35.8 us
 //    that way, 22.9 us two to a CU);
@@ -1525,7 +1560,7 @@ void launch_topp_one(const HeadArgs& f, int G, dim3 grid, hipStream_t s) {
 // FUSE: the kernels score the candidates themselves (page lists).
 template <bool TOK, int FUSE = 0, int BITS = 4>
 int launch_topp(HeadArgs f, const TwDims& d, int cand_stride, hipStream_t s) {
-  const dim3 grid(d.Hq, d.batch);
+  const dim3 grid(d.Hq * (FUSE == 3 ? f.parts : 1), d.batch);
   const long long heads = (long long)d.batch * d.Hq;
   f.remap = (FUSE != 0 && ((long long)d.batch * d.Hkv) % 8 == 0) ? 1 : 0;
   f.n_above = -1; f.n_upto = cand_stride;
@@ -1536,6 +1571,11 @@ int launch_topp(HeadArgs f, const TwDims& d, int cand_stride, hipStream_t s) {
     if (int e = tw_prof_after(s)) return e;
     f.n_above = 4096; f.n_upto = cand_stride;
   }
+  if constexpr (FUSE == 3) {
+    tw_prof_before(TW_K_SELECT_SCORE_TOPP, s);
+    launch_topp_one<1024, 8, TOK, FUSE, BITS>(f, d.G, grid, s);
+    return tw_prof_after(s);
+  } else {
   tw_prof_before(FUSE == 2 ? TW_K_SELECT_SCORE_TOPP : (FUSE == 1 ? TW_K_SCORE_TOPP : TW_K_TOPP), s);
   if (FUSE == 2 && heads > tw_num_cus() && cand_stride <= 1024 && d.max_pages <= 1024) launch_topp_one<FUSE == 2 ? 256 : 512, 4, TOK, FUSE, BITS>(f, d.G, grid, s);
   else if (cand_stride <= 2048 && (FUSE != 2 || d.max_pages <= 2048)) launch_topp_one<512, 4, TOK, FUSE, BITS>(f, d.G, grid, s);
@@ -1544,6 +1584,7 @@ int launch_topp(HeadArgs f, const TwDims& d, int cand_stride, hipStream_t s) {
   else if (FUSE == 2 ? heads > tw_num_cus() : FUSE != 0 && heads > 2ll * tw_num_cus()) launch_topp_one<512, FUSE != 0 ? 16 : 8, TOK, FUSE, BITS>(f, d.G, grid, s);
   else launch_topp_one<1024, 8, TOK, FUSE, BITS>(f, d.G, grid, s);
   return tw_prof_after(s);
+  }
 }
 
 }  // namespace
@@ -1662,7 +1703,7 @@ extern "C" int twilight_topp_prune(const twilight_kv_t* kv, const void* q, const
     f.Hq = d.Hq; f.Hkv = d.Hkv; f.max_pages = d.max_pages; f.max_sel = max_sel; f.cand_stride = cand_stride;
     f.kept_stride = kept_stride; f.words_stride = words_stride; f.union_stride = union_stride; f.p = p;
     f.q = nullptr; f.page_table = nullptr; f.kq_pool = nullptr; f.kq_meta = nullptr; f.pool_pages = 0;
-    f.bounds = nullptr; f.budget = nullptr; f.sel_pages_w = nullptr; f.sel_count_w = nullptr;
+    f.bounds = nullptr; f.budget = nullptr; f.sel_pages_w = nullptr; f.sel_count_w = nullptr; f.scores_w = nullptr; f.parts = 1;
     return launch_topp<false>(f, d, cand_stride, s);
   }
 }
@@ -1675,13 +1716,25 @@ bool tw_prune_fused_ok(const TwDims& d, int max_sel, bool with_select) {
   if (max_sel <= 0 || !tw_prune_uses_head_kernel(d, false, max_sel) || (d.bits != 4 && !with_select)) return false;
   return !with_select || d.max_pages <= 4096;      // the selection's keys share the kernel's LDS staging array
 }
+// Workgroups per head when it is to be split (see topp_head_kernel, FUSE == 3), 1: not.  As many as give every CU one, for
+// lists above 4096 candidates on at most half as many heads as CUs (steps, us: 1 x 32 heads x 4096 pages x 8192 candidates
+// 46.5 -> 42.5, 2 x 32 53.9 -> 49.3, 4 x 32 65.2 -> 61.0).  Shorter lists lose: the hand-off costs 1.4 us and reading the
+// scores back 2 (32 heads x 4096 candidates 19.9 us in one workgroup each, 21.4 split; 64 x 2000 14.4 and 20.1).
+int tw_prune_parts(const TwDims& d, int max_sel) {
+  const long long heads = (long long)d.batch * d.Hq;
+  if (max_sel <= 0 || !tw_prune_uses_head_kernel(d, false, max_sel) || d.max_pages > 8192) return 1;
+  if (max_sel * TW_PAGE <= 4096 || 2 * heads > tw_num_cus()) return 1;
+  const long long fit = tw_num_cus() / heads;
+  return (int)(fit > 8 ? 8 : fit);
+}
 int tw_prune_fused(const twilight_kv_t* kv, const TwDims& d, const void* q, const float* bounds, const int32_t* budget,
                    int32_t* sel_pages, int32_t* sel_count, int32_t max_sel, float p, int32_t* kept_count, int32_t* kept_idx,
                    int32_t kept_stride, int32_t* union_count, int32_t* union_idx, int32_t union_stride,
-                   uint32_t* status, void* ws, hipStream_t s) {
+                   uint32_t* status, void* ws, int parts, hipStream_t s) {
   const PruneWs L = tw_prune_layout(d, max_sel, false);
   HeadArgs f;
-  f.scores = nullptr; f.sel_pages = sel_pages; f.sel_count = sel_count; f.seq_lens = kv->seq_lens;
+  f.parts = parts;
+  f.scores = f.scores_w = parts > 1 ? (float*)((char*)ws + L.scores) : nullptr; f.sel_pages = sel_pages; f.sel_count = sel_count; f.seq_lens = kv->seq_lens;
   f.kept_count = kept_count; f.kept_idx = kept_idx; f.bitmaps = (uint32_t*)((char*)ws + L.bitmaps);
   f.arrive = (uint32_t*)((char*)ws + L.arrive);
   f.union_count = union_count; f.union_idx = union_idx; f.status = status;
@@ -1690,6 +1743,9 @@ int tw_prune_fused(const twilight_kv_t* kv, const TwDims& d, const void* q, cons
   f.q = (const uint16_t*)q; f.page_table = kv->page_table; f.kq_pool = (const uint4*)kv->kq_pool;
   f.kq_meta = (const uint32_t*)kv->kq_meta; f.pool_pages = d.pool_pages;
   f.bounds = bounds; f.budget = budget; f.sel_pages_w = sel_pages; f.sel_count_w = sel_count;
+  if (parts > 1 && d.bits == 8) return launch_topp<false, 3, 8>(f, d, max_sel * TW_PAGE, s);
+  if (parts > 1 && d.bits == 2) return launch_topp<false, 3, 2>(f, d, max_sel * TW_PAGE, s);
+  if (parts > 1) return launch_topp<false, 3>(f, d, max_sel * TW_PAGE, s);
   if (bounds && d.bits == 8) return launch_topp<false, 2, 8>(f, d, max_sel * TW_PAGE, s);
   if (bounds && d.bits == 2) return launch_topp<false, 2, 2>(f, d, max_sel * TW_PAGE, s);
   if (bounds) return launch_topp<false, 2>(f, d, max_sel * TW_PAGE, s);
@@ -1787,6 +1843,6 @@ extern "C" int twilight_topp_prune_tokens(const twilight_kv_t* kv, const void* q
   f.Hq = d.Hq; f.Hkv = d.Hkv; f.max_pages = d.max_pages; f.max_sel = max_cand; f.cand_stride = max_cand;
   f.kept_stride = kept_stride; f.words_stride = L.words_stride; f.union_stride = union_stride; f.p = p;
   f.q = nullptr; f.page_table = nullptr; f.kq_pool = nullptr; f.kq_meta = nullptr; f.pool_pages = 0;
-  f.bounds = nullptr; f.budget = nullptr; f.sel_pages_w = nullptr; f.sel_count_w = nullptr;
+  f.bounds = nullptr; f.budget = nullptr; f.sel_pages_w = nullptr; f.sel_count_w = nullptr; f.scores_w = nullptr; f.parts = 1;
   return launch_topp<true>(f, d, max_cand, s);
 }

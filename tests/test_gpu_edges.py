@@ -240,3 +240,39 @@ def test_kept_tokens_of_the_last_page_reach_the_union(n, max_sel, seqs, separate
         kept = np.unique(np.concatenate([st.kept_idx[0, h, :int(st.kept_count[0, h])].cpu().numpy() for h in range(4 * g, 4 * g + 4)]))
         assert set(range(n - 16, n)) <= set(kept.tolist())
         assert st.union_idx[g, :int(st.union_count[g])].cpu().numpy().tolist() == kept.tolist()
+@pytest.mark.parametrize("bits,heads,lens,max_sel", [
+    (4, (8, 2), [131072, 40, 9000], 512), (4, (8, 1), [131065], 511), (4, (16, 16), [66000, 1, 16], 300), (4, (4, 2), [131072] * 2, 257),
+    (2, (32, 8), [65536, 20000, 4100], 512), (8, (32, 8), [65536, 20000, 4100], 400), (4, (64, 8), [70001, 300], 512),
+    (4, (12, 12), [40000, 2, 70000], 509)])
+def test_one_launch_select_prune_of_few_heads_with_long_lists(bits, heads, lens, max_sel):
+    """Lists above 4096 candidates on at most half as many heads as CUs: 2 to 8 workgroups per head, with and without a
+    multiple of 8 KV groups, lists shorter than the workgroups are many, 8192 pages; twice on the same workspace, against
+    the separate calls bit for bit."""
+    T = _T()
+    w = synth.make_workload("split", lens, num_q_heads=heads[0], num_kv_heads=heads[1], budget=[max_sel * 16 - 5] + [max(0, n // 3 - 20) for n in lens[1:]],
+                            p=0.9, heavy_frac=0.01, alpha_range=(0.0, 3.0), shuffle_pool=True, need_v=False, seed=95)
+    cache = build_cache(w, bits=bits)
+    q, budget = w.q.to(cache.device), w.budget.to(cache.device)
+    sa, sb = (T.DecodeStep(cache, max_sel=max_sel, with_kept_idx=True) for _ in range(2))
+    sa.select(q, budget)
+    sa.prune(q, w.p)
+    for again in (False, True):
+        for t in (sb.sel_pages, sb.sel_count, sb.kept_count, sb.kept_idx, sb.union_count, sb.union_idx):
+            t.fill_(-7)
+        T.twilight_prof_enable(1)
+        sb.select_prune(None, None, None, q, budget, w.p)
+        torch.cuda.synchronize()
+        names = [name for name, _ in T.twilight_prof_collect()]
+        T.twilight_prof_enable(0)
+        assert names == ["page_score", "select_score_topp"]
+        _same_lists(sa, sb)
+
+
+def _same_lists(sa, sb):
+    assert torch.equal(sa.status, sb.status)
+    for name, count in (("sel_pages", "sel_count"), ("kept_idx", "kept_count"), ("union_idx", "union_count")):
+        ca, cb = getattr(sa, count).flatten().tolist(), getattr(sb, count).flatten().tolist()
+        assert ca == cb, name
+        xa, xb = (getattr(s, name).reshape(len(ca), -1).cpu() for s in (sa, sb))
+        for i, c in enumerate(ca):
+            assert torch.equal(xa[i, :c], xb[i, :c]), (name, i)
