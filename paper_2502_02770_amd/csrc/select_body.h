@@ -25,6 +25,7 @@ constexpr int SEL_REG_TWO = 16384;       // rows up to here run two 1024-thread 
 constexpr int SEL_REG_MAX = 32768;       // longest row whose keys fit in a workgroup's registers
 constexpr int SEL_CAP = 64;              // candidates of the exact finish: one per lane
 constexpr int SEL_GROUP = 4;             // slots skipped together where a thread has more than 8
+constexpr uint32_t SEL_ALL_EQ = 0xFFFFFFFFu;   // every key equal to the threshold is taken
 
 // entries of a sequence's row and how many of them the budget asks for (UNIT = tokens per entry: 16 or 1)
 template <int UNIT>
@@ -93,7 +94,7 @@ __device__ __forceinline__ void tw_seg_prefix(const uint32_t* cnt, int entries, 
 }
 
 // Threshold of the Kp (0 < Kp < P) largest of the row's keys, ties to the lower index: the entries with a key above
-// *T_out and the first *need_eq_out of those equal to it.  key[e] of thread t is entry e * NT + t (tw_select_key when E > 8, else the
+// *T_out and the first *need_eq_out of those equal to it (SEL_ALL_EQ: all).  key[e] of thread t is entry e * NT + t (tw_select_key when E > 8, else the
 // float's key, of any value beyond the row's end).
 // Called by all NT threads of the workgroup; hist and cand are LDS of the caller.  SB: first phase-stamp slot (timing builds).
 template <int NT, int E, int SNB, int SB>
@@ -215,7 +216,9 @@ __device__ __forceinline__ void tw_select_threshold(uint32_t (&key)[E], int P, u
       const int last = __ffsll((long long)__ballot((uint32_t)lane < pop && rank == need - 1)) - 1;
       T = (uint32_t)__builtin_amdgcn_readlane((int)(mineK >> 32), last);
       // how many of the keys equal to T are taken: those ranked up to `last`
-      need_eq = (uint32_t)__popcll(__ballot((uint32_t)lane < pop && (uint32_t)(mineK >> 32) == T && rank <= need - 1));
+      const unsigned long long eq = __ballot((uint32_t)lane < pop && (uint32_t)(mineK >> 32) == T);
+      const unsigned long long in = eq & __ballot(rank <= need - 1);
+      need_eq = in == eq ? SEL_ALL_EQ : (uint32_t)__popcll(in);
       break;
     }
     // narrow to the bucket's keys
@@ -232,7 +235,7 @@ __device__ __forceinline__ void tw_select_threshold(uint32_t (&key)[E], int P, u
     __syncthreads();
     klo = (uint32_t)__builtin_amdgcn_readfirstlane((int)~tw_row_max_u32(~red_lo[lane & (NW - 1)]));
     khi = (uint32_t)__builtin_amdgcn_readfirstlane((int)tw_row_max_u32(red_hi[lane & (NW - 1)]));
-    if (pop == need) { T = klo; need_eq = 0xFFFFFFFFu; break; }   // the whole bucket is taken
+    if (pop == need) { T = klo; need_eq = SEL_ALL_EQ; break; }    // the whole bucket is taken
     __syncthreads();                              // red_* and hist are rewritten by the next pass
   }
   tw_forget<E>(key);
@@ -248,13 +251,33 @@ __device__ __forceinline__ void tw_select_list(uint32_t (&key)[E], int P, uint32
   constexpr int NW = NT / 64, SEGS = E * NW, Q = (SEGS + 63) / 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = E > 8 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
   const auto live = [&](int e) { return E > 8 || e * NT + tid < P; };
+  uint32_t excl[Q], total;
+  // Block-uniform, and so but for ties that are cut: one comparison and one ballot per entry (instructions bound this
+  // phase once 16 waves share a CU's four vector units: 256 x 32768 entries 32.0 -> 29.7 us, 32 heads x 8192 2.9 -> 2.4).
+  if (need_eq == SEL_ALL_EQ) {
+    static_assert(E <= 64, "a lane per slot");
+    uint32_t mine = 0;                            // lane e: how many of this wave's slots e are taken
+    tw_each_slot<NT, E>(P, [&](int e) {
+      const uint32_t c = (uint32_t)__popcll(__ballot(live(e) && key[e] >= T));
+      mine = lane == e ? c : mine;
+    });
+    if (lane < E) cnt[lane * NW + wave] = mine;
+    __syncthreads();
+    tw_forget<E>(key);
+    tw_seg_prefix<Q>(cnt, ((P + NT - 1) / NT) * NW, excl, &total);
+    tw_each_slot<NT, E>(P, [&](int e) {
+      const bool in = live(e) && key[e] >= T;
+      const uint32_t below = tw_bits_below(__ballot(in));
+      if (in) put((uint32_t)__builtin_amdgcn_readlane((int)excl[(e * NW) >> 6], ((e * NW) & 63) + wave) + below, e);
+    });
+    return;
+  }
   tw_each_slot<NT, E>(P, [&](int e) {
     const uint32_t gt = (uint32_t)__popcll(__ballot(live(e) && key[e] > T)), eq = (uint32_t)__popcll(__ballot(live(e) && key[e] == T));
     if (lane == 0) cnt[e * NW + wave] = gt | (eq << 16);
   });
   __syncthreads();
   tw_forget<E>(key);
-  uint32_t excl[Q], total;
   tw_seg_prefix<Q>(cnt, ((P + NT - 1) / NT) * NW, excl, &total);
   tw_each_slot<NT, E>(P, [&](int e) {
     const bool gt = live(e) && key[e] > T, eq = live(e) && key[e] == T;
