@@ -302,7 +302,7 @@ def profile_figures(dom):
     HBM traffic per dispatch from the counter runs.  Read from the committed summaries at run time; None when the
     summaries do not list a kernel of that stage."""
     from paper_2502_02770_amd.rocprof_summary import read_trace_table, read_traffic_table
-    stem = {"page_score": "page_score_kernel", "int4_score": "int4_score", "sparse_decode": "sparse_decode_kernel",
+    stem = {"page_score": "page_score", "int4_score": "int4_score", "sparse_decode": "sparse_decode_kernel",
             "topp": "topp_head_kernel", "score_topp": "topp_head_kernel", "select_score_topp": "topp_head_kernel",
             "page_select": "page_select", "combine": "combine_kernel",
             "kquant_append": "kquant_append_kernel"}.get(dom, dom)

@@ -11,7 +11,7 @@
 //              registers (select_body.h), longer ones by a 4 x 8-bit radix
 //              select on the order-preserving key over global memory.
 //
-// page_score<G, true> also appends the decode step's one new token per sequence on its way
+// page_score with APPEND also appends the decode step's one new token per sequence on its way
 // (twilight_append_select): the 16 lanes that own the page the token falls into store its K/V
 // rows, quantise K, and fold it into the page's bounds before scoring them.
 #include <atomic>
@@ -24,6 +24,7 @@
 namespace {
 
 constexpr int PS_PAGES_PER_WG = 32;   // 4 waves x 4 pages x 2 iterations
+constexpr int PS_LONG_PAGES = 64;     // of a workgroup of the form for many pages: 4 iterations
 
 struct ScoreArgs {
   const uint32_t* q;          // bf16 pairs [b][Hq][64]
@@ -44,6 +45,99 @@ struct ScoreArgs {
   uint4* page_minmax_w;
   uint32_t* arrive;           // [b][Hkv] arrival counters of a top-p launch that follows, cleared here, or nullptr
 };
+
+// The step's new token, by the 16 lanes that own its page: its K/V rows stored, K quantised, the page's bounds (*rmn, *rmx)
+// folded and stored.
+template <int BITS>
+__device__ __forceinline__ void ps_append(const ScoreArgs& a, long long row, long long page, int g, int sp, int seg, uint4* rmn, uint4* rmx) {
+  const uint4 raw = a.k_new[row * 16 + seg];
+  const long long slot = (page * a.Hkv + g) * TW_PAGE + (sp & 15);
+  if (a.k_pool) a.k_pool[slot * 16 + seg] = raw;
+  if (a.v_new) a.v_pool[slot * 16 + seg] = a.v_new[row * 16 + seg];
+  float x[8];
+  tw_unpack8(raw, x);
+  uint32_t word, word2, meta;
+  tw_quantize_lane8<BITS>(x, seg, &word, &word2, &meta);
+  if (BITS == 4) a.kq_pool[slot * 16 + seg] = word;
+  else if (BITS == 8) ((uint2*)a.kq_pool)[slot * 16 + seg] = make_uint2(word, word2);
+  else if ((seg & 1) == 0) a.kq_pool[slot * 8 + (seg >> 1)] = word;
+  if ((seg & 3) == 0) a.kq_meta[slot * 4 + (seg >> 2)] = meta;
+  // bounds: the token alone if it opens the page, else folded into the page's older tokens
+  float mn[8], mx[8];
+  tw_unpack8(*rmn, mn);
+  tw_unpack8(*rmx, mx);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    mn[i] = (sp & 15) ? fminf(mn[i], x[i]) : x[i];
+    mx[i] = (sp & 15) ? fmaxf(mx[i], x[i]) : x[i];
+  }
+  // min / max of bf16 values are bf16 values: the top 16 bits are exact
+  uint4 wmn, wmx;
+  wmn.x = (__float_as_uint(mn[0]) >> 16) | (__float_as_uint(mn[1]) & 0xFFFF0000u);
+  wmn.y = (__float_as_uint(mn[2]) >> 16) | (__float_as_uint(mn[3]) & 0xFFFF0000u);
+  wmn.z = (__float_as_uint(mn[4]) >> 16) | (__float_as_uint(mn[5]) & 0xFFFF0000u);
+  wmn.w = (__float_as_uint(mn[6]) >> 16) | (__float_as_uint(mn[7]) & 0xFFFF0000u);
+  wmx.x = (__float_as_uint(mx[0]) >> 16) | (__float_as_uint(mx[1]) & 0xFFFF0000u);
+  wmx.y = (__float_as_uint(mx[2]) >> 16) | (__float_as_uint(mx[3]) & 0xFFFF0000u);
+  wmx.z = (__float_as_uint(mx[4]) >> 16) | (__float_as_uint(mx[5]) & 0xFFFF0000u);
+  wmx.w = (__float_as_uint(mx[6]) >> 16) | (__float_as_uint(mx[7]) & 0xFFFF0000u);
+  uint4* pm = a.page_minmax_w + (page * a.Hkv + g) * 32;
+  pm[seg] = wmn;
+  pm[16 + seg] = wmx;
+  *rmn = wmn;
+  *rmx = wmx;
+}
+
+// The bounds of a page for the G heads, by its 16 lanes; put(h, bound) in the lane that ends with head h's.
+// (The signs of 4 heads' queries fill the scalar registers; those of further heads are compared anew, or they spill.)
+template <int G, typename Put>
+__device__ __forceinline__ void ps_score(float (&q)[G][8], const uint4& cmn, const uint4& cmx, int seg, Put put) {
+  float mn[8], mx[8];
+  tw_unpack8(cmn, mn);
+  tw_unpack8(cmx, mx);
+  float part[G];
+#pragma unroll
+  for (int h = 0; h < G; ++h) {
+    float acc = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      // the product of two bf16 values is exact in fp32, so this fused
+      // multiply-add rounds exactly like "acc + q*v"
+      if (h >= 4) asm volatile("" : "+v"(q[h][i]));
+      const float v = q[h][i] > 0.f ? mx[i] : mn[i];
+      acc = __builtin_fmaf(q[h][i], v, acc);
+    }
+    part[h] = acc;
+  }
+  if constexpr (G >= 4) {
+    // The pairwise tree over the 16 lanes (l^1, l^2, l^4, l^8) for four heads at once: at the first two levels a
+    // lane keeps the half of its values that one bit of its lane id selects and adds the partner's copy of them
+    // (the same two operands as the plain tree adds, so the same sums), which leaves lane l with the quad sum of
+    // head 2 * (l & 1) + ((l >> 1) & 1); the last two levels rotate the row by 4 and by 8 (a lane reads lane
+    // l - 4, then l - 8, modulo 16), which for lanes 4..7 are exactly l ^ 4 and l ^ 8 of the same head.  Lanes 4..7
+    // end with the four totals: 5 additions and 6 selects per four heads instead of 16 additions.
+    const bool b0 = seg & 1, b1 = seg & 2;
+#pragma unroll
+    for (int h4 = 0; h4 < G; h4 += 4) {
+      const float k0 = b0 ? part[h4 + 2] : part[h4 + 0], s0 = b0 ? part[h4 + 0] : part[h4 + 2];
+      const float k1 = b0 ? part[h4 + 3] : part[h4 + 1], s1 = b0 ? part[h4 + 1] : part[h4 + 3];
+      const float a0 = __fadd_rn(k0, tw_dpp_f<TW_DPP_XOR1>(s0));     // head h4 + 2 * b0
+      const float a1 = __fadd_rn(k1, tw_dpp_f<TW_DPP_XOR1>(s1));     // head h4 + 2 * b0 + 1
+      const float kk = b1 ? a1 : a0, ss = b1 ? a0 : a1;
+      float t = __fadd_rn(kk, tw_dpp_f<TW_DPP_XOR2>(ss));            // head h4 + 2 * b0 + b1, summed over the quad
+      t = __fadd_rn(t, tw_dpp_f<0x124>(t));                          // row_ror:4 - lanes 4..7 and 12..15 read l ^ 4
+      t = __fadd_rn(t, tw_dpp_f<0x128>(t));                          // row_ror:8 - every lane reads l ^ 8
+      if ((seg >> 2) == 1)
+        put(h4 + 2 * (seg & 1) + ((seg >> 1) & 1), __fadd_rn(t, 0.0f));
+    }
+  } else {
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      const float acc = tw_row16_sum(part[h]);
+      if (seg == 0) put(h, __fadd_rn(acc, 0.0f));
+    }
+  }
+}
 
 template <int G, bool APPEND, int BITS = 4>
 __global__ __launch_bounds__(256) void page_score_kernel(ScoreArgs a) {
@@ -105,43 +199,7 @@ __global__ __launch_bounds__(256) void page_score_kernel(ScoreArgs a) {
 #pragma unroll
       for (int it = 0; it < IT; ++it) {
         if (it == (off >> 4) && ok[it]) {
-          const long long row = (long long)b * a.Hkv + g;
-          const uint4 raw = a.k_new[row * 16 + seg];
-          const long long slot = (pool[it] * a.Hkv + g) * TW_PAGE + (sp & 15);
-          if (a.k_pool) a.k_pool[slot * 16 + seg] = raw;
-          if (a.v_new) a.v_pool[slot * 16 + seg] = a.v_new[row * 16 + seg];
-          float x[8];
-          tw_unpack8(raw, x);
-          uint32_t word, word2, meta;
-          tw_quantize_lane8<BITS>(x, seg, &word, &word2, &meta);
-          if (BITS == 4) a.kq_pool[slot * 16 + seg] = word;
-          else if (BITS == 8) ((uint2*)a.kq_pool)[slot * 16 + seg] = make_uint2(word, word2);
-          else if ((seg & 1) == 0) a.kq_pool[slot * 8 + (seg >> 1)] = word;
-          if ((seg & 3) == 0) a.kq_meta[slot * 4 + (seg >> 2)] = meta;
-          // bounds: the token alone if it opens the page, else folded into the page's older tokens
-          float mn[8], mx[8];
-          tw_unpack8(rmn[it], mn);
-          tw_unpack8(rmx[it], mx);
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            mn[i] = (sp & 15) ? fminf(mn[i], x[i]) : x[i];
-            mx[i] = (sp & 15) ? fmaxf(mx[i], x[i]) : x[i];
-          }
-          // min / max of bf16 values are bf16 values: the top 16 bits are exact
-          uint4 wmn, wmx;
-          wmn.x = (__float_as_uint(mn[0]) >> 16) | (__float_as_uint(mn[1]) & 0xFFFF0000u);
-          wmn.y = (__float_as_uint(mn[2]) >> 16) | (__float_as_uint(mn[3]) & 0xFFFF0000u);
-          wmn.z = (__float_as_uint(mn[4]) >> 16) | (__float_as_uint(mn[5]) & 0xFFFF0000u);
-          wmn.w = (__float_as_uint(mn[6]) >> 16) | (__float_as_uint(mn[7]) & 0xFFFF0000u);
-          wmx.x = (__float_as_uint(mx[0]) >> 16) | (__float_as_uint(mx[1]) & 0xFFFF0000u);
-          wmx.y = (__float_as_uint(mx[2]) >> 16) | (__float_as_uint(mx[3]) & 0xFFFF0000u);
-          wmx.z = (__float_as_uint(mx[4]) >> 16) | (__float_as_uint(mx[5]) & 0xFFFF0000u);
-          wmx.w = (__float_as_uint(mx[6]) >> 16) | (__float_as_uint(mx[7]) & 0xFFFF0000u);
-          uint4* pm = a.page_minmax_w + (pool[it] * a.Hkv + g) * 32;
-          pm[seg] = wmn;
-          pm[16 + seg] = wmx;
-          rmn[it] = wmn;
-          rmx[it] = wmx;
+          ps_append<BITS>(a, (long long)b * a.Hkv + g, pool[it], g, sp, seg, &rmn[it], &rmx[it]);
         }
       }
     }
@@ -149,53 +207,99 @@ __global__ __launch_bounds__(256) void page_score_kernel(ScoreArgs a) {
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
     const int lp = base + it * 16 + grp;
-    float mn[8], mx[8];
-    tw_unpack8(rmn[it], mn);
-    tw_unpack8(rmx[it], mx);
-    float part[G];
+    ps_score<G>(q, rmn[it], rmx[it], seg, [&](int h, float t) {
+      if (live[it])
+        a.scores[((long long)(b * a.Hq + g * G + h)) * a.max_pages + lp] = ok[it] ? t : -3.402823466e38f;   // unmapped page: ranks last
+    });
+  }
+  if (clears) a.arrive[(b * a.Hkv + g) * TW_CTR + tid] = 0;
+}
+
+// The same for many pages.  What bounds page_score_kernel there is that a workgroup waits for its length, then its page-table
+// entries, then two steps' bounds, and ends; its scores are pieces of 16 bytes.  Here a workgroup asks for four steps' bounds at
+// once (at most 128 registers, four workgroups per CU), its page-table entries are one load per wave, the new token comes
+// last, where the registers are free, and the scores leave through LDS in whole lines.  Decode steps, us: 16 x 32768 tokens,
+// 64 heads over 8 127.1 -> 121.6, 32 x 32768, 32 over 8 147.1 -> 144.5, 64 ragged sequences of up to 65536 240.9 -> 234.6.
+template <int G, bool APPEND, int BITS = 4>
+__global__ __launch_bounds__(256, 4) void page_score_long_kernel(ScoreArgs a) {
+  constexpr int STEPS = PS_LONG_PAGES / 16;
+  // KV head fastest in dispatch order: the 8 heads' bounds of a pool page are 4 KiB contiguous,
+  // and the workgroups that read them start next to each other
+  const int b = blockIdx.z, g = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, seg = tid & 15, grp = tid >> 4;   // grp: 0..15 page slot in a step
+  __shared__ float sh[G][PS_LONG_PAGES], sh_app[G];
+  TW_STAMP(0);
+  const int n = a.seq_lens[b];
+  // last pages first: the workgroup that appends the step's new token (the sequence's last page) has the longest
+  // chain of dependent accesses and should not be the one that starts last
+  const int base = (int)(gridDim.y - 1 - blockIdx.y) * PS_LONG_PAGES;
+  // all page-table entries of the wave's pages in one load, lane 4 * it + j that of page j of step it: issued before the
+  // sequence length is known (any entry of the row may be read; entries beyond the last page are ignored below)
+  const int mine = base + ((lane >> 2) < STEPS ? lane >> 2 : 0) * 16 + (tid >> 6) * 4 + (lane & 3);
+  int entry = a.page_table[(long long)b * a.max_pages + (mine < a.max_pages ? mine : a.max_pages - 1)];
+  int P = (n + TW_PAGE - 1) / TW_PAGE;
+  if (P > a.max_pages) P = a.max_pages;
+  // (the counters of a top-p launch that follows are cleared on the way out, after every load of the kernel: a store
+  //  ahead of them would turn the scalar loads of the prologue into vector loads that wait for one another)
+  const bool clears = a.arrive && blockIdx.y == 0 && tid <= G;      // the group's counter and one per head
+  if (base >= P) {
+    if (clears) a.arrive[(b * a.Hkv + g) * TW_CTR + tid] = 0;
+    return;
+  }
+  const int pages = P - base < PS_LONG_PAGES ? P - base : PS_LONG_PAGES, steps = (pages + 15) >> 4;
+
+  // q of the G heads, the 8 dims of this lane; the sign decides which corner
+  // of the [min,max] box maximises q_d * k_d.
+  float q[G][8];
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-      float acc = 0.f;
+  for (int h = 0; h < G; ++h) {
+    const uint4 r = *(const uint4*)(a.q + ((long long)(b * a.Hq + g * G + h)) * 64 + seg * 4);
+    tw_unpack8(r, q[h]);
+  }
+  // the page of the new token, if it lies in this workgroup's pages
+  int app = -1, sp = 0;
+  if (APPEND) {
+    sp = a.new_pos[b];
+    const int off = (sp >> 4) - base;
+    if (sp >= 0 && sp < n && off >= 0 && off < PS_LONG_PAGES) app = off;
+  }
+  if (mine >= P || entry < 0 || entry >= a.pool_pages) entry = -1;
+
+  // clamped addresses, unconditional loads, so that they are in flight together and their waits can be counted;
+  // unmapped pages and steps beyond the last are masked afterwards
+  int pool[STEPS];
+  uint4 rmn[STEPS], rmx[STEPS];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        // the product of two bf16 values is exact in fp32, so this fused
-        // multiply-add rounds exactly like "acc + q*v"
-        const float v = q[h][i] > 0.f ? mx[i] : mn[i];
-        acc = __builtin_fmaf(q[h][i], v, acc);
-      }
-      part[h] = acc;
+  for (int it = 0; it < STEPS; ++it) {
+    pool[it] = __shfl(entry, it * 4 + (lane >> 4), 64);
+    const uint4* pm = a.page_minmax + ((long long)(pool[it] >= 0 ? pool[it] : 0) * a.Hkv + g) * 32;
+    rmn[it] = tw_ld_stream(pm + seg);
+    rmx[it] = tw_ld_stream(pm + 16 + seg);
+  }
+#pragma unroll
+  for (int it = 0; it < STEPS; ++it) {
+    if (it >= steps) break;                       // (block-uniform)
+    // unmapped page: ranks last
+    ps_score<G>(q, rmn[it], rmx[it], seg, [&](int h, float t) { sh[h][it * 16 + grp] = pool[it] >= 0 ? t : -3.402823466e38f; });
+  }
+  // The new token, behind the steps, where the registers are free: one row of lanes of the wave that has its page.  (The steps
+  // saw the page's old bounds: its scores are kept apart.)
+  if (APPEND && app >= 0 && (tid >> 6) == ((app & 15) >> 2)) {                      // (wave-uniform)
+    const int page = __shfl(entry, (app >> 4) * 4 + (app & 3), 64);
+    if (page < 0) {
+      if (lane < G) sh_app[lane] = -3.402823466e38f;
+    } else if (lane < 16) {
+      const uint4* pm = a.page_minmax + ((long long)page * a.Hkv + g) * 32;
+      uint4 mn = pm[seg], mx = pm[16 + seg];
+      ps_append<BITS>(a, (long long)b * a.Hkv + g, page, g, sp, seg, &mn, &mx);
+      ps_score<G>(q, mn, mx, seg, [&](int h, float t) { sh_app[h] = t; });
     }
-    if constexpr (G >= 4) {
-      // The pairwise tree over the 16 lanes (l^1, l^2, l^4, l^8) for four heads at once: at the first two levels a
-      // lane keeps the half of its values that one bit of its lane id selects and adds the partner's copy of them
-      // (the same two operands as the plain tree adds, so the same sums), which leaves lane l with the quad sum of
-      // head 2 * (l & 1) + ((l >> 1) & 1); the last two levels rotate the row by 4 and by 8 (a lane reads lane
-      // l - 4, then l - 8, modulo 16), which for lanes 4..7 are exactly l ^ 4 and l ^ 8 of the same head.  Lanes 4..7
-      // end with the four totals: 5 additions and 6 selects per four heads instead of 16 additions.
-      const bool b0 = seg & 1, b1 = seg & 2;
+  }
+  __syncthreads();
 #pragma unroll
-      for (int h4 = 0; h4 < G; h4 += 4) {
-        const float k0 = b0 ? part[h4 + 2] : part[h4 + 0], s0 = b0 ? part[h4 + 0] : part[h4 + 2];
-        const float k1 = b0 ? part[h4 + 3] : part[h4 + 1], s1 = b0 ? part[h4 + 1] : part[h4 + 3];
-        const float a0 = __fadd_rn(k0, tw_dpp_f<TW_DPP_XOR1>(s0));     // head h4 + 2 * b0
-        const float a1 = __fadd_rn(k1, tw_dpp_f<TW_DPP_XOR1>(s1));     // head h4 + 2 * b0 + 1
-        const float kk = b1 ? a1 : a0, ss = b1 ? a0 : a1;
-        float t = __fadd_rn(kk, tw_dpp_f<TW_DPP_XOR2>(ss));            // head h4 + 2 * b0 + b1, summed over the quad
-        t = __fadd_rn(t, tw_dpp_f<0x124>(t));                          // row_ror:4 - lanes 4..7 and 12..15 read l ^ 4
-        t = __fadd_rn(t, tw_dpp_f<0x128>(t));                          // row_ror:8 - every lane reads l ^ 8
-        if ((seg >> 2) == 1 && live[it])
-          a.scores[((long long)(b * a.Hq + g * G + h4 + 2 * (seg & 1) + ((seg >> 1) & 1))) * a.max_pages + lp] =
-              ok[it] ? __fadd_rn(t, 0.0f) : -3.402823466e38f;          // unmapped page: ranks last
-      }
-    } else {
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        const float acc = tw_row16_sum(part[h]);
-        if (seg == 0 && live[it])
-          a.scores[((long long)(b * a.Hq + g * G + h)) * a.max_pages + lp] =
-              ok[it] ? __fadd_rn(acc, 0.0f) : -3.402823466e38f;   // unmapped page: ranks last
-      }
-    }
+  for (int i = tid; i < G * PS_LONG_PAGES; i += 256) {
+    const int h = i / PS_LONG_PAGES, j = i % PS_LONG_PAGES;
+    if (j < pages) a.scores[((long long)(b * a.Hq + g * G + h)) * a.max_pages + base + j] = j == app ? sh_app[h] : sh[h][j];
   }
   if (clears) a.arrive[(b * a.Hkv + g) * TW_CTR + tid] = 0;
 }
@@ -343,8 +447,14 @@ __global__ __launch_bounds__(NT, E == 8 || E == 16 ? 8 : 1) void page_select_reg
 }
 
 template <int G>
-void launch_score(const ScoreArgs& a, dim3 grid, bool append, int bits, hipStream_t s) {
-  if (!append)        TW_LAUNCH((page_score_kernel<G, false>), grid, dim3(256), 0, s, a);
+void launch_score(const ScoreArgs& a, dim3 grid, bool many, bool append, int bits, hipStream_t s) {
+  if (many) {
+    if (!append)        TW_LAUNCH((page_score_long_kernel<G, false>), grid, dim3(256), 0, s, a);
+    else if (bits == 4) TW_LAUNCH((page_score_long_kernel<G, true, 4>), grid, dim3(256), 0, s, a);
+    else if (bits == 8) TW_LAUNCH((page_score_long_kernel<G, true, 8>), grid, dim3(256), 0, s, a);
+    else                TW_LAUNCH((page_score_long_kernel<G, true, 2>), grid, dim3(256), 0, s, a);
+  }
+  else if (!append)   TW_LAUNCH((page_score_kernel<G, false>), grid, dim3(256), 0, s, a);
   else if (bits == 4) TW_LAUNCH((page_score_kernel<G, true, 4>), grid, dim3(256), 0, s, a);
   else if (bits == 8) TW_LAUNCH((page_score_kernel<G, true, 8>), grid, dim3(256), 0, s, a);
   else                TW_LAUNCH((page_score_kernel<G, true, 2>), grid, dim3(256), 0, s, a);
@@ -418,13 +528,19 @@ static int select_impl(const twilight_kv_t* kv, const void* q, const int32_t* bu
   a.kq_pool = (uint32_t*)kv->kq_pool; a.kq_meta = (uint32_t*)kv->kq_meta;
   a.page_minmax_w = (uint4*)kv->page_minmax;
   a.arrive = arrive;
-  dim3 grid(d.Hkv, (d.max_pages + PS_PAGES_PER_WG - 1) / PS_PAGES_PER_WG, d.batch);
+  // page_score_long_kernel from 16 of its workgroups per CU on: both forms, us, at 16 x 32768 tokens (4096 workgroups) 86.0 / 85.0,
+  // at 32 ragged sequences of up to 16384, most of whose workgroups are empty, 56.2 / 56.5; below it has too few to fill the
+  // chip (512: 2 x 32768 36.2 / 37.2, 4 x 16384 with 8 bits 32.8 / 33.5).  128 pages per workgroup: 64 ragged of up to 16384
+  // 86.4 / 88.6.
+  const int wide = (d.max_pages + PS_LONG_PAGES - 1) / PS_LONG_PAGES;
+  const bool many = (long long)d.batch * d.Hkv * wide >= 16ll * tw_num_cus();
+  const dim3 grid(d.Hkv, many ? wide : (d.max_pages + PS_PAGES_PER_WG - 1) / PS_PAGES_PER_WG, d.batch);
   tw_prof_before(TW_K_PAGE_SCORE, s);
   switch (d.G) {
-    case 1: launch_score<1>(a, grid, append, d.bits, s); break;
-    case 2: launch_score<2>(a, grid, append, d.bits, s); break;
-    case 4: launch_score<4>(a, grid, append, d.bits, s); break;
-    default: launch_score<8>(a, grid, append, d.bits, s); break;
+    case 1: launch_score<1>(a, grid, many, append, d.bits, s); break;
+    case 2: launch_score<2>(a, grid, many, append, d.bits, s); break;
+    case 4: launch_score<4>(a, grid, many, append, d.bits, s); break;
+    default: launch_score<8>(a, grid, many, append, d.bits, s); break;
   }
   if (int e = tw_prof_after(s)) return e;
   if (bounds_only) return TW_OK;

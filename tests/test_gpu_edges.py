@@ -276,3 +276,53 @@ def _same_lists(sa, sb):
         xa, xb = (getattr(s, name).reshape(len(ca), -1).cpu() for s in (sa, sb))
         for i, c in enumerate(ca):
             assert torch.equal(xa[i, :c], xb[i, :c]), (name, i)
+
+
+@pytest.mark.parametrize("G,bits", [(1, 4), (2, 2), (4, 4), (4, 8), (8, 4)])
+def test_page_bounds_under_a_long_page_table(G, bits):
+    """The bound scores' workgroups cover 32 or 64 pages, by the width of the page table: lists, bounds of every page and
+    the cache with the step's token appended are the same under both, at rows that end at the edges of 16-page steps and of workgroups, with unmapped pages, a token on one of them, and a sequence without a new token."""
+    T = _T()
+    lens = [1, 16 * 32, 16 * 32 + 1, 16 * 64, 16 * 64 + 1, 16 * 128 + 1, 16 * 256, 16 * 256 + 1, 16 * 80 + 5, 16 * 49 - 3, 777]
+    w = synth.make_workload("steps", lens, num_q_heads=8 * G, num_kv_heads=8, budget=[max(16, n // 4) for n in lens], p=0.9,
+                            heavy_frac=0.01, alpha_range=(0.0, 3.0), shuffle_pool=True, extra_pool_pages=3, seed=29)
+    dev = "cuda"
+    table = w.page_table.clone()
+    table[4, 3] = table[8, 80] = -1                       # (sequence 8: its last page, that of the new token)
+    offs = torch.tensor(w.seq_offsets[:-1], dtype=torch.int32, device=dev)
+    k, v, q, budget = w.k.to(dev), w.v.to(dev), w.q.to(dev), w.budget.to(dev)
+    last = torch.tensor([o - 1 for o in w.seq_offsets[1:]], dtype=torch.int64, device=dev)
+    pos = (w.seq_lens.to(dev, torch.int32) - 1).contiguous()
+    pos[10] = -1
+    max_sel = max(-(-int(b) // 16) for b in w.budget)
+    got = []
+    for width in (table.shape[1], 3000, 3009):            # 11 x 8 rows: 440 and 4136 workgroups of 64 pages, for 256 CUs
+        wide = torch.full((len(lens), width), -1, dtype=torch.int32)
+        wide[:, :table.shape[1]] = table
+        c = T.PagedKV(8 * G, 8, wide, w.seq_lens, w.num_pool_pages, dev, quant_bits=bits)
+        c.append(k, v, torch.zeros_like(pos), torch.where(pos >= 0, c.seq_lens - 1, c.seq_lens), offs, max(lens))
+        st = T.DecodeStep(c, max_sel=max_sel)
+        st.append_select(k[last].contiguous(), v[last].contiguous(), pos, q, budget)
+        torch.cuda.synchronize()
+        rows = st.ws_select[:len(lens) * 8 * G * width * 4].view(torch.int32).view(len(lens), 8 * G, width)
+        got.append([[rows[b, :, :(n + 15) // 16].cpu() for b, n in enumerate(lens)], c, st])
+        again = T.DecodeStep(c, max_sel=max_sel)          # nothing appended: the same lists (sequence 10 has its old bounds either way)
+        again.select(q, budget)
+        for b in range(len(lens)):
+            for h in range(8 * G):
+                n = int(st.sel_count[b, h])
+                assert n == int(again.sel_count[b, h]) and torch.equal(st.sel_pages[b, h, :n], again.sel_pages[b, h, :n]), (width, b, h)
+    base = got[0]
+    for rows, c, st in got[1:]:
+        for b in range(len(lens)):
+            assert torch.equal(rows[b], base[0][b]), (c.max_pages, b)
+        for name in ("k_pool", "v_pool", "kq_pool", "kq_meta", "page_minmax"):
+            assert torch.equal(getattr(c, name).view(torch.uint8), getattr(base[1], name).view(torch.uint8)), (c.max_pages, name)
+    # the bounds themselves, of one sequence, from the cache's page bounds
+    mm = base[1].page_minmax[table[7].to(dev).long()].double().cpu()               # [pages, 8, 2, 128]
+    qd = w.q[7].double().view(8, G, 1, 128)
+    want = torch.maximum(qd * mm[:, :, 0].permute(1, 0, 2)[:, None], qd * mm[:, :, 1].permute(1, 0, 2)[:, None]).sum(-1).view(8 * G, -1)
+    have = base[0][7].view(torch.float32).double()
+    # 128 fp32 additions: at most 12 in a chain (8 in a lane, 4 levels), each within 2^-24 of sums below the sum of magnitudes
+    lim = 12 * 2.0 ** -24 * (qd.abs() * mm.abs().amax(2).permute(1, 0, 2)[:, None]).sum(-1).view(8 * G, -1)
+    assert bool(((have - want).abs() <= lim).all())
