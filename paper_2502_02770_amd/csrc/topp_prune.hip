@@ -339,15 +339,22 @@ __global__ __launch_bounds__(256) void int4_score_tokens_kernel(ScoreArgs a) {
   const long long row = ((long long)(b * a.Hq + h0)) * a.cand_stride;
   long long slot4[IT];                              // (token slot in the pool) * 4 + group, or -1
   auto translate = [&]() {
+    // unconditional loads at clamped places (by minima: a selected index became a branch with a wait of its own), so
+    // that no step's wait for another's: 33.6 -> 30.4 us for 256 heads x 4096 of 32768 tokens
+    uint32_t tok[IT], pp[IT];
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
       const int c = wg_first + it * 64 + (tid >> 2);
-      const int tok = c < count ? a.sel_pages[row + c] : -1;
-      slot4[it] = -1;
-      if (tok >= 0 && tok < ntok) {
-        const int pp = a.page_table[(long long)b * a.max_pages + (tok >> 4)];
-        if (pp >= 0 && pp < a.pool_pages) slot4[it] = ((((long long)pp * a.Hkv + g) * TW_PAGE + (tok & 15)) << 2) + j;
-      }
+      tok[it] = a.sel_pages[row + min(c, count - 1)];
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it)
+      pp[it] = a.page_table[(long long)b * a.max_pages + (min(tok[it], (uint32_t)max(ntok - 1, 0)) >> 4)];
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const bool ok = (tok[it] < (uint32_t)ntok) & (wg_first + it * 64 + (tid >> 2) < count) & ((long long)pp[it] < a.pool_pages);
+      const long long slot = (((((long long)pp[it] * a.Hkv + g) * TW_PAGE + (tok[it] & 15)) << 2) + j);
+      slot4[it] = ok ? slot : -1ll;
     }
   };
   translate();
