@@ -325,8 +325,8 @@ __global__ __launch_bounds__(256) void int4_score_tokens_kernel(ScoreArgs a) {
   constexpr int IT = 4;
   const int tid = threadIdx.x, j = tid & 3;
   const int b = blockIdx.y / a.Hq, h0 = blockIdx.y % a.Hq, g = h0 / (a.Hq / a.Hkv);
-  const int n = a.seq_lens[b];
-  const int ntok = n < a.max_pages * TW_PAGE ? n : a.max_pages * TW_PAGE;
+  // (at least 0: the bound of the unsigned comparison below, and an empty sequence's length may be negative)
+  const int ntok = max(0, min(a.seq_lens[b], a.max_pages * TW_PAGE));
   int count = a.sel_count[b * a.Hq + h0];
   if (count > a.max_sel) count = a.max_sel;
   // chunk columns as in the page-list kernel: a grid a multiple of 8 wide is rotated by the KV group's number
@@ -1206,7 +1206,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
     for (int e = 0; e < EPT; ++e) {
       if ((keep >> e) & 1u) {                       // kept => valid score => a token inside the sequence
         const int tok = pg[e % NPG];
-        if (tok < BWORDS * 32) atomicOr(&bitmap[tok >> 5], 1u << (tok & 31));
+        if ((uint32_t)tok < (uint32_t)(BWORDS * 32)) atomicOr(&bitmap[tok >> 5], 1u << (tok & 31));
         if (out) { if (pos < (uint32_t)a.kept_stride) out[pos] = tok; ++pos; }
       }
     }

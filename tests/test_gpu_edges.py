@@ -326,3 +326,37 @@ def test_page_bounds_under_a_long_page_table(G, bits):
     # 128 fp32 additions: at most 12 in a chain (8 in a lane, 4 levels), each within 2^-24 of sums below the sum of magnitudes
     lim = 12 * 2.0 ** -24 * (qd.abs() * mm.abs().amax(2).permute(1, 0, 2)[:, None]).sum(-1).view(8 * G, -1)
     assert bool(((have - want).abs() <= lim).all())
+
+
+@pytest.mark.parametrize("bits", [2, 4, 8])
+def test_token_lists_of_sequences_without_tokens(bits):
+    """Lengths of 0 and below next to a sequence of 100 tokens: no entry of an empty sequence's lists lies inside it, whatever
+    its value, so its scores are -inf, its integer dot products 0, and nothing of it is kept."""
+    T = _T()
+    w = synth.make_workload("empty", [100] * 5, num_q_heads=4, num_kv_heads=2, budget=64, p=1.0, seed=97)
+    cache = build_cache(w, bits=bits)
+    lens = [0, -1, 100, -33, -2 ** 31]
+    cache.seq_lens.copy_(torch.tensor(lens, dtype=torch.int32))
+    dev, max_cand = cache.device, 272                     # more than the 256 candidates of a scoring workgroup
+    ids = np.resize(np.array([-2 ** 31, -4097, -5, -1, 0, 1, 15, 16, 31, 99, 100, 111, 112, 1 << 20, 2 ** 31 - 1], np.int32), max_cand)
+    cand = torch.from_numpy(np.tile(ids, (5, 4, 1))).to(dev)
+    cnt = torch.tensor([max_cand, 15, 1, 271], dtype=torch.int32, device=dev).repeat(5, 1)
+    q = w.q.to(dev)
+    sc = torch.full((5, 4, max_cand), 7.0, dtype=torch.float32, device=dev)
+    dots = torch.full((5, 4, max_cand, 4), 7, dtype=torch.int32, device=dev)
+    T.twilight_int4_score_tokens(cache.kv, q, cand, cnt, max_cand, sc, dots)
+    st = T.DecodeStep(cache, max_sel=max_cand // 16, with_kept_idx=True)
+    ws = torch.empty(T.twilight_workspace_bytes(T.TW_WS_PRUNE_TOKENS, cache.kv, max_cand), dtype=torch.uint8, device=dev)
+    T.twilight_topp_prune_tokens(cache.kv, q, cand, cnt, max_cand, w.p, st.kept_count, st.kept_idx, st.kept_stride,
+                                 st.union_count, st.union_idx, st.union_stride, st.status, ws)
+    torch.cuda.synchronize()
+    for b, n in enumerate(lens):
+        for h in range(4):
+            c = int(cnt[b, h])
+            inside = (ids[:c] >= 0) & (ids[:c] < n)
+            assert np.array_equal(np.isfinite(sc[b, h, :c].cpu().numpy()), inside), (b, h)
+            assert not dots[b, h, :c].cpu().numpy()[~inside].any(), (b, h)
+            assert st.kept_idx[b, h, :int(st.kept_count[b, h])].cpu().numpy().tolist() == ids[:c][inside].tolist(), (b, h)
+        for g in range(2):
+            inside = np.unique(ids[(ids >= 0) & (ids < n)])
+            assert st.union_idx[2 * b + g, :int(st.union_count[2 * b + g])].cpu().numpy().tolist() == inside.tolist(), (b, g)
