@@ -300,7 +300,8 @@ def describe(w, scale):
 def profile_figures(dom):
     """What profiles/ holds for the dominant kernel of the headline configuration: the kernel-trace duration and the
     HBM traffic per dispatch from the counter runs.  Read from the committed summaries at run time; None when the
-    summaries do not list a kernel of that stage."""
+    summaries do not list a kernel of that stage, the traffic also when its summary lists that kernel at another grid
+    (or another kernel of the stage): it is then an earlier kernel's."""
     from paper_2502_02770_amd.rocprof_summary import read_trace_table, read_traffic_table
     stem = {"page_score": "page_score", "int4_score": "int4_score", "sparse_decode": "sparse_decode_kernel",
             "topp": "topp_head_kernel", "score_topp": "topp_head_kernel", "select_score_topp": "topp_head_kernel",
@@ -308,18 +309,16 @@ def profile_figures(dom):
             "kquant_append": "kquant_append_kernel"}.get(dom, dom)
     tr_file, tf_file = "c2_decode_step_kernel_trace.md", "c2_decode_step_hbm_traffic.md"
     tr = {k: v for k, v in read_trace_table(os.path.join(PROFILES, tr_file)).items() if k.startswith(stem)}
-    tf = {k: v for k, v in read_traffic_table(os.path.join(PROFILES, tf_file)).items() if k[0].startswith(stem)}
     out = {"traffic": None, "traffic_source": None, "rocprofv3_kernel_us": None, "rocprofv3_source": None}
     if tr:
         name = max(tr, key=lambda k: tr[k]["calls"])
         out["rocprofv3_kernel_us"] = tr[name]["avg_ns"] / 1e3
         out["rocprofv3_kernel_median_us"] = tr[name]["median_ns"] / 1e3
         out["rocprofv3_source"] = "profiles/%s: `%s`, %d calls" % (tr_file, name, tr[name]["calls"])
-        tf = {k: v for k, v in tf.items() if k[0] == name} or tf
-    if tf:
-        key = max(tf, key=lambda k: tf[k])
-        out["traffic"] = tf[key]
-        out["traffic_source"] = "profiles/%s: `%s` (FETCH_SIZE and WRITE_SIZE scaled by the copy-kernel calibration stated there)" % (tf_file, key[0])
+        traffic = read_traffic_table(os.path.join(PROFILES, tf_file)).get((name, tr[name]["threads"]))
+        if traffic is not None:
+            out["traffic"] = traffic
+            out["traffic_source"] = "profiles/%s: `%s` (FETCH_SIZE and WRITE_SIZE scaled by the copy-kernel calibration stated there)" % (tf_file, name)
     return out
 
 

@@ -15,6 +15,7 @@ duration and the HBM traffic of its dominant kernel beside the live figure.
 import collections
 import csv
 import glob
+import math
 import os
 import re
 import sys
@@ -45,7 +46,7 @@ def trace_rows(d):
     for r in csv.DictReader(open(_one("*kernel_trace.csv", d))):
         k = short_name(r["Kernel_Name"])
         dur[k].append(int(r["End_Timestamp"]) - int(r["Start_Timestamp"]))
-        grid[k] = "%sx%s" % (r.get("Grid_Size_X", r.get("Grid_Size", "?")), r.get("Grid_Size_Y", "1"))
+        grid[k] = "%sx%sx%s" % (r.get("Grid_Size_X", r.get("Grid_Size", "?")), r.get("Grid_Size_Y", "1"), r.get("Grid_Size_Z", "1"))
     rows = []
     for k, v in sorted(dur.items(), key=lambda kv: -sum(kv[1])):
         if k.startswith("torch_") or "rocclr" in k or "Cijk" in k:
@@ -104,22 +105,22 @@ def _table(path):
 
 
 def read_trace_table(path):
-    """-> {kernel name: {"calls", "median_ns", "avg_ns"}} from a summary written by `trace`."""
+    """-> {kernel name: {"threads", "calls", "median_ns", "avg_ns"}} from a summary written by `trace`."""
     out = {}
     for r in _table(path):
         try:
-            out[r[0]] = {"calls": int(r[2]), "median_ns": int(r[3]), "avg_ns": int(r[4])}
+            out[r[0]] = {"threads": math.prod(int(x) for x in r[1].split("x")), "calls": int(r[2]), "median_ns": int(r[3]), "avg_ns": int(r[4])}
         except (IndexError, ValueError):         # a table of another layout
             pass
     return out
 
 
 def read_traffic_table(path):
-    """-> {(kernel name, grid): HBM bytes per dispatch} from a summary written by `traffic`."""
+    """-> {(kernel name, threads): HBM bytes per dispatch} from a summary written by `traffic`."""
     out = {}
     for r in _table(path):
         try:
-            out[(r[0], r[1])] = int(r[5])
+            out[(r[0], int(r[1]))] = int(r[5])
         except (IndexError, ValueError):
             pass
     return out
