@@ -56,7 +56,6 @@ __device__ __forceinline__ float tw_row_bcast(float v) {
 }
 #define TW_DPP_ROR4 0x124
 #define TW_DPP_ROR8 0x128
-#define TW_DPP_ROR12 0x12C
 
 typedef __bf16 tw_bf16x2 __attribute__((ext_vector_type(2)));
 // a.lo * b.lo + a.hi * b.hi + c on bf16 pairs (v_dot2c_f32_bf16)

@@ -772,7 +772,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
   // SELECT with few candidates: the row of pages is bounded too (the launch's rule), and LDS is sized for that
   constexpr bool SMALL = FUSE == 2 && NT <= 512 && EPT == 4;
   constexpr int SEL_E = SMALL ? 4 : (SPLIT ? 8192 : 4096) / NT;
-  constexpr int BWORDS = SMALL ? SEL_E * NT * TW_PAGE / 32 : (SELECT ? SEL_E * NT * TW_PAGE / 32 : HP_BITMAP_WORDS);
+  constexpr int BWORDS = SELECT ? SEL_E * NT * TW_PAGE / 32 : HP_BITMAP_WORDS;
   constexpr int USTAGE = SMALL ? 4 * NT : HP_USTAGE;
   constexpr int AREA = SELECT ? (NT * EPT > USTAGE ? NT * EPT : USTAGE) : USTAGE;
   constexpr bool SEL_EARLY = SELECT && NT >= 1024;
@@ -1571,12 +1571,14 @@ int launch_topp(HeadArgs f, const TwDims& d, int cand_stride, hipStream_t s) {
   const long long heads = (long long)d.batch * d.Hq;
   f.remap = (FUSE != 0 && ((long long)d.batch * d.Hkv) % 8 == 0) ? 1 : 0;
   f.n_above = -1; f.n_upto = cand_stride;
-  if (FUSE == 0 && cand_stride > 4096 && heads > 2ll * tw_num_cus()) {
-    f.n_upto = 4096;
-    tw_prof_before(TW_K_TOPP, s);
-    launch_topp_one<512, 8, TOK, FUSE, BITS>(f, d.G, grid, s);
-    if (int e = tw_prof_after(s)) return e;
-    f.n_above = 4096; f.n_upto = cand_stride;
+  if constexpr (FUSE == 0) {
+    if (cand_stride > 4096 && heads > 2ll * tw_num_cus()) {
+      f.n_upto = 4096;
+      tw_prof_before(TW_K_TOPP, s);
+      launch_topp_one<512, 8, TOK, FUSE, BITS>(f, d.G, grid, s);
+      if (int e = tw_prof_after(s)) return e;
+      f.n_above = 4096; f.n_upto = cand_stride;
+    }
   }
   if constexpr (FUSE == 3) {
     tw_prof_before(TW_K_SELECT_SCORE_TOPP, s);
