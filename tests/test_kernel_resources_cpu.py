@@ -70,11 +70,13 @@ def test_selection_of_up_to_16384_entries_runs_two_workgroups_per_cu(kernels, sl
 
 
 @pytest.mark.parametrize("bits", [2, 4, 8])
-@pytest.mark.parametrize("candidates,workgroups", [(8, 4), (16, 3)])
-def test_one_launch_pruner_of_many_heads_shares_the_cu(kernels, candidates, workgroups, bits):
+@pytest.mark.parametrize("candidates,workgroups,spilled", [(8, 4, 8), (16, 3, 0)])
+def test_one_launch_pruner_of_many_heads_shares_the_cu(kernels, candidates, workgroups, spilled, bits):
+    """The launch bounds make the registers fit, by spilling if need be: what they may spill is what was measured to pay."""
     for G in (1, 2, 4, 8):
         k = kernels["topp_head_kernel<512, %d, %d, false, 2, %d>" % (candidates, G, bits)]
         assert _fits(k, workgroups), k[".vgpr_count"]
+        assert k[".vgpr_spill_count"] <= spilled and k[".private_segment_fixed_size"] <= (68 if spilled else 0)
         assert k[".group_segment_fixed_size"] * workgroups <= 160 * 1024
 
 
