@@ -183,23 +183,14 @@ def percentiles(t):
     return {"p10": float(qs[0]), "p50": float(qs[1]), "p90": float(qs[2]), "max": float(x.max()), "mean": float(x.mean())}
 
 
-def decode_balance(T, cache, union_count, union_stride):
-    """How evenly the flattened attention work list spreads over the persistent grid: the kernel's own rule
-    (chunk length of twilight_prof.h; workgroup w takes items w, w + grid, ...) applied to the list lengths read back from the device."""
-    grid, c0, ipw = T.twilight_decode_plan(cache.kv, T.TW_WS_DECODE, False)
-    cnt = [min(int(c), union_stride) for c in union_count.cpu().tolist()]
-    total, lists = sum(cnt), len(cnt)
-    wgs = min(grid, lists * -(-union_stride // c0))
-    best = None
-    for r in range(1 + lists // wgs, 1 + lists // wgs + ipw):
-        c = max(c0, (total // (wgs * r - lists // 2) + 64) // 64 * 64)
-        if best is None or r * (c + 64) < best[0]:
-            best = (r * (c + 64), c, r)
-    _, chunk, rounds = best
-    for _ in range(3):
-        if sum(-(-n // chunk) for n in cnt) <= rounds * wgs:
-            break
-        chunk += (chunk // 32 + 64) // 64 * 64
+def decode_balance(T, cache, st):
+    """How evenly the flattened attention work list of the last step spreads over the persistent grid (workgroup w takes items
+    w, w + grid, ...): the lists' lengths and the numbers of chunks that the kernel cut them into, which it leaves at the start
+    of its workspace, read back from the device; the chunk length is the shortest multiple of 64 that gives those numbers."""
+    grid, _, _ = T.twilight_decode_plan(cache.kv, T.TW_WS_DECODE, False)
+    cnt = [min(int(c), st.union_stride) for c in st.union_count.cpu().tolist()]
+    first = st.ws_decode[:4 * (len(cnt) + 1)].view(st.union_count.dtype).cpu().tolist()
+    chunk = max([64] + [-(-n // (64 * (b - a))) * 64 for n, a, b in zip(cnt, first, first[1:]) if b > a])
     items = []
     for n in cnt:
         items += [min(chunk, n - t0) for t0 in range(0, n, chunk)]
@@ -617,7 +608,7 @@ def main():
     hist = {"kept_per_head": percentiles(st.kept_count), "union_per_group": percentiles(st.union_count)}
     if not st.full:
         hist["candidates_per_head"] = percentiles(st.sel_count * 16)
-    balance = decode_balance(T, cache, st.union_count, st.union_stride) if w.v.numel() else None
+    balance = decode_balance(T, cache, st) if w.v.numel() else None
 
     # dense decode attention through the same kernel, for the "below dense" comparison
     dense_us = None

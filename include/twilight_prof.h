@@ -60,9 +60,11 @@ const char* twilight_kernel_name(int kernel_id);
  * workgroup the kernel weighs against each other.  With W workgroups, T list
  * entries in N lists and r0 = 1 + N / W, for r = r0 .. r0 + items_per_wg - 1:
  * c = T / (W * r - N / 2) rounded up to a multiple of 64 (more than T / ...,
- * at least chunk0); the r with the least r * (c + 64) gives the chunk, made
- * longer by steps of 1/32 (at least 64) up to three times while the lists
- * still have more than r * W chunks.
+ * at least chunk0), priced at r * (c + 64).  Up to 64 lists: the cheapest
+ * gives the chunk, made longer by steps of 1/32 (at least 64) up to three
+ * times while the lists still have more than r * W chunks.  More lists:
+ * against the longest list in 1 to 4 pieces too, and where the counted chunks
+ * are more than foreseen, the cheapest by the counted ones.
  * which = TW_WS_DECODE or TW_WS_DECODE_PER_HEAD.  For reports on how evenly
  * ragged lists spread over the workgroups (Section 4.2, load balancing).
  */

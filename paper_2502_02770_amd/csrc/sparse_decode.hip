@@ -24,7 +24,8 @@ constexpr float kLn2 = 0x1.62e43p-1f;
 constexpr float kNegBig = -1.0e30f;              // finite stand-in for -inf in running maxima
 constexpr unsigned DEC_MAX_ROUNDS = 3;           // items per workgroup that decode_chunk weighs against each other
 constexpr unsigned DEC_UNIT = 64;                // entries of a step of the four waves
-constexpr unsigned DEC_ITEM_ROWS = 64;           // rows that an item's set-up and merge are worth
+constexpr unsigned DEC_ITEM_ROWS = 64;           // rows that an item's set-up and merge are worth ...
+constexpr unsigned DEC_CUT_ROWS = 64;            // ... and that merging the pieces of cut lists is
 
 struct DecodeArgs {
   const uint4* q;             // bf16 [b][Hq][16 x uint4]
@@ -107,6 +108,57 @@ __device__ __forceinline__ uint32_t decode_chunk(uint32_t T, uint32_t NG, uint32
 // more than that many items after all (lists whose last chunks are emptier)
 __device__ __forceinline__ uint32_t decode_longer(uint32_t chunk) { return chunk + (((chunk >> 5) + DEC_UNIT) & ~(DEC_UNIT - 1u)); }
 
+// The same for more than 64 lists, where whole lists can be the better items.  Lane j of the wave weighs one way, 0 .. 3: every
+// list in at most j + 1 pieces, which is certain to leave a workgroup no more than ceil(NG * (j + 1) / W) items; 4 .. 6: the
+// three of decode_chunk, which may turn out more (many short lists: their last chunks are emptier).
+struct DecodePlan {
+  uint32_t W, chunk, rounds;   // the best of the ways and its items per workgroup
+  uint32_t other;              // chunk of the best of the other numbers of items, 0: none
+  uint32_t longer, best, best_chunk;
+  int state;
+  __device__ __forceinline__ DecodePlan(uint32_t T, uint32_t longest, uint32_t NG, uint32_t W_, uint32_t chunk0) : W(W_), state(0) {
+    const uint32_t lane = threadIdx.x & 63u, k = lane < 4u ? lane + 1u : 1u;
+    const bool sure = lane < 4u;
+    const uint32_t units = (longest + DEC_UNIT - 1u) / DEC_UNIT;
+    const uint32_t q = (sure ? NG * k + W - 1u : NG) / W, r = sure ? q : q + lane - 3u;
+    const uint32_t len = (sure ? units + k - 1u : T) / (sure ? k : W * r - NG / 2u);
+    uint32_t c = sure ? len * DEC_UNIT : (len + DEC_UNIT) & ~(DEC_UNIT - 1u);
+    c = c < chunk0 ? chunk0 : c;
+    const bool whole = c >= units * DEC_UNIT;
+    const uint32_t cost = lane < 4u + DEC_MAX_ROUNDS ? r * ((whole ? units * DEC_UNIT : c) + DEC_ITEM_ROWS) + (whole ? 0u : DEC_CUT_ROWS) : 0xFFFFFFFFu;
+    // of equals the first: fewer items
+    auto least = [&](uint32_t x) -> int { return __builtin_ctzll(__ballot(x == ~tw_wave_max_u32(~x))); };
+    const int at = least(cost), at_sure = least(sure ? cost : 0xFFFFFFFFu);
+    chunk = longer = (uint32_t)__builtin_amdgcn_readlane((int)c, at);
+    rounds = (uint32_t)__builtin_amdgcn_readlane((int)r, at);
+    best = (uint32_t)__builtin_amdgcn_readlane((int)cost, at_sure);
+    best_chunk = (uint32_t)__builtin_amdgcn_readlane((int)c, at_sure);
+    const uint32_t others = !sure && c != chunk ? cost : 0xFFFFFFFFu;
+    const int at_other = least(others);
+    other = (uint32_t)__builtin_amdgcn_readlane((int)others, at_other) == 0xFFFFFFFFu ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)c, at_other);
+  }
+  // The chunks have `items` items.  False: they are taken.  True: `chunk` is another length, to be counted: that of another
+  // number of items per workgroup, then longer ones while they can still be better, then the best of all if it was not the last.
+  // (Made longer only, 744 lists of 61 entries on average ended at 256: 16.6 us, now 15.0; 1088 of 82 at 320: 27.1 and 19.6.)
+  __device__ __forceinline__ bool again(uint32_t items) {
+    if (state == 5 || (state == 0 && items <= rounds * W)) return false;
+    const uint32_t cost = (items + W - 1u) / W * (chunk + DEC_ITEM_ROWS) + DEC_CUT_ROWS;
+    if (cost < best || (cost == best && chunk > best_chunk)) { best = cost; best_chunk = chunk; }
+    if (++state == 1) {
+      if (other) { chunk = other; return true; }
+      ++state;
+    }
+    if (state < 5) {
+      longer = decode_longer(longer);
+      if (rounds * (longer + DEC_ITEM_ROWS) + DEC_CUT_ROWS < best) { chunk = longer; return true; }
+    }
+    state = 5;
+    if (chunk == best_chunk) return false;
+    chunk = best_chunk;
+    return true;
+  }
+};
+
 // What bounds it: few and short lists the chain length -> list entry -> page table -> K/V row -> merge, so every wave
 // makes the item map and looks its rows up by itself and the only barrier of an item is the merge's (1 x 4096 tokens 5.9 ->
 // 4.7 us, 4 x 16384 8.6 -> 7.3; with the map, the rows and the running maxima passed around the workgroup through LDS
@@ -119,6 +171,7 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : (G == 4 ? 3 : 4)) void sparse_dec
   constexpr int R = (G + 3) / 4;                 // score values a lane ends up owning per step
   extern __shared__ int32_t prefix[];            // [NG + 1]
   __shared__ uint32_t wsum[16];
+  __shared__ uint2 sum_s[4];
   __shared__ float2 macc[4][G][64];              // the waves' accumulators ...
   __shared__ float2 ml_s[4][G];                  // ... and their (maximum, denominator)
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), seg = tid & 15, row = lane >> 4;
@@ -134,10 +187,11 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : (G == 4 ? 3 : 4)) void sparse_dec
 
   // ---- chunk length, item map (exclusive prefix of the lists' chunk counts) and this workgroup's first item
   const uint32_t W = gridDim.x;
-  uint32_t chunk, rounds;
+  uint32_t chunk;
   int total_items, item = blockIdx.x, gi = 0, ck = 0, nchunks = 0;
   if (a.NG <= 64) {                               // block-uniform: lane l of every wave holds list l, no barrier
     const uint32_t c = lane < a.NG ? length(lane) : 0u;
+    uint32_t rounds;
     chunk = decode_chunk((uint32_t)__builtin_amdgcn_readlane((int)tw_wave_scan_u32(c), 63), (uint32_t)a.NG, W, (uint32_t)a.chunk0, &rounds);
     uint32_t n = 0, incl = 0;
 #pragma unroll 1
@@ -155,26 +209,49 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : (G == 4 ? 3 : 4)) void sparse_dec
     if (wave == 0 && lane < a.NG) prefix[lane] = (int32_t)(incl - n);
     if (tid == 0) prefix[a.NG] = total_items;
   } else {                                        // thread t: the lists t * K ..
-    const int K = (a.NG + 255) >> 8, i0 = tid * K;
-    const uint32_t c0 = i0 < a.NG ? length(i0) : 0u, c1 = K > 1 && i0 + 1 < a.NG ? length(i0 + 1) : 0u;   // (the others are read again)
-    auto len_of = [&](int k) -> uint32_t { return k == 0 ? c0 : (k == 1 ? c1 : (i0 + k < a.NG ? length(i0 + k) : 0u)); };
-    uint32_t T = 0, total;
-    for (int k = 0; k < K; ++k) T += len_of(k);
-    (void)tw_block_scan_u32(T, wsum, &total);
-    chunk = decode_chunk(total, (uint32_t)a.NG, W, (uint32_t)a.chunk0, &rounds);
-    uint32_t n = 0, incl = 0;
-#pragma unroll 1
-    for (int trial = 0; trial < 4; ++trial) {
-      if (trial) chunk = decode_longer(chunk);
-      n = 0;
-      for (int k = 0; k < K; ++k) n += (len_of(k) + chunk - 1u) / chunk;
-      incl = tw_block_scan_u32(n, wsum, &total);
-      if (total <= rounds * W) break;             // (block-uniform)
+    // (more than two to a thread: read in whole lines, through LDS, K odd so that the lanes' words lie on different banks; read
+    //  by their threads in every pass 6144 lists took 59.4 us, now 37.9)
+    const int K1 = (a.NG + 255) >> 8, K = K1 > 2 ? K1 | 1 : K1, i0 = tid * K;
+    uint32_t T = 0, longest = 0, c0 = 0, c1 = 0;
+    if (K > 2) {
+      for (int i = tid; i < a.NG; i += 256) {
+        const uint32_t v = length(i);
+        prefix[i] = (int32_t)v;
+        T += v;
+        longest = v > longest ? v : longest;
+      }
+    } else {
+      c0 = i0 < a.NG ? length(i0) : 0u;
+      c1 = K > 1 && i0 + 1 < a.NG ? length(i0 + 1) : 0u;
+      T = c0 + c1;
+      longest = c0 > c1 ? c0 : c1;
     }
+    T = tw_wave_scan_u32(T);
+    longest = tw_wave_max_u32(longest);
+    if (lane == 63) sum_s[wave] = make_uint2(T, longest);
+    __syncthreads();
+    T = 0; longest = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const uint2 x = sum_s[w];
+      T += x.x;
+      longest = x.y > longest ? x.y : longest;
+    }
+    DecodePlan plan(T, longest, (uint32_t)a.NG, W, (uint32_t)a.chunk0);
+    auto len_of = [&](int k) -> uint32_t { return K > 2 ? (i0 + k < a.NG ? (uint32_t)prefix[i0 + k] : 0u) : (k ? c1 : c0); };
+    uint32_t n = 0, incl = 0, total;
+#pragma unroll 1
+    do {                                          // (block-uniform)
+      n = 0;
+      for (int k = 0; k < K; ++k) n += (len_of(k) + plan.chunk - 1u) / plan.chunk;
+      incl = tw_block_scan_u32(n, wsum, &total);
+    } while (plan.again(total));
+    chunk = plan.chunk;
     n = incl - n;
     for (int k = 0; k < K; ++k) {
+      const uint32_t v = len_of(k);
       if (i0 + k < a.NG) prefix[i0 + k] = (int32_t)n;
-      n += (len_of(k) + chunk - 1u) / chunk;
+      n += (v + chunk - 1u) / chunk;
     }
     total_items = (int)total;
     if (tid == 0) prefix[a.NG] = total_items;

@@ -391,3 +391,83 @@ def test_token_lists_of_sequences_without_tokens(bits):
         for g in range(2):
             inside = np.unique(ids[(ids >= 0) & (ids < n)])
             assert st.union_idx[2 * b + g, :int(st.union_count[2 * b + g])].cpu().numpy().tolist() == inside.tolist(), (b, g)
+
+
+def _attend_lists(T, G, H, lens, n, seed):
+    """Attention of sequences of n tokens over lists of lens[l] entries (H lists per sequence): outputs against float64."""
+    batch, P, stride = len(lens) // H, (n + 15) // 16, max(64, int(max(lens)))
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    cache = T.PagedKV(G * H, H, torch.randperm(batch * P, generator=torch.Generator().manual_seed(seed)).int().view(batch, P), torch.full((batch,), n), batch * P)
+    cache.k_pool.normal_(generator=g)
+    cache.v_pool.normal_(generator=g)
+    q = torch.randn(batch, G * H, 128, device="cuda", generator=g).to(torch.bfloat16)
+    lens = torch.as_tensor(lens, device="cuda")
+    idx = torch.rand(len(lens), n, device="cuda", generator=g).argsort(dim=1)[:, :stride]
+    idx = idx.masked_fill(torch.arange(idx.shape[1], device="cuda") >= lens[:, None], n).sort(dim=1).values       # n: does not count
+    st = T.DecodeStep(cache, max_sel=1, union_stride=stride)
+    st.union_count.copy_(lens)
+    st.union_idx.fill_(-1)
+    st.union_idx[:, :idx.shape[1]].copy_(idx)
+    st.attend(q)
+    torch.cuda.synchronize()
+    page = cache.page_table.long().gather(1, idx.clamp(max=n - 1).view(batch, -1) // 16).view(len(lens), -1)
+    head = (torch.arange(len(lens), device="cuda") % H)[:, None]
+    for lo in range(0, len(lens), 64):
+        s = slice(lo, lo + 64)
+        k, v = (pool[page[s], head[s], idx[s] % 16].double() for pool in (cache.k_pool, cache.v_pool))
+        live = (idx[s] < n)[:, None, :]
+        logit = ((q.view(len(lens), G, 128)[s].double()[:, :, None] * k[:, None]).sum(-1) / 128 ** 0.5).masked_fill(~live, float("-inf"))
+        m = logit.amax(-1, keepdim=True).clamp(min=-1e300)
+        w = (logit - m).exp()
+        want = (w[..., None] * v[:, None]).sum(2) / w.sum(-1, keepdim=True).clamp(min=1e-300)
+        out = st.out.view(len(lens), G, 128)[s].double()
+        # bf16 result (2^-9 of a value), fp32 logits of bf16 products: the bars of the other attention tests
+        assert bool(((out - want).norm(dim=-1) <= 4e-3 * want.norm(dim=-1) + 1e-6).all()), lo
+        lse = (m + w.sum(-1, keepdim=True).log()).squeeze(-1)
+        have = st.lse.view(len(lens), G)[s].double()
+        empty = ~live.any(-1).expand_as(have)
+        assert bool(torch.isneginf(have[empty]).all()) and bool(((have - lse).abs()[~empty] <= 1e-3 * lse.abs()[~empty].clamp(min=1.0)).all()), lo
+
+
+@pytest.mark.parametrize("G,lists,longest,kind", [
+    (1, 72, 180, "same"), (2, 256, 300, "mixed"), (4, 512, 129, "same"), (8, 520, 946, "same"), (4, 744, 377, "mixed"), (1, 1088, 745, "mixed"),
+    (2, 1280, 500, "same"), (8, 1384, 200, "mixed"), (1, 2048, 900, "same"), (1, 6144, 40, "mixed"), (2, 776, 64, "empty")])
+def test_attention_over_many_lists(G, lists, longest, kind):
+    """More than 64 lists, one, two and more to a thread of the item map: equal ones (whole or in equal pieces), lists of
+    widely different lengths, of which many are shorter than a chunk, and mostly empty ones, against float64."""
+    T = _T()
+    rng = np.random.default_rng(lists)
+    lens = np.full(lists, longest)
+    if kind != "same":
+        lens = np.exp(rng.uniform(0, np.log(longest + 1), lists)).astype(np.int64)
+        lens[rng.integers(lists)] = longest
+    if kind == "empty":
+        lens[rng.random(lists) < 0.9] = 0
+    _attend_lists(T, G, 8, lens, 2 * longest, seed=lists + G)
+
+
+def _dense_us(T, batch, n):
+    """Median time of dense attention over `batch` sequences of n tokens, 2 query heads on each of 8 KV heads."""
+    B = T.binding
+    P = (n + 15) // 16
+    cache = T.PagedKV(16, 8, torch.arange(batch * P, dtype=torch.int32).view(batch, P), torch.full((batch,), n), batch * P)
+    q = torch.randn(batch, 16, 128, device="cuda").to(torch.bfloat16)
+    st = T.DecodeStep(cache, max_sel=1)
+    for _ in range(3):
+        st.dense(q)
+    torch.cuda.synchronize()
+    B.twilight_prof_enable(1)
+    for _ in range(15):
+        st.dense(q)
+    torch.cuda.synchronize()
+    us = [ms * 1e3 for name, ms in B.twilight_prof_collect() if name == "sparse_decode"]
+    B.twilight_prof_enable(0)
+    return float(np.median(us))
+
+
+def test_lists_about_as_many_as_workgroups_are_shared_evenly():
+    """560 lists of 1440 tokens cost what 280 of 2880 do (65.4 and 68.0 us): cut into a long and a short piece each, with the
+    long pieces all on the same workgroups, they took 85.5."""
+    T = _T()
+    many, few = _dense_us(T, 70, 1440), _dense_us(T, 35, 2880)
+    assert many < 1.12 * few, (many, few)
