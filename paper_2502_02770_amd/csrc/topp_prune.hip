@@ -741,6 +741,7 @@ constexpr int HP_USTAGE = 4096;               // union lists up to this length l
 // pulls too slowly.  Each selects the head's pages (the same list in each), scores its share of them into the head's row,
 // and the last one to get there goes on with top-p alone (1 x 32 heads x 8192 pages, 8192 candidates: page_select 11.4 +
 // int4_score 6.3 + topp 12.8 us -> 27.9; 4 x 32 heads x 4096 pages 32.9 -> 30.5).
+// FUSE == 4: FUSE == 2 with the scores in registers where that would leave them in LDS.
 // BITS: width of the quantised copy's codes (FUSE >= 2; else 4).
 template <int NT, int EPT, int G, bool TOK = false, int FUSE = 0, int BITS = 4>
 __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FUSE != 2 && EPT > 8 ? 4 : 6))) void topp_head_kernel(HeadArgs a) {
@@ -749,7 +750,9 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
   // The workgroups that are there to share a CU (many heads, 8 or 16 candidates per thread, scored here) leave the scores
   // in LDS, where every phase reads them again, instead of holding them in registers: three of 16 candidates per thread
   // fit a CU instead of two, four of 8 instead of three, and one's scoring streams while the others wait at barriers
-  // (64 ragged sequences x 32 heads 116.6 -> 104.0 us, 32 x 32 heads x 4096 candidates 56.2 -> 53.7).
+  // (64 ragged sequences x 32 heads 116.6 -> 104.0 us, 32 x 32 heads x 4096 candidates 56.2 -> 53.7).  The price is in the phases:
+  // reading the scores again, 64 registers (74 with 16 candidates per thread) of which the form with 8 spills 8, 68 bytes of
+  // scratch per lane.  Where four to a CU do not save a round of workgroups over three, FUSE == 4 is quicker (launch_topp).
   constexpr bool INLDS = FUSE == 2 && NT <= 512 && EPT > 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const unsigned parts = SPLIT ? (unsigned)a.parts : 1u;
@@ -1547,9 +1550,12 @@ void launch_topp_one(const HeadArgs& f, int G, dim3 grid, hipStream_t s) {
 
 // Register-resident top-p over rows of at most 8192 candidates (cand_stride = row bound).
 //  - few heads: one 1024-thread workgroup per head (4 or 8 candidates per thread), or several (tw_prune_parts);
-//  - more heads than CUs and rows of at most 4096 candidates: 512-thread workgroups, three or (selection and scores inside)
-//    four to a CU (a 1024-thread workgroup has a CU to itself at this register count: 8 x 32 x 4 = 1024 heads took 35.8 us
-//    that way, 22.9 us two to a CU);
+//  - more heads than CUs and rows of at most 4096 candidates: 512-thread workgroups, three to a CU (a 1024-thread workgroup has a
+//    CU to itself at this register count: 8 x 32 x 4 = 1024 heads took 35.8 us that way, 22.9 us two to a CU).  Selection and scores
+//    inside: four to a CU, whose phases are longer, where that takes a round less and either the only one or the tables are short (a
+//    thread of 512 has 8 of 4096 bounds, which the 64 registers hold worst).  Three and four to a CU, us, 4096 candidates of 1024 pages:
+//    512 heads 27.5 / 30.0, 768 34.7 / 37.0, 1024 50.0 / 45.3, 1536 70.3 / 72.0, 2048 90.8 / 89.8, 4096 162.5 / 159.3; 2224 of 3750:
+//    288 heads 26.9 / 31.0, 768 35.1 / 40.5, 1024 52.2 / 48.2, 2048 88.5 / 92.7;
 //  - rows of at most 2048 candidates (and, with the selection inside, at most 2048 pages): 512-thread workgroups with 4
 //    candidates per thread, whatever the number of heads.  The kernel is a chain of block barriers; half the waves make
 //    each shorter (32 heads x 1024 candidates 13.4 -> 10.8 us, 320 x 1136 15.6 -> 12.0), and with the LDS arrays sized
@@ -1568,11 +1574,13 @@ void launch_topp_one(const HeadArgs& f, int G, dim3 grid, hipStream_t s) {
 template <bool TOK, int FUSE = 0, int BITS = 4>
 int launch_topp(HeadArgs f, const TwDims& d, int cand_stride, hipStream_t s) {
   const dim3 grid(d.Hq * (FUSE == 3 ? f.parts : 1), d.batch);
-  const long long heads = (long long)d.batch * d.Hq;
+  const long long heads = (long long)d.batch * d.Hq, cus = tw_num_cus();
   f.remap = (FUSE != 0 && ((long long)d.batch * d.Hkv) % 8 == 0) ? 1 : 0;
   f.n_above = -1; f.n_upto = cand_stride;
+  // four workgroups of 8 candidates per thread to a CU instead of three
+  const bool four = (heads + 4 * cus - 1) / (4 * cus) < (heads + 3 * cus - 1) / (3 * cus) && (heads <= 4 * cus || d.max_pages <= 1024);
   if constexpr (FUSE == 0) {
-    if (cand_stride > 4096 && heads > 2ll * tw_num_cus()) {
+    if (cand_stride > 4096 && heads > 2 * cus) {
       f.n_upto = 4096;
       tw_prof_before(TW_K_TOPP, s);
       launch_topp_one<512, 8, TOK, FUSE, BITS>(f, d.G, grid, s);
@@ -1586,11 +1594,13 @@ int launch_topp(HeadArgs f, const TwDims& d, int cand_stride, hipStream_t s) {
     return tw_prof_after(s);
   } else {
   tw_prof_before(FUSE == 2 ? TW_K_SELECT_SCORE_TOPP : (FUSE == 1 ? TW_K_SCORE_TOPP : TW_K_TOPP), s);
-  if (FUSE == 2 && heads > tw_num_cus() && cand_stride <= 1024 && d.max_pages <= 1024) launch_topp_one<FUSE == 2 ? 256 : 512, 4, TOK, FUSE, BITS>(f, d.G, grid, s);
+  if (FUSE == 2 && heads > cus && cand_stride <= 1024 && d.max_pages <= 1024) launch_topp_one<FUSE == 2 ? 256 : 512, 4, TOK, FUSE, BITS>(f, d.G, grid, s);
   else if (cand_stride <= 2048 && (FUSE != 2 || d.max_pages <= 2048)) launch_topp_one<512, 4, TOK, FUSE, BITS>(f, d.G, grid, s);
-  else if (cand_stride <= 4096 && heads > tw_num_cus()) launch_topp_one<512, 8, TOK, FUSE, BITS>(f, d.G, grid, s);
+  else if (FUSE == 2 && cand_stride <= 4096 && heads > cus && !four)
+    launch_topp_one<512, 8, TOK, FUSE == 2 ? 4 : FUSE, BITS>(f, d.G, grid, s);
+  else if (cand_stride <= 4096 && heads > cus) launch_topp_one<512, 8, TOK, FUSE, BITS>(f, d.G, grid, s);
   else if (cand_stride <= 4096) launch_topp_one<1024, 4, TOK, FUSE, BITS>(f, d.G, grid, s);
-  else if (FUSE == 2 ? heads > tw_num_cus() : FUSE != 0 && heads > 2ll * tw_num_cus()) launch_topp_one<512, FUSE != 0 ? 16 : 8, TOK, FUSE, BITS>(f, d.G, grid, s);
+  else if (FUSE == 2 ? heads > cus : FUSE != 0 && heads > 2 * cus) launch_topp_one<512, FUSE != 0 ? 16 : 8, TOK, FUSE, BITS>(f, d.G, grid, s);
   else launch_topp_one<1024, 8, TOK, FUSE, BITS>(f, d.G, grid, s);
   return tw_prof_after(s);
   }

@@ -268,6 +268,66 @@ def test_one_launch_select_prune_of_few_heads_with_long_lists(bits, heads, lens,
         _same_lists(sa, sb)
 
 
+def _random_codes(T, batch, pages, heads, bits=4, pool=4096):
+    """Cache of random page bounds and codes (pool pages shared by the sequences), a query."""
+    g = torch.Generator(device="cuda").manual_seed(5)
+    table = (torch.arange(batch * pages, dtype=torch.int32) * 7 % pool).view(batch, pages)
+    cache = T.PagedKV(heads[0], heads[1], table, torch.full((batch,), 16 * pages - 5), pool, need_v=False, quant_bits=bits)
+    cache.page_minmax.copy_(torch.randn(pool, heads[1], 2, 128, device="cuda", generator=g).sort(dim=2).values)
+    cache.kq_pool.random_(0, 256, generator=g)
+    cache.kq_meta[..., 0] = 4.0 / (1 << bits)
+    cache.kq_meta[..., 1] = -2.0
+    return cache, torch.randn(batch, heads[0], 128, device="cuda", generator=g).to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("bits,heads,batch,pages,max_sel", [
+    (4, (32, 8), 9, 300, 129), (4, (32, 8), 24, 1100, 256), (4, (16, 16), 48, 1024, 200), (8, (16, 8), 40, 2050, 150), (2, (64, 8), 12, 4096, 256),
+    (4, (8, 2), 96, 260, 256), (4, (32, 8), 32, 1030, 130), (8, (12, 12), 100, 700, 140), (4, (32, 8), 56, 1024, 129), (2, (32, 8), 56, 1025, 129)])
+def test_one_launch_select_prune_of_middling_lists(bits, heads, batch, pages, max_sel):
+    """2049 to 4096 candidates on more heads than CUs, three workgroups to a CU (scores in registers) or four (in LDS), by heads and
+    table width on both sides of the rule: against the separate calls bit for bit, lists of every length up to the bound."""
+    T = _T()
+    cache, q = _random_codes(T, batch, pages, heads, bits)
+    rng = np.random.default_rng(batch)
+    cache.seq_lens[1::2] = torch.from_numpy(rng.integers(0, 16 * pages + 1, batch // 2).astype(np.int32)).cuda()
+    budget = torch.from_numpy(rng.integers(0, 16 * max_sel + 100, batch).astype(np.int32)).cuda()
+    budget[0] = 16 * max_sel
+    sa, sb = (T.DecodeStep(cache, max_sel=max_sel, with_kept_idx=True) for _ in range(2))
+    sa.select(q, budget)
+    sa.prune(q, 0.9)
+    T.twilight_prof_enable(1)
+    sb.select_prune(None, None, None, q, budget, 0.9)
+    torch.cuda.synchronize()
+    names = [name for name, _ in T.twilight_prof_collect()]
+    T.twilight_prof_enable(0)
+    assert names == ["page_score", "select_score_topp"]
+    _same_lists(sa, sb)
+
+
+def _select_prune_us(T, batch, pages, max_sel):
+    """Median time of the one launch that selects, scores and prunes for `batch` x 32 heads."""
+    cache, q = _random_codes(T, batch, pages, (32, 8))
+    st = T.DecodeStep(cache, max_sel=max_sel)
+    budget = torch.full((batch,), 16 * max_sel, dtype=torch.int32, device="cuda")
+    for _ in range(3):
+        st.select_prune(None, None, None, q, budget, 0.9)
+    torch.cuda.synchronize()
+    T.twilight_prof_enable(1)
+    for _ in range(15):
+        st.select_prune(None, None, None, q, budget, 0.9)
+    torch.cuda.synchronize()
+    us = [ms * 1e3 for name, ms in T.twilight_prof_collect() if name == "select_score_topp"]
+    T.twilight_prof_enable(0)
+    return float(np.median(us))
+
+
+def test_two_heads_per_cu_do_not_pay_for_four():
+    """512 heads of 3008 candidates take 0.60 of what 1024 do (34.2 and 56.6 us), in the form that puts four to a CU 0.69 (39.0)."""
+    T = _T()
+    half, full = _select_prune_us(T, 16, 3750, 188), _select_prune_us(T, 32, 3750, 188)
+    assert half < 0.645 * full, (half, full)
+
+
 def _same_lists(sa, sb):
     assert torch.equal(sa.status, sb.status)
     for name, count in (("sel_pages", "sel_count"), ("kept_idx", "kept_count"), ("union_idx", "union_count")):
