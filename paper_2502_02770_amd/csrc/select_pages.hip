@@ -528,16 +528,16 @@ static int select_impl(const twilight_kv_t* kv, const void* q, const int32_t* bu
   a.kq_pool = (uint32_t*)kv->kq_pool; a.kq_meta = (uint32_t*)kv->kq_meta;
   a.page_minmax_w = (uint4*)kv->page_minmax;
   a.arrive = arrive;
-  // page_score_long_kernel from 16 of its workgroups per CU on, and with query heads that share a KV head on page tables of at
-  // least 1536 pages.  Steps in both forms, us: 16 x 32768 tokens (4096 workgroups) 86.3 / 85.1, 32 ragged sequences of up to 32768
-  // 76.7 / 75.3, 48 of up to 24576 87.3 / 85.5; with fewer workgroups it does not fill the chip (512: 2 x 32768 36.2 / 37.2).  On
-  // narrower tables a workgroup in a few has the new token, whose bounds and quantised row come last in its chain, and a ragged
-  // batch's rows fill few of its 64 pages: 128 ragged of up to 4096 75.6 / 78.7, of up to 8192 91.7 / 93.3, 32 of up to 16384 49.6
-  // / 50.7 (full rows of 16384 gain, 64 x 16384 154.2 / 151.8, but their lengths are not known here).  With one query head the rest
-  // of the chain is short enough: 128 ragged of up to 4096 125.6 / 122.8, 32 x 4096 62.2 / 61.6.  128 pages per workgroup: 64 ragged
-  // of up to 16384 86.4 / 88.6.
+  // page_score_long_kernel from 16 of its workgroups per CU on, on page tables of at least 1536 pages (one query head per KV head:
+  // 512).  Steps in both forms, us: 16 x 32768 tokens (4096 workgroups) 86.3 / 85.1, 32 ragged sequences of up to 32768 76.7 / 75.3,
+  // 48 of up to 24576 87.3 / 85.5; with fewer workgroups it does not fill the chip (512: 2 x 32768 36.2 / 37.2).  On narrower tables
+  // a workgroup in a few has the new token, whose bounds and quantised row come last in its chain, and a ragged batch's rows fill few
+  // of its 64 pages: 128 ragged of up to 4096 75.6 / 78.7, of up to 8192 91.7 / 93.3, 32 of up to 16384 49.6 / 50.7 (full rows of
+  // 16384 gain, 64 x 16384 154.2 / 151.8, but their lengths are not known here).  With one query head the rest of the chain is
+  // shorter: the kernel alone, 32 KV heads, 128 ragged of up to 8192 67.7 / 63.7, of up to 2048 22.9 / 22.3, of up to 1024 16.1 / 17.2,
+  // 192 x 300 17.5 / 21.5; 16 KV heads, 64 of up to 4096 12.5 / 14.0.  128 pages per workgroup: 64 ragged of up to 16384 86.4 / 88.6.
   const int wide = (d.max_pages + PS_LONG_PAGES - 1) / PS_LONG_PAGES;
-  const bool many = (long long)d.batch * d.Hkv * wide >= 16ll * tw_num_cus() && (d.G == 1 || d.max_pages >= 1536);
+  const bool many = (long long)d.batch * d.Hkv * wide >= 16ll * tw_num_cus() && d.max_pages >= (d.G == 1 ? 512 : 1536);
   const dim3 grid(d.Hkv, many ? wide : (d.max_pages + PS_PAGES_PER_WG - 1) / PS_PAGES_PER_WG, d.batch);
   tw_prof_before(TW_K_PAGE_SCORE, s);
   switch (d.G) {
