@@ -201,15 +201,18 @@ int twilight_append_select(const twilight_kv_t* kv, const void* k_new, const voi
  * what twilight_append_select (k_new given) or twilight_select_pages (k_new,
  * v_new, new_pos all NULL) followed by twilight_topp_prune over the selected
  * pages computes - the same cache update, page lists, kept sets and unions,
- * bit for bit.  Where a head's list is short enough for one workgroup
- * (max_sel <= 512 pages, sequences of at most 4096 pages, and not just a few
- * heads with more than 4096 candidates each) the call is two launches instead
- * of four: the bounds of all pages, then one workgroup per query head that
- * picks the head's pages, scores their tokens from the quantised K copy, runs
- * top-p and, as the last head of its group, lists the union.  Sequences of up
- * to 196608 tokens keep the selection launch in between (quant_bits = 4).
- * Otherwise it runs the launches of the separate calls.  The
- * workspace needs no initialising.
+ * bit for bit.  Lists of at most 512 pages (max_sel) on page tables of at
+ * most 4096 pages take two launches instead of four: the bounds of all pages,
+ * then one workgroup per query head that picks the head's pages, scores their
+ * tokens from the quantised K copy, runs top-p and, as the last head of its
+ * group, lists the union.  With lists of more than 256 pages on at most half
+ * as many heads as CUs, and page tables of up to 8192 pages, several
+ * workgroups per head select and score, the last of them runs top-p; on more
+ * heads than that but fewer than CUs the separate calls' launches are
+ * quicker and are run.  Page tables of up to 12288 pages keep the selection
+ * launch in between (quant_bits = 4; as many heads as CUs where the lists
+ * have more than 256 pages).  Otherwise it runs the launches of the separate
+ * calls.  The workspace needs no initialising.
  *   sel_pages, sel_count   out, as twilight_select_pages
  *   kept_count ... status  out, as twilight_topp_prune
  *   ws             >= twilight_workspace_bytes(TW_WS_SELECT_PRUNE, kv, max_sel, 0)

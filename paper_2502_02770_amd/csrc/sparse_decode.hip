@@ -605,7 +605,7 @@ extern "C" int twilight_debug_stamps_decode(unsigned long long* host_out) {
 }
 #endif
 
-// Items are `chunk` list entries: short for sparse lists (many small items keep
+// The shortest chunk that decode_chunk may choose: a step of the four waves for sparse lists (many small items keep
 // all CUs busy on short, latency-bound gathers), longer for the dense sweep.
 int tw_decode_chunk(bool dense) {
 #ifdef TW_TUNING                                 // tuning builds only: the shipped library reads no environment
@@ -670,8 +670,8 @@ static int decode_impl(const twilight_kv_t* kv, const void* q, const int32_t* co
 }
 
 // Launch shape of the decode kernel for this cache shape (host only): workgroups of the persistent grid (before
-// it is cut to the number of work items), the shortest chunk, and how many items a workgroup may take before
-// the kernel doubles the chunk.  For benchmarks that report the balance of the work list.
+// it is cut to the number of work items), the shortest chunk, and how many numbers of items per workgroup
+// decode_chunk weighs.  For benchmarks that report the balance of the work list.
 extern "C" int twilight_decode_plan(const twilight_kv_t* kv, int which, int32_t dense, int32_t* grid, int32_t* chunk0,
                                     int32_t* items_per_wg) {
   TwDims d;

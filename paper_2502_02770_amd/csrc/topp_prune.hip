@@ -822,7 +822,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
   __shared__ unsigned long long cand_mass[HP_CAP];
   __shared__ uint32_t cand_key[HP_CAP];
   // position bitmap, then the union list on its way out; before that the selection's arrays and the scores, read 16
-  // bytes at a time: behind the bitmap (SELECT, whose bitmap covers 4096 pages) or from its first word
+  // bytes at a time: behind the bitmap (SELECT, whose bitmap covers the pages that its keys can be: NT * SEL_E) or from its first word
   __shared__ __align__(16) uint32_t big_s[BWORDS + AREA];
   static_assert(__alignof__(big_s) >= 16 && BWORDS % 4 == 0, "read as float4 and as 64-bit words");
   uint32_t* const bitmap = big_s;
