@@ -89,7 +89,8 @@ __device__ __forceinline__ void ps_append(const ScoreArgs& a, long long row, lon
 }
 
 // The bounds of a page for the G heads, by its 16 lanes; put(h, bound) in the lane that ends with head h's.
-// (The signs of 4 heads' queries fill the scalar registers; those of further heads are compared anew, or they spill.)
+// (The signs of 4 heads' queries fill the scalar registers; those of further heads are compared anew, or they spill.  With 8 heads
+//  and the append page_score_long_kernel still spills 8 scalar registers, page_score_kernel none.)
 template <int G, typename Put>
 __device__ __forceinline__ void ps_score(float (&q)[G][8], const uint4& cmn, const uint4& cmx, int seg, Put put) {
   float mn[8], mx[8];
