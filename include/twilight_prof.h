@@ -65,6 +65,8 @@ const char* twilight_kernel_name(int kernel_id);
  * times while the lists still have more than r * W chunks.  More lists:
  * against the longest list in 1 to 4 pieces too, and where the counted chunks
  * are more than foreseen, the cheapest by the counted ones.
+ * One query head per KV head, at least 128 lists of at least 144 entries on
+ * average: chunks of at least 128.
  * which = TW_WS_DECODE or TW_WS_DECODE_PER_HEAD.  For reports on how evenly
  * ragged lists spread over the workgroups (Section 4.2, load balancing).
  */

@@ -237,7 +237,13 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : (G == 4 ? 3 : 4)) void sparse_dec
       T += x.x;
       longest = x.y > longest ? x.y : longest;
     }
-    DecodePlan plan(T, longest, (uint32_t)a.NG, W, (uint32_t)a.chunk0);
+    // One query head per KV head, 128 lists and more of 144 entries and more on average: no items of a single step.  A second
+    // step's rows arrive behind the first's, and half as many workgroups share a CU and write pieces.  Attention with combine, us,
+    // shortest chunk 64 / 128: 256 lists of 160 entries 11.8 / 10.9, 320 of 151 13.1 / 12.0, 320 of 210 14.0 / 13.3, 128 of 160
+    // 9.5 / 8.8, 160 of 196 11.2 / 11.2; shorter or fewer lists leave the chip idle: 256 of 65 9.8 / 10.3, 224 of 129 10.2 / 10.4,
+    // 96 of 299 10.4 / 10.8.
+    const bool longer = G == 1 && a.kv_div == 1 && a.NG >= 128 && T >= 144u * (uint32_t)a.NG;
+    DecodePlan plan(T, longest, (uint32_t)a.NG, W, longer ? max((uint32_t)a.chunk0, 2u * DEC_UNIT) : (uint32_t)a.chunk0);
     auto len_of = [&](int k) -> uint32_t { return K > 2 ? (i0 + k < a.NG ? (uint32_t)prefix[i0 + k] : 0u) : (k ? c1 : c0); };
     uint32_t n = 0, incl = 0, total;
 #pragma unroll 1
