@@ -271,7 +271,7 @@ def other_config(T, idx, steps, warmup, layers, batch=None):
                                        if k in kavg and nbytes.get(k)},
            "dense_decode_frac_of_peak": (nbytes["dense_decode"] / (d_us * 1e-6) / 1e9 / HBM_PEAK_GBS) if d_us else None,
            "workload_stats": stats,
-           "decode_work_list": decode_balance(T, cache, st.union_count, st.union_stride) if w.v.numel() and not st.full else None,
+           "decode_work_list": decode_balance(T, cache, st) if w.v.numel() and not st.full else None,
            "kquant_append_bulk": setup.get("append_bulk"),
            "seconds": None}
     del w, cache, st, q, step, dense
