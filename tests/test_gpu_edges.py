@@ -545,3 +545,33 @@ def test_lists_about_as_many_as_workgroups_are_shared_evenly():
     T = _T()
     many, few = _dense_us(T, 70, 1440), _dense_us(T, 35, 2880)
     assert many < 1.12 * few, (many, few)
+
+
+@pytest.mark.parametrize("heads", [(2, 2), (4, 2)])
+def test_dots_at_the_ends_of_the_query_and_code_ranges(heads):
+    """Integer dots of 4-bit codes bit for bit where the query's int8 values are at the ends of their range and of its 4-bit
+    halves, against keys whose codes are 0 and 15 in whole groups."""
+    T = _T()
+    Hq, Hkv = heads
+    ramp = np.concatenate([np.arange(-127, -63), np.arange(64, 128)])
+    rows = [np.full(128, 127), np.full(128, -127), np.where(np.arange(128) % 2, 127, -127), ramp, np.roll(ramp[::-1], 5),
+            np.resize([-16, -1, 15, 16, 112, 119, 120, 127], 128), np.resize([0, -128 + 1, 8, -8, 7, -9], 128), np.arange(128)]
+    n = 40
+    w = synth.make_workload("ends", [n] * len(rows), num_q_heads=Hq, num_kv_heads=Hkv, budget=32, p=0.9, need_v=False, seed=97)
+    for b, row in enumerate(rows):
+        w.q[b] = torch.from_numpy(np.stack([np.roll(row, 7 * h) for h in range(Hq)]).astype(np.float32)).to(torch.bfloat16)
+    w.k[::3] = torch.where(torch.arange(128) % 2 == 0, 1.0, -1.0).to(torch.bfloat16)       # codes 15 and 0
+    w.k[1::5, :, :64] = 2.0                                                                   # constant groups
+    cache = build_cache(w)
+    stride = cache.page_table.shape[1] * 16
+    sc = torch.zeros(w.batch, Hq, stride, dtype=torch.float32, device="cuda")
+    dots = torch.zeros(w.batch, Hq, stride, 4, dtype=torch.int32, device="cuda")
+    T.twilight_int4_score(cache.kv, w.q.cuda(), None, None, 0, sc, dots)
+    torch.cuda.synchronize()
+    for b in range(w.batch):
+        for h in range(Hq):
+            u, s, z = O.quantize_k(synth.bits(w.seq_k(b)[:, h // (Hq // Hkv)]))
+            qi, sq = O.quantize_q(synth.bits(w.q[b, h]))
+            I, _ = O.int4_dots(qi, u)
+            assert np.array_equal(dots[b, h, :n].cpu().numpy(), I), (b, h)
+            assert np.array_equal(sc[b, h, :n].cpu().numpy(), O.int4_scores(qi, sq, u, s, z)), (b, h)
