@@ -12,6 +12,11 @@
 // staged in LDS, with the crossing bucket, the rank and the list offsets handed around through LDS, took 8.  Against that
 // form: selection inside the per-head kernel 5.0 -> 4.1 us (32 heads x 256 pages 5.0 -> 3.7), page_select 6.7 -> 5.5 us
 // at 128 heads x 1024 pages, 10.8 -> 9.0 at 256 x 8192, 47 -> 26 at 256 x 32768 entries.
+// With 8 and more keys per thread, and for what 16 waves do alike, it is the vector instructions (80 per key and wave of 59 k
+// cycles at 32768 entries, 70 % of them vector issue): the first pass, whose keys are all inside the interval, adds without a test or
+// a branch per key, and of the lane that the threshold falls to the waves look at one bucket per lane instead of walking its 8
+// to 32.  256 x 32768 entries 30.7 -> 26.8 us with the list leaving through LDS (2 us of that); the step of one sequence of 8192
+// pages 45.8 -> 43.3, of 8 x 2048 pages 52.1 -> 51.3.
 //
 // Slots beyond the row's length are skipped by the whole workgroup, so that a row costs what its own length does: one by
 // one up to 8 slots per thread, in groups of 4 beyond.  (512 rows x 9000 entries with 16 slots 15.5 us in groups of 4,
@@ -25,6 +30,9 @@ constexpr int SEL_REG_TWO = 16384;       // rows up to here run two 1024-thread 
 constexpr int SEL_REG_MAX = 32768;       // longest row whose keys fit in a workgroup's registers
 constexpr int SEL_CAP = 64;              // candidates of the exact finish: one per lane
 constexpr int SEL_GROUP = 4;             // slots skipped together where a thread has more than 8
+// Words of the histogram of SNB buckets: bucket r, from the top, in word r, with 16 or more to a scanning lane four words further for
+// every lane before its own, so that the lanes' 16-byte reads begin on different banks; 64 words for slots beyond the row.
+constexpr int tw_sel_words(int SNB) { return SNB + (SNB >= 1024 ? 4 * 64 : 0) + 64; }
 constexpr uint32_t SEL_ALL_EQ = 0xFFFFFFFFu;   // every key equal to the threshold is taken
 
 // entries of a sequence's row and how many of them the budget asks for (UNIT = tokens per entry: 16 or 1)
@@ -96,13 +104,15 @@ __device__ __forceinline__ void tw_seg_prefix(const uint32_t* cnt, int entries, 
 // Threshold of the Kp (0 < Kp < P) largest of the row's keys, ties to the lower index: the entries with a key above
 // *T_out and the first *need_eq_out of those equal to it (SEL_ALL_EQ: all).  key[e] of thread t is entry e * NT + t (tw_select_key when E > 8, else the
 // float's key, of any value beyond the row's end).
-// Called by all NT threads of the workgroup; hist and cand are LDS of the caller.  SB: first phase-stamp slot (timing builds).
+// Called by all NT threads of the workgroup; hist (16-byte aligned) and cand are LDS of the caller.  SB: first phase-stamp slot (timing builds).
 template <int NT, int E, int SNB, int SB>
-__device__ __forceinline__ void tw_select_threshold(uint32_t (&key)[E], int P, uint32_t Kp, uint32_t* hist /* [SNB] */,
+__device__ __forceinline__ void tw_select_threshold(uint32_t (&key)[E], int P, uint32_t Kp, uint32_t* hist /* [tw_sel_words(SNB)] */,
                                                     unsigned long long* cand /* [SEL_CAP] */, uint32_t* T_out, uint32_t* need_eq_out) {
   constexpr int NW = NT / 64, BPL = SNB / 64;         // waves; histogram buckets per lane of a scanning wave
   constexpr int LB = BPL == 8 ? 3 : (BPL == 16 ? 4 : 5);
   static_assert(BPL == (1 << LB), "SNB is 512, 1024 or 2048");
+  constexpr int PAD = BPL >= 16 ? 4 : 0, LANE = BPL + PAD, BEYOND = 64 * LANE;     // words per scanning lane; the first word for slots beyond the row
+  auto word = [&](int r) -> int { return PAD ? r + (r >> LB) * PAD : r; };
   const int tid = threadIdx.x, lane = tid & 63, wave = E > 8 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
   const auto live = [&](int e) { return E > 8 || e * NT + tid < P; };   // (more than 8: the key says so)
   __shared__ uint32_t red_lo[NW], red_hi[NW];
@@ -123,13 +133,13 @@ __device__ __forceinline__ void tw_select_threshold(uint32_t (&key)[E], int P, u
   if (lane == 0) { red_lo[wave] = lo; red_hi[wave] = hi; }
   if (tid == 0) sh_n = 0;
   if (tid < SEL_CAP) cand[tid] = 0;
-  for (int i = tid; i < SNB; i += NT) hist[i] = 0;
+  for (int i = tid; i < BEYOND; i += NT) hist[i] = 0;
   __syncthreads();
   uint32_t klo = ~tw_row_max_u32(~red_lo[lane & (NW - 1)]) + (E > 8 ? 1u : 0u), khi = tw_row_max_u32(red_hi[lane & (NW - 1)]);
   klo = (uint32_t)__builtin_amdgcn_readfirstlane((int)klo);
   khi = (uint32_t)__builtin_amdgcn_readfirstlane((int)khi);
 
-  constexpr bool KEEP = E <= 8, REREAD = BPL > 16;
+  constexpr bool KEEP = E <= 8;
   int kept_bk[KEEP ? E : 1];
   uint32_t need = Kp, T = 0, need_eq = 0;
   tw_forget<E>(key);
@@ -146,10 +156,11 @@ __device__ __forceinline__ void tw_select_threshold(uint32_t (&key)[E], int P, u
     const bool by_key = !(scale <= 3.0e38f) || !(smx - smn >= 1.1754944e-38f) || pass >= 3;
     const uint32_t span = khi - klo;
     const int kshift = span < (uint32_t)SNB ? 0 : 32 - __clz(span) - (LB + 6);
+    // place from the top, 0 .. SNB - 1, of a key inside the interval
     auto bucket_of = [&](uint32_t k) -> int {
-      if (by_key) return (int)((k - klo) >> kshift);
-      const int bk = (int)((tw_key_to_float(k) - smn) * scale);
-      return bk > SNB - 1 ? SNB - 1 : (bk < 0 ? 0 : bk);
+      if (by_key) return (int)((khi - k) >> kshift);
+      const int r = (int)((smx - tw_key_to_float(k)) * scale);
+      return r < SNB - 1 ? r : SNB - 1;
     };
     // is entry e of this thread in bucket bkt?  (rows of up to 8 entries per thread keep the bucket numbers)
     auto in_bucket = [&](int e, int bkt) -> bool {
@@ -157,42 +168,44 @@ __device__ __forceinline__ void tw_select_threshold(uint32_t (&key)[E], int P, u
       return live(e) && key[e] - klo <= span && bucket_of(key[e]) == bkt;
     };
     if (pass > 0) {
-      for (int i = tid; i < SNB; i += NT) hist[i] = 0;
+      for (int i = tid; i < BEYOND; i += NT) hist[i] = 0;
       __syncthreads();
     }
-    // Bucket b, r = SNB - 1 - b = BPL * l + j, is counted in word j * 64 + l: the scanning lane l, which owns the BPL
-    // buckets r = BPL * l .. from the top, reads one word per j with consecutive lanes on consecutive banks.  The longest
-    // rows rotate the words of a j by j, so that their many adds, which crowd into neighbouring buckets, spread over the
-    // banks too (with the registers of tw_select_key and tw_forget 256 rows x 32768 entries 41 -> 31 us; with 16 slots or
-    // fewer it costs more than it gives: 512 rows x 9000 entries 17.3 -> 18.5).
-    tw_each_slot<NT, E>(P, [&](int e) {
-      const bool in = live(e) && key[e] - klo <= span;
-      const int bk = bucket_of(key[e]);
-      if (KEEP) kept_bk[KEEP ? e : 0] = in ? bk : -1;
-      if (in) {
-        const int r = SNB - 1 - bk;
-        atomicAdd(&hist[((r & (BPL - 1)) << 6) | (((r >> LB) + (E > 16 ? r & (BPL - 1) : 0)) & 63)], 1u);
-      }
-    }, [&](int e) { if (KEEP) kept_bk[KEEP ? e : 0] = -1; });
+    if (pass == 0 && !by_key) {                   // (block-uniform)
+      // every key of the row is inside: no branch around the add, so that the keys' chains overlap; slots beyond the row count
+      // in words of their own
+      tw_each_slot<NT, E>(P, [&](int e) {
+        const int r = min((int)((smx - tw_key_to_float(key[e])) * scale), SNB - 1);
+        const bool in = E > 8 ? key[e] != 0u : e * NT + tid < P;
+        if (KEEP) kept_bk[KEEP ? e : 0] = in ? r : -1;
+        atomicAdd(&hist[in ? word(r) : BEYOND + lane], 1u);
+      }, [&](int e) { if (KEEP) kept_bk[KEEP ? e : 0] = -1; });
+    } else {
+      tw_each_slot<NT, E>(P, [&](int e) {
+        const bool in = live(e) && key[e] - klo <= span;
+        const int r = bucket_of(key[e]);
+        if (KEEP) kept_bk[KEEP ? e : 0] = in ? r : -1;
+        if (in) atomicAdd(&hist[word(r)], 1u);
+      }, [&](int e) { if (KEEP) kept_bk[KEEP ? e : 0] = -1; });
+    }
     __syncthreads();
     TW_STAMP(SB + 2);
-    uint32_t c[BPL], mine = 0;
+    // lane l sums the buckets BPL * l .. up; then, of the lane that the threshold falls to, one bucket per lane
+    uint32_t mine = 0;
 #pragma unroll
-    for (int j = 0; j < BPL; ++j) { c[j] = hist[j * 64 + ((lane + (E > 16 ? j : 0)) & 63)]; mine += c[j]; }
-    uint32_t above = tw_wave_scan_u32(mine) - mine;
-    const int src = __ffsll((long long)__ballot(above < need && above + mine >= need)) - 1;   // the interval holds the threshold
-    uint32_t asel = 0, csel = 0;
-    if (REREAD) asm volatile("" ::: "memory");
-    int jsel = 0;
-#pragma unroll
-    for (int j = 0; j < BPL; ++j) {
-      const uint32_t cj = REREAD ? hist[j * 64 + ((lane + j) & 63)] : c[j];   // (read again rather than kept)
-      if (above < need && above + cj >= need) { jsel = j; asel = above; csel = cj; }
-      above += cj;
+    for (int j = 0; j < BPL; j += 4) {
+      const uint4 x = *(const uint4*)(hist + LANE * lane + j);
+      mine += x.x + x.y + x.z + x.w;
     }
-    const int bkt = SNB - 1 - (BPL * src + __builtin_amdgcn_readlane(jsel, src));
-    need -= (uint32_t)__builtin_amdgcn_readlane((int)asel, src);
-    const uint32_t pop = (uint32_t)__builtin_amdgcn_readlane((int)csel, src);
+    const uint32_t above = tw_wave_scan_u32(mine) - mine;
+    const int src = __ffsll((long long)__ballot(above < need && above + mine >= need)) - 1;   // the interval holds the threshold
+    need -= (uint32_t)__builtin_amdgcn_readlane((int)above, src);
+    const uint32_t c = lane < BPL ? hist[LANE * src + lane] : 0u;
+    const uint32_t upto = tw_wave_scan_u32(c);
+    const int at = __ffsll((long long)__ballot(upto >= need)) - 1;
+    const int bkt = BPL * src + at;
+    const uint32_t pop = (uint32_t)__builtin_amdgcn_readlane((int)c, at);
+    need -= (uint32_t)__builtin_amdgcn_readlane((int)upto, at) - pop;
     tw_forget<E>(key);
     if (pop <= (uint32_t)SEL_CAP) {
       // exact: the bucket's keys, with the lower index the larger of two equals, ranked by every wave on its own - one

@@ -833,8 +833,9 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
     constexpr int SNB = SPLIT ? 1024 : 512;
     static_assert(SNB % 2 == 0, "the candidates behind the histogram are 64-bit words");
     uint32_t* const hist = area;                    // the selection's arrays lie there
-    unsigned long long* const cand = (unsigned long long*)(area + SNB);
-    uint32_t* const cnt = area + SNB + 2 * SEL_CAP;
+    unsigned long long* const cand = (unsigned long long*)(area + tw_sel_words(SNB));
+    uint32_t* const cnt = area + tw_sel_words(SNB) + 2 * SEL_CAP;
+    static_assert(tw_sel_words(SNB) + 2 * SEL_CAP + SEL_E * NT / 64 <= AREA, "the selection's arrays fit");
     int32_t* const out = a.sel_pages_w + (long long)bh * a.max_sel;
     const int32_t* const ptab = a.page_table + (long long)b * a.max_pages;
     if (tid == 0 && part == 0) a.sel_count_w[bh] = count;

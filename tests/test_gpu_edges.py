@@ -575,3 +575,21 @@ def test_dots_at_the_ends_of_the_query_and_code_ranges(heads):
             I, _ = O.int4_dots(qi, u)
             assert np.array_equal(dots[b, h, :n].cpu().numpy(), I), (b, h)
             assert np.array_equal(sc[b, h, :n].cpu().numpy(), O.int4_scores(qi, sq, u, s, z)), (b, h)
+
+
+@pytest.mark.parametrize("pages,take", [(8192, 8191), (16384, 8191), (16384, 8192), (16384, 8193), (32768, 8192), (32768, 8193), (32700, 31)])
+def test_page_lists_as_long_as_the_selection_stages(pages, take):
+    """Lists at the length up to which they leave through LDS, of rows at and just under the kernels' longest."""
+    T = _T()
+    lens = [16 * pages, 16 * (pages - 100)]
+    cache, q = _random_bounds(T, lens, pages, heads=(2, 1), pool=4096, seed=pages + take)
+    st = T.DecodeStep(cache, max_sel=take)
+    st.select(q, torch.full((2,), 16 * take, dtype=torch.int32, device="cuda"))
+    torch.cuda.synchronize()
+    mm = cache.page_minmax.cpu()
+    for b, n in enumerate(lens):
+        rows = mm[cache.page_table[b, :n // 16].cpu().long(), 0]
+        for h in range(2):
+            U = O.page_upper_bounds(synth.bits(q[b, h].cpu()), u16(rows[:, 0]), u16(rows[:, 1]))
+            want = O.select_pages(U, 16 * take, n)
+            assert st.sel_pages[b, h, :int(st.sel_count[b, h])].cpu().numpy().tolist() == want.tolist(), (b, h)
