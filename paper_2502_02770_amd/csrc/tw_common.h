@@ -171,6 +171,17 @@ __device__ __forceinline__ unsigned long long tw_wave_scan_u64(unsigned long lon
   x += tw_dpp64<TW_DPP_BCAST31, 0xC, false>(x);
   return x;
 }
+// The same over the first 8 lanes (and, apart from them, over every 16).
+__device__ __forceinline__ unsigned long long tw_scan8_u64(unsigned long long x) {
+  x += tw_dpp64<TW_DPP_ROW_SHR(1), 0xF, true>(x);
+  x += tw_dpp64<TW_DPP_ROW_SHR(2), 0xF, true>(x);
+  x += tw_dpp64<TW_DPP_ROW_SHR(4), 0xF, true>(x);
+  return x;
+}
+// lane's value to all, lane wave-uniform
+__device__ __forceinline__ unsigned long long tw_readlane_u64(unsigned long long x, int lane) {
+  return ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), lane) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane);
+}
 // Reductions over the 64 lanes; every lane gets the result (a scalar: the rows' results travel through the two row
 // broadcasts to lane 63 and come back by a lane read, which is quicker than two cross-row shuffles through LDS).
 __device__ __forceinline__ uint32_t tw_row_max_u32(uint32_t v) {       // over the 16 lanes of a row
