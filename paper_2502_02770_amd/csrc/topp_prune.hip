@@ -743,7 +743,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
   // in LDS, where every phase reads them again, instead of holding them in registers: three of 16 candidates per thread
   // fit a CU instead of two, four of 8 instead of three, and one's scoring streams while the others wait at barriers
   // (64 ragged sequences x 32 heads 116.6 -> 104.0 us, 32 x 32 heads x 4096 candidates 56.2 -> 53.7).  The price is in the phases:
-  // reading the scores again, 64 registers (74 with 16 candidates per thread) of which the form with 8 spills 8, 68 bytes of
+  // reading the scores again, 64 registers (75 with 16 candidates per thread) of which the form with 8 spills 8, up to 68 bytes of
   // scratch per lane.  Where four to a CU do not save a round of workgroups over three, FUSE == 4 is quicker (launch_topp).
   constexpr bool INLDS = FUSE == 2 && NT <= 512 && EPT > 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
