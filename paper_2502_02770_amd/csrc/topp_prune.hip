@@ -3,9 +3,10 @@
 //
 // int4_score       estimated logits from the quantised K copy.  One wave = one
 //                  page per step: 64 lanes x 16 B = the page's 1 KiB of codes,
-//                  lane = (token, group of 32 dims); 8 integer dot4 per lane
-//                  and head, scale/zero applied per group, quad DPP sum over
-//                  the 4 groups.  Templated on the code width (2 / 4 / 8 bits).
+//                  lane = (token, group of 32 dims); 8 integer products of 4
+//                  or, 4-bit codes of one head per page, 8 values per lane and
+//                  head, scale/zero applied per group, quad DPP sum over the
+//                  4 groups.  Templated on the code width (2 / 4 / 8 bits).
 // int4_score_mfma  the same scores on the matrix cores, used when every page
 //                  is a candidate and 4 or 8 query heads share each page.
 // topp_head        per (sequence, query head), scores in registers: max, then
@@ -126,8 +127,12 @@ __device__ __forceinline__ void tw_load_raw(const uint4* kq_pool, long long idx,
 // signed 4-bit number, one product sum each (the codes minus 8 are signed 4-bit numbers, their bits but for the top one of each).
 // Unpacked to bytes for 4-value products a page of the one-launch selector + pruner takes 41 instead of 34 vector instructions (steps,
 // us: 32 x 32768 tokens 142.0 -> 141.3, 8 x 32768 52.24 -> 51.95).
+// Not SPLIT (int4_score_kernel with two and more heads per loaded page, which share the codes once unpacked): 4-value products.  A wave's
+// few pages do not pay back the making of several heads' split words, and the registers cost a wave per SIMD (2 heads, dots stored: 66
+// for 64).  Two heads per KV head, us, split / not: 8 x 32 heads x 32768 tokens with dots 89.5 / 83.0 and without 69.6 / 69.8, without
+// dots 3 x 32 x 9001 9.25 / 8.98, 4 x 8 x 16384 5.58 / 5.37.
 // *qs = sum of the values, *i0 = where the group's sum starts.
-template <int BITS>
+template <int BITS, bool SPLIT = BITS == 4>
 __device__ __forceinline__ void tw_query_words(const int* q8, int (&qw)[8], int* qs, int* i0) {
   int sum = 0;
 #pragma unroll
@@ -137,7 +142,7 @@ __device__ __forceinline__ void tw_query_words(const int* q8, int (&qw)[8], int*
   }
   *qs = sum;
   *i0 = BITS == 8 ? 128 * sum : 0;                // 8-bit codes enter the signed product as code - 128
-  if (BITS == 4) {
+  if (SPLIT) {
     int high[4], low[4], hs = 0;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
@@ -152,9 +157,9 @@ __device__ __forceinline__ void tw_query_words(const int* q8, int (&qw)[8], int*
   }
 }
 // I = sum over the group's 32 dims of q * code
-template <int BITS>
+template <int BITS, bool SPLIT = BITS == 4>
 __device__ __forceinline__ int tw_group_dot(const int (&qw)[8], const uint4 (&r)[BITS == 8 ? 2 : 1], int i0) {
-  if (BITS == 4) {
+  if (SPLIT) {
     const uint32_t wv[4] = {r[0].x, r[0].y, r[0].z, r[0].w};
     int h = i0;
     uint32_t l = 0;
@@ -166,7 +171,12 @@ __device__ __forceinline__ int tw_group_dot(const int (&qw)[8], const uint4 (&r)
     return (int)(((uint32_t)h << 4) + l);
   }
   int u[8];
-  if (BITS == 2) {
+  if (BITS == 4) {
+    u[0] = r[0].x & 0x0F0F0F0F; u[1] = (r[0].x >> 4) & 0x0F0F0F0F;
+    u[2] = r[0].y & 0x0F0F0F0F; u[3] = (r[0].y >> 4) & 0x0F0F0F0F;
+    u[4] = r[0].z & 0x0F0F0F0F; u[5] = (r[0].z >> 4) & 0x0F0F0F0F;
+    u[6] = r[0].w & 0x0F0F0F0F; u[7] = (r[0].w >> 4) & 0x0F0F0F0F;
+  } else if (BITS == 2) {
     u[0] = r[0].x & 0x03030303; u[1] = (r[0].x >> 2) & 0x03030303; u[2] = (r[0].x >> 4) & 0x03030303; u[3] = (r[0].x >> 6) & 0x03030303;
     u[4] = r[0].y & 0x03030303; u[5] = (r[0].y >> 2) & 0x03030303; u[6] = (r[0].y >> 4) & 0x03030303; u[7] = (r[0].y >> 6) & 0x03030303;
   } else {
@@ -230,13 +240,14 @@ __global__ __launch_bounds__(256) void int4_score_kernel(ScoreArgs a) {
   __shared__ int qi_s[NH][32];
   __shared__ float c_s[NH];
   tw_quantize_q<NH>(a.q + ((long long)(b * a.Hq + h0)) * 128, qi_s, c_s, a.chmask ? a.chmask + g * 4 : nullptr);
+  constexpr bool SPLIT = BITS == 4 && NH == 1;
   const int j = lane & 3;                       // this lane's group of 32 dims
   int qw[NH][8], i0[NH];
   float qsf[NH], cc[NH];
 #pragma unroll
   for (int h = 0; h < NH; ++h) {
     int qs;
-    tw_query_words<BITS>(qi_s[h] + 8 * j, qw[h], &qs, &i0[h]);
+    tw_query_words<BITS, SPLIT>(qi_s[h] + 8 * j, qw[h], &qs, &i0[h]);
     qsf[h] = (float)qs;
     cc[h] = c_s[h];
   }
@@ -273,7 +284,7 @@ __global__ __launch_bounds__(256) void int4_score_kernel(ScoreArgs a) {
     const long long slot = (long long)(first + k) * TW_PAGE + (lane >> 2);
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
-      const int I = tw_group_dot<BITS>(qw[h], raw[kk], i0[h]);
+      const int I = tw_group_dot<BITS, SPLIT>(qw[h], raw[kk], i0[h]);
       const float T = tw_token_sum(meta, I, qsf[h]);
       const float s = valid ? __fmul_rn(T, cc[h]) : -__builtin_inff();
       if (k < npages) hm[h] = fmaxf(hm[h], s);

@@ -83,3 +83,12 @@ def test_one_launch_pruner_of_many_heads_shares_the_cu(kernels, candidates, work
 def test_the_selection_kernels_spill_no_vector_registers(kernels):
     spilled = {n: k[".vgpr_spill_count"] for n, k in kernels.items() if n.startswith("page_select")}
     assert len(spilled) == 14 and not any(spilled.values()), spilled
+
+
+@pytest.mark.parametrize("dots,pages", [(False, 4), (True, 2)])
+def test_scoring_of_two_heads_per_page_keeps_its_waves(kernels, dots, pages):
+    """4-bit codes, every page a candidate, two query heads per KV head: eight waves per SIMD with the integer dots stored, six
+    with four pages in flight."""
+    k = kernels["int4_score_kernel<2, true, %s, %d, 4>" % ("true" if dots else "false", pages)]
+    assert _fits(k, 8 if dots else 6), k[".vgpr_count"]
+    assert not k[".vgpr_spill_count"] and not k[".private_segment_fixed_size"]
