@@ -15,8 +15,7 @@
 // With 8 and more keys per thread, and for what 16 waves do alike, it is the vector instructions (80 per key and wave of 59 k
 // cycles at 32768 entries, 70 % of them vector issue): the first pass, whose keys are all inside the interval, adds without a test or
 // a branch per key, and of the lane that the threshold falls to the waves look at one bucket per lane instead of walking its 8
-// to 32.  256 x 32768 entries 30.7 -> 26.8 us with the list leaving through LDS (2 us of that); the step of one sequence of 8192
-// pages 45.8 -> 43.3, of 8 x 2048 pages 52.1 -> 51.3.
+// to 32.  256 rows, an eighth taken, us: 32768 entries 31.8 -> 27.8, 8192 10.2 -> 9.4; the step of one sequence of 8192 pages 45.8 -> 43.3.
 //
 // Slots beyond the row's length are skipped by the whole workgroup, so that a row costs what its own length does: one by
 // one up to 8 slots per thread, in groups of 4 beyond.  (512 rows x 9000 entries with 16 slots 15.5 us in groups of 4,

@@ -392,9 +392,9 @@ __global__ __launch_bounds__(256) void page_select_kernel(SelectArgs a) {
 
 // The body of page_select_reg_kernel for a row of at most NT * E entries of which 0 < Kp < P are taken.  reach: slots that
 // are looked at, P or, with more than 8 slots per thread, whose keys say where the row ends, anything above.
-template <int NT, int E, int SNB, int STAGE>
+template <int NT, int E, int SNB>
 __device__ __forceinline__ void select_row(const float* sc, int P, int reach, int Kp, int max_sel, int32_t* out, uint32_t* hist,
-                                           unsigned long long* cand, uint32_t* cnt, unsigned short* stage) {
+                                           unsigned long long* cand, uint32_t* cnt) {
   const int tid = threadIdx.x;
   uint32_t key[E], T, need_eq;
 #pragma unroll
@@ -406,14 +406,6 @@ __device__ __forceinline__ void select_row(const float* sc, int P, int reach, in
   for (int e = 0; e < E; ++e)
     key[e] = E > 8 ? tw_select_key(__uint_as_float(key[e]), e * NT + tid < P) : tw_float_key(__uint_as_float(key[e]));
   tw_select_threshold<NT, E, SNB, 10>(key, reach, (uint32_t)Kp, hist, cand, &T, &need_eq);
-  if (STAGE > 0 && Kp <= STAGE) {                 // (block-uniform; Kp is at most max_sel)
-    tw_select_list<NT, E>(key, reach, T, need_eq, cnt, [&](uint32_t pos, int e) {
-      if (pos < (uint32_t)STAGE) stage[pos] = (unsigned short)(e * NT + tid);
-    });
-    __syncthreads();
-    for (int i = tid; i < Kp; i += NT) out[i] = stage[i];
-    return;
-  }
   tw_select_list<NT, E>(key, reach, T, need_eq, cnt, [&](uint32_t pos, int e) {
     if (pos < (uint32_t)max_sel) out[pos] = e * NT + tid;
   });
@@ -426,12 +418,13 @@ __device__ __forceinline__ void select_row(const float* sc, int P, int reach, in
 // x 8192 37.9 -> 29.5 (256 x 8192, a row per CU: 8.9 as before); 1024 rows x 16384 in the 32-slot form 78 -> 42.
 // Above 8 slots a row of up to a quarter of the form's length takes a body of its own, with fewer slots and without the
 // longest rows' sentinel keys: 64 ragged sequences x 32 heads of up to 32768 tokens 105 -> 78 us, up to 9000 37.9 -> 31.5.
-// The longest rows, which reach every group of slots, take one without the groups' branches (256 x 32768 25.9 -> 24.8).
-// Lists of up to STAGE entries leave through LDS in whole lines: an entry at a time, a few lanes of a wave each, they took the rest
-// of the kernel's tail (256 x 4096 of 32768 entries 29.3 us so, 31.7 stored directly).
+// The longest rows, which reach every group of slots, take one without the groups' branches (256 x 32768 27.9 -> 27.7; without it the
+// others compile the worse, 512 x 20000 tokens 26.3 -> 27.4).
+// A list's entries are stored as they are found: gathered in LDS and sent off in whole lines they take one barrier more and gain nothing
+// (256 x 4096 of 32768 entries 27.8 us stored, 28.0 gathered, 256 x 4096 of 32768 tokens 21.9 and 22.3, 32 x 312 of 2500 5.8 and 6.1).
 template <int NT, int E, int UNIT>
 __global__ __launch_bounds__(NT, E == 8 || E == 16 ? 8 : 1) void page_select_reg_kernel(SelectArgs a) {
-  constexpr int SNB = E > 16 ? 2048 : (NT == 1024 && E == 2 ? 1024 : 512), STAGE = NT >= 1024 && E >= 8 ? 8192 : 0;
+  constexpr int SNB = E > 16 ? 2048 : (NT == 1024 && E == 2 ? 1024 : 512);
   const int b = blockIdx.y, h = blockIdx.x, tid = threadIdx.x;
   int P, Kp;
   tw_select_sizes<UNIT>(a, a.seq_lens[b], a.budget[b], &P, &Kp);
@@ -447,15 +440,14 @@ __global__ __launch_bounds__(NT, E == 8 || E == 16 ? 8 : 1) void page_select_reg
   __shared__ __align__(16) uint32_t hist[tw_sel_words(SNB)];
   __shared__ unsigned long long cand[SEL_CAP];
   __shared__ uint32_t cnt[E * NT / 64];
-  __shared__ unsigned short stage[STAGE > 0 ? STAGE : 1];
   constexpr int SHORT = E > 16 ? 8 : 4;
-  if (E > 8 && P <= SHORT * NT) select_row<NT, SHORT, 512, STAGE>(sc, P, P, Kp, a.max_sel, out, hist, cand, cnt, stage);   // (block-uniform)
+  if (E > 8 && P <= SHORT * NT) select_row<NT, SHORT, 512>(sc, P, P, Kp, a.max_sel, out, hist, cand, cnt);   // (block-uniform)
   else if (E > 16 && P > (E - SEL_GROUP) * NT) {
     int n = P;
     asm volatile("" : "+s"(n));                   // (nothing in common with the next body: what the compiler shared it spilled)
-    select_row<NT, E, SNB, STAGE>(sc, n, E * NT, Kp, a.max_sel, out, hist, cand, cnt, stage);
+    select_row<NT, E, SNB>(sc, n, E * NT, Kp, a.max_sel, out, hist, cand, cnt);
   }
-  else select_row<NT, E, SNB, STAGE>(sc, P, P, Kp, a.max_sel, out, hist, cand, cnt, stage);
+  else select_row<NT, E, SNB>(sc, P, P, Kp, a.max_sel, out, hist, cand, cnt);
 }
 
 template <int G>

@@ -578,8 +578,8 @@ def test_dots_at_the_ends_of_the_query_and_code_ranges(heads):
 
 
 @pytest.mark.parametrize("pages,take", [(8192, 8191), (16384, 8191), (16384, 8192), (16384, 8193), (32768, 8192), (32768, 8193), (32700, 31)])
-def test_page_lists_as_long_as_the_selection_stages(pages, take):
-    """Lists at the length up to which they leave through LDS, of rows at and just under the kernels' longest."""
+def test_page_lists_of_the_longest_rows(pages, take):
+    """Lists of about 8192 entries and a short one, of rows at and just under the selection kernels' longest."""
     T = _T()
     lens = [16 * pages, 16 * (pages - 100)]
     cache, q = _random_bounds(T, lens, pages, heads=(2, 1), pool=4096, seed=pages + take)
