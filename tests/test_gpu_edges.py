@@ -593,3 +593,54 @@ def test_page_lists_of_the_longest_rows(pages, take):
             U = O.page_upper_bounds(synth.bits(q[b, h].cpu()), u16(rows[:, 0]), u16(rows[:, 1]))
             want = O.select_pages(U, 16 * take, n)
             assert st.sel_pages[b, h, :int(st.sel_count[b, h])].cpu().numpy().tolist() == want.tolist(), (b, h)
+
+
+def _infinite_bounds(T, P, seqs, high, low, seed):
+    """Cache of `seqs` sequences of P pages of which `high` have an infinite bound, `low` minus infinity and one the largest
+    and one the smallest finite bound (their difference is infinite too); a query of positive values."""
+    g = torch.Generator().manual_seed(seed)
+    cache = T.PagedKV(2, 1, torch.arange(P, dtype=torch.int32).view(1, P).repeat(seqs, 1), torch.tensor([16 * P] * seqs), P, need_v=False)
+    mm = torch.randn(P, 1, 2, 128, generator=g).sort(dim=2).values
+    at = torch.randperm(P, generator=g)
+    mm[at[:high]], mm[at[high:high + low]] = 3e38, -3e38
+    for page, sign in ((at[-1], 1.0), (at[-2], -1.0)):
+        mm[page], mm[page, :, :, 0] = 0.0, sign * 3e38
+    cache.page_minmax.copy_(mm.to(torch.bfloat16))
+    q = torch.randn(seqs, 2, 128, generator=g).abs() + 1e-3
+    q[:, :, 0] = 1.0
+    return cache, q.to(torch.bfloat16)
+
+
+def _infinite_bounds_want(cache, q, P, take):
+    mm = cache.page_minmax.cpu()
+    with np.errstate(over="ignore"):
+        return [O.select_pages(O.page_upper_bounds(synth.bits(q[b, h]), u16(mm[:, 0, 0]), u16(mm[:, 0, 1])), 16 * take, 16 * P).tolist()
+                for b in range(q.shape[0]) for h in range(2)]
+
+
+@pytest.mark.parametrize("high,low", [(0, 0), (1, 0), (0, 1), (3, 5), (90, 100)])
+@pytest.mark.parametrize("P", [400, 600, 2050, 8194, 16388, 32768])
+def test_page_lists_of_rows_with_infinite_bounds(P, high, low):
+    """Bounds that overflow, and finite ones whose difference does, in rows of every selection kernel: the threshold among the
+    finite bounds, among the infinite ones and below them."""
+    T = _T()
+    cache, q = _infinite_bounds(T, P, 1, high, low, P + high)
+    for take in sorted({1, 70, P // 3, P - 60, P - 1}):
+        st = T.DecodeStep(cache, max_sel=take)
+        st.select(q.cuda(), torch.full((1,), 16 * take, dtype=torch.int32, device="cuda"))
+        torch.cuda.synchronize()
+        got = [st.sel_pages[0, h, :int(st.sel_count[0, h])].cpu().numpy().tolist() for h in range(2)]
+        assert got == _infinite_bounds_want(cache, q, P, take), take
+
+
+@pytest.mark.parametrize("P,seqs,take", [(400, 1, 50), (400, 200, 50), (2000, 1, 100), (4000, 1, 200), (4000, 200, 200), (4000, 200, 400), (8192, 2, 300)])
+def test_one_launch_selection_of_rows_with_infinite_bounds(P, seqs, take):
+    """The same where the pages are picked inside the pruner's kernel."""
+    T = _T()
+    for high, low in ((0, 0), (5, 3), (take + 40, 70)):
+        cache, q = _infinite_bounds(T, P, seqs, high, low, P + take)
+        st = T.DecodeStep(cache, max_sel=take)
+        st.select_prune(None, None, None, q.cuda(), torch.full((seqs,), 16 * take, dtype=torch.int32, device="cuda"), 0.9)
+        torch.cuda.synchronize()
+        got = [r[:n].tolist() for r, n in zip(st.sel_pages.view(2 * seqs, -1).cpu().numpy(), st.sel_count.view(-1).cpu().numpy())]
+        assert got == _infinite_bounds_want(cache, q, P, take), (high, low)
