@@ -547,11 +547,9 @@ def test_lists_about_as_many_as_workgroups_are_shared_evenly():
     assert many < 1.12 * few, (many, few)
 
 
-@pytest.mark.parametrize("heads", [(2, 2), (4, 2)])
-def test_dots_at_the_ends_of_the_query_and_code_ranges(heads):
-    """Integer dots of 4-bit codes bit for bit where the query's int8 values are at the ends of their range and of its 4-bit
-    halves, against keys whose codes are 0 and 15 in whole groups."""
-    T = _T()
+def _range_ends(heads, scale=1.0):
+    """Queries whose int8 values are at the ends of their range and of its 4-bit halves, against keys whose codes are 0 and 15 in
+    whole groups."""
     Hq, Hkv = heads
     ramp = np.concatenate([np.arange(-127, -63), np.arange(64, 128)])
     rows = [np.full(128, 127), np.full(128, -127), np.where(np.arange(128) % 2, 127, -127), ramp, np.roll(ramp[::-1], 5),
@@ -559,9 +557,26 @@ def test_dots_at_the_ends_of_the_query_and_code_ranges(heads):
     n = 40
     w = synth.make_workload("ends", [n] * len(rows), num_q_heads=Hq, num_kv_heads=Hkv, budget=32, p=0.9, need_v=False, seed=97)
     for b, row in enumerate(rows):
-        w.q[b] = torch.from_numpy(np.stack([np.roll(row, 7 * h) for h in range(Hq)]).astype(np.float32)).to(torch.bfloat16)
+        w.q[b] = torch.from_numpy(np.stack([np.roll(row, 7 * h) for h in range(Hq)]).astype(np.float32) * scale).to(torch.bfloat16)
     w.k[::3] = torch.where(torch.arange(128) % 2 == 0, 1.0, -1.0).to(torch.bfloat16)       # codes 15 and 0
     w.k[1::5, :, :64] = 2.0                                                                   # constant groups
+    return w, n
+
+
+def _range_ends_want(w, b, h):
+    """The oracle's integer dots and scores of a head over its sequence's tokens."""
+    u, s, z = O.quantize_k(synth.bits(w.seq_k(b)[:, h // (w.num_q_heads // w.num_kv_heads)]))
+    qi, sq = O.quantize_q(synth.bits(w.q[b, h]))
+    return O.int4_dots(qi, u)[0], O.int4_scores(qi, sq, u, s, z)
+
+
+@pytest.mark.parametrize("heads", [(2, 2), (4, 2)])
+def test_dots_at_the_ends_of_the_query_and_code_ranges(heads):
+    """Integer dots of 4-bit codes bit for bit where the query's int8 values are at the ends of their range and of its 4-bit
+    halves, against keys whose codes are 0 and 15 in whole groups."""
+    T = _T()
+    Hq, Hkv = heads
+    w, n = _range_ends(heads)
     cache = build_cache(w)
     stride = cache.page_table.shape[1] * 16
     sc = torch.zeros(w.batch, Hq, stride, dtype=torch.float32, device="cuda")
@@ -570,11 +585,57 @@ def test_dots_at_the_ends_of_the_query_and_code_ranges(heads):
     torch.cuda.synchronize()
     for b in range(w.batch):
         for h in range(Hq):
-            u, s, z = O.quantize_k(synth.bits(w.seq_k(b)[:, h // (Hq // Hkv)]))
-            qi, sq = O.quantize_q(synth.bits(w.q[b, h]))
-            I, _ = O.int4_dots(qi, u)
+            I, S = _range_ends_want(w, b, h)
             assert np.array_equal(dots[b, h, :n].cpu().numpy(), I), (b, h)
-            assert np.array_equal(sc[b, h, :n].cpu().numpy(), O.int4_scores(qi, sq, u, s, z)), (b, h)
+            assert np.array_equal(sc[b, h, :n].cpu().numpy(), S), (b, h)
+
+
+@pytest.mark.parametrize("heads", [(2, 2), (4, 2), (4, 1)])
+@pytest.mark.parametrize("tokens", [False, True], ids=["pages", "tokens"])
+def test_dots_of_lists_at_the_ends_of_the_query_and_code_ranges(heads, tokens):
+    """The same through the scoring of page lists and of token lists."""
+    T = _T()
+    Hq, Hkv = heads
+    w, n = _range_ends(heads)
+    cache = build_cache(w)
+    item = 1 if tokens else 16
+    entries = list(range(n)) if tokens else [0, 2, 1]
+    order = np.concatenate([np.arange(e * item, min(n, (e + 1) * item)) for e in entries])           # the slots' tokens ...
+    slots = np.concatenate([np.arange(i * item, i * item + min(n, (e + 1) * item) - e * item) for i, e in enumerate(entries)])
+    length = 48 if tokens else 3
+    lists = torch.zeros(w.batch, Hq, length, dtype=torch.int32, device="cuda")
+    lists[..., :len(entries)] = torch.tensor(entries, dtype=torch.int32, device="cuda")
+    count = torch.full((w.batch, Hq), len(entries), dtype=torch.int32, device="cuda")
+    sc = torch.zeros(w.batch, Hq, 48, dtype=torch.float32, device="cuda")
+    dots = torch.zeros(w.batch, Hq, 48, 4, dtype=torch.int32, device="cuda")
+    score = T.twilight_int4_score_tokens if tokens else T.twilight_int4_score
+    score(cache.kv, w.q.cuda(), lists, count, length, sc, dots)
+    torch.cuda.synchronize()
+    for b in range(w.batch):
+        for h in range(Hq):
+            I, S = _range_ends_want(w, b, h)
+            assert np.array_equal(dots[b, h].cpu().numpy()[slots], I[order]), (b, h)
+            assert np.array_equal(sc[b, h].cpu().numpy()[slots], S[order]), (b, h)
+
+
+@pytest.mark.parametrize("heads,max_sel", [((2, 2), 3), ((4, 1), 3), ((4, 2), 200), ((4, 1), 500)])
+def test_kept_sets_at_the_ends_of_the_query_and_code_ranges(heads, max_sel):
+    """The same scores inside the one-launch selector + pruner, by the tokens that it keeps (the query scaled by a power of
+    two, which leaves its integers alone and spreads the weights over the tokens)."""
+    T = _T()
+    w, n = _range_ends(heads, scale=2.0 ** -8)
+    cache = build_cache(w)
+    st = T.DecodeStep(cache, max_sel=max_sel, with_kept_idx=True)
+    for p in (0.3, 0.9, 0.99):
+        st.select_prune(None, None, None, w.q.cuda(), torch.full((w.batch,), n, dtype=torch.int32, device="cuda"), p)
+        torch.cuda.synchronize()
+        for b in range(w.batch):
+            for h in range(heads[0]):
+                S = _range_ends_want(w, b, h)[1]
+                mask, tau = O.topp_set(S, float(np.float32(p)))                  # (p crosses the C ABI as a float)
+                got = np.isin(np.arange(n), st.kept_idx[b, h, :int(st.kept_count[b, h])].cpu().numpy())
+                W = O.softmax_weights(S)
+                assert np.all(np.abs(W[got != mask] - tau) <= 1e-6), (b, h, p)
 
 
 @pytest.mark.parametrize("pages,take", [(8192, 8191), (16384, 8191), (16384, 8192), (16384, 8193), (32768, 8192), (32768, 8193), (32700, 31)])

@@ -76,8 +76,25 @@ def test_one_launch_pruner_of_many_heads_shares_the_cu(kernels, candidates, work
     for G in (1, 2, 4, 8):
         k = kernels["topp_head_kernel<512, %d, %d, false, 2, %d>" % (candidates, G, bits)]
         assert _fits(k, workgroups), k[".vgpr_count"]
-        assert k[".vgpr_spill_count"] <= spilled and k[".private_segment_fixed_size"] <= (68 if spilled else 0)
+        assert k[".vgpr_spill_count"] <= spilled and k[".private_segment_fixed_size"] <= (0 if not spilled else 68 if G == 1 else 36)
         assert k[".group_segment_fixed_size"] * workgroups <= 160 * 1024
+
+
+@pytest.mark.parametrize("bits", [2, 4, 8])
+@pytest.mark.parametrize("threads,workgroups", [(512, 4), (256, 8)])
+def test_one_launch_pruner_of_short_lists_fills_the_cu(kernels, threads, workgroups, bits):
+    """4 candidates per thread: 64 registers, every wave slot of the CU taken."""
+    for G in (1, 2, 4, 8):
+        k = kernels["topp_head_kernel<%d, 4, %d, false, 2, %d>" % (threads, G, bits)]
+        assert _fits(k, workgroups), k[".vgpr_count"]
+        assert k[".group_segment_fixed_size"] * workgroups <= 160 * 1024
+
+
+def test_pruner_kernels_without_a_spill(kernels):
+    """All but the forms that four to a CU are paid for with (8 candidates per thread in LDS), which the test above bounds."""
+    heads = {n: k for n, k in kernels.items() if n.startswith("topp_head_kernel") and not re.search(r"<512, 8, \d, false, 2, ", n)}
+    spilled = {n: (k[".vgpr_spill_count"], k[".private_segment_fixed_size"]) for n, k in heads.items()}
+    assert len(spilled) > 100 and not any(v != (0, 0) for v in spilled.values()), {n: v for n, v in spilled.items() if v != (0, 0)}
 
 
 def test_the_selection_kernels_spill_no_vector_registers(kernels):
