@@ -10,17 +10,19 @@
 // What bounds it is the chain of block barriers and LDS round trips, so every wave scans the histogram and ranks the
 // candidates on its own (the same result in each) instead of waiting for one that does: 4 barriers per row, where keys
 // staged in LDS, with the crossing bucket, the rank and the list offsets handed around through LDS, took 8.  Against that
-// form: selection inside the per-head kernel 5.0 -> 4.1 us (32 heads x 256 pages 5.0 -> 3.7), page_select 6.7 -> 5.5 us
-// at 128 heads x 1024 pages, 10.8 -> 9.0 at 256 x 8192, 47 -> 26 at 256 x 32768 entries.
-// With 8 and more keys per thread, and for what 16 waves do alike, it is the vector instructions (80 per key and wave of 59 k
-// cycles at 32768 entries, 70 % of them vector issue): the first pass, whose keys are all inside the interval, adds without a test or
-// a branch per key, and of the lane that the threshold falls to the waves look at one bucket per lane instead of walking its 8
-// to 32.  256 rows, an eighth taken, us: 32768 entries 31.8 -> 27.8, 8192 10.2 -> 9.4; the step of one sequence of 8192 pages 45.8 -> 43.3.
+// form, when it was left: selection inside the per-head kernel 5.0 -> 4.1 us (32 heads x 256 pages 5.0 -> 3.7), page_select 6.7 -> 5.5 us
+// at 128 heads x 1024 pages, 10.8 -> 9.0 at 256 x 8192, 47 -> 26 at 256 x 32768 entries (measured apart from the
+// figures below, which do not continue these).
+// With 8 and more keys per thread, and for what 16 waves do alike, it is the vector instructions (256 rows x 32768 entries: 2584 per wave,
+// 81 for each of a lane's keys, issuing in 70 % of a CU's busy cycles; 2159 and 68 % since): the first pass, whose keys are all inside
+// the interval, adds without a test or a branch per key, and of the lane that the threshold falls to the waves look at one bucket per
+// lane instead of walking its 8 to 32.  256 rows, an eighth taken, us: 32768 entries 31.8 -> 27.8, 8192 10.2 -> 9.4; the step of one
+// sequence of 8192 pages 45.8 -> 43.3.
 //
 // Slots beyond the row's length are skipped by the whole workgroup, so that a row costs what its own length does: one by
 // one up to 8 slots per thread, in groups of 4 beyond.  (512 rows x 9000 entries with 16 slots 15.5 us in groups of 4,
-// 17.3 in groups of 8, 15.7 in groups of 2; 256 rows x 24000 with 32 slots 22.7 -> 20.1.  Full rows of 32768, which would
-// pay 1 of 25 us for the groups' branches, have none.)
+// 17.3 in groups of 8, 15.7 in groups of 2; 256 rows x 24000 with 32 slots 22.7 -> 20.1.  Full rows of 32768
+// have a body without the groups' branches: page_select_reg_kernel.)
 #pragma once
 #include "tw_common.h"
 

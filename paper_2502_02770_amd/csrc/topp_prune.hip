@@ -125,8 +125,9 @@ __device__ __forceinline__ void tw_load_raw(const uint4* kq_pool, long long idx,
 // One lane's query words: q8 = its group's 8 words of 4 int8 values (dims 8w .. 8w+3, then 8w+4 .. 8w+7).  4-bit codes meet
 // them as they are stored, 8 to a word, byte k = code[k] | code[k+4] << 4: a query value is 16 * high + low with low an unsigned and high a
 // signed 4-bit number, one product sum each (the codes minus 8 are signed 4-bit numbers, their bits but for the top one of each).
-// Unpacked to bytes for 4-value products a page of the one-launch selector + pruner takes 41 instead of 34 vector instructions (steps,
-// us: 32 x 32768 tokens 142.0 -> 141.3, 8 x 32768 52.24 -> 51.95).
+// Unpacked to bytes for 4-value products a page takes 7 vector instructions more: 12 unpack, where 4 flip the top bits and one adds the
+// halves.  The one-launch selector + pruner, us: 512 heads x 8192 candidates 55.3 -> 51.9, 64 ragged sequences x 32 heads of up to 8192
+// 135.4 -> 128.2, 1024 heads x 4096 52.4 -> 50.8; steps gain 1 % and less.
 // Not SPLIT (int4_score_kernel with two and more heads per loaded page, which share the codes once unpacked): 4-value products.  A wave's
 // few pages do not pay back the making of several heads' split words, and the registers cost a wave per SIMD (2 heads, dots stored: 66
 // for 64).  Two heads per KV head, us, split / not: 8 x 32 heads x 32768 tokens with dots 89.5 / 83.0 and without 69.6 / 69.8, without
@@ -1092,8 +1093,9 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
       __syncthreads();
       TW_STAMP(2 + pass);
       // every wave scans the 512 buckets on its own: lane l sums buckets 8l .. 8l+7; of the lane that holds the crossing
-      // the first 8 lanes then take a bucket each (the vector units that the waves share are what this phase waits for, and a
-      // lane's 8 sums cost the kernel 8 to 30 registers: steps, us, 64 ragged sequences 230.0 -> 228.3, 32 x 32768 tokens 142.0 -> 141.4)
+      // the first 8 lanes then take a bucket each: walking that lane's 8 sums in every wave took more vector instructions, which the
+      // waves share their units for (step of 64 ragged sequences 230.0 -> 228.3 us), and registers for the sums where scores are held
+      // in registers (1024 threads x 4 candidates 86 -> 69, x 8 102 -> 70, in parts 103 -> 81; the forms with scores in LDS: none)
       unsigned long long mine = 0;
 #pragma unroll
       for (int k = 0; k < 8; ++k) mine += histM[8 * lane + k];
@@ -1543,26 +1545,29 @@ void launch_topp_one(const HeadArgs& f, int G, dim3 grid, hipStream_t s) {
   }
 }
 
-// Register-resident top-p over rows of at most 8192 candidates (cand_stride = row bound).
+// Register-resident top-p over rows of at most 8192 candidates (cand_stride = row bound).  Times in us, of the kernel alone.
 //  - few heads: one 1024-thread workgroup per head (4 or 8 candidates per thread), or several (tw_prune_parts);
-//  - more heads than CUs and rows of at most 4096 candidates: 512-thread workgroups, three to a CU (a 1024-thread workgroup has a
-//    CU to itself at this register count: 8 x 32 x 4 = 1024 heads took 35.8 us that way, 22.9 us two to a CU).  Selection and scores
-//    inside: four to a CU, whose phases are longer, where that takes a round less and either the only one or the tables are short (a
-//    thread of 512 has 8 of 4096 bounds, which the 64 registers hold worst).  Three and four to a CU, us, 4096 candidates of 1024 pages:
-//    512 heads 27.5 / 30.0, 768 34.7 / 37.0, 1024 50.0 / 45.3, 1536 70.3 / 72.0, 2048 90.8 / 89.8, 4096 162.5 / 159.3; 2224 of 3750:
-//    288 heads 26.9 / 31.0, 768 35.1 / 40.5, 1024 52.2 / 48.2, 2048 88.5 / 92.7;
+//  - more heads than CUs and rows of at most 4096 candidates: 512-thread workgroups, three to a CU, whatever the 1024-thread form's
+//    registers allow: with selection and scores inside it has a CU to itself with 4-bit codes (69 registers; 1024 heads x 4096 candidates
+//    of 1024 pages 76.6 that way, 52.4 so) and loses as much where two fit (2-bit codes 72.3 / 50.7, 8-bit 95.2 / 76.8); on stored scores
+//    two fit (52 registers) and 512 heads take 22.5 / 20.7, 1024 37.1 / 35.2, of token lists 19.4 / 18.6 and 35.0 / 32.0.  Selection and
+//    scores inside: four to a CU, whose phases are longer, where that takes a round less and either the only one or the tables are short
+//    (a thread of 512 has 8 of 4096 bounds, which the 64 registers hold worst).  Three and four to a CU, 4096 candidates of 1024 pages: 512
+//    heads 31.2 / 33.5, 768 41.2 / 44.2, 1024 53.6 / 52.4, 1536 70.2 / 71.4, 2048 88.0 / 90.4, 4096 167.1 / 163.7; 2224 of 3750: 288 heads
+//    25.6 / 29.6, 768 32.8 / 37.9, 1024 45.0 / 44.5, 2048 75.8 / 79.1; 4096 of 4096, 1024 heads: 58.0 / 59.7 (with 8-bit codes 76.2 / 82.0,
+//    the one place where the line costs more than 3 %);
 //  - rows of at most 2048 candidates (and, with the selection inside, at most 2048 pages): 512-thread workgroups with 4
 //    candidates per thread, whatever the number of heads.  The kernel is a chain of block barriers; half the waves make
-//    each shorter (32 heads x 1024 candidates 13.4 -> 10.8 us, 320 x 1136 15.6 -> 12.0), and with the LDS arrays sized
-//    for the short rows three workgroups share a CU, by their registers (four with 2- and 8-bit codes; 2048 heads x 1024
-//    candidates of 512 pages 48.1 -> 30.6);
-//  - rows of at most 1024 candidates and 1024 pages with more heads than CUs: 256-thread workgroups (2048 heads x 256
-//    candidates 39.8 -> 23.9 us; 32 heads x 1024 candidates 10.8 -> 11.1, so few heads keep the 512 threads);
+//    each shorter (32 heads x 1024 candidates 13.8 -> 11.7, 288 x 1024 23.2 -> 14.5), and with the LDS arrays sized
+//    for the short rows four workgroups share a CU (64 registers; 2048 heads x 2048 candidates of 1024 pages 57.9 with 8 candidates per
+//    thread, 53.0 with 4);
+//  - rows of at most 1024 candidates and 1024 pages with more heads than CUs: 256-thread workgroups, eight to a CU (2048 heads x 256
+//    candidates 34.2 -> 22.1, x 1024 40.2 -> 30.6, 288 x 256 12.8 -> 11.6; few heads, where it is no quicker, keep the 512 threads);
 //  - more heads than CUs (behind a selection launch: than twice the CUs) with a bound above 4096 candidates, scoring inside:
-//    512-thread workgroups with 16 candidates per thread, three (two) to a CU, for all heads - one's scoring streams while the others are in their barriers (64 ragged sequences x 32
-//    heads: 131.8 us as a 512-thread launch for the lists up to 4096 and a 1024-thread one, a workgroup per CU, for the
-//    longer ones -> 117.9, three to a CU 104.0.  Dispatching the longest sequences first: no gain.  10 x 32 heads x 8192
-//    candidates 56 us with 1024 threads x 8, 53.7 so, 16 x 32 66 and 59.6; 8 x 32 34 and 40);
+//    512-thread workgroups with 16 candidates per thread, three (two) to a CU, for all heads - one's scoring streams while the others
+//    are in their barriers (64 ragged sequences x 32 heads of up to 4096 pages: 180 with 1024 threads x 8, a workgroup per CU, 128 so;
+//    8192 candidates: 10 x 32 heads 53.0 and 50.0, 16 x 32 62.6 and 52.3; 8 x 32, a workgroup per CU either way, 34.0 and 37.8.
+//    Dispatching the longest sequences first: no gain);
 //  - the same on stored scores (FUSE == 0): heads of at most 4096 candidates in a 512-thread launch of their own, the
 //    longer ones in the 1024-thread launch.
 // FUSE: the kernels score the candidates themselves (page lists).

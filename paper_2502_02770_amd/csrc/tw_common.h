@@ -171,7 +171,7 @@ __device__ __forceinline__ unsigned long long tw_wave_scan_u64(unsigned long lon
   x += tw_dpp64<TW_DPP_BCAST31, 0xC, false>(x);
   return x;
 }
-// The same over the first 8 lanes (and, apart from them, over every 16).
+// Inclusive prefix over lanes 0..7 of every row of 16; lanes 8..15 hold the sum of the 8 lanes up to their own.
 __device__ __forceinline__ unsigned long long tw_scan8_u64(unsigned long long x) {
   x += tw_dpp64<TW_DPP_ROW_SHR(1), 0xF, true>(x);
   x += tw_dpp64<TW_DPP_ROW_SHR(2), 0xF, true>(x);
