@@ -743,8 +743,8 @@ constexpr int HP_USTAGE = 4096;               // union lists up to this length l
 // FUSE == 2: the page list too is made here, from the bounds of all pages (the selection of page_select_reg_kernel).
 // FUSE == 3: the same with a.parts workgroups per head, for few heads with long lists, whose lists one workgroup per head
 // pulls too slowly.  Each selects the head's pages (the same list in each), scores its share of them into the head's row,
-// and the last one to get there goes on with top-p alone (1 x 32 heads x 8192 pages, 8192 candidates: page_select 11.4 +
-// int4_score 6.3 + topp 12.8 us -> 27.9; 4 x 32 heads x 4096 pages 32.9 -> 30.5).
+// and the last one to get there goes on with top-p alone (1 x 32 heads x 8192 pages, 8192 candidates: page_select 6.6 +
+// int4_score 5.0 + topp 19.2 us -> 30.4; 4 x 32 heads x 4096 pages 35.5 -> 32.0).
 // FUSE == 4: FUSE == 2 with the scores in registers where that would leave them in LDS.
 // BITS: width of the quantised copy's codes (FUSE >= 2; else 4).
 template <int NT, int EPT, int G, bool TOK = false, int FUSE = 0, int BITS = 4>
@@ -1736,8 +1736,8 @@ bool tw_prune_fused_ok(const TwDims& d, int max_sel, bool with_select) {
   return !with_select || d.max_pages <= 4096;      // the selection's keys share the kernel's LDS staging array
 }
 // Workgroups per head when it is to be split (see topp_head_kernel, FUSE == 3), 1: not.  As many as give every CU one, for
-// lists above 4096 candidates on at most half as many heads as CUs (steps, us: 1 x 32 heads x 4096 pages x 8192 candidates
-// 46.5 -> 42.5, 2 x 32 53.9 -> 49.3, 4 x 32 65.2 -> 61.0).  Shorter lists lose: the hand-off costs 1.4 us and reading the
+// lists above 4096 candidates on at most half as many heads as CUs (selector and pruner, us, against launches of their own: 1 x 32 heads
+// x 4096 pages x 8192 candidates 33.6 -> 31.5, 2 x 32 41.1 -> 37.1, 4 x 32 49.7 -> 45.8).  Shorter lists lose: the hand-off costs 1.4 us and reading the
 // scores back 2 (32 heads x 4096 candidates 19.9 us in one workgroup each, 21.4 split; 64 x 2000 14.4 and 20.1).
 int tw_prune_parts(const TwDims& d, int max_sel) {
   const long long heads = (long long)d.batch * d.Hq;
