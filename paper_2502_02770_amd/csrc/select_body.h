@@ -154,8 +154,9 @@ __device__ __forceinline__ void tw_select_threshold(uint32_t (&key)[E], int P, u
     // for the first passes.  Otherwise (spans in the subnormal range, infinite scores, finite ones whose difference
     // is not, NaN, rows that keep falling into one bucket) they are linear in the order-preserving key, which splits any
     // span of at least SNB keys SNB ways and resolves a shorter one exactly, so every pass narrows the interval.
-    // (An infinite span makes the scale 0 and a place the conversion of 0 * inf, which no bound holds.)
-    const bool by_key = !(scale > 0.f && scale <= 3.0e38f) || !(smx - smn >= 1.1754944e-38f) || pass >= 3;
+    // (An infinite span makes the scale 0 and a place the conversion of 0 * inf, which no bound holds; a scale up to 3e38 is that
+    // of a span of at least SNB / 3e38, a normal number.)
+    const bool by_key = !(scale > 0.f && scale <= 3.0e38f) || pass >= 3;
     const uint32_t span = khi - klo;
     const int kshift = span < (uint32_t)SNB ? 0 : 32 - __clz(span) - (LB + 6);
     // place from the top, 0 .. SNB - 1, of a key inside the interval
