@@ -122,6 +122,30 @@ __device__ __forceinline__ void tw_load_raw(const uint4* kq_pool, long long idx,
   else if (BITS == 2) { const uint2 c = ((const uint2*)kq_pool)[idx]; r[0] = make_uint4(c.x, c.y, 0u, 0u); }
   else { r[0] = kq_pool[idx * 2]; r[BITS == 8 ? 1 : 0] = kq_pool[idx * 2 + 1]; }
 }
+// A whole page's codes and (scale, zero) words by a wave, the page (row = pool page * Hkv + KV head) the same for all lanes: as
+// buffers of the page's own size, so that the addresses are scalar and a page that is not there reads as zeros without going to memory.
+// (What bounds many heads' scoring is vector instructions, next to the phases' barriers: 35 per page and wave with 64-bit vector
+// addresses, a validity test per token and (scale, zero) words converted before they were multiplied, 22 so.  The one-launch
+// selector + pruner, us: 5 x 64 heads x 5960 candidates 40.8 -> 36.6, 48 ragged sequences x 32 heads of up to 5000 51.9 -> 45.0,
+// 64 of up to 8192 100.5 -> 95.5, 1024 x 4096 55.9 -> 54.2, 8 x 32 x 4096 21.1 -> 20.7.)
+template <int BITS>
+__device__ __forceinline__ void tw_load_page(const uint4* kq_pool, const uint32_t* kq_meta, long long row, bool there, int lane,
+                                             uint4 (&r)[BITS == 8 ? 2 : 1], uint32_t* meta) {
+  constexpr int BYTES = 256 * BITS, FORMAT = 0x00027000;
+  const auto codes = __builtin_amdgcn_make_buffer_rsrc((char*)kq_pool + row * BYTES, 0, there ? BYTES : 0, FORMAT);
+  const auto words = __builtin_amdgcn_make_buffer_rsrc((char*)kq_meta + row * 256, 0, there ? 256 : 0, FORMAT);
+  if (BITS == 2) {
+    const auto c = __builtin_amdgcn_raw_buffer_load_b64(codes, lane * 8, 0, 0);
+    r[0] = make_uint4(c[0], c[1], 0u, 0u);
+  } else {
+#pragma unroll
+    for (int i = 0; i < (BITS == 8 ? 2 : 1); ++i) {
+      const auto c = __builtin_amdgcn_raw_buffer_load_b128(codes, lane * (4 * BITS) + 16 * i, 0, 0);
+      r[i] = make_uint4(c[0], c[1], c[2], c[3]);
+    }
+  }
+  *meta = __builtin_amdgcn_raw_buffer_load_b32(words, lane * 4, 0, 0);
+}
 // One lane's query words: q8 = its group's 8 words of 4 int8 values (dims 8w .. 8w+3, then 8w+4 .. 8w+7).  4-bit codes meet
 // them as they are stored, 8 to a word, byte k = code[k] | code[k+4] << 4: a query value is 16 * high + low with low an unsigned and high a
 // signed 4-bit number, one product sum each (the codes minus 8 are signed 4-bit numbers, their bits but for the top one of each).
@@ -154,7 +178,7 @@ __device__ __forceinline__ void tw_query_words(const int* q8, int (&qw)[8], int*
     }
 #pragma unroll
     for (int w = 0; w < 4; ++w) { qw[w] = high[w]; qw[4 + w] = low[w]; }
-    *i0 = 8 * hs;
+    *i0 = 128 * hs;
   }
 }
 // I = sum over the group's 32 dims of q * code
@@ -162,8 +186,8 @@ template <int BITS, bool SPLIT = BITS == 4>
 __device__ __forceinline__ int tw_group_dot(const int (&qw)[8], const uint4 (&r)[BITS == 8 ? 2 : 1], int i0) {
   if (SPLIT) {
     const uint32_t wv[4] = {r[0].x, r[0].y, r[0].z, r[0].w};
-    int h = i0;
-    uint32_t l = 0;
+    int h = 0;
+    uint32_t l = (uint32_t)i0;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
       h = __builtin_amdgcn_sdot8(qw[w], (int)(wv[w] ^ 0x88888888u), h, false);
@@ -193,9 +217,11 @@ __device__ __forceinline__ int tw_group_dot(const int (&qw)[8], const uint4 (&r)
 // the group's term of the score: fl(scale * I) + fl(zero * sum q), summed over the 4 groups of the
 // token (the 4 lanes of a quad) in the fixed order (T0 + T1) + (T2 + T3)
 __device__ __forceinline__ float tw_token_sum(uint32_t meta, int I, float qsf) {
-  const float sc = __half2float(__ushort_as_half((unsigned short)(meta & 0xFFFFu)));
-  const float ze = __half2float(__ushort_as_half((unsigned short)(meta >> 16)));
-  return tw_quad_sum(__fadd_rn(__fmul_rn(sc, (float)I), __fmul_rn(ze, qsf)));
+  // (each product rounded as it is: fma with -0, the half-precision factor taken as it lies in its word)
+  float sI, zq;
+  asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(sI) : "v"(meta), "v"((float)I), "s"(0x80000000u));
+  asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(zq) : "v"(meta), "v"(qsf), "s"(0x80000000u));
+  return tw_quad_sum(__fadd_rn(sI, zq));
 }
 
 // NH = heads scored per loaded page: 1 with per-head page lists, G when every
@@ -755,7 +781,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
   // in LDS, where every phase reads them again, instead of holding them in registers: three of 16 candidates per thread
   // fit a CU instead of two, four of 8 instead of three, and one's scoring streams while the others wait at barriers
   // (64 ragged sequences x 32 heads 116.6 -> 104.0 us, 32 x 32 heads x 4096 candidates 56.2 -> 53.7).  The price is in the phases:
-  // reading the scores again, 64 registers (75 with 16 candidates per thread) of which the form with 8 spills 8, up to 68 bytes of
+  // reading the scores again, 64 registers (74 with 16 candidates per thread) of which the form with 8 spills 8, 36 bytes of
   // scratch per lane.  Where four to a CU do not save a round of workgroups over three, FUSE == 4 is quicker (launch_topp).
   constexpr bool INLDS = FUSE == 2 && NT <= 512 && EPT > 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -918,30 +944,23 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
     const float qsf = (float)qs, cc = qc_s[0];
     // UF pages in flight per wave.  Several workgroups to a CU: as a ring - a page's codes and (scale, zero) words are asked
     // for in the registers of the page used last, so that loads keep going out while the wave computes (unconditional, or
-    // the wait for one page would take in the pages behind it: a page past the wave's last reads 16 bytes of the wave's
-    // first); 2 us of the two times above.  One workgroup to a CU, whose waves have a round or two each: in rounds, all of
+    // the wait for one page would take in the pages behind it: one past the wave's last reads as zeros); 2 us of the two
+    // times above.  One workgroup to a CU, whose waves have a round or two each: in rounds, all of
     // a round's loads first (8 x 32 heads x 256 pages 22.0 us, as a ring 23.9).  Lanes past the wave's last page hold pool
-    // -1, read pool page 0 in the rounds, and their scores are -inf (inside the array: NW * ppw <= NT * EPT / 16 pages).
+    // -1; what the rounds store for them lies beyond the list (inside the array: NW * ppw <= NT * EPT / 16 pages).
     uint4 nib[UF][BITS == 8 ? 2 : 1];
     uint32_t meta[UF];
-    const int own = __builtin_amdgcn_readfirstlane(my_pool), spare = own >= 0 ? own : 0;
     auto ask = [&](int kk, int k) {
       const int pl = INLDS && k >= npages ? -1 : __builtin_amdgcn_readlane(my_pool, k & 63);   // (lanes past the last page hold -1)
-      const long long blk = ((long long)(pl >= 0 ? pl : (INLDS ? spare : 0)) * a.Hkv + g) * 64;
-      const int at = INLDS && pl < 0 ? 0 : lane;
-      tw_load_raw<BITS>(a.kq_pool, blk + at, nib[kk]);
-      meta[kk] = a.kq_meta[blk + at];
+      tw_load_page<BITS>(a.kq_pool, a.kq_meta, (long long)pl * a.Hkv + g, pl >= 0, lane, nib[kk], &meta[kk]);
     };
     // every lane of a quad stores the token's score (same word)
-    auto use = [&](int kk, int k) {
-      const int lp = __builtin_amdgcn_readlane(my_lp, k & 63), pl = __builtin_amdgcn_readlane(my_pool, k & 63);
-      const bool valid = pl >= 0 && lp * TW_PAGE + (lane >> 2) < n;
-      const float T = tw_token_sum(meta[kk], tw_group_dot<BITS>(qw, nib[kk], i0), qsf);
-      const float sc = valid ? __fmul_rn(T, cc) : -__builtin_inff();
+    auto put = [&](int k, float sc) {
       const int slot = (first + k) * TW_PAGE + (lane >> 2);
       if (!SPLIT) sc_s[slot] = sc;
       else if (k < npages) __hip_atomic_store(a.scores_w + (long long)bh * a.cand_stride + slot, sc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
+    auto use = [&](int kk, int k) { put(k, __fmul_rn(tw_token_sum(meta[kk], tw_group_dot<BITS>(qw, nib[kk], i0), qsf), cc)); };
     int k0 = 0;
     if (INLDS) {
 #pragma unroll
@@ -964,9 +983,16 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
       for (; k0 < npages; k0 += UF) {
 #pragma unroll
         for (int kk = 0; kk < UF; ++kk) ask(kk, k0 + kk);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int kk = 0; kk < UF; ++kk) use(kk, k0 + kk);
       }
+    }
+    // Pages that are not there, and the sequence's last one where it is not full: what does not count is stored anew.
+    const int my_end = my_pool >= 0 ? n - my_lp * TW_PAGE : 0;      // tokens of this lane's page
+    for (unsigned long long part_pages = __ballot(my_end < TW_PAGE && lane < npages); part_pages; part_pages &= part_pages - 1) {
+      const int k = __ffsll((long long)part_pages) - 1;
+      if ((lane >> 2) >= __builtin_amdgcn_readlane(my_end, k)) put(k, -__builtin_inff());
     }
     if (SPLIT) {
       // the hand-off of the bitmaps below: write-through stores, acknowledged, then one count per workgroup; the last one
@@ -1025,6 +1051,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
     if constexpr (INLDS) {
 #pragma unroll
       for (int v = 0; v < EPT / 4; ++v) {
+        if (EPT > 8 && v * 4 * NT >= N) break;     // (block-uniform; of 16 slots a thread most heads of a ragged batch fill few)
         const int at = v * 4 * NT + tid * 4;
         const float4 x = *(const float4*)(sc_s + at);
         f(4 * v, at < N ? x.x : -__builtin_inff());
@@ -1095,7 +1122,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
       // every wave scans the 512 buckets on its own: lane l sums buckets 8l .. 8l+7; of the lane that holds the crossing
       // the first 8 lanes then take a bucket each: walking that lane's 8 sums in every wave took more vector instructions, which the
       // waves share their units for (step of 64 ragged sequences 230.0 -> 228.3 us), and registers for the sums where scores are held
-      // in registers (1024 threads x 4 candidates 86 -> 69, x 8 102 -> 70, in parts 103 -> 81; the forms with scores in LDS: none)
+      // in registers (1024 threads x 4 candidates 86 -> 66, x 8 102 -> 72, in parts 103 -> 80; the forms with scores in LDS: none)
       unsigned long long mine = 0;
 #pragma unroll
       for (int k = 0; k < 8; ++k) mine += histM[8 * lane + k];
@@ -1183,6 +1210,10 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
     TW_STAMP(9);
   }
 
+  // What is needed from here on is read from the kernel's arguments again, or its registers go back and forth between scalar and
+  // vector ones all the way here (16 to 42 of them in the forms that share a CU).
+  const __attribute__((address_space(4))) HeadArgs* late = (const __attribute__((address_space(4))) HeadArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(late));
   // ---- kept flags, count, optional ascending list; bitmap over token positions
   uint32_t cnt = 0, keep = 0;
   each([&](int e, float x) {
@@ -1191,7 +1222,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
     cnt += k ? 1u : 0u;
   });
   uint32_t pos = 0;
-  if (INLDS || !a.kept_idx) {
+  if (INLDS || !late->kept_idx) {
     const uint32_t wsumc = tw_wave_scan_u32(cnt);
     if (lane == 63 && wsumc) atomicAdd(&sh_kept, wsumc);
   } else {                                         // ordered positions need a scan over the block
@@ -1201,13 +1232,13 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
     if (tid == 0) sh_kept = total;
   }
   if (TOK) {
-    int32_t* out = a.kept_idx ? a.kept_idx + (long long)bh * a.kept_stride : nullptr;
+    int32_t* out = late->kept_idx ? late->kept_idx + (long long)bh * late->kept_stride : nullptr;
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
       if ((keep >> e) & 1u) {                       // kept => valid score => a token inside the sequence
         const int tok = pg[e % NPG];
         if ((uint32_t)tok < (uint32_t)(BWORDS * 32)) atomicOr(&bitmap[tok >> 5], 1u << (tok & 31));
-        if (out) { if (pos < (uint32_t)a.kept_stride) out[pos] = tok; ++pos; }
+        if (out) { if (pos < (uint32_t)late->kept_stride) out[pos] = tok; ++pos; }
       }
     }
   } else if (INLDS) {
@@ -1217,14 +1248,14 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
       const uint32_t mask = (keep >> (4 * v)) & 15u;
       const int tok0 = pg[v] * TW_PAGE + (tid * 4 & 15);
       if (mask && tok0 + 3 < BWORDS * 32) atomicOr(&bitmap[tok0 >> 5], mask << (tok0 & 31));
-      if (a.kept_idx) {                             // ordered positions: the slots of v, of all threads, behind those of v - 1
+      if (late->kept_idx) {                             // ordered positions: the slots of v, of all threads, behind those of v - 1
         uint32_t total;
         const uint32_t c = __popc(mask), incl = tw_block_scan_u32(c, ws32, &total);
         pos = run + incl - c;
-        int32_t* out = a.kept_idx + (long long)bh * a.kept_stride;
+        int32_t* out = late->kept_idx + (long long)bh * late->kept_stride;
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if ((mask >> e) & 1u) { if (pos < (uint32_t)a.kept_stride) out[pos] = tok0 + e; ++pos; }
+          if ((mask >> e) & 1u) { if (pos < (uint32_t)late->kept_stride) out[pos] = tok0 + e; ++pos; }
         run += total;
       }
     }
@@ -1236,16 +1267,16 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
     if (mask) {
       const int tok0 = pg[v] * TW_PAGE + (EPT < 16 ? (c0 & 15) : 0);
       if (tok0 + PB - 1 < BWORDS * 32) atomicOr(&bitmap[tok0 >> 5], mask << (tok0 & 31));
-      if (a.kept_idx) {
-        int32_t* out = a.kept_idx + (long long)bh * a.kept_stride;
+      if (late->kept_idx) {
+        int32_t* out = late->kept_idx + (long long)bh * late->kept_stride;
 #pragma unroll
         for (int e = 0; e < PB; ++e)
-          if ((mask >> e) & 1u) { if (pos < (uint32_t)a.kept_stride) out[pos] = tok0 + e; ++pos; }
+          if ((mask >> e) & 1u) { if (pos < (uint32_t)late->kept_stride) out[pos] = tok0 + e; ++pos; }
       }
     }
   }
   __syncthreads();
-  uint32_t* bm = a.bitmaps + (long long)bh * a.words_stride;
+  uint32_t* bm = late->bitmaps + (long long)bh * late->words_stride;
 #ifdef TW_FORMAL_ORDER
   // Measurement build: the hand-off written with the memory model's own pair - plain stores, a workgroup
   // barrier, one agent-scope acq_rel read-modify-write by thread 0 (release: everything the block wrote is
@@ -1253,21 +1284,21 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
   for (int i = tid; i < nwords; i += NT) bm[i] = bitmap[i];
   if (tid == 0) {
     uint32_t kc = sh_kept;
-    if (a.kept_idx && kc > (uint32_t)a.kept_stride) { atomicOr(a.status, TW_STATUS_KEPT_TRUNCATED); kc = a.kept_stride; }
-    a.kept_count[bh] = (int32_t)kc;
+    if (late->kept_idx && kc > (uint32_t)late->kept_stride) { atomicOr(late->status, TW_STATUS_KEPT_TRUNCATED); kc = late->kept_stride; }
+    late->kept_count[bh] = (int32_t)kc;
   }
   const int gi = b * a.Hkv + h / G;
   __syncthreads();
   if (tid == 0)
-    sh_last = __hip_atomic_fetch_add(a.arrive + gi * TW_CTR, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(G - 1) ? 1u : 0u;
+    sh_last = __hip_atomic_fetch_add(late->arrive + gi * TW_CTR, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(G - 1) ? 1u : 0u;
   __syncthreads();
 #else
   // device-scope (write-through) stores: the group's last head reads these words from another CU
   for (int i = tid; i < nwords; i += NT) __hip_atomic_store(bm + i, bitmap[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (tid == 0) {
     uint32_t kc = sh_kept;
-    if (a.kept_idx && kc > (uint32_t)a.kept_stride) { atomicOr(a.status, TW_STATUS_KEPT_TRUNCATED); kc = a.kept_stride; }
-    a.kept_count[bh] = (int32_t)kc;
+    if (late->kept_idx && kc > (uint32_t)late->kept_stride) { atomicOr(late->status, TW_STATUS_KEPT_TRUNCATED); kc = late->kept_stride; }
+    late->kept_count[bh] = (int32_t)kc;
   }
   TW_STAMP(12);
 
@@ -1282,15 +1313,15 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (tid == 0)
-    sh_last = __hip_atomic_fetch_add(a.arrive + gi * TW_CTR, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(G - 1) ? 1u : 0u;
+    sh_last = __hip_atomic_fetch_add(late->arrive + gi * TW_CTR, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(G - 1) ? 1u : 0u;
   __syncthreads();
 #endif
   if (!sh_last) return;
   TW_STAMP_IF(gi == 0, 14);
-  if (tid == 0) __hip_atomic_store(a.arrive + gi * TW_CTR, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
+  if (tid == 0) __hip_atomic_store(late->arrive + gi * TW_CTR, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
   // OR of the group's bitmaps into LDS (this block's own bitmap is no longer needed there): coalesced,
   // four words per thread and bitmap in flight
-  const uint32_t* bmg = a.bitmaps + ((long long)(b * a.Hq + (h / G) * G)) * a.words_stride;
+  const uint32_t* bmg = late->bitmaps + ((long long)(b * a.Hq + (h / G) * G)) * late->words_stride;
   for (int base = 0; base < nwords; base += 4 * NT) {
     uint32_t x[4];
 #pragma unroll
@@ -1302,9 +1333,9 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
 #pragma unroll
         for (int hh = 0; hh < G; ++hh)
 #ifdef TW_FORMAL_ORDER
-          x[k] |= bmg[(long long)hh * a.words_stride + wi];
+          x[k] |= bmg[(long long)hh * late->words_stride + wi];
 #else
-          x[k] |= __hip_atomic_load(bmg + (long long)hh * a.words_stride + wi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          x[k] |= __hip_atomic_load(bmg + (long long)hh * late->words_stride + wi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #endif
       }
     }
@@ -1316,7 +1347,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
   }
   __syncthreads();
   TW_STAMP_IF(gi == 0, 15);
-  int32_t* uout = a.union_idx + (long long)gi * a.union_stride;
+  int32_t* uout = late->union_idx + (long long)gi * late->union_stride;
   uint32_t utotal;
   // (block-uniform choice: long sequences - more than two bitmap words per thread - take the wave-cooperative
   //  listing; with fewer words per thread the plain per-thread walk is as quick and needs fewer registers, which
@@ -1345,7 +1376,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
     const bool staged = utotal <= (uint32_t)USTAGE;
     auto put = [&](uint32_t pos, int tok) {
       if (staged) ustage[pos] = tok;
-      else if (pos < (uint32_t)a.union_stride) uout[pos] = tok;
+      else if (pos < (uint32_t)late->union_stride) uout[pos] = tok;
     };
     for (int r = 0; r < wpw; r += 64) {               // wave-uniform trip count
       const int i = wbase + r + lane;
@@ -1381,7 +1412,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
     }
     if (staged) {
       __syncthreads();
-      const uint32_t lim = utotal < (uint32_t)a.union_stride ? utotal : (uint32_t)a.union_stride;
+      const uint32_t lim = utotal < (uint32_t)late->union_stride ? utotal : (uint32_t)late->union_stride;
       for (uint32_t i = tid; i < lim; i += NT) uout[i] = ustage[i];
     }
   } else {
@@ -1405,7 +1436,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
         }
       }
       __syncthreads();
-      const uint32_t lim = utotal < (uint32_t)a.union_stride ? utotal : (uint32_t)a.union_stride;
+      const uint32_t lim = utotal < (uint32_t)late->union_stride ? utotal : (uint32_t)late->union_stride;
       for (uint32_t i = tid; i < lim; i += NT) uout[i] = ustage[i];
     } else {
       for (int i = w0; i < w1; ++i) {
@@ -1413,15 +1444,15 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
         while (x) {
           const int bit = __ffs(x) - 1;
           x &= x - 1;
-          if (upos < (uint32_t)a.union_stride) uout[upos] = i * 32 + bit;
+          if (upos < (uint32_t)late->union_stride) uout[upos] = i * 32 + bit;
           ++upos;
         }
       }
     }
   }
   if (tid == 0) {
-    if (utotal > (uint32_t)a.union_stride) { atomicOr(a.status, TW_STATUS_UNION_TRUNCATED); utotal = a.union_stride; }
-    a.union_count[gi] = (int32_t)utotal;
+    if (utotal > (uint32_t)late->union_stride) { atomicOr(late->status, TW_STATUS_UNION_TRUNCATED); utotal = late->union_stride; }
+    late->union_count[gi] = (int32_t)utotal;
   }
   TW_STAMP_IF(gi == 0, 13);
 }
@@ -1548,7 +1579,7 @@ void launch_topp_one(const HeadArgs& f, int G, dim3 grid, hipStream_t s) {
 // Register-resident top-p over rows of at most 8192 candidates (cand_stride = row bound).  Times in us, of the kernel alone.
 //  - few heads: one 1024-thread workgroup per head (4 or 8 candidates per thread), or several (tw_prune_parts);
 //  - more heads than CUs and rows of at most 4096 candidates: 512-thread workgroups, three to a CU, whatever the 1024-thread form's
-//    registers allow: with selection and scores inside it has a CU to itself with 4-bit codes (69 registers; 1024 heads x 4096 candidates
+//    registers allow: with selection and scores inside it has a CU to itself with 4-bit codes (66 registers; 1024 heads x 4096 candidates
 //    of 1024 pages 76.6 that way, 52.4 so) and loses as much where two fit (2-bit codes 72.3 / 50.7, 8-bit 95.2 / 76.8); on stored scores
 //    two fit (52 registers) and 512 heads take 22.5 / 20.7, 1024 37.1 / 35.2, of token lists 19.4 / 18.6 and 35.0 / 32.0.  Selection and
 //    scores inside: four to a CU, whose phases are longer, where that takes a round less and either the only one or the tables are short

@@ -2059,3 +2059,28 @@ def test_one_launch_select_prune_of_many_heads_with_long_lists(bits, heads, seqs
     for g in range(heads[1]):
         mine = np.unique(np.concatenate([sb.kept_idx[0, h, :int(sb.kept_count[0, h])].cpu().numpy() for h in range(g * G, g * G + G)]))
         assert sb.union_idx[g, :int(sb.union_count[g])].cpu().numpy().tolist() == mine.tolist()
+
+
+@pytest.mark.parametrize("bits", [2, 4, 8])
+@pytest.mark.parametrize("seqs,max_sel,n", [(2, 30, 1500), (36, 60, 1500), (36, 100, 2500), (36, 200, 4500), (104, 200, 4500), (36, 300, 6000), (2, 300, 6000)])
+def test_one_launch_select_prune_with_unmapped_and_partial_pages(bits, seqs, max_sel, n):
+    """Pages that are not in the pool, whose codes the one-launch selector + pruner does not read, and last pages of 1 to 16
+    tokens, with budgets that cover the sequences (every hole and every last page listed) or not: every workgroup form
+    (few and many heads with lists of up to 480, 960, 1600, 3200 and 4800 candidates) against the separate calls."""
+    T = _T()
+    lens = [n] + [17 + (53 * i) % (n // 3) for i in range(1, seqs)]
+    w = synth.make_workload("holes", lens, num_q_heads=8, num_kv_heads=2, budget=[max_sel * 16] + [max_sel * 16 if i % 2 else 200 for i in range(1, seqs)],
+                            p=0.9, heavy_frac=0.01, alpha_range=(0.0, 3.0), shuffle_pool=True, need_v=False, seed=95)
+    w.page_table = w.page_table.clone()
+    for b in range(seqs):
+        w.page_table[b, (5 * b + 1) % (-(-lens[b] // 16))] = -1 if b % 2 else int(w.num_pool_pages) + b
+    cache = build_cache(w, bits=bits)
+    q, budget = w.q.to(cache.device), w.budget.to(cache.device)
+    for p in (w.p, 1.0):
+        sa = T.DecodeStep(cache, max_sel=max_sel, with_kept_idx=True)
+        sb = T.DecodeStep(cache, max_sel=max_sel, with_kept_idx=True)
+        sa.select(q, budget)
+        sa.prune(q, p)
+        sb.select_prune(None, None, None, q, budget, p)
+        torch.cuda.synchronize()
+        _lists_equal(sa, sb, "p=%g" % p)
