@@ -44,7 +44,33 @@ struct ScoreArgs {
   uint32_t* kq_meta;
   uint4* page_minmax_w;
   uint32_t* arrive;           // [b][Hkv] arrival counters of a top-p launch that follows, cleared here, or nullptr
+  const int32_t* budget;      // with ORDER: the sequences' budgets ...
+  int batch, max_sel;         // ... their number, and the bound of the lists
 };
+
+// The sequences in the order of their heads' work in a launch that follows, the most first: place i's at tw_order_word(i).  By one
+// workgroup, a sequence a thread.  (A listed page's scores cost about what sixteen pages' bounds do.)
+__device__ __forceinline__ void ps_order(const ScoreArgs& a) {
+  static_assert(TW_ORDER_MAX <= 256, "a thread a sequence");
+  const int tid = threadIdx.x, lane = tid & 63;
+  auto work = [&](int i) -> int {
+    if (i >= a.batch) return -1;
+    int P, K;
+    tw_select_sizes<TW_PAGE>(a.seq_lens[i], a.budget[i], a.max_pages, a.max_sel, &P, &K);
+    return K * 16 + P;
+  };
+  const int mine = work(tid);
+  int rank = 0;
+  for (int i0 = 0; i0 < a.batch; i0 += 64) {
+    const int other = work(i0 + lane);
+#pragma unroll 8
+    for (int j = 0; j < 64; ++j) {
+      const int w = __builtin_amdgcn_readlane(other, j);
+      rank += w > mine || (w == mine && i0 + j < tid) ? 1 : 0;
+    }
+  }
+  if (tid < a.batch) a.arrive[tw_order_word(rank, a.Hkv)] = (uint32_t)tid;
+}
 
 // The step's new token, by the 16 lanes that own its page: its K/V rows stored, K quantised, the page's bounds (*rmn, *rmx)
 // folded and stored.
@@ -140,7 +166,7 @@ __device__ __forceinline__ void ps_score(float (&q)[G][8], const uint4& cmn, con
   }
 }
 
-template <int G, bool APPEND, int BITS = 4>
+template <int G, bool APPEND, int BITS = 4, bool ORDER = false>
 __global__ __launch_bounds__(256) void page_score_kernel(ScoreArgs a) {
   // KV head fastest in dispatch order: the 8 heads' bounds of a pool page are 4 KiB contiguous,
   // and the workgroups that read them start next to each other
@@ -148,6 +174,7 @@ __global__ __launch_bounds__(256) void page_score_kernel(ScoreArgs a) {
   const int tid = threadIdx.x, seg = tid & 15, grp = tid >> 4;   // grp: 0..15 page slot in the WG
   TW_STAMP(0);
   const int n = a.seq_lens[b];
+  const int pos_early = APPEND && ORDER ? a.new_pos[b] : -1;       // (with the stores of ps_order behind it not a scalar load any more further down)
   // last pages first: the workgroup that appends the step's new token (the sequence's last page) has the longest
   // chain of dependent accesses and should not be the one that starts last
   const int base = (int)(gridDim.y - 1 - blockIdx.y) * PS_PAGES_PER_WG;
@@ -165,7 +192,8 @@ __global__ __launch_bounds__(256) void page_score_kernel(ScoreArgs a) {
   // (the counters of a top-p launch that follows are cleared on the way out, after every load of the kernel: a store
   //  ahead of them would turn the scalar loads of the prologue into vector loads that wait for one another)
   const bool clears = a.arrive && blockIdx.y == 0 && tid <= G;      // the group's counter and one per head
-  if (base >= P) {
+  const bool orders = ORDER && base == 0 && (blockIdx.x | blockIdx.z) == 0;    // (does not leave early, whatever that sequence's length)
+  if (base >= P && !orders) {
     if (clears) a.arrive[(b * a.Hkv + g) * TW_CTR + tid] = 0;
     return;
   }
@@ -194,7 +222,7 @@ __global__ __launch_bounds__(256) void page_score_kernel(ScoreArgs a) {
   }
   if (APPEND) {
     // the page of the new token, if it lies in this workgroup's pages: its 16 owner lanes append
-    const int sp = a.new_pos[b];
+    const int sp = ORDER ? pos_early : a.new_pos[b];
     const int off = (sp >> 4) - base;
     if (sp >= 0 && sp < n && off >= 0 && off < PS_PAGES_PER_WG && (off & 15) == grp) {
 #pragma unroll
@@ -214,6 +242,7 @@ __global__ __launch_bounds__(256) void page_score_kernel(ScoreArgs a) {
     });
   }
   if (clears) a.arrive[(b * a.Hkv + g) * TW_CTR + tid] = 0;
+  if constexpr (ORDER) { if (orders) ps_order(a); }
 }
 
 // The same for many pages.  What bounds page_score_kernel there is that a workgroup waits for its length, then its page-table
@@ -221,7 +250,7 @@ __global__ __launch_bounds__(256) void page_score_kernel(ScoreArgs a) {
 // once (at most 128 registers, four workgroups per CU), its page-table entries are one load per wave, the new token comes
 // last, where the registers are free, and the scores leave through LDS in whole lines.  Decode steps, us: 16 x 32768 tokens,
 // 64 heads over 8 127.1 -> 123.9, 32 x 32768, 32 over 8 144.5 -> 142.3, 64 ragged sequences of up to 65536 241.8 -> 233.8.
-template <int G, bool APPEND, int BITS = 4>
+template <int G, bool APPEND, int BITS = 4, bool ORDER = false>
 __global__ __launch_bounds__(256, 4) void page_score_long_kernel(ScoreArgs a) {
   constexpr int STEPS = PS_LONG_PAGES / 16;
   // KV head fastest in dispatch order: the 8 heads' bounds of a pool page are 4 KiB contiguous,
@@ -243,7 +272,8 @@ __global__ __launch_bounds__(256, 4) void page_score_long_kernel(ScoreArgs a) {
   // (the counters of a top-p launch that follows are cleared on the way out, after every load of the kernel: a store
   //  ahead of them would turn the scalar loads of the prologue into vector loads that wait for one another)
   const bool clears = a.arrive && blockIdx.y == 0 && tid <= G;      // the group's counter and one per head
-  if (base >= P) {
+  const bool orders = ORDER && base == 0 && (blockIdx.x | blockIdx.z) == 0;    // (does not leave early, whatever that sequence's length)
+  if (base >= P && !orders) {
     if (clears) a.arrive[(b * a.Hkv + g) * TW_CTR + tid] = 0;
     return;
   }
@@ -303,6 +333,7 @@ __global__ __launch_bounds__(256, 4) void page_score_long_kernel(ScoreArgs a) {
     if (j < pages) a.scores[((long long)(b * a.Hq + g * G + h)) * a.max_pages + base + j] = j == app ? sh_app[h] : sh[h][j];
   }
   if (clears) a.arrive[(b * a.Hkv + g) * TW_CTR + tid] = 0;
+  if constexpr (ORDER) { if (orders) ps_order(a); }
 }
 
 struct SelectArgs {
@@ -450,18 +481,23 @@ __global__ __launch_bounds__(NT, E == 8 || E == 16 ? 8 : 1) void page_select_reg
   else select_row<NT, E, SNB>(sc, P, P, Kp, a.max_sel, out, hist, cand, cnt);
 }
 
-template <int G>
+template <int G, bool ORDER>
 void launch_score(const ScoreArgs& a, dim3 grid, bool many, bool append, int bits, hipStream_t s) {
   if (many) {
-    if (!append)        TW_LAUNCH((page_score_long_kernel<G, false>), grid, dim3(256), 0, s, a);
-    else if (bits == 4) TW_LAUNCH((page_score_long_kernel<G, true, 4>), grid, dim3(256), 0, s, a);
-    else if (bits == 8) TW_LAUNCH((page_score_long_kernel<G, true, 8>), grid, dim3(256), 0, s, a);
-    else                TW_LAUNCH((page_score_long_kernel<G, true, 2>), grid, dim3(256), 0, s, a);
+    if (!append)        TW_LAUNCH((page_score_long_kernel<G, false, 4, ORDER>), grid, dim3(256), 0, s, a);
+    else if (bits == 4) TW_LAUNCH((page_score_long_kernel<G, true, 4, ORDER>), grid, dim3(256), 0, s, a);
+    else if (bits == 8) TW_LAUNCH((page_score_long_kernel<G, true, 8, ORDER>), grid, dim3(256), 0, s, a);
+    else                TW_LAUNCH((page_score_long_kernel<G, true, 2, ORDER>), grid, dim3(256), 0, s, a);
   }
-  else if (!append)   TW_LAUNCH((page_score_kernel<G, false>), grid, dim3(256), 0, s, a);
-  else if (bits == 4) TW_LAUNCH((page_score_kernel<G, true, 4>), grid, dim3(256), 0, s, a);
-  else if (bits == 8) TW_LAUNCH((page_score_kernel<G, true, 8>), grid, dim3(256), 0, s, a);
-  else                TW_LAUNCH((page_score_kernel<G, true, 2>), grid, dim3(256), 0, s, a);
+  else if (!append)   TW_LAUNCH((page_score_kernel<G, false, 4, ORDER>), grid, dim3(256), 0, s, a);
+  else if (bits == 4) TW_LAUNCH((page_score_kernel<G, true, 4, ORDER>), grid, dim3(256), 0, s, a);
+  else if (bits == 8) TW_LAUNCH((page_score_kernel<G, true, 8, ORDER>), grid, dim3(256), 0, s, a);
+  else                TW_LAUNCH((page_score_kernel<G, true, 2, ORDER>), grid, dim3(256), 0, s, a);
+}
+template <int G>
+void launch_score(const ScoreArgs& a, dim3 grid, bool many, bool order, bool append, int bits, hipStream_t s) {
+  if (order) launch_score<G, true>(a, grid, many, append, bits, s);
+  else launch_score<G, false>(a, grid, many, append, bits, s);
 }
 
 }  // namespace
@@ -508,11 +544,24 @@ static int launch_select(SelectArgs sa, const TwDims& d, hipStream_t s) {
   return tw_prof_after(s);
 }
 
+// page_score_long_kernel from 16 of its workgroups per CU on, on page tables of at least 1536 pages (one query head per KV head:
+// 512).  Steps in both forms, us: 16 x 32768 tokens (4096 workgroups) 86.3 / 85.1, 32 ragged sequences of up to 32768 76.7 / 75.3,
+// 48 of up to 24576 87.3 / 85.5; with fewer workgroups it does not fill the chip (512: 2 x 32768 36.2 / 37.2).  On narrower tables
+// a workgroup in a few has the new token, whose bounds and quantised row come last in its chain, and a ragged batch's rows fill few
+// of its 64 pages: 128 ragged of up to 4096 75.6 / 78.7, of up to 8192 91.7 / 93.3, 32 of up to 16384 49.6 / 50.7 (full rows of
+// 16384 gain, 64 x 16384 154.2 / 151.8, but their lengths are not known here).  With one query head the rest of the chain is
+// shorter: the kernel alone, 32 KV heads, 128 ragged of up to 8192 67.7 / 63.7, of up to 2048 22.9 / 22.3, of up to 1024 16.1 / 17.2,
+// 192 x 300 17.5 / 21.5; 16 KV heads, 64 of up to 4096 12.5 / 14.0.  128 pages per workgroup: 64 ragged of up to 16384 86.4 / 88.6.
+static int score_columns(const TwDims& d) { return (d.max_pages + PS_LONG_PAGES - 1) / PS_LONG_PAGES; }
+static bool score_many(const TwDims& d) {
+  return (long long)d.batch * d.Hkv * score_columns(d) >= 16ll * tw_num_cus() && d.max_pages >= (d.G == 1 ? 512 : 1536);
+}
+
 static int select_impl(const twilight_kv_t* kv, const void* q, const int32_t* budget_tokens,
                        int32_t* sel_pages, int32_t* sel_count, int32_t max_sel,
                        void* ws, size_t ws_bytes, void* stream,
                        bool append, const void* k_new, const void* v_new, const int32_t* new_pos,
-                       uint32_t* arrive = nullptr, bool bounds_only = false) {
+                       uint32_t* arrive = nullptr, bool bounds_only = false, bool order = false) {
   TwDims d;
   if (int e = tw_check_kv(kv, &d)) return e;
   if (!q || !budget_tokens || !sel_pages || !sel_count || max_sel <= 0 || !kv->page_minmax) return TW_EINVAL;
@@ -532,23 +581,15 @@ static int select_impl(const twilight_kv_t* kv, const void* q, const int32_t* bu
   a.kq_pool = (uint32_t*)kv->kq_pool; a.kq_meta = (uint32_t*)kv->kq_meta;
   a.page_minmax_w = (uint4*)kv->page_minmax;
   a.arrive = arrive;
-  // page_score_long_kernel from 16 of its workgroups per CU on, on page tables of at least 1536 pages (one query head per KV head:
-  // 512).  Steps in both forms, us: 16 x 32768 tokens (4096 workgroups) 86.3 / 85.1, 32 ragged sequences of up to 32768 76.7 / 75.3,
-  // 48 of up to 24576 87.3 / 85.5; with fewer workgroups it does not fill the chip (512: 2 x 32768 36.2 / 37.2).  On narrower tables
-  // a workgroup in a few has the new token, whose bounds and quantised row come last in its chain, and a ragged batch's rows fill few
-  // of its 64 pages: 128 ragged of up to 4096 75.6 / 78.7, of up to 8192 91.7 / 93.3, 32 of up to 16384 49.6 / 50.7 (full rows of
-  // 16384 gain, 64 x 16384 154.2 / 151.8, but their lengths are not known here).  With one query head the rest of the chain is
-  // shorter: the kernel alone, 32 KV heads, 128 ragged of up to 8192 67.7 / 63.7, of up to 2048 22.9 / 22.3, of up to 1024 16.1 / 17.2,
-  // 192 x 300 17.5 / 21.5; 16 KV heads, 64 of up to 4096 12.5 / 14.0.  128 pages per workgroup: 64 ragged of up to 16384 86.4 / 88.6.
-  const int wide = (d.max_pages + PS_LONG_PAGES - 1) / PS_LONG_PAGES;
-  const bool many = (long long)d.batch * d.Hkv * wide >= 16ll * tw_num_cus() && d.max_pages >= (d.G == 1 ? 512 : 1536);
-  const dim3 grid(d.Hkv, many ? wide : (d.max_pages + PS_PAGES_PER_WG - 1) / PS_PAGES_PER_WG, d.batch);
+  a.budget = budget_tokens; a.batch = d.batch; a.max_sel = max_sel;
+  const bool many = score_many(d);
+  const dim3 grid(d.Hkv, many ? score_columns(d) : (d.max_pages + PS_PAGES_PER_WG - 1) / PS_PAGES_PER_WG, d.batch);
   tw_prof_before(TW_K_PAGE_SCORE, s);
   switch (d.G) {
-    case 1: launch_score<1>(a, grid, many, append, d.bits, s); break;
-    case 2: launch_score<2>(a, grid, many, append, d.bits, s); break;
-    case 4: launch_score<4>(a, grid, many, append, d.bits, s); break;
-    default: launch_score<8>(a, grid, many, append, d.bits, s); break;
+    case 1: launch_score<1>(a, grid, many, order, append, d.bits, s); break;
+    case 2: launch_score<2>(a, grid, many, order, append, d.bits, s); break;
+    case 4: launch_score<4>(a, grid, many, order, append, d.bits, s); break;
+    default: launch_score<8>(a, grid, many, order, append, d.bits, s); break;
   }
   if (int e = tw_prof_after(s)) return e;
   if (bounds_only) return TW_OK;
@@ -670,9 +711,17 @@ extern "C" int twilight_select_prune(const twilight_kv_t* kv, const void* k_new,
                                union_idx, union_stride, status, ws_prune, ws_bytes - sel_bytes, stream);
   }
   uint32_t* arrive = (uint32_t*)((char*)ws_prune + tw_prune_layout(d, max_sel, false).arrive);
+  // Sequences whose heads' work differs, in more workgroups than run at once: the most first (ps_order), or what begins last ends long
+  // after the rest.  Steps, us, as they come / in order: 64 ragged sequences of up to 65536 tokens 222.8 / 206.6, 40 161.2 / 143.8, 16 with
+  // 64 heads 92.0 / 84.7, 32 of up to 32768 69.9 / 65.3, 48 of up to 20000 with an eighth in the lists 81.3 / 78.1, with a quarter
+  // 90.4 / 84.4.  With shorter lists heads differ less, and the order costs 0.4 us of bounds and a load ahead of all others in every
+  // workgroup: 64 ragged of up to 20000 with an eighth in the lists, of 8-bit codes 94.0 / 95.4 (of 2-bit codes 88.7 / 87.7), 128 of up to
+  // 8192 87.5 / 88.1, 64 x 12000 129.5 / 129.9.
+  const bool order = mode == 2 && parts == 1 && max_sel * TW_PAGE > 2560 && d.batch > 1 && d.batch <= TW_ORDER_MAX &&
+                     (long long)d.batch * d.Hq > 3ll * tw_num_cus();
   if (int e = select_impl(kv, q, budget_tokens, sel_pages, sel_count, max_sel, ws, sel_bytes, stream, append, k_new, v_new,
-                          new_pos, arrive, mode == 2)) return e;
+                          new_pos, arrive, mode == 2, order)) return e;
   return tw_prune_fused(kv, d, q, mode == 2 ? (const float*)ws : nullptr, budget_tokens, sel_pages, sel_count, max_sel, p,
                         kept_count, kept_idx, kept_stride, union_count, union_idx, union_stride, status, ws_prune,
-                        parts, (hipStream_t)stream);
+                        parts, order, (hipStream_t)stream);
 }

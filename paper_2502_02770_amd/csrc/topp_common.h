@@ -41,10 +41,15 @@ bool tw_prune_fused_ok(const TwDims& d, int max_sel, bool with_select);
 int tw_prune_fused(const twilight_kv_t* kv, const TwDims& d, const void* q, const float* bounds, const int32_t* budget,
                    int32_t* sel_pages, int32_t* sel_count, int32_t max_sel, float p, int32_t* kept_count, int32_t* kept_idx,
                    int32_t kept_stride, int32_t* union_count, int32_t* union_idx, int32_t union_stride,
-                   uint32_t* status, void* ws, int parts, hipStream_t s);
+                   uint32_t* status, void* ws, int parts, bool ordered, hipStream_t s);
+// Batches of more heads than run at once, of at most TW_ORDER_MAX sequences: the kernel that clears the counters leaves the order in
+// which their heads are to be dispatched, place i's sequence in a spare word of the counters' lines.
+constexpr int TW_ORDER_MAX = 256;
 int tw_prune_parts(const TwDims& d, int max_sel);   // workgroups per head of the split form, which selects its pages itself; 1: not split
 
 #ifdef __HIPCC__
+__device__ __forceinline__ long long tw_order_word(int i, int Hkv) { return (long long)i * Hkv * TW_CTR + TW_CTR - 1; }
+
 // softmax numerator e in [0, 1] -> floor(e * 2^40), exactly: the top 8 bits and the remaining 32
 // bits are taken by two float -> integer truncations (every step below is exact in fp32: scaling by
 // a power of two, the integer part of a value below 2^9, and the difference of the two)

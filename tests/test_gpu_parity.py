@@ -2084,3 +2084,29 @@ def test_one_launch_select_prune_with_unmapped_and_partial_pages(bits, seqs, max
         sb.select_prune(None, None, None, q, budget, p)
         torch.cuda.synchronize()
         _lists_equal(sa, sb, "p=%g" % p)
+
+
+@pytest.mark.parametrize("seqs,longest", [(97, 2700), (97, 24700), (256, 2700), (257, 2700)])
+def test_one_launch_select_prune_takes_every_sequence_once(seqs, longest):
+    """More heads than three to a CU with lists above 2560 candidates: the sequences are dispatched in the order of their
+    heads' work (up to 256 of them), which the bounds' kernel leaves in both of its forms (the tables of 24700 tokens take the
+    one for many pages) - with an empty sequence first, sequences of equal work and a zero budget - against the separate calls."""
+    T = _T()
+    lens = [40] + [1 + (37 * (i // 2)) % 400 for i in range(1, seqs - 1)] + [longest]
+    budget = [16 if i % 3 else 5000 for i in range(seqs)]
+    budget[5] = 0
+    w = synth.make_workload("order", lens, num_q_heads=8, num_kv_heads=2, budget=budget, p=0.9, heavy_frac=0.01, alpha_range=(0.0, 3.0),
+                            shuffle_pool=True, need_v=False, seed=96)
+    cache = build_cache(w)
+    cache.seq_lens[0] = 0
+    q, budget = w.q.to(cache.device), w.budget.to(cache.device)
+    sa = T.DecodeStep(cache, max_sel=161, with_kept_idx=True)
+    sb = T.DecodeStep(cache, max_sel=161, with_kept_idx=True)
+    sa.select(q, budget)
+    sa.prune(q, w.p)
+    for rep in range(2):
+        for t in (sb.sel_count, sb.kept_count, sb.union_count):
+            t.fill_(-1)
+        sb.select_prune(None, None, None, q, budget, w.p)
+        torch.cuda.synchronize()
+        _lists_equal(sa, sb, "rep %d" % rep)
