@@ -60,13 +60,6 @@ __device__ __forceinline__ unsigned long long hp_fix(float e) {
   const uint32_t lo = (uint32_t)(rem * 4294967296.0f);
   return ((unsigned long long)hi << 32) | lo;
 }
-// the same value in two parts of 20 bits (floor(e * 2^40) = hi * 2^20 + lo, hi <= 2^20), whose sums over a few
-// thousand scores fit 32 bits each
-__device__ __forceinline__ void hp_fix20(float e, uint32_t* hi, uint32_t* lo) {
-  const float t = e * 1048576.0f;
-  *hi = (uint32_t)t;
-  *lo = (uint32_t)((t - (float)*hi) * 1048576.0f);
-}
 constexpr float HP_REACH = 27.5f;              // logits below the max at which a score stops taking part
 // rank of a score: distance to the max logit in 2^-22 units; HP_NONE when the score is
 // invalid or more than 27.5 logits below the max (its 2^-40 fixed-point mass is at most one unit there)

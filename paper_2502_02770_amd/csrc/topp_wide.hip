@@ -231,89 +231,103 @@ __global__ __launch_bounds__(64) void wide_decide_kernel(WideArgs a) {
   if (lane == 0) a.range[bh] = make_float4(m, d_hi, d_lo, 0.f);
 }
 
+// Two words that are the same in all lanes, to one lane.  (The wait is the one from a comparison's lane mask to its use by a vector instruction.)
+__device__ __forceinline__ void wide_to_lane(int lane, unsigned long long x, uint32_t& lo, uint32_t& hi) {
+  asm("s_nop 1\n\tv_writelane_b32 %0, %2, %4\n\tv_writelane_b32 %1, %3, %4" : "+v"(lo), "+v"(hi) : "s"((uint32_t)x), "s"((uint32_t)(x >> 32)), "n"(lane));
+}
+
+// A wave covers 64 * W_SLOTS consecutive slots, 64 at a time, so that a comparison's lane mask is two words of the bitmap.
+// What bounds it is vector instructions, then the read of the rows.  Masses, floor(e * 2^40), are summed by one
+// 64-bit fma each, rounded towards zero in an accumulator between 2^52 and 2^53, whose last place is 1: the integers' sum, exactly.
+// (As two 20-bit parts, with the flags gathered per lane and joined across lanes, 30 instructions a score; 15 so.  4 x 64 heads x
+// 262144 51.9 -> 46.4 us, 268 MB at 5.8 TB/s; 4 x 32 29.2 -> 24.9, 1 x 64 17.0 -> 14.8, 16 x 32 x 32768 17.3 -> 15.0.)
 template <int NT>
 __global__ __launch_bounds__(NT) void wide_emit_kernel(WideArgs a) {
   constexpr int W_CHUNK = NT * W_SLOTS, NW = NT / 64;
-  const int bh = blockIdx.y, b = bh / a.Hq, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int bh = blockIdx.y, b = bh / a.Hq, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int count = wide_count(a, b, bh);
   const int N = count * TW_PAGE;
   if ((long long)blockIdx.x * W_CHUNK >= N) return;
-  const int chunk0 = blockIdx.x * W_CHUNK;
+  const int w0 = blockIdx.x * W_CHUNK + wave * 64 * W_SLOTS;       // this wave's first slot
+  const float* const row = a.scores + (long long)bh * a.cand_stride;
   float s[W_SLOTS];
-  wide_load<NT>(a.scores + (long long)bh * a.cand_stride, chunk0, tid, N, a.cand_stride, s);
-  const float4 rg = a.range[bh];
-  int pg[W_SLOTS / 4];                            // logical page of each group of 4 slots (page lists only)
+  if (w0 + 64 * W_SLOTS <= N) {                   // (wave-uniform)
 #pragma unroll
-  for (int v = 0; v < W_SLOTS / 4; ++v) {
-    pg[v] = 0;
-    if (a.sel_pages) {
-      const int pi = wide_slot<NT>(chunk0, v, tid) >> 4;
-      pg[v] = a.sel_pages[(long long)bh * a.max_sel + (pi < a.max_sel ? pi : a.max_sel - 1)];
-    }
+    for (int e = 0; e < W_SLOTS; ++e) s[e] = row[w0 + e * 64 + lane];
+  } else {
+#pragma unroll
+    for (int e = 0; e < W_SLOTS; ++e) s[e] = row[w0 + e * 64 + lane < N ? w0 + e * 64 + lane : N - 1];
+#pragma unroll
+    for (int e = 0; e < W_SLOTS; ++e) s[e] = w0 + e * 64 + lane < N ? s[e] : -__builtin_inff();
   }
-  uint32_t mask = 0, umask = 0;                   // bit e: slot e of this thread is kept / undecided
-  unsigned long long Z = 0, A = 0;                // masses of all, of the kept
+  const float4 rg = a.range[bh];
+  const float m = rg.x, d_hi = rg.y, d_lo = rg.z;
+  uint32_t klo = 0, khi = 0, ulo = 0, uhi = 0;    // lane e: the kept and the undecided of the slots w0 + 64 * e .. up
+  uint32_t cnt = 0;                               // kept (wave-uniform)
+  uint32_t any = 0;
+  double Zd, Ad;
+  asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 2, 2), 3" ::: "memory");    // 64-bit results towards zero, to the kernel's end
+  {
+    unsigned long long one = 0x4330000000000000ull;                               // 2^52
+    asm volatile("" : "+v"(one));
+    Zd = Ad = __builtin_bit_cast(double, one);
+  }
   if (a.keep_all) {
 #pragma unroll
-    for (int e = 0; e < W_SLOTS; ++e) mask |= (s[e] > -__builtin_inff() ? 1u : 0u) << e;
+    for (int e = 0; e < W_SLOTS; ++e) {
+      const unsigned long long keep = __ballot(s[e] > -__builtin_inff());
+      cnt += (uint32_t)__popcll(keep);
+      wide_to_lane(e, keep, klo, khi);
+    }
   } else {
-    const float m = rg.x, d_hi = rg.y, d_lo = rg.z;
-    uint32_t zh = 0, zl = 0, ah = 0, al = 0;                    // sums of the masses' upper and lower 20 bits
 #pragma unroll
     for (int e = 0; e < W_SLOTS; ++e) {
       const float d = __fsub_rn(m, s[e]);
-      uint32_t h, l;
-      hp_fix20(__expf(-(d < HP_REACH ? d : 100.f)), &h, &l);    // beyond the reach: no mass
-      const bool keep = d < d_hi;
-      zh += h; zl += l;
-      ah += keep ? h : 0u; al += keep ? l : 0u;
-      mask |= (keep ? 1u : 0u) << e;
-      umask |= (d < d_lo ? 1u : 0u) << e;
-      if ((e & 3) == 3) __builtin_amdgcn_sched_barrier(0);       // four at a time: all 32 interleaved take twice the registers
+      const float x = __expf(-(d < HP_REACH ? d : 100.f));         // beyond the reach: no mass
+      const bool kept = d < d_hi;
+      asm("v_fma_f64 %0, %1, %2, %0" : "+v"(Zd) : "v"((double)x), "s"(0x1p40));
+      asm("v_fma_f64 %0, %1, %2, %0" : "+v"(Ad) : "v"((double)(kept ? x : 0.f)), "s"(0x1p40));
+      const unsigned long long keep = __ballot(kept), und = __ballot(d < d_lo) & ~keep;
+      cnt += (uint32_t)__popcll(keep);
+      wide_to_lane(e, keep, klo, khi);
+      if (und) { any = 1; wide_to_lane(e, und, ulo, uhi); }        // (wave-uniform)
     }
-    umask &= ~mask;
-    Z = ((unsigned long long)zh << 20) + zl;
-    A = ((unsigned long long)ah << 20) + al;
   }
+  unsigned long long Z = __builtin_bit_cast(unsigned long long, Zd) & 0xFFFFFFFFFFFFFull, A = __builtin_bit_cast(unsigned long long, Ad) & 0xFFFFFFFFFFFFFull;
   // undecided scores go onto the head's list: one atomic per wave reserves room for all its lanes
-  {
-    const uint32_t mine = __popc(umask);
+  if (any) {                                      // wave-uniform
+    const uint32_t mine = __popc(ulo) + __popc(uhi);
     const uint32_t incl = tw_wave_scan_u32(mine);
-    const uint32_t wtotal = __shfl(incl, 63, 64);
-    if (wtotal) {                                   // wave-uniform
-      uint32_t ubase = 0;
-      if (lane == 63) ubase = atomicAdd(&a.ucount[(long long)bh * TW_CTR], wtotal);
-      uint32_t at = __shfl(ubase, 63, 64) + incl - mine;
-      // (few scores: their words are read again, so that none of the 32 has to stay in a register for this)
-      for (uint32_t x = umask; x; x &= x - 1, ++at) {
-        const int e = __ffs((int)x) - 1;
-        const int slot = wide_slot<NT>(chunk0, e >> 2, tid) + (e & 3);
-        if (at < (uint32_t)W_CAP) {
-          const int tok = a.sel_pages ? a.sel_pages[(long long)bh * a.max_sel + (slot >> 4)] * TW_PAGE + (slot & 15) : slot;
-          a.ulist[(long long)bh * W_CAP + at] = make_uint2(tw_float_key(a.scores[(long long)bh * a.cand_stride + slot]), (uint32_t)tok);
-        }
+    uint32_t ubase = 0;
+    if (lane == 63) ubase = atomicAdd(&a.ucount[(long long)bh * TW_CTR], incl);
+    uint32_t at = __shfl(ubase, 63, 64) + incl - mine;
+    // (few scores: their words are read again, so that none of the 32 has to stay in a register for this)
+    for (unsigned long long x = ((unsigned long long)uhi << 32) | ulo; x; x &= x - 1, ++at) {
+      const int slot = w0 + lane * 64 + __ffsll((long long)x) - 1;
+      if (at < (uint32_t)W_CAP) {
+        const int tok = a.sel_pages ? a.sel_pages[(long long)bh * a.max_sel + (slot >> 4)] * TW_PAGE + (slot & 15) : slot;
+        a.ulist[(long long)bh * W_CAP + at] = make_uint2(tw_float_key(row[slot]), (uint32_t)tok);
       }
     }
   }
-  // bitmap: the 4 bits of a group join those of the neighbouring lanes (4 lanes = one page of 16
-  // slots, 8 lanes = one word of 32 slots) through DPP, then one lane stores
   uint32_t* bm = a.bitmaps + (long long)bh * a.words_stride;
-#pragma unroll
-  for (int v = 0; v < W_SLOTS / 4; ++v) {
-    const int c = wide_slot<NT>(chunk0, v, tid);
-    uint32_t x = ((mask >> (4 * v)) & 0xFu) << (4 * (lane & 7));
-    x |= (uint32_t)tw_dpp_i<TW_DPP_XOR1>((int)x);
-    x |= (uint32_t)tw_dpp_i<TW_DPP_XOR2>((int)x);
+  if (lane < W_SLOTS) {
+    const int c = w0 + lane * 64;
     if (a.sel_pages) {                            // one 16-bit half word per selected page
-      const uint32_t half = (x >> (16 * ((lane >> 2) & 1))) & 0xFFFFu;
-      if ((lane & 3) == 0 && (c >> 4) < count && pg[v] >= 0 && (pg[v] >> 1) < a.words_stride)   // ids outside the row: no bits, no store
-        ((unsigned short*)bm)[pg[v]] = (unsigned short)half;
-    } else {                                      // slots are token positions: one word per 8 lanes
-      x |= (uint32_t)tw_dpp_i<TW_DPP_HALF_MIRROR>((int)x);
-      if ((lane & 7) == 0 && c < N && (c >> 5) < a.words_stride) bm[c >> 5] = x;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int pi = (c >> 4) + v;
+        if (pi < count) {
+          const int pg = a.sel_pages[(long long)bh * a.max_sel + pi];
+          if (pg >= 0 && (pg >> 1) < a.words_stride)   // ids outside the row: no bits, no store
+            ((unsigned short*)bm)[pg] = (unsigned short)((v < 2 ? klo : khi) >> (16 * (v & 1)));
+        }
+      }
+    } else {                                      // slots are token positions
+      if (c < N && (c >> 5) < a.words_stride) bm[c >> 5] = klo;
+      if (c + 32 < N && (c >> 5) + 1 < a.words_stride) bm[(c >> 5) + 1] = khi;
     }
   }
-  const uint32_t cnt = tw_wave_scan_u32(__popc(mask));
   Z = tw_wave_scan_u64(Z);
   A = tw_wave_scan_u64(A);
   __shared__ uint32_t wc[NW];

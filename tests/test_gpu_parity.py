@@ -2110,3 +2110,25 @@ def test_one_launch_select_prune_takes_every_sequence_once(seqs, longest):
         sb.select_prune(None, None, None, q, budget, w.p)
         torch.cuda.synchronize()
         _lists_equal(sa, sb, "rep %d" % rep)
+
+
+@pytest.mark.parametrize("heads", [(4, 1), (2, 1)], ids=["histogram_in_scoring", "histogram_pass"])
+@pytest.mark.parametrize("p", [0.9, 1.0])
+def test_long_rows_at_the_limits_of_a_wave(heads, p):
+    """The pass of the multi-workgroup top-p that decides every score gives a wave 64 tokens at a time and 2048 in all: rows
+    that end at, before and behind these and behind a bitmap word, the sets and counts the oracle's."""
+    lens = [8192, 2047, 2049, 2080, 2111, 63, 65, 4096, 10273, 1]
+    w = synth.make_workload("waves", lens, num_q_heads=heads[0], num_kv_heads=heads[1], p=p, heavy_frac=0.005, alpha_range=(0.0, 4.0),
+                            full_selector=True, need_v=False, shuffle_pool=True, seed=97)
+    st, q = run_pipeline(w, build_cache(w))
+    assert int(st.status.item()) == 0
+    for b in range(len(lens)):
+        r = oracle_seq(w, b)
+        for h in range(heads[0]):
+            kept = st.kept_idx[b, h, :int(st.kept_count[b, h])].cpu().numpy()
+            if p == 1.0:
+                assert kept.tolist() == list(range(lens[b]))
+            else:
+                check_topp(kept, r["s_hat"][h], r["cand"][h], p)
+        mine = np.unique(np.concatenate([st.kept_idx[b, h, :int(st.kept_count[b, h])].cpu().numpy() for h in range(heads[0])]))
+        assert st.union_idx[b, :int(st.union_count[b])].cpu().numpy().tolist() == mine.tolist()
