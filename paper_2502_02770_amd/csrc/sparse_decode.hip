@@ -166,14 +166,19 @@ struct DecodePlan {
 // used and only then followed by the next step's, dense attention over 8 x 32768 tokens read 5.6 TB/s, now 6.2 (192 -> 173
 // us), and 32 x 32768 gathered rows take 30.5 instead of 31.8.  Three workgroups per CU with four query heads per KV head:
 // the registers of four (128) do not hold the addresses of the rows asked for ahead.
-template <int G>
-__global__ __launch_bounds__(256, G == 8 ? 2 : (G == 4 ? 3 : 4)) void sparse_decode_kernel(DecodeArgs a) {
+//
+// WHOLE: every list is one item, of a workgroup of NW waves, and its result final: no item map, no partial results, no combine
+// launch.  For lists that cannot be long (decode_whole).
+template <int G, int NW = 4, bool WHOLE = false>
+__global__ __launch_bounds__(64 * NW, NW == 8 || G == 8 ? 2 : (G == 4 ? 3 : 4)) void sparse_decode_kernel(DecodeArgs a) {
   constexpr int R = (G + 3) / 4;                 // score values a lane ends up owning per step
+  constexpr int NT = 64 * NW, STEP = 16 * NW;    // entries of a step of the waves
+  static_assert(WHOLE || (NW == 4 && STEP == (int)DEC_UNIT), "the item map is made by four waves");
   extern __shared__ int32_t prefix[];            // [NG + 1]
   __shared__ uint32_t wsum[16];
   __shared__ uint2 sum_s[4];
-  __shared__ float2 macc[4][G][64];              // the waves' accumulators ...
-  __shared__ float2 ml_s[4][G];                  // ... and their (maximum, denominator)
+  __shared__ float2 macc[NW][G][64];             // the waves' accumulators ...
+  __shared__ float2 ml_s[NW][G];                 // ... and their (maximum, denominator)
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), seg = tid & 15, row = lane >> 4;
   const bool dense = a.union_idx == nullptr;
   const bool b3 = seg & 8, b2 = seg & 4, b1 = seg & 2, b0 = seg & 1;
@@ -189,7 +194,11 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : (G == 4 ? 3 : 4)) void sparse_dec
   const uint32_t W = gridDim.x;
   uint32_t chunk;
   int total_items, item = blockIdx.x, gi = 0, ck = 0, nchunks = 0;
-  if (a.NG <= 64) {                               // block-uniform: lane l of every wave holds list l, no barrier
+  if constexpr (WHOLE) {
+    chunk = (uint32_t)most;
+    total_items = a.NG; nchunks = 1;
+    gi = item;
+  } else if (a.NG <= 64) {                        // block-uniform: lane l of every wave holds list l, no barrier
     const uint32_t c = lane < a.NG ? length(lane) : 0u;
     uint32_t rounds;
     chunk = decode_chunk((uint32_t)__builtin_amdgcn_readlane((int)tw_wave_scan_u32(c), 63), (uint32_t)a.NG, W, (uint32_t)a.chunk0, &rounds);
@@ -263,19 +272,20 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : (G == 4 ? 3 : 4)) void sparse_dec
     if (tid == 0) prefix[a.NG] = total_items;
     __syncthreads();
   }
-  if (blockIdx.x == 0) {                          // for the combine kernel
+  if (!WHOLE && blockIdx.x == 0) {                // for the combine kernel
     __syncthreads();
     for (int i = tid; i <= a.NG; i += 256) a.ws_prefix[i] = prefix[i];
   }
   TW_STAMP(1);
   // list of an item: the last one with prefix <= item (empty lists begin where the next one does)
   auto find = [&]() {
+    if (WHOLE) { gi = item; return; }
     int lo = 0, hi = a.NG;
     while (hi - lo > 1) { const int mid = (lo + hi) >> 1; if (prefix[mid] <= item) lo = mid; else hi = mid; }
     gi = lo; ck = item - prefix[lo]; nchunks = prefix[lo + 1] - prefix[lo];
   };
   if (item >= total_items) return;
-  if (a.NG > 64) find();
+  if (!WHOLE && a.NG > 64) find();
 
 #pragma unroll 1
   for (;;) {
@@ -284,9 +294,9 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : (G == 4 ? 3 : 4)) void sparse_dec
     // the list's length, this lane's list entry - any entry of the list's row may be read, those at or beyond the
     // count are ignored below - and q.  The page-table entries then depend on the list entries, the K/V rows on those:
     // three round trips to memory per item.
-    // In a row of 16 lanes, lane seg looks up entry (seg % 4) * 16 + wave * 4 + row of a step's 64.
+    // In a row of 16 lanes, lane seg looks up entry (seg % 4) * 4 * NW + wave * 4 + row of a step's 16 * NW.
     const int t0 = ck * (int)chunk;
-    const int e0 = (seg & 3) * 16 + wave * 4 + row;
+    const int e0 = (seg & 3) * (STEP / 4) + wave * 4 + row;
     int nseq = a.seq_lens[b];                    // list entries at or beyond the sequence's end are ignored
     const int32_t* const cnt_p = dense ? a.seq_lens + b : a.union_count + gi;
     int cnt = *cnt_p;
@@ -294,7 +304,7 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : (G == 4 ? 3 : 4)) void sparse_dec
     const int32_t* const list = dense ? a.seq_lens + b : a.union_idx + (long long)gi * a.union_stride;
     const int list_end = dense ? 0 : a.union_stride - 1;
     auto entry = [&](int e) -> int { return list[t0 + e < list_end ? t0 + e : list_end]; };
-    int raw0 = entry(e0), raw1 = entry(e0 + 64), raw2 = entry(e0 + 128);
+    int raw0 = entry(e0), raw1 = entry(e0 + STEP), raw2 = entry(e0 + 2 * STEP);
     // q of the G heads, this lane's 8 dims, as loaded (bf16 pairs)
     uint4 q[G];
 #pragma unroll
@@ -318,7 +328,7 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : (G == 4 ? 3 : 4)) void sparse_dec
       return tk >= 0 && pp >= 0 && pp < a.pool_pages ? (pp * a.Hkv + g) * TW_PAGE + (tk & 15) : -1;
     };
     int tok = token(raw0, e0), pp = page(tok);
-    const int tok1 = token(raw1, e0 + 64), pp1 = page(tok1);
+    const int tok1 = token(raw1, e0 + STEP), pp1 = page(tok1);
     int ids = pool_row(tok, pp);
     tok = tok1; pp = pp1;
     if (item == 0) TW_STAMP(2);
@@ -334,7 +344,7 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : (G == 4 ? 3 : 4)) void sparse_dec
     // products are done, its V rows behind this step's sums, so that a wave's loads keep going out while it computes -
     // in the registers of the rows just used.  (Unconditional loads, or a wait for one step's rows would take in the
     // next one's: entries that do not count all read the same 16 bytes and are masked.)
-    const int steps = (len - wave * 4 + 63) >> 6;
+    const int steps = (len - wave * 4 + STEP - 1) >> (NW == 8 ? 7 : 6);
     if (steps > 0) {                              // (wave-uniform)
       const int own = __builtin_amdgcn_readfirstlane(ids), spare = own < 0 ? 0 : own;
       uint4 kr[4], vr[4];
@@ -359,9 +369,9 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : (G == 4 ? 3 : 4)) void sparse_dec
         // the pool rows of step st + 1, whose page-table entries were asked for a step ago; those of step st + 2 and the
         // list entries of step st + 3 are asked for
         ids = pool_row(tok, pp);
-        tok = token(raw2, (st + 2) * 64 + e0);
+        tok = token(raw2, (st + 2) * STEP + e0);
         pp = page(tok);
-        raw2 = entry((st + 3) * 64 + e0);
+        raw2 = entry((st + 3) * STEP + e0);
         // ---- partial dot products of this lane's 8 dims: val[t*4 + h%4][h/4]
         float val[16][R];
 #pragma unroll
@@ -480,23 +490,25 @@ __global__ __launch_bounds__(256, G == 8 ? 2 : (G == 4 ? 3 : 4)) void sparse_dec
       if (lane < 4 && r * 4 + lane < G) ml_s[wave][r * 4 + lane] = make_float2(M[r], lr);
     }
     __syncthreads();
-    // ---- the four waves: thread -> 2 adjacent output dims of one head
+    // ---- the waves: thread -> 2 adjacent output dims of one head
 #pragma unroll
-    for (int c2 = tid; c2 < G * 64; c2 += 256) {
+    for (int c2 = tid; c2 < G * 64; c2 += NT) {
       const int h = c2 >> 6, d2 = c2 & 63;
-      float2 ml[4];
+      float2 ml[NW];
 #pragma unroll
-      for (int w = 0; w < 4; ++w) ml[w] = ml_s[w][h];
-      const float mx = fmaxf(fmaxf(ml[0].x, ml[1].x), fmaxf(ml[2].x, ml[3].x));
+      for (int w = 0; w < NW; ++w) ml[w] = ml_s[w][h];
+      float mx = fmaxf(fmaxf(ml[0].x, ml[1].x), fmaxf(ml[2].x, ml[3].x));
+#pragma unroll
+      for (int w = 4; w < NW; ++w) mx = fmaxf(mx, ml[w].x);
       float ox = 0.f, oy = 0.f, L = 0.f;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
+      for (int w = 0; w < NW; ++w) {
         const float f = tw_exp2(ml[w].x - mx);
         const float2 v = macc[w][h][d2];
         ox = __builtin_fmaf(v.x, f, ox); oy = __builtin_fmaf(v.y, f, oy);
         L = __builtin_fmaf(ml[w].y, f, L);
       }
-      if (nchunks == 1) {                       // the item is the whole list: final result
+      if (WHOLE || nchunks == 1) {              // the item is the whole list: final result
         const int qh = b * a.Hq + l * G + h;
         const float inv = L > 0.f ? 1.0f / L : 0.f;
         ((uint32_t*)a.out)[(long long)qh * 64 + d2] = tw_f32_to_bf16(ox * inv) | (tw_f32_to_bf16(oy * inv) << 16);
@@ -603,6 +615,23 @@ void launch_decode(const DecodeArgs& a, long long max_items, size_t lds, hipStre
   TW_LAUNCH((sparse_decode_kernel<G>), dim3((unsigned)grid), dim3(256), lds, s, a);
 }
 
+// Lists that cannot be long take a workgroup each and need no combine launch, which costs a step 2.4 us, nor the item map (1.2 us of the
+// kernel's chain): eight waves up to a list per CU, four beyond, where three workgroups share a CU.  How long a list is only the
+// device knows; a workgroup takes 1.1 us for every 128 entries, so the line lies where the longest would still lose nothing: at
+// 512 entries, 256 with eight query heads to a row, and where there are lists for half the CUs, so that cut ones would run no wider
+// either, at 1280.  Steps, us, cut / whole: 2 x 628 tokens (16 lists of up to 320) 22.3 / 19.7, 15 x 607 ragged (120, 256) 24.3 / 21.1,
+// 43 x 1668 multi-head (1376, 208) 63.8 / 56.6, 31 x 1254 (248, 1264) 41.5 / 38.1, 27 x 1175, 64 heads over 8 (216, 1184) 37.5 / 34.5;
+// beyond it 7 x 703, 64 heads over 8 (56, 704) 25.6 / 27.5, 2 x 10218 multi-head (64, 1280) 27.3 / 30.5, 34 x 5731 multi-head (1088, 1440)
+// 126.9 / 130.7, and where nearly all of 8 x 4096 tokens' candidates are kept (64, 2048) 33.1 / 41.3.
+bool decode_whole(int NG, int G, int stride) {
+  return stride <= (2 * NG >= tw_num_cus() ? 1280 : G == 8 ? 256 : 512);
+}
+template <int G>
+void launch_whole(const DecodeArgs& a, hipStream_t s) {
+  if (a.NG <= tw_num_cus()) TW_LAUNCH((sparse_decode_kernel<G, 8, true>), dim3(a.NG), dim3(512), 0, s, a);
+  else TW_LAUNCH((sparse_decode_kernel<G, 4, true>), dim3(a.NG), dim3(256), 0, s, a);
+}
+
 }  // namespace
 
 #ifdef TW_PHASE_TIMING
@@ -659,6 +688,15 @@ static int decode_impl(const twilight_kv_t* kv, const void* q, const int32_t* co
   a.NG = NG; a.chunk0 = tw_decode_chunk(dense); a.pool_pages = d.pool_pages;
   const size_t lds = (size_t)(NG + 1) * 4;
   tw_prof_before(TW_K_DECODE, s);
+  if (!dense && decode_whole(NG, Gk, stride)) {
+    switch (Gk) {
+      case 1: launch_whole<1>(a, s); break;
+      case 2: launch_whole<2>(a, s); break;
+      case 4: launch_whole<4>(a, s); break;
+      default: launch_whole<8>(a, s); break;
+    }
+    return tw_prof_after(s);
+  }
   switch (Gk) {
     case 1: launch_decode<1>(a, max_items, lds, s); break;
     case 2: launch_decode<2>(a, max_items, lds, s); break;
@@ -677,7 +715,8 @@ static int decode_impl(const twilight_kv_t* kv, const void* q, const int32_t* co
 
 // Launch shape of the decode kernel for this cache shape (host only): workgroups of the persistent grid (before
 // it is cut to the number of work items), the shortest chunk, and how many numbers of items per workgroup
-// decode_chunk weighs.  For benchmarks that report the balance of the work list.
+// decode_chunk weighs.  For benchmarks that report the balance of the work list.  (Of lists that are cut: those that decode_whole
+// gives a workgroup each are not.)
 extern "C" int twilight_decode_plan(const twilight_kv_t* kv, int which, int32_t dense, int32_t* grid, int32_t* chunk0,
                                     int32_t* items_per_wg) {
   TwDims d;

@@ -2132,3 +2132,50 @@ def test_long_rows_at_the_limits_of_a_wave(heads, p):
                 check_topp(kept, r["s_hat"][h], r["cand"][h], p)
         mine = np.unique(np.concatenate([st.kept_idx[b, h, :int(st.kept_count[b, h])].cpu().numpy() for h in range(heads[0])]))
         assert st.union_idx[b, :int(st.union_count[b])].cpu().numpy().tolist() == mine.tolist()
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(4, 4), (4, 2), (8, 2), (16, 2)])
+@pytest.mark.parametrize("batch,stride", [(6, 256), (6, 512), (80, 512), (64, 1280), (140, 300)])
+def test_attention_over_short_lists_one_workgroup_each(Hq, Hkv, batch, stride):
+    """Lists whose bound lets a workgroup take each whole (eight waves, or four with more lists than CUs): lengths around the
+    steps of 64 and 128 entries, none, one, the bound and beyond it, entries outside the sequence - against the oracle, and
+    against the same lists in rows wide enough for the cut form, whose sums differ in order only."""
+    T = _T()
+    dev, n = "cuda", 1400
+    g = torch.Generator().manual_seed(98)
+    w = synth.make_workload("short", [n] * batch, num_q_heads=Hq, num_kv_heads=Hkv, budget=16, p=0.9, heavy_frac=0.0, alpha_range=(0.0, 0.0),
+                            shuffle_pool=True, seed=98)
+    cache = build_cache(w)
+    q = w.q.to(dev)
+    NG = batch * Hkv
+    lens = [0, 1, 63, 64, 65, 127, 128, 129, stride - 1, stride, 17, 200]
+    count = torch.tensor([lens[i % len(lens)] for i in range(NG)], dtype=torch.int32)
+    idx = torch.zeros(NG, stride, dtype=torch.int32)
+    for i in range(NG):
+        idx[i] = torch.sort(torch.randperm(n, generator=g)[:stride]).values.int()
+    idx[4, 7], idx[4, 20] = -3, n + 5                      # ignored
+    wide = torch.zeros(NG, 4096, dtype=torch.int32)
+    wide[:, :stride] = idx
+    outs = []
+    for lists in (idx, wide):
+        st = T.DecodeStep(cache, max_sel=1, union_stride=lists.shape[1])
+        st.union_count.copy_(count + (1000 if lists is idx else 0) * (count == stride))     # (a count beyond the row is the row's length)
+        st.union_idx.copy_(lists)
+        st.attend(q)
+        torch.cuda.synchronize()
+        outs.append((st.out.float().cpu().numpy().astype(np.float64), st.lse.cpu()))
+    G = Hq // Hkv
+    for i in list(range(12)) + [NG - 1]:
+        b, kv = divmod(i, Hkv)
+        sel = idx[i, :int(count[i])].numpy()
+        sel = sel[(sel >= 0) & (sel < n)]
+        for h in range(kv * G, kv * G + G):
+            if len(sel) == 0:
+                assert not outs[0][0][b, h].any() and outs[0][1][b, h] == -np.inf
+                continue
+            ref, lse = O.attention(synth.bits(w.q[b, h]), synth.bits(w.seq_k(b)[:, kv]), synth.bits(w.seq_v(b)[:, kv]), sel)
+            assert_attention(outs[0][0][b, h], ref)
+    # both forms, every head: one bf16 rounding of sums that differ by fp32 roundings
+    assert np.abs(outs[0][0] - outs[1][0]).max() <= 2 ** -7 * np.abs(outs[1][0]).max()
+    fin = torch.isfinite(outs[1][1])
+    assert torch.equal(fin, torch.isfinite(outs[0][1])) and (outs[0][1][fin] - outs[1][1][fin]).abs().max() <= 1e-5
