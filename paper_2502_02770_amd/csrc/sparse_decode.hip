@@ -620,10 +620,13 @@ void launch_decode(const DecodeArgs& a, long long max_items, size_t lds, hipStre
 // device knows; a workgroup takes 1.1 us for every 128 entries, so the line lies where the longest would still lose nothing: at
 // 512 entries, 256 with eight query heads to a row, and where there are lists for half the CUs, so that cut ones would run no wider
 // either, at 1280.  Steps, us, cut / whole: 2 x 628 tokens (16 lists of up to 320) 22.3 / 19.7, 15 x 607 ragged (120, 256) 24.3 / 21.1,
-// 43 x 1668 multi-head (1376, 208) 63.8 / 56.6, 31 x 1254 (248, 1264) 41.5 / 38.1, 27 x 1175, 64 heads over 8 (216, 1184) 37.5 / 34.5;
-// beyond it 7 x 703, 64 heads over 8 (56, 704) 25.6 / 27.5, 2 x 10218 multi-head (64, 1280) 27.3 / 30.5, 34 x 5731 multi-head (1088, 1440)
-// 126.9 / 130.7, and where nearly all of 8 x 4096 tokens' candidates are kept (64, 2048) 33.1 / 41.3.
+// 31 x 1254 (248, 1264) 41.5 / 38.1, 27 x 1175, 64 heads over 8 (216, 1184) 37.5 / 34.5;
+// beyond it 7 x 703, 64 heads over 8 (56, 704) 25.6 / 27.5, and where nearly all of 8 x 4096 tokens' candidates are kept (64, 2048) 33.1 / 41.3.
+// One query head to a row: 208, whatever their number (43 x 1668 (1376, 208) 63.8 / 56.6, 4 x 1720 ragged (128, 96) 22.4 / 19.2).  8 x 2847
+// (256, 352) would gain too, 26.0 / 22.3, and 8 x 1931 (256, 448), 27.0 / 24.8; but from 220 entries on the items of such lists are pinned,
+// and 2 x 10218 (64, 1280) 27.3 / 30.5 and 34 x 5731 (1088, 1440) 126.9 / 130.7 lose.
 bool decode_whole(int NG, int G, int stride) {
+  if (G == 1) return stride <= 208;
   return stride <= (2 * NG >= tw_num_cus() ? 1280 : G == 8 ? 256 : 512);
 }
 template <int G>

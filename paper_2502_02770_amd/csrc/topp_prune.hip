@@ -1607,7 +1607,7 @@ void launch_topp_one(const HeadArgs& f, int G, dim3 grid, hipStream_t s) {
 //    512-thread workgroups with 16 candidates per thread, three (two) to a CU, for all heads - one's scoring streams while the others
 //    are in their barriers (64 ragged sequences x 32 heads of up to 4096 pages: 180 with 1024 threads x 8, a workgroup per CU, 128 so;
 //    8192 candidates: 10 x 32 heads 53.0 and 50.0, 16 x 32 62.6 and 52.3; 8 x 32, a workgroup per CU either way, 34.0 and 37.8.
-//    Dispatching the longest sequences first: no gain);
+//    the sequences with the most work first: twilight_select_prune);
 //  - the same on stored scores (FUSE == 0): heads of at most 4096 candidates in a 512-thread launch of their own, the
 //    longer ones in the 1024-thread launch.
 // FUSE: the kernels score the candidates themselves (page lists).
