@@ -783,6 +783,11 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
   // reading the scores again, 64 registers (74 with 16 candidates per thread) of which the form with 8 spills 8, 36 bytes of
   // scratch per lane.  Where four to a CU do not save a round of workgroups over three, FUSE == 4 is quicker (launch_topp).
   constexpr bool INLDS = FUSE == 2 && NT <= 512 && EPT > 4;
+  // Arguments of the last phases read again there, where keeping them takes more scalar registers than there are: 6 to 40 of them went
+  // back and forth between scalar and vector ones all the way (21 of the form with four to a CU still do).  Each is a trip to the scalar
+  // cache behind the search's barriers, which the other forms lose by: token lists of 256 heads 8.0 us, 7.55 without, of 32 7.6 / 7.3,
+  // page lists of 32 heads 10.8 / 10.6.
+  constexpr bool LATE = INLDS || SPLIT || FUSE == 4 || (FUSE == 1 && EPT == 16);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const unsigned parts = SPLIT ? (unsigned)a.parts : 1u;
   int b_ = blockIdx.y, h_ = blockIdx.x / parts, part = blockIdx.x % parts;
@@ -1219,10 +1224,16 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
     TW_STAMP(9);
   }
 
-  // What is needed from here on is read from the kernel's arguments again, or its registers go back and forth between scalar and
-  // vector ones all the way here (16 to 42 of them in the forms that share a CU).
-  const __attribute__((address_space(4))) HeadArgs* late = (const __attribute__((address_space(4))) HeadArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(late));
+  // ---- LATE: the kernel's arguments, to be read again
+  const auto late = [&] {
+    if constexpr (LATE) {
+      auto args = (const __attribute__((address_space(4))) HeadArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+      asm volatile("" : "+s"(args));
+      return args;
+    } else {
+      return &a;
+    }
+  }();
   // ---- kept flags, count, optional ascending list; bitmap over token positions
   uint32_t cnt = 0, keep = 0;
   each([&](int e, float x) {

@@ -29,8 +29,9 @@ def kernels():
             name = blob[pos + 24:pos + 24 + idlen]
             pos += 24 + idlen
             if b"gfx950" in name:
-                for k in _metadata(blob[at + off:at + off + size]):
-                    found[k[".name"]] = k
+                elf = blob[at + off:at + off + size]
+                for k in _metadata(elf):
+                    found[k[".name"]] = dict(k, elf=elf)
         at = blob.find(magic, at + 1)
     names = list(found)
     plain = subprocess.run(["c++filt"], input="\n".join(names), capture_output=True, text=True, check=True).stdout.splitlines()
@@ -109,3 +110,26 @@ def test_scoring_of_two_heads_per_page_keeps_its_waves(kernels, dots, pages):
     k = kernels["int4_score_kernel<2, true, %s, %d, 4>" % ("true" if dots else "false", pages)]
     assert _fits(k, 8 if dots else 6), k[".vgpr_count"]
     assert not k[".vgpr_spill_count"] and not k[".private_segment_fixed_size"]
+
+
+@pytest.mark.parametrize("tokens", ["false", "true"])
+def test_top_p_on_stored_scores_reads_its_arguments_once(kernels, tokens, tmp_path):
+    """These forms hold all arguments in scalar registers from the start.  Read again behind the search's barriers they were 23 to 31
+    scalar loads instead of 12, each a trip to the scalar cache in a chain of phases: 256 heads' token lists 8.0 us instead of 7.55."""
+    for shape in ("512, 4", "512, 8", "1024, 4", "1024, 8"):
+        k = kernels["topp_head_kernel<%s, 4, %s, 0, 4>" % (shape, tokens)]
+        assert not k[".sgpr_spill_count"]
+        (tmp_path / "code").write_bytes(k["elf"])
+        out = subprocess.run([os.environ.get("LLVM_OBJDUMP", "/opt/rocm/llvm/bin/llvm-objdump"), "-d", "--disassemble-symbols=" + k[".name"], str(tmp_path / "code")],
+                             capture_output=True, text=True, check=True).stdout
+        assert "s_endpgm" in out
+        assert len(re.findall(r"\bs_load_dword", out)) <= 16, shape
+
+
+def test_forms_that_share_a_cu_spill_few_scalar_registers(kernels):
+    """Four workgroups of 8 candidates per thread to a CU: 21, 40 with the arguments of the last phases held; all other forms of the
+    one-launch pruner none, up to 16 so."""
+    spilled = {n: k[".sgpr_spill_count"] for n, k in kernels.items() if n.startswith("topp_head_kernel")}
+    four = {n: v for n, v in spilled.items() if re.search(r"<512, 8, \d, false, 2, ", n)}
+    assert len(four) == 12 and max(four.values()) <= 24, four
+    assert not any(v for n, v in spilled.items() if n not in four), {n: v for n, v in spilled.items() if v}
