@@ -2112,6 +2112,52 @@ def test_one_launch_select_prune_takes_every_sequence_once(seqs, longest):
         _lists_equal(sa, sb, "rep %d" % rep)
 
 
+@pytest.mark.parametrize("bits", [2, 4, 8])
+@pytest.mark.parametrize("long_table", [False, True], ids=["bounds", "bounds_long"])
+@pytest.mark.parametrize("kv_heads", [8, 4, 2, 1])
+def test_one_launch_select_prune_in_order_of_work_with_append(kv_heads, long_table, bits):
+    """The step's new token where the heads are dispatched in the order of their work: one, two, four and eight query heads to a
+    row, in both forms of the bounds' kernel, every width of the codes; an empty sequence first (the workgroup that makes
+    the order is its), one without a new token, new tokens that open a page - pools, codes, bounds, lists and unions those of
+    twilight_append_select and twilight_topp_prune, bit for bit."""
+    T = _T()
+    dev, seqs = "cuda", 97
+    longest = {8: 8300, 4: 24700, 2: 24700, 1: 44200}[kv_heads] if long_table else 2700
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert seqs * 8 > 3 * cus and (seqs * kv_heads * -(-longest // 1024) >= 16 * cus) == long_table
+    lens = [40] + [1 + (37 * (i // 2)) % 400 for i in range(1, seqs - 1)] + [longest]
+    lens[3], lens[4] = 33, 49                              # their new tokens are the first of a page
+    budget = [16 if i % 3 else 5000 for i in range(seqs)]
+    budget[5] = 0
+    w = synth.make_workload("order", lens, num_q_heads=8, num_kv_heads=kv_heads, budget=budget, p=0.9, heavy_frac=0.01,
+                            alpha_range=(0.0, 3.0), shuffle_pool=True, seed=99)
+    k, v, q, budget = w.k.to(dev), w.v.to(dev), w.q.to(dev), w.budget.to(dev)
+    last = torch.tensor(w.seq_offsets[1:], dtype=torch.int64, device=dev) - 1
+    k_last, v_last = k[last].contiguous(), v[last].contiguous()
+    offs = torch.tensor(w.seq_offsets[:-1], dtype=torch.int32, device=dev)
+    pos = torch.tensor(lens, dtype=torch.int32, device=dev) - 1
+    steps = []
+    for _ in range(2):
+        c = T.PagedKV(8, kv_heads, w.page_table, w.seq_lens, w.num_pool_pages, dev, quant_bits=bits)
+        c.append(k, v, torch.zeros_like(c.seq_lens), c.seq_lens - 1, offs, longest - 1)
+        c.seq_lens[0] = 0
+        steps.append(T.DecodeStep(c, max_sel=161, with_kept_idx=True))
+    pos[0] = pos[7] = -1
+    before = steps[0].cache.kq_pool.clone()
+    steps[0].append_select(k_last, v_last, pos, q, budget)
+    steps[0].prune(q, w.p)
+    assert not torch.equal(before, steps[0].cache.kq_pool)
+    for rep in range(2):                                   # (the second writes the same token again)
+        for t in (steps[1].sel_count, steps[1].kept_count, steps[1].union_count):
+            t.fill_(-1)
+        steps[1].select_prune(k_last, v_last, pos, q, budget, w.p)
+        torch.cuda.synchronize()
+        for name in ("k_pool", "v_pool", "kq_pool", "kq_meta", "page_minmax"):
+            x, y = (getattr(st.cache, name).view(torch.uint8) for st in steps)
+            assert torch.equal(x, y), name
+        _lists_equal(steps[0], steps[1], "rep %d" % rep)
+
+
 @pytest.mark.parametrize("heads", [(4, 1), (2, 1)], ids=["histogram_in_scoring", "histogram_pass"])
 @pytest.mark.parametrize("p", [0.9, 1.0])
 def test_long_rows_at_the_limits_of_a_wave(heads, p):
