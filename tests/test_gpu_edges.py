@@ -454,23 +454,29 @@ def test_token_lists_of_sequences_without_tokens(bits):
             assert st.union_idx[2 * b + g, :int(st.union_count[2 * b + g])].cpu().numpy().tolist() == inside.tolist(), (b, g)
 
 
-def _attend_lists(T, G, H, lens, n, seed):
-    """Attention of sequences of n tokens over lists of lens[l] entries (H lists per sequence): outputs against float64."""
-    batch, P, stride = len(lens) // H, (n + 15) // 16, max(64, int(max(lens)))
+def _attend_lists(T, G, H, lens, n, seed, bound=0):
+    """Attention of sequences of n tokens over lists of lens[l] entries (H lists per sequence), in rows of `bound` entries if the
+    longest has no more: outputs against float64.  `combined` of the step returned: whether the lists were cut and combined."""
+    batch, P, cols = len(lens) // H, (n + 15) // 16, max(64, int(max(lens)))
+    stride = max(cols, bound)
     g = torch.Generator(device="cuda").manual_seed(seed)
     cache = T.PagedKV(G * H, H, torch.randperm(batch * P, generator=torch.Generator().manual_seed(seed)).int().view(batch, P), torch.full((batch,), n), batch * P)
     cache.k_pool.normal_(generator=g)
     cache.v_pool.normal_(generator=g)
     q = torch.randn(batch, G * H, 128, device="cuda", generator=g).to(torch.bfloat16)
     lens = torch.as_tensor(lens, device="cuda")
-    idx = torch.rand(len(lens), n, device="cuda", generator=g).argsort(dim=1)[:, :stride]
+    idx = torch.rand(len(lens), n, device="cuda", generator=g).argsort(dim=1)[:, :cols]
     idx = idx.masked_fill(torch.arange(idx.shape[1], device="cuda") >= lens[:, None], n).sort(dim=1).values       # n: does not count
     st = T.DecodeStep(cache, max_sel=1, union_stride=stride)
     st.union_count.copy_(lens)
     st.union_idx.fill_(-1)
     st.union_idx[:, :idx.shape[1]].copy_(idx)
+    torch.cuda.synchronize()
+    T.twilight_prof_enable(1)
     st.attend(q)
     torch.cuda.synchronize()
+    st.combined = [name for name, _ in T.twilight_prof_collect()] == ["sparse_decode", "combine"]
+    T.twilight_prof_enable(0)
     page = cache.page_table.long().gather(1, idx.clamp(max=n - 1).view(batch, -1) // 16).view(len(lens), -1)
     head = (torch.arange(len(lens), device="cuda") % H)[:, None]
     for lo in range(0, len(lens), 64):
@@ -491,12 +497,14 @@ def _attend_lists(T, G, H, lens, n, seed):
     return st
 
 
+@pytest.mark.parametrize("bound", [0, 1344], ids=["narrow_rows", "wide_rows"])
 @pytest.mark.parametrize("G,lists,longest,kind", [
     (1, 72, 180, "same"), (2, 256, 300, "mixed"), (4, 512, 129, "same"), (8, 520, 946, "same"), (4, 744, 377, "mixed"), (1, 1088, 745, "mixed"),
     (2, 1280, 500, "same"), (8, 1384, 200, "mixed"), (1, 2048, 900, "same"), (1, 6144, 40, "mixed"), (2, 776, 64, "empty")])
-def test_attention_over_many_lists(G, lists, longest, kind):
+def test_attention_over_many_lists(G, lists, longest, kind, bound):
     """More than 64 lists, one, two and more to a thread of the item map: equal ones (whole or in equal pieces), lists of
-    widely different lengths, of which many are shorter than a chunk, and mostly empty ones, against float64."""
+    widely different lengths, of which many are shorter than a chunk, and mostly empty ones, against float64.  In rows of 1344
+    entries; in rows as wide as the longest list those short enough take a workgroup each and no item map."""
     T = _T()
     rng = np.random.default_rng(lists)
     lens = np.full(lists, longest)
@@ -505,7 +513,8 @@ def test_attention_over_many_lists(G, lists, longest, kind):
         lens[rng.integers(lists)] = longest
     if kind == "empty":
         lens[rng.random(lists) < 0.9] = 0
-    _attend_lists(T, G, 8, lens, 2 * longest, seed=lists + G)
+    st = _attend_lists(T, G, 8, lens, 2 * longest, seed=lists + G, bound=bound)
+    assert st.combined or not bound
 
 
 @pytest.mark.parametrize("lists,longest,chunk", [(256, 300, 128), (128, 300, 128), (256, 220, 64), (120, 300, 64)])
