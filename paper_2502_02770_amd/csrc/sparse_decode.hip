@@ -617,17 +617,22 @@ void launch_decode(const DecodeArgs& a, long long max_items, size_t lds, hipStre
 
 // Lists that cannot be long take a workgroup each and need no combine launch, which costs a step 2.4 us, nor the item map (1.2 us of the
 // kernel's chain): eight waves up to a list per CU, four beyond, where three workgroups share a CU.  How long a list is only the
-// device knows; a workgroup takes 1.1 us for every 128 entries, so the line lies where the longest would still lose nothing: at
-// 512 entries, 256 with eight query heads to a row, and where there are lists for half the CUs, so that cut ones would run no wider
-// either, at 1280.  Steps, us, cut / whole: 2 x 628 tokens (16 lists of up to 320) 22.3 / 19.7, 15 x 607 ragged (120, 256) 24.3 / 21.1,
-// 31 x 1254 (248, 1264) 41.5 / 38.1, 27 x 1175, 64 heads over 8 (216, 1184) 37.5 / 34.5;
-// beyond it 7 x 703, 64 heads over 8 (56, 704) 25.6 / 27.5, and where nearly all of 8 x 4096 tokens' candidates are kept (64, 2048) 33.1 / 41.3.
-// One query head to a row: 208, whatever their number (43 x 1668 (1376, 208) 63.8 / 56.6, 4 x 1720 ragged (128, 96) 22.4 / 19.2).  8 x 2847
-// (256, 352) would gain too, 26.0 / 22.3, and 8 x 1931 (256, 448), 27.0 / 24.8; but from 220 entries on the items of such lists are pinned,
-// and 2 x 10218 (64, 1280) 27.3 / 30.5 and 34 x 5731 (1088, 1440) 126.9 / 130.7 lose.
+// device knows; a workgroup takes 1.1 us for every 128 entries, so the line lies where one list as long as its row among many a
+// sixteenth of it, which the cut form shares out, loses nothing: at 512 entries, 256 with eight query heads to a row, and where there
+// are lists for half the CUs, so that cut ones would run no wider either, at 768 and 512.  Steps over caches larger than the last-level
+// one, us, cut / whole, (lists, bound), such lists:
+//   2 heads to a row   (64, 512) 24.0 / 23.7  (64, 640) 24.1 / 24.8  (136, 768) 26.2 / 25.8  (512, 768) 31.8 / 30.4
+//   4                  (64, 512) 24.2 / 24.1  (64, 640) 24.3 / 24.6  (136, 768) 27.1 / 27.4  (512, 768) 40.8 / 38.7
+//   8                  (64, 256) 26.2 / 24.7  (64, 384) 26.4 / 26.8  (136, 512) 30.9 / 30.5  (512, 512) 57.9 / 51.3
+// and beyond the lines, caches as the steps before left them: 4 heads (264, 1024) 31.4 / 32.6, (264, 1280) 32.5 / 35.4, 8 heads
+// (136, 640) 29.9 / 31.0, (136, 1280) 31.3 / 36.8.  Lists of log-uniform or equal lengths gain at and
+// below the lines: 4 heads (264, 768) 34.1 / 30.4, 8 heads (264, 512) 43.7 / 38.0.
+// One query head to a row: 208, whatever their number (43 x 1668 (1376, 208) 63.8 / 56.6, 4 x 1720 ragged (128, 96) 22.4 / 19.2), since the
+// items of longer lists are pinned.
 bool decode_whole(int NG, int G, int stride) {
   if (G == 1) return stride <= 208;
-  return stride <= (2 * NG >= tw_num_cus() ? 1280 : G == 8 ? 256 : 512);
+  const bool many = 2 * NG >= tw_num_cus();
+  return stride <= (G == 8 ? (many ? 512 : 256) : many ? 768 : 512);
 }
 template <int G>
 void launch_whole(const DecodeArgs& a, hipStream_t s) {

@@ -529,6 +529,39 @@ def test_middling_lists_of_single_heads_are_cut_into_two_steps(lists, longest, c
     assert np.array_equal(np.diff(first), -(-lens // chunk))
 
 
+@pytest.mark.parametrize("G,lists,bound", [(2, 64, 512), (4, 64, 512), (8, 64, 256), (2, 136, 768), (4, 264, 768), (8, 136, 512), (8, 264, 512)])
+def test_short_lists_take_a_workgroup_each_up_to_the_line(G, lists, bound):
+    """At the bound up to which a workgroup takes a list whole (2 * lists below and above the 256 CUs, lists above them) and one entry
+    beyond it, where lists are cut: a list as long as its row, some a step or two long, empty ones, against float64."""
+    T = _T()
+    for width, cut in ((bound, False), (bound + 1, True)):
+        lens = np.resize([width, 0, width // 16, 64, 65, 128, 129, 1], lists)
+        st = _attend_lists(T, G, 8, lens, 2 * bound, seed=lists + bound)
+        assert st.combined == cut, width
+
+
+@pytest.mark.parametrize("G,lists,bound", [(4, 136, 1280), (4, 264, 1280), (8, 136, 768), (8, 136, 1280), (8, 264, 1280)])
+def test_a_long_list_among_short_ones_is_shared_out(G, lists, bound):
+    """One list as long as its row among ones a sixteenth of it costs what it does in rows of 4096 entries, where lists are cut: taken
+    whole by a workgroup it was 18 to 35 us of attention instead of 11 to 18."""
+    T = _T()
+    B, lens, us = T.binding, np.full(lists, bound // 16), []
+    lens[lists // 3] = bound
+    for width in (bound, 4096):
+        st = _attend_lists(T, G, 8, lens, 2 * bound, seed=lists, bound=width)
+        q = torch.randn(lists // 8, 8 * G, 128, device="cuda").to(torch.bfloat16)
+        B.twilight_prof_enable(1)
+        for _ in range(24):
+            st.attend(q)
+        torch.cuda.synchronize()
+        kern = {}
+        for name, ms in B.twilight_prof_collect():
+            kern.setdefault(name, []).append(ms * 1e3)
+        B.twilight_prof_enable(0)
+        us.append(sum(float(np.median(v)) for v in kern.values()))
+    assert us[0] < 1.1 * us[1], us
+
+
 def _dense_us(T, batch, n):
     """Median time of dense attention over `batch` sequences of n tokens, 2 query heads on each of 8 KV heads."""
     B = T.binding

@@ -2181,11 +2181,12 @@ def test_long_rows_at_the_limits_of_a_wave(heads, p):
 
 
 @pytest.mark.parametrize("Hq,Hkv", [(4, 4), (4, 2), (8, 2), (16, 2)])
-@pytest.mark.parametrize("batch,stride", [(6, 256), (6, 512), (80, 512), (64, 1280), (140, 208)])
+@pytest.mark.parametrize("batch,stride", [(6, 256), (6, 512), (80, 512), (64, 768), (64, 1280), (140, 208)])
 def test_attention_over_short_lists_one_workgroup_each(Hq, Hkv, batch, stride):
-    """Lists whose bound lets a workgroup take each whole (eight waves, or four with more lists than CUs): lengths around the
-    steps of 64 and 128 entries, none, one, the bound and beyond it, entries outside the sequence - against the oracle, and
-    against the same lists in rows wide enough for the cut form, whose sums differ in order only."""
+    """Lists whose bound lets a workgroup take each whole (eight waves, or four with more lists than CUs), and beyond it (1280 entries,
+    and eight heads to a row above 256 or 512): lengths around the steps of 64 and 128 entries, none, one, the bound and beyond
+    it, entries outside the sequence - against the oracle, and against the same lists in rows wide enough for the cut form,
+    whose sums differ in order only."""
     T = _T()
     dev, n = "cuda", 1400
     g = torch.Generator().manual_seed(98)
