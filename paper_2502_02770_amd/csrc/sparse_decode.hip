@@ -621,16 +621,15 @@ void launch_decode(const DecodeArgs& a, long long max_items, size_t lds, hipStre
 // sixteenth of it, which the cut form shares out, loses nothing: at 512 entries, 256 with eight query heads to a row, and where there
 // are lists for half the CUs, so that cut ones would run no wider either, at 768 and 512.  Steps over caches larger than the last-level
 // one, us, cut / whole, (lists, bound), such lists:
-//   2 heads to a row   (64, 512) 24.0 / 23.7  (64, 640) 24.1 / 24.8  (136, 768) 26.2 / 25.8  (512, 768) 31.8 / 30.4
+//   1 head to a row    (32, 512) 23.9 / 24.0  (32, 640) 24.9 / 25.7  (128, 768) 27.4 / 27.6  (512, 768) 32.2 / 31.5
+//   2                  (64, 512) 24.0 / 23.7  (64, 640) 24.1 / 24.8  (136, 768) 26.2 / 25.8  (512, 768) 31.8 / 30.4
 //   4                  (64, 512) 24.2 / 24.1  (64, 640) 24.3 / 24.6  (136, 768) 27.1 / 27.4  (512, 768) 40.8 / 38.7
 //   8                  (64, 256) 26.2 / 24.7  (64, 384) 26.4 / 26.8  (136, 512) 30.9 / 30.5  (512, 512) 57.9 / 51.3
 // and beyond the lines, caches as the steps before left them: 4 heads (264, 1024) 31.4 / 32.6, (264, 1280) 32.5 / 35.4, 8 heads
-// (136, 640) 29.9 / 31.0, (136, 1280) 31.3 / 36.8.  Lists of log-uniform or equal lengths gain at and
-// below the lines: 4 heads (264, 768) 34.1 / 30.4, 8 heads (264, 512) 43.7 / 38.0.
-// One query head to a row: 208, whatever their number (43 x 1668 (1376, 208) 63.8 / 56.6, 4 x 1720 ragged (128, 96) 22.4 / 19.2), since the
-// items of longer lists are pinned.
+// (136, 640) 29.9 / 31.0, (136, 1280) 31.3 / 36.8, 1 head (256, 1280) 31.8 / 34.3.  Lists of log-uniform or equal lengths gain at and
+// below the lines: 4 heads (264, 768) 34.1 / 30.4, 8 heads (264, 512) 43.7 / 38.0, 1 head (256, 448) 29.1 / 24.3, 43 x 1668 multi-head
+// (1376, 208) 63.8 / 56.6.
 bool decode_whole(int NG, int G, int stride) {
-  if (G == 1) return stride <= 208;
   const bool many = 2 * NG >= tw_num_cus();
   return stride <= (G == 8 ? (many ? 512 : 256) : many ? 768 : 512);
 }
