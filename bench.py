@@ -186,9 +186,14 @@ def percentiles(t):
 def decode_balance(T, cache, st):
     """How evenly the flattened attention work list of the last step spreads over the persistent grid (workgroup w takes items
     w, w + grid, ...): the lists' lengths and the numbers of chunks that the kernel cut them into, which it leaves at the start
-    of its workspace, read back from the device; the chunk length is the shortest multiple of 64 that gives those numbers."""
+    of its workspace, read back from the device; the chunk length is the shortest multiple of 64 that gives those numbers.
+    Lists that cannot be long are not cut: a workgroup takes each, and no chunk is reported."""
     grid, _, _ = T.twilight_decode_plan(cache.kv, T.TW_WS_DECODE, False)
     cnt = [min(int(c), st.union_stride) for c in st.union_count.cpu().tolist()]
+    if T.twilight_decode_whole(cache.kv, T.TW_WS_DECODE, st.union_stride):
+        mean = sum(cnt) / len(cnt)
+        return {"grid_workgroups": len(cnt), "chunk": None, "items": len(cnt),
+                "rows_per_workgroup_max_over_mean": max(cnt) / mean if mean else None, "items_per_workgroup_max_over_mean": 1.0}
     first = st.ws_decode[:4 * (len(cnt) + 1)].view(st.union_count.dtype).cpu().tolist()
     chunk = max([64] + [-(-n // (64 * (b - a))) * 64 for n, a, b in zip(cnt, first, first[1:]) if b > a])
     items = []

@@ -69,9 +69,18 @@ const char* twilight_kernel_name(int kernel_id);
  * average: chunks of at least 128.
  * which = TW_WS_DECODE or TW_WS_DECODE_PER_HEAD.  For reports on how evenly
  * ragged lists spread over the workgroups (Section 4.2, load balancing).
+ * Where lists are cut: those of rows that twilight_decode_whole names are not.
  */
 int twilight_decode_plan(const struct twilight_kv* kv, int which, int32_t dense, int32_t* grid /*host, out*/,
                          int32_t* chunk0 /*host, out*/, int32_t* items_per_wg /*host, out*/);
+
+/*
+ * 1: lists in rows of union_stride entries are so short that a workgroup takes
+ * each whole (one launch; nothing is left in the workspace), 0: they are cut
+ * and their parts combined (the numbers of items before every list are at the
+ * start of the workspace afterwards), negative: an error.  Host only.
+ */
+int twilight_decode_whole(const struct twilight_kv* kv, int which, int32_t union_stride);
 
 #ifdef __cplusplus
 }

@@ -70,6 +70,8 @@ def lib():
     L.twilight_kernel_name.argtypes = [ctypes.c_int]
     L.twilight_decode_plan.argtypes = [kvp, ctypes.c_int, _i32, ctypes.POINTER(_i32), ctypes.POINTER(_i32), ctypes.POINTER(_i32)]
     L.twilight_decode_plan.restype = ctypes.c_int
+    L.twilight_decode_whole.argtypes = [kvp, ctypes.c_int, _i32]
+    L.twilight_decode_whole.restype = ctypes.c_int
     L.twilight_kernel_name.restype = ctypes.c_char_p
     for f in ("twilight_select_prune", "twilight_ds_select_tokens", "twilight_kquant_append", "twilight_select_pages", "twilight_select_pages_static", "twilight_append_select", "twilight_int4_score", "twilight_topp_prune",
               "twilight_int4_score_tokens", "twilight_topp_prune_tokens",
@@ -207,6 +209,13 @@ def twilight_decode_plan(kv, which=TW_WS_DECODE, dense=False):
     g, c, i = _i32(), _i32(), _i32()
     _check(lib().twilight_decode_plan(ctypes.byref(kv), int(which), int(bool(dense)), ctypes.byref(g), ctypes.byref(c), ctypes.byref(i)))
     return g.value, c.value, i.value
+
+
+def twilight_decode_whole(kv, which, union_stride):
+    """Does a workgroup of the attention kernel take each list of rows of union_stride entries whole (or are lists cut)?"""
+    r = lib().twilight_decode_whole(ctypes.byref(kv), int(which), int(union_stride))
+    _check(min(r, 0))
+    return r == 1
 
 
 def twilight_prof_enable(mode):

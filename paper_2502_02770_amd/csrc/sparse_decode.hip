@@ -722,19 +722,25 @@ static int decode_impl(const twilight_kv_t* kv, const void* q, const int32_t* co
 
 // Launch shape of the decode kernel for this cache shape (host only): workgroups of the persistent grid (before
 // it is cut to the number of work items), the shortest chunk, and how many numbers of items per workgroup
-// decode_chunk weighs.  For benchmarks that report the balance of the work list.  (Of lists that are cut: those that decode_whole
-// gives a workgroup each are not.)
+// decode_chunk weighs.  For benchmarks that report the balance of the work list, where lists are cut (twilight_decode_whole).
+static int plan_dims(const twilight_kv_t* kv, int which, TwDims* d, int* LH, int* Gk) {
+  if (!kv) return TW_EINVAL;
+  twilight_kv_t tmp = *kv;                       // the pointers are not needed here: check the shape fields only
+  int dummy = 0;
+  tmp.page_table = &dummy; tmp.seq_lens = &dummy;
+  if (int e = tw_check_kv(&tmp, d)) return e;
+  if (which != TW_WS_DECODE && which != TW_WS_DECODE_PER_HEAD) return TW_EINVAL;
+  *LH = which == TW_WS_DECODE_PER_HEAD ? d->Hq : d->Hkv;
+  *Gk = which == TW_WS_DECODE_PER_HEAD ? 1 : d->G;
+  return TW_OK;
+}
+
 extern "C" int twilight_decode_plan(const twilight_kv_t* kv, int which, int32_t dense, int32_t* grid, int32_t* chunk0,
                                     int32_t* items_per_wg) {
   TwDims d;
-  twilight_kv_t tmp;
-  if (!kv || !grid || !chunk0 || !items_per_wg) return TW_EINVAL;
-  tmp = *kv;                                     // the pointers are not needed here: check the shape fields only
-  int dummy = 0;
-  tmp.page_table = &dummy; tmp.seq_lens = &dummy;
-  if (int e = tw_check_kv(&tmp, &d)) return e;
-  if (which != TW_WS_DECODE && which != TW_WS_DECODE_PER_HEAD) return TW_EINVAL;
-  const int LH = which == TW_WS_DECODE_PER_HEAD ? d.Hq : d.Hkv, Gk = which == TW_WS_DECODE_PER_HEAD ? 1 : d.G;
+  int LH, Gk;
+  if (!grid || !chunk0 || !items_per_wg) return TW_EINVAL;
+  if (int e = plan_dims(kv, which, &d, &LH, &Gk)) return e;
   const size_t lds = (size_t)(d.batch * LH + 1) * 4;
   int occ = 1;
   switch (Gk) {
@@ -747,6 +753,14 @@ extern "C" int twilight_decode_plan(const twilight_kv_t* kv, int which, int32_t 
   *chunk0 = tw_decode_chunk(dense != 0);
   *items_per_wg = (int32_t)DEC_MAX_ROUNDS;
   return TW_OK;
+}
+
+extern "C" int twilight_decode_whole(const twilight_kv_t* kv, int which, int32_t union_stride) {
+  TwDims d;
+  int LH, Gk;
+  if (union_stride <= 0) return TW_EINVAL;
+  if (int e = plan_dims(kv, which, &d, &LH, &Gk)) return e;
+  return decode_whole(d.batch * LH, Gk, union_stride) ? 1 : 0;
 }
 
 extern "C" int twilight_sparse_decode(const twilight_kv_t* kv, const void* q, const int32_t* union_count,

@@ -85,6 +85,11 @@ def test_bad_arguments_are_rejected_on_the_host(T):
     assert L.twilight_sparse_decode_per_head(ctypes.byref(kv), one, one, None, 64, one, None, one, 1 << 20, None) == -1
     assert L.twilight_sparse_decode_per_head(ctypes.byref(kv), one, None, one, 64, one, None, one, 1 << 20, None) == -1
     assert L.twilight_sparse_decode_per_head(ctypes.byref(kv), one, one, one, 64, one, None, one, 8, None) == -2
+    # which lists are taken whole: a list bound, one of the two attention workspaces
+    whole = lambda which, stride, cache=kv: L.twilight_decode_whole(ctypes.byref(cache), which, stride)
+    assert whole(T.TW_WS_DECODE, 0) == -1 and whole(T.TW_WS_PRUNE, 64) == -1 and L.twilight_decode_whole(None, T.TW_WS_DECODE, 64) == -1
+    assert whole(T.TW_WS_DECODE, 64, T.make_kv(8, 32, 5, 16, 16, None, None)) < 0
+    assert not T.twilight_decode_whole(kv, T.TW_WS_DECODE, 1 << 20)
     # code width of the quantised K copy: 0 (= 4), 2, 4, 8 only
     kv.quant_bits = 3
     assert L.twilight_select_pages(ctypes.byref(kv), one, one, one, one, 4, one, 1 << 20, None) == -1

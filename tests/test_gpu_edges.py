@@ -538,7 +538,21 @@ def test_short_lists_take_a_workgroup_each_up_to_the_line(G, lists, bound):
     for width, cut in ((bound, False), (bound + 1, True)):
         lens = np.resize([width, 0, width // 16, 64, 65, 128, 129, 1], lists)
         st = _attend_lists(T, G, 8, lens, 2 * bound, seed=lists + bound)
-        assert st.combined == cut, width
+        assert st.combined == cut and T.twilight_decode_whole(st.cache.kv, T.TW_WS_DECODE, width) != cut, width
+
+
+@pytest.mark.parametrize("bound,items,chunk", [(512, 6, None), (2048, 12, 64)])
+def test_balance_of_the_work_list_of_lists_taken_whole(bound, items, chunk):
+    """The benchmark's report on lists that are not cut, which leave nothing in the workspace, and on the same ones cut."""
+    import bench
+    T = _T()
+    st = _attend_lists(T, 2, 3, np.array([128, 64, 130, 1, 64, 200]), 400, seed=1, bound=bound)
+    if chunk is None:
+        st.ws_decode.fill_(255)
+    got = bench.decode_balance(T, st.cache, st)
+    assert got["items"] == items and got["chunk"] == chunk
+    if chunk is None:
+        assert got["grid_workgroups"] == 6 and got["rows_per_workgroup_max_over_mean"] == pytest.approx(200 * 6 / 587)
 
 
 @pytest.mark.parametrize("G,lists,bound", [(1, 128, 1280), (4, 136, 1280), (4, 264, 1280), (8, 136, 768), (8, 136, 1280), (8, 264, 1280)])
