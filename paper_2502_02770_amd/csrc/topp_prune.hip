@@ -213,12 +213,19 @@ __device__ __forceinline__ int tw_group_dot(const int (&qw)[8], const uint4 (&r)
   return I;
 }
 // the group's term of the score: fl(scale * I) + fl(zero * sum q), summed over the 4 groups of the
-// token (the 4 lanes of a quad) in the fixed order (T0 + T1) + (T2 + T3)
+// token (the 4 lanes of a quad) in the fixed order (T0 + T1) + (T2 + T3).  MIX: the half-precision factors are taken as they lie in
+// their word, each product rounded as it is by an fma with -0: for the head kernel's scoring loop, which vector instructions bound.  (The
+// scoring launches wait for memory and gain nothing: token lists of 4 x 32 heads 4.65 us, 4.9 with it, of 10 x 32 6.25 and 6.3.)
+template <bool MIX = false>
 __device__ __forceinline__ float tw_token_sum(uint32_t meta, int I, float qsf) {
-  // (each product rounded as it is: fma with -0, the half-precision factor taken as it lies in its word)
   float sI, zq;
-  asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(sI) : "v"(meta), "v"((float)I), "s"(0x80000000u));
-  asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(zq) : "v"(meta), "v"(qsf), "s"(0x80000000u));
+  if (MIX) {
+    asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(sI) : "v"(meta), "v"((float)I), "s"(0x80000000u));
+    asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(zq) : "v"(meta), "v"(qsf), "s"(0x80000000u));
+  } else {
+    sI = __fmul_rn(__half2float(__ushort_as_half((unsigned short)(meta & 0xFFFFu))), (float)I);
+    zq = __fmul_rn(__half2float(__ushort_as_half((unsigned short)(meta >> 16))), qsf);
+  }
   return tw_quad_sum(__fadd_rn(sI, zq));
 }
 
@@ -962,7 +969,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
       if (!SPLIT) sc_s[slot] = sc;
       else if (k < npages) __hip_atomic_store(a.scores_w + (long long)bh * a.cand_stride + slot, sc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    auto use = [&](int kk, int k) { put(k, __fmul_rn(tw_token_sum(meta[kk], tw_group_dot<BITS>(qw, nib[kk], i0), qsf), cc)); };
+    auto use = [&](int kk, int k) { put(k, __fmul_rn(tw_token_sum<true>(meta[kk], tw_group_dot<BITS>(qw, nib[kk], i0), qsf), cc)); };
     // The first pages are asked for, then the query is quantised, by every wave on its own (by two of them for all, two barriers ahead of
     // the first load: 48 ragged sequences x 32 heads 36.1 -> 35.1 us, 4 x 32 heads of 8-bit codes 14.9 -> 14.4, the step of 1 x 4096 tokens 21.8 -> 21.6).
 #pragma unroll
