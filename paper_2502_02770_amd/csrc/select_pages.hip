@@ -116,7 +116,8 @@ __device__ __forceinline__ void ps_append(const ScoreArgs& a, long long row, lon
 
 // The bounds of a page for the G heads, by its 16 lanes; put(h, bound) in the lane that ends with head h's.
 // (The signs of 4 heads' queries fill the scalar registers; those of further heads are compared anew, or they spill.  With 8 heads
-//  and the append page_score_long_kernel still spills 8 scalar registers, page_score_kernel none.)
+//  and the append page_score_long_kernel still spills 8 scalar registers, page_score_kernel none; the variants that leave the order of
+//  work spill more: 15 with 8 heads and 3 with 4, both with the append, on long tables, 2 to 5 with 8 heads on short ones.)
 template <int G, typename Put>
 __device__ __forceinline__ void ps_score(float (&q)[G][8], const uint4& cmn, const uint4& cmx, int seg, Put put) {
   float mn[8], mx[8];

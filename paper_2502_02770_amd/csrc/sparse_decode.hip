@@ -139,7 +139,8 @@ struct DecodePlan {
   }
   // The chunks have `items` items.  False: they are taken.  True: `chunk` is another length, to be counted: that of another
   // number of items per workgroup, then longer ones while they can still be better, then the best of all if it was not the last.
-  // (Made longer only, 744 lists of 61 entries on average ended at 256: 16.6 us, now 15.0; 1088 of 82 at 320: 27.1 and 19.6.)
+  // (Made longer only, 744 lists of 61 entries on average ended at 256: 16.6 us, now 15.0; 1088 of 82 at 320: 27.1 and 19.6, times
+  // of lists that rows beyond decode_whole's bound hold.)
   __device__ __forceinline__ bool again(uint32_t items) {
     if (state == 5 || (state == 0 && items <= rounds * W)) return false;
     const uint32_t cost = (items + W - 1u) / W * (chunk + DEC_ITEM_ROWS) + DEC_CUT_ROWS;
@@ -219,7 +220,7 @@ __global__ __launch_bounds__(64 * NW, NW == 8 || G == 8 ? 2 : (G == 4 ? 3 : 4)) 
     if (tid == 0) prefix[a.NG] = total_items;
   } else {                                        // thread t: the lists t * K ..
     // (more than two to a thread: read in whole lines, through LDS, K odd so that the lanes' words lie on different banks; read
-    //  by their threads in every pass 6144 lists took 59.4 us, now 37.9)
+    //  by their threads in every pass 6144 lists took 59.4 us, now 37.9; of lists in rows beyond decode_whole's bound)
     const int K1 = (a.NG + 255) >> 8, K = K1 > 2 ? K1 | 1 : K1, i0 = tid * K;
     uint32_t T = 0, longest = 0, c0 = 0, c1 = 0;
     if (K > 2) {

@@ -1143,7 +1143,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 1 : (FUSE == 2 && EPT == 8 ? 8 : (FU
       // every wave scans the 512 buckets on its own: lane l sums buckets 8l .. 8l+7; of the lane that holds the crossing
       // the first 8 lanes then take a bucket each: walking that lane's 8 sums in every wave took more vector instructions, which the
       // waves share their units for (step of 64 ragged sequences 230.0 -> 228.3 us), and registers for the sums where scores are held
-      // in registers (1024 threads x 4 candidates 86 -> 66, x 8 102 -> 72, in parts 103 -> 80; the forms with scores in LDS: none)
+      // in registers (1024 threads x 4 candidates 86 -> 64, x 8 102 -> 68, in parts 103 -> 80; the forms with scores in LDS: none)
       unsigned long long mine = 0;
 #pragma unroll
       for (int k = 0; k < 8; ++k) mine += histM[8 * lane + k];
@@ -1605,10 +1605,11 @@ void launch_topp_one(const HeadArgs& f, int G, dim3 grid, hipStream_t s) {
 
 // Register-resident top-p over rows of at most 8192 candidates (cand_stride = row bound).  Times in us, of the kernel alone.
 //  - few heads: one 1024-thread workgroup per head (4 or 8 candidates per thread), or several (tw_prune_parts);
-//  - more heads than CUs and rows of at most 4096 candidates: 512-thread workgroups, three to a CU, whatever the 1024-thread form's
-//    registers allow: with selection and scores inside it has a CU to itself with 4-bit codes (66 registers; 1024 heads x 4096 candidates
-//    of 1024 pages 76.6 that way, 52.4 so) and loses as much where two fit (2-bit codes 72.3 / 50.7, 8-bit 95.2 / 76.8); on stored scores
-//    two fit (52 registers) and 512 heads take 22.5 / 20.7, 1024 37.1 / 35.2, of token lists 19.4 / 18.6 and 35.0 / 32.0.  Selection and
+//  - more heads than CUs and rows of at most 4096 candidates: 512-thread workgroups, three to a CU, though two 1024-thread ones would
+//    share a CU as well (64 registers with 4-bit codes, 52 on stored scores): three are at different phases, and each phase's barrier is
+//    for half the waves.  With selection and scores inside, 1024 / 512 threads, by events: 4096 candidates of 1024 pages 288 heads 31.3 /
+//    24.5, 512 35.5 / 25.6, 768 51.4 / 32.4, 1024 66.8 / 39.4, of 2048 pages 32.3 / 25.1, 35.8 / 27.0, 52.8 / 35.1, 68.1 / 45.5, of 8-bit
+//    codes 512 heads 40.8 / 32.4; on stored scores 512 heads take 22.5 / 20.7, 1024 37.1 / 35.2, of token lists 19.4 / 18.6 and 35.0 / 32.0.  Selection and
 //    scores inside: four to a CU, whose phases are longer, where that takes a round less and either the only one or the tables are short
 //    (a thread of 512 has 8 of 4096 bounds, which the 64 registers hold worst).  Three and four to a CU, 4096 candidates of 1024 pages: 512
 //    heads 31.2 / 33.5, 768 41.2 / 44.2, 1024 53.6 / 52.4, 1536 70.2 / 71.4, 2048 88.0 / 90.4, 4096 167.1 / 163.7; 2224 of 3750: 288 heads

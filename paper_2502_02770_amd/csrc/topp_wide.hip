@@ -240,7 +240,8 @@ __device__ __forceinline__ void wide_to_lane(int lane, unsigned long long x, uin
 // What bounds it is vector instructions, then the read of the rows.  Masses, floor(e * 2^40), are summed by one
 // 64-bit fma each, rounded towards zero in an accumulator between 2^52 and 2^53, whose last place is 1: the integers' sum, exactly.
 // (As two 20-bit parts, with the flags gathered per lane and joined across lanes, 30 instructions a score; 15 so.  4 x 64 heads x
-// 262144 51.9 -> 46.4 us, 268 MB at 5.8 TB/s; 4 x 32 29.2 -> 24.9, 1 x 64 17.0 -> 14.8, 16 x 32 x 32768 17.3 -> 15.0.)
+// 262144, in a kernel trace of the pruner's steps, 55.6 -> 52.2 us, 268 MB at 5.1 TB/s; by events around the launch 51.9 -> 46.4,
+// 4 x 32 heads 29.2 -> 24.9, 1 x 64 17.0 -> 14.8, 16 x 32 x 32768 17.3 -> 15.0.)
 template <int NT>
 __global__ __launch_bounds__(NT) void wide_emit_kernel(WideArgs a) {
   constexpr int W_CHUNK = NT * W_SLOTS, NW = NT / 64;
